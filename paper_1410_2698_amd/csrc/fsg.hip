@@ -22,6 +22,7 @@
 #include <hip/hip_ext.h>
 
 #include "canon.hpp"
+#include "radix_sort.hpp"
 #include "tds_internal.hpp"
 
 namespace tds {
@@ -120,9 +121,12 @@ __global__ __launch_bounds__(kFT) void k_fsg_list(const EntryF64* __restrict__ e
 
 // first[c] = number of listings with a cell below c (c = 0..ncells): one
 // thread per cell, a binary search of the sorted cell keys.
-__global__ __launch_bounds__(kFT) void k_fsg_cell_first(const uint64_t* __restrict__ keys,
+__global__ __launch_bounds__(kFT) void k_fsg_cell_first(const uint32_t* __restrict__ k0,
+                                                        const uint32_t* __restrict__ k1,
+                                                        const SortControl* __restrict__ ctl,
                                                         uint32_t nl, uint32_t ncells,
                                                         uint32_t* __restrict__ first) {
+    const uint32_t* keys = ctl->side() ? k1 : k0;
     const uint32_t c = blockIdx.x * kFT + threadIdx.x;
     if (c > ncells) return;
     uint32_t l = 0, h = nl;
@@ -132,6 +136,15 @@ __global__ __launch_bounds__(kFT) void k_fsg_cell_first(const uint64_t* __restri
         else h = mid;
     }
     first[c] = l;
+}
+
+// The sorted listings, from the sort's side that holds them.
+__global__ __launch_bounds__(kFT) void k_fsg_take(const uint32_t* __restrict__ v0,
+                                                  const uint32_t* __restrict__ v1,
+                                                  const SortControl* __restrict__ ctl, uint32_t nl,
+                                                  uint32_t* __restrict__ list) {
+    const uint64_t i = (uint64_t)blockIdx.x * kFT + threadIdx.x;
+    if (i < nl) list[i] = ctl->side() ? v1[i] : v0[i];
 }
 
 struct FsgArgs {
@@ -312,30 +325,46 @@ int fsg_build(const tds_index* idx, uint32_t gx, uint32_t gy, uint32_t gz, hipSt
     }
     uint32_t nl = 0;
     TDS_TRY(exclusive_scan_u32(cnt, n, &nl, s));
-    uint64_t *keys = nullptr, *keys2 = nullptr;
-    uint32_t *vals = nullptr, *vals2 = nullptr;
-    TDS_TRY(dmalloc(&keys, std::max<uint32_t>(nl, 1)));
+    uint64_t *keys = nullptr, *keys2 = nullptr, *status = nullptr;
+    uint32_t *vals = nullptr, *vals2 = nullptr, *list = nullptr;
+    SortControl* ctl = nullptr;
+    const uint32_t na = std::max<uint32_t>(nl, 1);
+    TDS_TRY(dmalloc(&keys, na));
     B.p[2] = keys;
-    TDS_TRY(dmalloc(&keys2, std::max<uint32_t>(nl, 1)));
+    TDS_TRY(dmalloc(&keys2, na));
     B.p[3] = keys2;
-    TDS_TRY(dmalloc(&vals2, std::max<uint32_t>(nl, 1)));
-    B.p[4] = vals2;
-    TDS_TRY(dmalloc(&vals, std::max<uint32_t>(nl, 1)));  // becomes the grid's list
-    hipLaunchKernelGGL(k_fsg_list<true>, dim3(nb), dim3(kFT), 0, s, idx->e64, n, G, cnt, keys, vals);
+    TDS_TRY(dmalloc(&vals, na));
+    B.p[4] = vals;
+    TDS_TRY(dmalloc(&vals2, na));
+    B.p[5] = vals2;
+    TDS_TRY(dmalloc(&status, sort_status_len(na)));
+    B.p[6] = status;
+    TDS_TRY(dmalloc(&ctl, 1));
+    B.p[7] = ctl;
     int bits = 1;
     while ((1ull << bits) < ncells) ++bits;
-    int st = radix_sort_u64(keys, vals, keys2, vals2, nl, bits, s);
+    // cell numbers fit 32 bits (at most 2^24 cells); an entry's listings are
+    // written from its offset, so its position is the value to carry
+    const SortJob sort{nl, keys, vals, keys, keys2, vals, vals2, ctl, status};
+    TDS_TRY(sort_clear(sort, s));
+    hipLaunchKernelGGL(k_fsg_list<true>, dim3(nb), dim3(kFT), 0, s, idx->e64, n, G, cnt, keys, vals);
+    TDS_TRY(sort_plan(sort, bits, s));
+    TDS_TRY(sort_passes(sort, sort_npass(bits), true, s));
+    int st = dmalloc(&list, na);
     uint32_t* first = nullptr;
     if (st == TDS_OK) st = dmalloc(&first, ncells + 1);
     if (st == TDS_OK) {
-        hipLaunchKernelGGL(k_fsg_cell_first, dim3(ceil_div(ncells + 1, kFT)), dim3(kFT), 0, s, keys,
-                           nl, (uint32_t)ncells, first);
+        const uint32_t* k1 = reinterpret_cast<const uint32_t*>(keys2);
+        hipLaunchKernelGGL(k_fsg_cell_first, dim3(ceil_div(ncells + 1, kFT)), dim3(kFT), 0, s,
+                           k1 + nl, k1, ctl, nl, (uint32_t)ncells, first);
+        hipLaunchKernelGGL(k_fsg_take, dim3(ceil_div(na, kFT)), dim3(kFT), 0, s, vals, vals2, ctl,
+                           nl, list);
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
             st = TDS_E_DEVICE;
     }
     tds_fsg* f = (st == TDS_OK) ? new (std::nothrow) tds_fsg() : nullptr;
     if (!f) {
-        dfree(vals);
+        dfree(list);
         dfree(first);
         return st == TDS_OK ? TDS_E_NOMEM : st;
     }
@@ -347,7 +376,7 @@ int fsg_build(const tds_index* idx, uint32_t gx, uint32_t gy, uint32_t gz, hipSt
         f->cw[a] = G.cw[a];
     }
     f->cell_first = first;
-    f->list = vals;
+    f->list = list;
     f->nlist = nl;
     *out = f;
     return TDS_OK;

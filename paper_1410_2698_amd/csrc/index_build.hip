@@ -21,6 +21,7 @@
 #include <utility>
 
 #include "hilbert.hpp"
+#include "radix_sort.hpp"
 #include "tds_internal.hpp"
 
 namespace tds {
@@ -44,7 +45,6 @@ constexpr int kPart = 9;
 __global__ __launch_bounds__(kBT) void k_seg_prep(SegView S, EntryF64* __restrict__ tmp64,
                                                   EntryF32* __restrict__ tmp32,
                                                   uint64_t* __restrict__ keys,
-                                                  uint32_t* __restrict__ vals,
                                                   double* __restrict__ part, uint32_t* err) {
     __shared__ double sp[kPart][kBT];
     const uint32_t tid = threadIdx.x;
@@ -80,7 +80,6 @@ __global__ __launch_bounds__(kBT) void k_seg_prep(SegView S, EntryF64* __restric
         f.pad1 = 0.f;
         tmp32[i] = f;
         keys[i] = order_key(ts);
-        vals[i] = (uint32_t)i;
         v[0] = ts;
         v[1] = te;
         v[2] = dt;
@@ -138,7 +137,9 @@ __global__ __launch_bounds__(kBT) void k_spatial_key(uint64_t n, const EntryF64*
     keys[i] = ((uint64_t)bin_of(tmp64[i].ts, tmin, bw, m) << 30) | h;
 }
 
-__global__ __launch_bounds__(kBT) void k_gather(uint64_t n, const uint32_t* __restrict__ perm,
+__global__ __launch_bounds__(kBT) void k_gather(uint64_t n, const uint32_t* __restrict__ v0,
+                                                const uint32_t* __restrict__ v1,
+                                                const SortControl* __restrict__ ctl,
                                                 const EntryF64* __restrict__ tmp64,
                                                 const EntryF32* __restrict__ tmp32,
                                                 const uint32_t* __restrict__ traj_in,
@@ -149,7 +150,7 @@ __global__ __launch_bounds__(kBT) void k_gather(uint64_t n, const uint32_t* __re
                                                 uint32_t* __restrict__ traj) {
     const uint64_t i = (uint64_t)blockIdx.x * kBT + threadIdx.x;
     if (i >= n) return;
-    const uint32_t src = perm[i];
+    const uint32_t src = ctl->side() ? v1[i] : v0[i];
     const EntryF64 e = tmp64[src];
     e64[i] = e;
     e32[i] = tmp32[src];
@@ -380,7 +381,7 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
     TDS_TRY(dmalloc(&err, 1));
     sc.p[9] = err;
     TDS_HIP(hipMemsetAsync(err, 0, sizeof(uint32_t), stream));
-    hipLaunchKernelGGL(k_seg_prep, dim3(nb), dim3(kBT), 0, stream, S, tmp64, tmp32, keys, vals,
+    hipLaunchKernelGGL(k_seg_prep, dim3(nb), dim3(kBT), 0, stream, S, tmp64, tmp32, keys,
                        part, err);
     TDS_HIP(hipGetLastError());
     std::vector<double> hpart(kPart * (size_t)nb);
@@ -428,7 +429,16 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
         while ((1u << bin_bits) < m) ++bin_bits;
         key_bits = 30 + bin_bits;
     }
-    TDS_TRY(radix_sort_u64(keys, vals, keys2, vals2, (uint32_t)n, key_bits, stream));
+    SortControl* ctl = nullptr;
+    uint64_t* status = nullptr;
+    TDS_TRY(dmalloc(&ctl, 1));
+    sc.p[10] = ctl;
+    TDS_TRY(dmalloc(&status, sort_status_len((uint32_t)n)));
+    sc.p[11] = status;
+    const SortJob sort{(uint32_t)n, keys, nullptr, keys, keys2, vals, vals2, ctl, status};
+    TDS_TRY(sort_clear(sort, stream));
+    TDS_TRY(sort_plan(sort, key_bits, stream));
+    TDS_TRY(sort_passes(sort, sort_npass(key_bits), false, stream));
 
     // ---- the index object
     tds_index* idx = new (std::nothrow) tds_index();
@@ -464,7 +474,7 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
     idx->device_bytes = n * (sizeof(EntryF64) + sizeof(EntryF32) + sizeof(EntryV32) + 8) +
                         (size_t)m * 52 + 4 +
                         (idx->bbox ? (size_t)nblk * sizeof(BlockBox) : 0);
-    hipLaunchKernelGGL(k_gather, dim3(nb), dim3(kBT), 0, stream, n, vals, tmp64, tmp32, S.traj,
+    hipLaunchKernelGGL(k_gather, dim3(nb), dim3(kBT), 0, stream, n, vals, vals2, ctl, tmp64, tmp32, S.traj,
                        idx->e64, idx->e32, idx->ev32, idx->seg_id, idx->traj);
     hipLaunchKernelGGL(k_bin_first, dim3(nb), dim3(kBT), 0, stream, n, idx->e64, tmin, bw, m,
                        idx->bin_first);

@@ -1,47 +1,291 @@
-// Stable LSD radix sort of (u64 key, u32 value) pairs with 8-bit digits.
+// Stable LSD radix sort of (key, u32 value) pairs with 8-bit digits.
 //
-// Used by the index build to order the entry segments by t_start (Sec. 4.2.1
-// sorts D by ascending start time and renumbers it); stability keeps equal
-// start times in input order, which makes the renumbering deterministic.
+// Used by the index build to order the entry segments (Sec. 4.2.1 sorts D by
+// ascending start time and renumbers it), by the grid build to group the
+// listings by cell, and by the trajectory merge.  Stability keeps equal keys in
+// input order, which makes the renumbering deterministic.
 //
-// One pass per digit, five kernels per pass:
-//   rs_hist    each block counts the digits of its 2048-key tile in LDS;
-//   rs_scan_*  turn the digit-major count table into exclusive offsets
-//              (digit d of block b starts after every smaller digit and after
-//              digit d of the blocks before b): tile sums, a scan of the tile
-//              sums, then each tile scanned from its offset;
-//   rs_scatter each block re-reads its tile and writes every key to its
-//              offset; the rank of a key among equal digits of its tile comes
-//              from wave ballots (wave-local) plus per-wave digit counts in
-//              LDS, processed in tile order, so the pass is stable.
+//   rs_hist   the digit counts of every pass at once, one read of the keys;
+//   rs_plan   exclusive sums of each digit's counts, and the digits to sort
+//             by (a digit that is the same in every key is skipped);
+//   rs_pass   one launch per digit: a workgroup takes the next tile of keys,
+//             ranks them by digit (wave ballots, per-wave counts in LDS),
+//             learns from the tiles before it where its keys go (decoupled
+//             look-back: Merrill & Garland, "Single-pass Parallel Prefix Scan
+//             with Decoupled Look-back", 2016; Adinets & Merrill, "Onesweep",
+//             2022), orders the tile in LDS and writes each digit's keys as
+//             one contiguous run.
+//
+// What bounds it: HBM traffic for large inputs (a pass reads and writes a key
+// and a value once), launches for small ones (one per digit here).  Before, a
+// pass was five launches (count, three scan steps, scatter), read the keys
+// twice and wrote each key straight to its place from the lane that held it:
+// 2.1-3.1 ms per pass at 171e6 pairs, 5 x 4 us at 86,000.
+//
+// Tiles are taken in order from a counter, so every tile before a waiting one
+// is held by a workgroup that is running and publishes its counts without
+// waiting for anything: each look-back ends.
 #include <algorithm>
 
-#include "tds_internal.hpp"
+#include "radix_sort.hpp"
 
 namespace tds {
 
 namespace {
 
-constexpr int kRsThreads = 256;
-constexpr int kRsItems = 8;
-constexpr int kRsTile = kRsThreads * kRsItems;
-constexpr int kRadix = 256;
-constexpr int kRsWaves = kRsThreads / kWave;
+constexpr int kRadix = kSortRadix;
+constexpr int kThreads = kSortThreads;
+constexpr int kWaves = kThreads / kWave;
 
-__global__ __launch_bounds__(kRsThreads) void rs_hist(const uint64_t* __restrict__ keys, uint32_t n,
-                                                      int shift, uint32_t* __restrict__ hist,
-                                                      uint32_t nblocks) {
-    __shared__ uint32_t h[kRadix];
-    const int tid = threadIdx.x;
-    h[tid] = 0;
+// Look-back status word of one (tile, digit): the pass it belongs to, whether
+// it is the tile's own count or the sum up to and including the tile, and the
+// count.  Words of an earlier pass read as "not yet published".
+constexpr int kEpochShift = 56;
+constexpr uint64_t kOwn = 1ull << 54, kSum = 2ull << 54, kFlags = 3ull << 54;
+constexpr uint64_t kCount = (1ull << 54) - 1;
+
+__device__ inline uint64_t lanemask_lt() {
+    const uint32_t lane = __lane_id();
+    return (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+}
+
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+__global__ __launch_bounds__(256) void rs_clear(uint32_t* __restrict__ ctl,
+                                                uint64_t* __restrict__ status, uint64_t words) {
+    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x, step = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = t; i < sizeof(SortControl) / 4; i += step) ctl[i] = 0u;
+    for (uint64_t i = t; i < words; i += step) status[i] = 0ull;
+}
+
+// Digit counts of all passes.  A wave whose keys share a digit adds 64 to it
+// at once (keys that come sorted, or high digits that hardly vary, would
+// otherwise queue 64 atomics on one LDS address).
+__global__ __launch_bounds__(kThreads) void rs_hist(const uint64_t* __restrict__ keys, uint64_t n,
+                                                    int npass, SortControl* __restrict__ ctl) {
+    __shared__ uint32_t h[8][kRadix];
+    const uint32_t tid = threadIdx.x;
+    for (int p = 0; p < npass; ++p)
+        for (uint32_t d = tid; d < (uint32_t)kRadix; d += kThreads) h[p][d] = 0;
     __syncthreads();
-    const uint64_t base = (uint64_t)blockIdx.x * kRsTile;
-    for (int k = 0; k < kRsItems; ++k) {
-        uint64_t i = base + (uint64_t)k * kRsThreads + tid;
-        if (i < n) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & (kRadix - 1)], 1u);
+    const PairPack pk = ctl->pack();
+    const uint64_t step = (uint64_t)gridDim.x * kThreads;
+    const uint64_t rounds = (n + step - 1) / step;
+    for (uint64_t r = 0; r < rounds; ++r) {
+        const uint64_t i = r * step + (uint64_t)blockIdx.x * kThreads + tid;
+        const bool valid = i < n;
+        const uint64_t key = valid ? pk.apply(keys[i]) : 0ull;
+        const bool full = __ballot(valid) == ~0ull;
+        for (int p = 0; p < npass; ++p) {
+            const uint32_t d = (uint32_t)(key >> (8 * p)) & (kRadix - 1);
+            const uint32_t d0 = (uint32_t)__shfl((int)d, 0);
+            const bool same = __ballot(d == d0) == ~0ull;
+            if (full && same) {
+                if (__lane_id() == 0) atomicAdd(&h[p][d], (uint32_t)kWave);
+            } else if (valid) {
+                atomicAdd(&h[p][d], 1u);
+            }
+        }
     }
     __syncthreads();
-    hist[(uint64_t)tid * nblocks + blockIdx.x] = h[tid];
+    for (int p = 0; p < npass; ++p)
+        for (uint32_t d = tid; d < (uint32_t)kRadix; d += kThreads)
+            if (h[p][d]) atomicAdd(&ctl->hist[p][d], h[p][d]);
+}
+
+// One workgroup of kRadix threads: exclusive sums per digit position, and the
+// digit positions in use, in order (at least one, so that the values are
+// written and the keys packed).
+__global__ __launch_bounds__(kRadix) void rs_plan(SortControl* __restrict__ ctl, int npass,
+                                                  uint32_t n) {
+    __shared__ uint32_t wsum[kRadix / kWave];
+    __shared__ uint32_t varies[8];
+    const uint32_t t = threadIdx.x, lane = t % kWave, wv = t / kWave;
+    if (t < 8) varies[t] = 0;
+    __syncthreads();
+    for (int p = 0; p < npass; ++p) {
+        const uint32_t v = ctl->hist[p][t];
+        uint32_t x = v;
+        for (uint32_t o = 1; o < kWave; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o);
+            if (lane >= o) x += y;
+        }
+        if (lane == kWave - 1) wsum[wv] = x;
+        if (v && v != n) varies[p] = 1;
+        __syncthreads();
+        uint32_t before = 0;
+        for (uint32_t k = 0; k < wv; ++k) before += wsum[k];
+        ctl->hist[p][t] = before + x - v;
+        __syncthreads();
+    }
+    if (t == 0) {
+        uint32_t m = 0;
+        for (int p = 0; p < npass; ++p)
+            if (varies[p]) ctl->digit[m++] = (uint32_t)p;
+        if (m == 0) {
+            ctl->digit[0] = 0;
+            m = 1;
+        }
+        ctl->npass = m;
+    }
+}
+
+// Pass number `pass` of the plan (a launch past the plan's end does nothing).
+// Passes alternate between the two buffer pairs (k0, v0) and (k1, v1); pass 0
+// reads its keys from `raw` (packed on the way) and its values from vinit or,
+// without one, takes the positions.
+//
+// A tile is kThreads * kItems pairs, wave w holding its w-th contiguous part,
+// item k of the part's lanes consecutive.  The keys and then the values go
+// through one LDS buffer (half the LDS of two, so four workgroups share a
+// compute unit).  Keys past n are given digit 255: they come last in the last
+// tile, whose counts no other tile reads.
+template <class K, int kItems, bool kFirst>
+__global__ __launch_bounds__(kThreads) void rs_pass(const uint64_t* __restrict__ raw,
+                                                    const uint32_t* __restrict__ vinit, K* k0,
+                                                    uint32_t* v0, K* k1, uint32_t* v1, uint32_t n,
+                                                    uint32_t pass, SortControl* __restrict__ ctl,
+                                                    uint64_t* __restrict__ status) {
+    constexpr uint32_t kTile = kThreads * kItems;
+    __shared__ K s_buf[kTile];
+    __shared__ uint32_t s_cnt[kWaves][kRadix];
+    __shared__ uint32_t s_start[kRadix];  // first position of a digit in the tile
+    __shared__ uint32_t s_dst[kRadix];    // its first position in the output, minus s_start
+    __shared__ uint32_t s_wsum[kRadix / kWave];
+    __shared__ uint32_t s_tile;
+    if (pass >= ctl->npass) return;
+    const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = tid / kWave;
+    const uint32_t dp = ctl->digit[pass];
+    const int shift = 8 * (int)dp;
+    const K* kin = (pass & 1) ? k1 : k0;
+    const uint32_t* vin = (pass & 1) ? v1 : v0;
+    K* kout = (pass & 1) ? k0 : k1;
+    uint32_t* vout = (pass & 1) ? v0 : v1;
+    if (tid == 0) s_tile = atomicAdd(&ctl->ticket[pass], 1u);
+    for (uint32_t d = lane; d < (uint32_t)kRadix; d += kWave) s_cnt[wv][d] = 0;
+    __syncthreads();
+    const uint32_t tile = s_tile;
+    const uint64_t base = (uint64_t)tile * kTile;
+    const uint64_t mine = base + (uint64_t)wv * (kWave * kItems) + lane;
+    const uint32_t nvalid = (uint32_t)min((uint64_t)kTile, (uint64_t)n - base);
+    K key[kItems];
+    uint32_t val[kItems], rank[kItems];
+    const PairPack pk = ctl->pack();
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const uint64_t i = mine + (uint64_t)k * kWave;
+        if (i < n) key[k] = kFirst ? (K)pk.apply(raw[i]) : kin[i];
+        else key[k] = (K)~(K)0;
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const uint64_t i = mine + (uint64_t)k * kWave;
+        if (kFirst && !vinit) val[k] = (uint32_t)i;
+        else if (kFirst) val[k] = i < n ? vinit[i] : 0u;
+        else val[k] = i < n ? vin[i] : 0u;
+    }
+    // rank among the wave's keys of the same digit
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const uint32_t d = (uint32_t)(key[k] >> shift) & (kRadix - 1);
+        uint64_t same = ~0ull;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const bool set = (d >> b) & 1u;
+            const uint64_t m = __ballot(set);
+            same &= set ? m : ~m;
+        }
+        const uint32_t below = (uint32_t)__popcll(same & lanemask_lt());
+        const uint32_t c = s_cnt[wv][d];
+        wave_sync();
+        if (below == 0) s_cnt[wv][d] = c + (uint32_t)__popcll(same);
+        wave_sync();
+        rank[k] = c + below;
+    }
+    __syncthreads();
+    uint32_t total = 0, before = 0;
+    if (tid < (uint32_t)kRadix) {
+        for (int w = 0; w < kWaves; ++w) {
+            const uint32_t c = s_cnt[w][tid];
+            s_cnt[w][tid] = total;
+            total += c;
+        }
+        const uint64_t epoch = (uint64_t)(pass + 1) << kEpochShift;
+        uint64_t* st = status + (uint64_t)tile * kRadix + tid;
+        __hip_atomic_store(st, epoch | (tile ? kOwn : kSum) | total, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        // sum over the waves below (their scan of the digit totals follows)
+        uint32_t x = total;
+        for (uint32_t o = 1; o < kWave; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o);
+            if (lane >= o) x += y;
+        }
+        if (lane == kWave - 1) s_wsum[wv] = x;
+        before = x - total;
+        // look back over the tiles before this one, four words at a time
+        uint64_t sum = 0;
+        if (tile) {
+            int64_t p = (int64_t)tile - 1;
+            bool done = false;
+            while (!done) {
+                uint64_t w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    w[q] = p >= q ? __hip_atomic_load(status + (uint64_t)(p - q) * kRadix + tid,
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                  : 0ull;
+                bool more = true;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bool ready = (w[q] >> kEpochShift) == (uint64_t)(pass + 1);
+                    more = more && ready && !done;
+                    if (more) {
+                        sum += w[q] & kCount;
+                        --p;
+                        done = (w[q] & kFlags) == kSum;
+                    }
+                }
+            }
+            __hip_atomic_store(st, epoch | kSum | (sum + total), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+        s_dst[tid] = ctl->hist[dp][tid] + (uint32_t)sum;
+    }
+    __syncthreads();
+    if (tid < (uint32_t)kRadix) {
+        for (uint32_t w = 0; w < wv; ++w) before += s_wsum[w];
+        s_start[tid] = before;
+        s_dst[tid] -= before;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const uint32_t d = (uint32_t)(key[k] >> shift) & (kRadix - 1);
+        rank[k] += s_start[d] + s_cnt[wv][d];  // position in the tile
+        s_buf[rank[k]] = key[k];
+    }
+    __syncthreads();
+    uint32_t dst[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const uint32_t p = (uint32_t)k * kThreads + tid;
+        const K x = s_buf[p];
+        dst[k] = s_dst[(uint32_t)(x >> shift) & (kRadix - 1)] + p;
+        if (p < nvalid) kout[dst[k]] = x;
+    }
+    __syncthreads();
+    uint32_t* s_val = reinterpret_cast<uint32_t*>(s_buf);
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) s_val[rank[k]] = val[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const uint32_t p = (uint32_t)k * kThreads + tid;
+        if (p < nvalid) vout[dst[k]] = s_val[p];
+    }
 }
 
 // Exclusive scan of `len` u32 values in place, in three coalesced steps:
@@ -122,141 +366,73 @@ __global__ __launch_bounds__(kScanThreads) void rs_scan_down(uint32_t* __restric
     }
 }
 
-__device__ inline uint64_t lanemask_lt() {
-    const uint32_t lane = __lane_id();
-    return (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-}
+// Items per thread of a pass: tiles of 4,096 pairs once there are enough of
+// them for the 256 compute units, else tiles of 1,024.
+constexpr int kItemsLarge = 8, kItemsSmall = 2;
+constexpr uint32_t kLargeFrom = 1u << 20;
 
-__global__ __launch_bounds__(kRsThreads) void rs_scatter(const uint64_t* __restrict__ kin,
-                                                         const uint32_t* __restrict__ vin,
-                                                         uint64_t* __restrict__ kout,
-                                                         uint32_t* __restrict__ vout, uint32_t n,
-                                                         int shift,
-                                                         const uint32_t* __restrict__ offs,
-                                                         uint32_t nblocks) {
-    __shared__ uint32_t base[kRadix];
-    __shared__ uint32_t wcnt[kRsWaves][kRadix];
-    const int tid = threadIdx.x;
-    const int wave = tid / kWave;
-    base[tid] = offs[(uint64_t)tid * nblocks + blockIdx.x];
-    for (int w = 0; w < kRsWaves; ++w) wcnt[w][tid] = 0;
-    __syncthreads();
-    const uint64_t tile = (uint64_t)blockIdx.x * kRsTile;
-    for (int k = 0; k < kRsItems; ++k) {
-        const uint64_t i = tile + (uint64_t)k * kRsThreads + tid;
-        const bool valid = i < n;
-        uint64_t key = valid ? kin[i] : 0ull;
-        uint32_t val = valid ? vin[i] : 0u;
-        // 9-bit class: digits 0..255, 256 for lanes without a key
-        const uint32_t digit = valid ? ((uint32_t)(key >> shift) & (kRadix - 1)) : (uint32_t)kRadix;
-        uint64_t same = __ballot(1);
-        for (int bit = 0; bit < 9; ++bit) {
-            const bool set = (digit >> bit) & 1u;
-            const uint64_t m = __ballot(set);
-            same &= set ? m : ~m;
-        }
-        const uint32_t rank = __popcll(same & lanemask_lt());
-        const bool leader = rank == 0;
-        if (valid && leader) wcnt[wave][digit] = __popcll(same);
-        __syncthreads();
-        // per digit: exclusive offsets over the waves of this round
-        {
-            uint32_t run = 0;
-            for (int w = 0; w < kRsWaves; ++w) {
-                uint32_t c = wcnt[w][tid];
-                wcnt[w][tid] = run;
-                run += c;
-            }
-            // run = total of digit tid in this round; add after the scatter
-            __syncthreads();
-            if (valid) {
-                const uint32_t pos = base[digit] + wcnt[wave][digit] + rank;
-                kout[pos] = key;
-                vout[pos] = val;
-            }
-            __syncthreads();
-            base[tid] += run;
-            for (int w = 0; w < kRsWaves; ++w) wcnt[w][tid] = 0;
-            __syncthreads();
-        }
+int items_of(uint32_t n) { return n >= kLargeFrom ? kItemsLarge : kItemsSmall; }
+
+uint32_t tiles_of(uint32_t n) { return ceil_div(n, (uint64_t)kThreads * items_of(n)); }
+
+template <class K>
+void launch_pass(const SortJob& J, K* k0, K* k1, uint32_t p, hipStream_t s) {
+    const dim3 g(tiles_of(J.n)), b(kThreads);
+    const auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, g, b, 0, s, J.raw, J.vinit, k0, J.v0, k1, J.v1, J.n, p, J.ctl, J.status);
+    };
+    if (items_of(J.n) == kItemsLarge) {
+        if (p == 0) go(rs_pass<K, kItemsLarge, true>);
+        else go(rs_pass<K, kItemsLarge, false>);
+    } else {
+        if (p == 0) go(rs_pass<K, kItemsSmall, true>);
+        else go(rs_pass<K, kItemsSmall, false>);
     }
 }
 
 }  // namespace
 
-size_t radix_hist_len(uint32_t n) { return (size_t)kRadix * ceil_div(n, kRsTile); }
+size_t sort_status_len(uint32_t n) {
+    // tiles of either size, so that a buffer sized for n serves any smaller input
+    const uint32_t small = std::min(n, kLargeFrom - 1);
+    return (size_t)kSortRadix * std::max(tiles_of(n), tiles_of(small));
+}
+
+size_t sort_status_used(uint32_t n) { return (size_t)kSortRadix * tiles_of(n); }
+
+int sort_clear(const SortJob& J, hipStream_t s, size_t extra) {
+    const uint64_t words = sort_status_used(J.n) + extra;
+    hipLaunchKernelGGL(rs_clear, dim3((uint32_t)std::min<uint64_t>((words + 255) / 256, 2048)),
+                       dim3(256), 0, s, reinterpret_cast<uint32_t*>(J.ctl), J.status, words);
+    TDS_HIP(hipGetLastError());
+    return TDS_OK;
+}
+
+int sort_plan(const SortJob& J, int key_bits, hipStream_t s) {
+    const int npass = (int)sort_npass(key_bits);
+    const uint32_t blocks = std::min(ceil_div(J.n, (uint64_t)kThreads * 4), 1024u);
+    hipLaunchKernelGGL(rs_hist, dim3(blocks), dim3(kThreads), 0, s, J.raw, (uint64_t)J.n, npass,
+                       J.ctl);
+    hipLaunchKernelGGL(rs_plan, dim3(1), dim3(kSortRadix), 0, s, J.ctl, npass, J.n);
+    TDS_HIP(hipGetLastError());
+    return TDS_OK;
+}
+
+int sort_passes(const SortJob& J, uint32_t npass, bool narrow, hipStream_t s) {
+    for (uint32_t p = 0; p < npass; ++p) {
+        if (narrow) {
+            // two arrays of 32-bit keys in the space of the second 64-bit one
+            uint32_t* a = reinterpret_cast<uint32_t*>(J.k1);
+            launch_pass<uint32_t>(J, a + J.n, a, p, s);
+        } else {
+            launch_pass<uint64_t>(J, J.k0, J.k1, p, s);
+        }
+    }
+    TDS_HIP(hipGetLastError());
+    return TDS_OK;
+}
 
 size_t scan_part_len(size_t len) { return (size_t)ceil_div(len, kScanTile) + 1; }
-
-int radix_sort_u64_digits(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
-                          uint32_t n, uint32_t digit_mask, hipStream_t stream, uint32_t* hist,
-                          uint32_t* part) {
-    if (n <= 1) return TDS_OK;
-    const uint32_t nblocks = ceil_div(n, kRsTile);
-    const uint64_t hlen = (uint64_t)kRadix * nblocks;
-    if (hlen >= (1ull << 32)) return TDS_E_INVALID;
-    const uint32_t nparts = ceil_div(hlen, kScanTile);
-    uint32_t* own_hist = nullptr;
-    uint32_t* own_part = nullptr;
-    if (!hist) {
-        TDS_TRY(dmalloc(&own_hist, hlen));
-        hist = own_hist;
-    }
-    if (!part) {
-        if (dmalloc(&own_part, (size_t)nparts + 1) != TDS_OK) {
-            dfree(own_hist);
-            return TDS_E_NOMEM;
-        }
-        part = own_part;
-    }
-    uint64_t* ka = keys;
-    uint32_t* va = vals;
-    uint64_t* kb = keys_alt;
-    uint32_t* vb = vals_alt;
-    int status = TDS_OK;
-    for (int p = 0; p < 8; ++p) {
-        if (!((digit_mask >> p) & 1u)) continue;
-        const int shift = 8 * p;
-        hipLaunchKernelGGL(rs_hist, dim3(nblocks), dim3(kRsThreads), 0, stream, ka, n, shift, hist,
-                           nblocks);
-        hipLaunchKernelGGL(rs_scan_part, dim3(nparts), dim3(kScanThreads), 0, stream, hist,
-                           (uint32_t)hlen, part);
-        hipLaunchKernelGGL(rs_scan_top, dim3(1), dim3(kScanThreads), 0, stream, part, nparts);
-        hipLaunchKernelGGL(rs_scan_down, dim3(nparts), dim3(kScanThreads), 0, stream, hist,
-                           (uint32_t)hlen, part);
-        hipLaunchKernelGGL(rs_scatter, dim3(nblocks), dim3(kRsThreads), 0, stream, ka, va, kb, vb,
-                           n, shift, hist, nblocks);
-        if (hipGetLastError() != hipSuccess) {
-            status = TDS_E_DEVICE;
-            break;
-        }
-        std::swap(ka, kb);
-        std::swap(va, vb);
-    }
-    if (status == TDS_OK && ka != keys) {
-        if (hipMemcpyAsync(keys, ka, (size_t)n * sizeof(uint64_t), hipMemcpyDeviceToDevice, stream) !=
-                hipSuccess ||
-            hipMemcpyAsync(vals, va, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, stream) !=
-                hipSuccess)
-            status = TDS_E_DEVICE;
-    }
-    if (own_hist || own_part) {
-        // buffers of this call: wait before freeing them
-        if (hipStreamSynchronize(stream) != hipSuccess) status = TDS_E_DEVICE;
-        dfree(own_hist);
-        dfree(own_part);
-    }
-    return status;
-}
-
-int radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
-                   uint32_t n, int key_bits, hipStream_t stream) {
-    const int passes = std::min(8, (key_bits + 7) / 8);
-    const uint32_t mask = (passes >= 8) ? 0xFFu : ((1u << passes) - 1u);
-    int st = radix_sort_u64_digits(keys, vals, keys_alt, vals_alt, n, mask, stream, nullptr, nullptr);
-    if (st == TDS_OK && hipStreamSynchronize(stream) != hipSuccess) st = TDS_E_DEVICE;
-    return st;
-}
 
 int exclusive_scan_u32(uint32_t* v, uint32_t len, uint32_t* total, hipStream_t stream) {
     return exclusive_scan_u32_with(v, len, total, stream, nullptr);

@@ -412,22 +412,6 @@ __host__ __device__ inline bool box_overlap(const Box32& b, const Box32& q) {
            (q.lz <= b.hz);
 }
 
-// Stable LSD radix sort of (key, value) pairs on `stream`; keys_bits is the
-// number of low key bits that may differ (passes of 8 bits).  Buffers *_alt
-// are scratch of the same size; the sorted data ends up in keys/vals.
-int radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
-                   uint32_t n, int key_bits, hipStream_t stream);
-
-// The same sort over the 8-bit digits set in digit_mask (bit p: key bits
-// 8p..8p+7), e.g. only the digits that differ between keys.  hist
-// (radix_hist_len(n) entries) and part (scan_part_len(radix_hist_len(n)))
-// are device scratch; when null they are allocated and freed by the call
-// (which then waits for the stream).  With caller scratch the call does not
-// wait: the sorted data is ready in stream order.
-int radix_sort_u64_digits(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
-                          uint32_t n, uint32_t digit_mask, hipStream_t stream, uint32_t* hist,
-                          uint32_t* part);
-size_t radix_hist_len(uint32_t n);
 size_t scan_part_len(size_t len);
 
 // Device segment staging: copies host arrays to the device when needed.

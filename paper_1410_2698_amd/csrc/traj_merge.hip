@@ -2,11 +2,25 @@
 // time intervals per (q_traj, e_traj) pair (the trajectory-level answer to
 // the motivating query of Sec. 1, built on the segment records of Sec. 3.1).
 //
-//   1. stable radix sort of the record indices by t_lo, then by the
-//      trajectory pair: the records in (q_traj, e_traj, t_lo) order, equal
-//      keys in input order.  One reduction first finds which 8-bit digits of
-//      the t_lo keys differ and how many bits the trajectory ids need, so the
-//      sorts make only the passes that can change the order;
+// One-pass form (pairs of at most kHalo records, every record an interval
+// with t_lo <= t_hi):
+//   1. k_pair_keys: the trajectory pair of every record, the largest ids and
+//      whether a record is no interval;
+//   2. a stable radix sort of the record positions by pair alone, the ids
+//      packed into as many bits as they need (32-bit keys where that is
+//      enough and the input large);
+//   3. k_merge_tiles: a workgroup takes the runs (records of one pair) that
+//      start in its tile of the sorted positions, reads their times once,
+//      orders each run by t_lo in LDS, finds where an interval starts (t_lo
+//      past every earlier t_hi of the run), learns the number of intervals
+//      before its own by look-back over the tiles, and writes its own.
+// No step needs a number on the host before it is launched, except that a
+// large input (kHostPlanFrom) waits once for the id ranges, which pays for
+// itself in passes not made.
+//
+// General form (a pair with more records than a tile's window, or a record
+// whose t_lo <= t_hi does not hold), found out on the device and run instead:
+//   1. stable radix sorts of the record positions by t_lo, then by pair;
 //   2. k_run_heads / scan: one run per trajectory pair;
 //   3. k_merge_runs<false>: one thread per run walks its records and counts
 //      the merged intervals (an interval is extended while the next record
@@ -16,7 +30,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "tds_internal.hpp"
+#include "radix_sort.hpp"
 
 namespace tds {
 
@@ -24,72 +38,287 @@ namespace {
 
 constexpr int kMT = 256;
 
+// Why the one-pass form does not apply (SortControl::odd).
+constexpr uint32_t kOddRecord = 1, kOddRun = 2;
+
 __device__ inline uint64_t order_key_f64(double t) {
     // order-preserving map of a double to u64 (-0 and +0 are equal)
     uint64_t u = (t == 0.0) ? 0ull : (uint64_t)__double_as_longlong(t);
     return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
 
-// red[0] = OR of the t_lo keys, red[1] = AND, red[2] = max q_traj, red[3] =
-// max e_traj (k_red_init sets the identities).
-__global__ void k_red_init(unsigned long long* red) {
-    red[0] = 0ull;
-    red[1] = ~0ull;
-    red[2] = 0ull;
-    red[3] = 0ull;
-}
-
-__global__ __launch_bounds__(kMT) void k_keys_tlo(const tds_result* __restrict__ recs, uint32_t n,
-                                                  uint64_t* __restrict__ keys,
-                                                  uint32_t* __restrict__ vals,
-                                                  unsigned long long* red) {
-    __shared__ unsigned long long s_or[kMT], s_and[kMT], s_q[kMT], s_e[kMT];
-    const uint32_t i = blockIdx.x * kMT + threadIdx.x;
-    unsigned long long ko = 0ull, ka = ~0ull, mq = 0ull, me = 0ull;
-    if (i < n) {
+// Pair keys (q_traj << 32 | e_traj), the largest ids and the records that
+// are no intervals.  Reads every record once (32 bytes) and writes 8: bound by
+// HBM.  The workgroups loop and add to the control block once each: with one
+// workgroup per 256 records and four atomics each on one line this step took
+// 30 ms of the 73 ms of a merge of 171e6 records.
+__global__ __launch_bounds__(kMT) void k_pair_keys(const tds_result* __restrict__ recs, uint32_t n,
+                                                   uint64_t* __restrict__ keys,
+                                                   SortControl* __restrict__ ctl) {
+    __shared__ uint32_t s_q[kMT], s_e[kMT], s_o[kMT];
+    uint32_t mq = 0, me = 0, odd = 0;
+    for (uint64_t i = (uint64_t)blockIdx.x * kMT + threadIdx.x; i < n;
+         i += (uint64_t)gridDim.x * kMT) {
         const tds_result r = recs[i];
-        const uint64_t k = order_key_f64(r.t_lo);
-        keys[i] = k;
-        vals[i] = i;
-        ko = ka = k;
-        mq = r.q_traj;
-        me = r.e_traj;
+        keys[i] = ((uint64_t)r.q_traj << 32) | r.e_traj;
+        mq = max(mq, r.q_traj);
+        me = max(me, r.e_traj);
+        if (!(r.t_lo <= r.t_hi)) odd = kOddRecord;
     }
-    s_or[threadIdx.x] = ko;
-    s_and[threadIdx.x] = ka;
     s_q[threadIdx.x] = mq;
     s_e[threadIdx.x] = me;
+    s_o[threadIdx.x] = odd;
     __syncthreads();
     for (uint32_t off = kMT / 2; off > 0; off >>= 1) {
         if (threadIdx.x < off) {
-            s_or[threadIdx.x] |= s_or[threadIdx.x + off];
-            s_and[threadIdx.x] &= s_and[threadIdx.x + off];
             s_q[threadIdx.x] = max(s_q[threadIdx.x], s_q[threadIdx.x + off]);
             s_e[threadIdx.x] = max(s_e[threadIdx.x], s_e[threadIdx.x + off]);
+            s_o[threadIdx.x] |= s_o[threadIdx.x + off];
         }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        atomicOr(&red[0], s_or[0]);
-        atomicAnd(&red[1], s_and[0]);
-        atomicMax(&red[2], s_q[0]);
-        atomicMax(&red[3], s_e[0]);
+        atomicMax(&ctl->max_high, s_q[0]);
+        atomicMax(&ctl->max_low, s_e[0]);
+        if (s_o[0]) atomicOr(&ctl->odd, s_o[0]);
+        ctl->pairs = 1;  // the same value from every workgroup
     }
 }
 
-// Pair key q_traj << e_bits | e_traj (e_bits: bits of the largest e_traj).
+// Tiles of the one-pass merge: kTilePos sorted positions, whose runs may
+// reach kHalo positions past the tile's end.  1,536 positions of times and
+// keys are 44 KB of LDS (38 with 32-bit keys): three or four workgroups of
+// eight waves per compute unit.  kHalo bounds the records per pair: a pair of
+// trajectories of 400 time steps has at most 400 or so.
+constexpr int kTileThreads = 512;
+constexpr uint32_t kTilePos = 1024, kHalo = 512, kWindow = kTilePos + kHalo;
+constexpr uint32_t kPerThread = kWindow / kTileThreads;
+constexpr uint16_t kNoRun = 0xFFFFu;
+constexpr uint64_t kTileOwn = 1ull << 62, kTileSum = 2ull << 62, kTileCount = (1ull << 62) - 1;
+
+// Exclusive prefix over the workgroup of one value per thread (op: max or +).
+template <class Op>
+__device__ inline uint32_t block_excl(uint32_t v, uint32_t id, Op op, uint32_t* s_w,
+                                      uint32_t* total) {
+    const uint32_t lane = __lane_id(), wv = threadIdx.x / kWave;
+    uint32_t x = v;
+    for (uint32_t o = 1; o < kWave; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o);
+        if (lane >= o) x = op(x, y);
+    }
+    if (lane == kWave - 1) s_w[wv] = x;
+    const uint32_t up = __shfl_up(x, 1);
+    __syncthreads();
+    uint32_t before = id, all = id;
+    for (uint32_t k = 0; k < (uint32_t)(kTileThreads / kWave); ++k) {
+        if (k < wv) before = op(before, s_w[k]);
+        all = op(all, s_w[k]);
+    }
+    __syncthreads();
+    *total = all;
+    return lane ? op(before, up) : before;
+}
+
+// What bounds it: the gather of the records' times (16 bytes of a 32-byte
+// record, at the record's place in the input) and, for long runs, the LDS
+// reads of the ordering (each record compares itself with its run).  The walk
+// by one thread per run that this replaces read every record twice, each
+// thread one after another.
+template <class K>
+__global__ __launch_bounds__(kTileThreads) void k_merge_tiles(
+    const tds_result* __restrict__ recs, const K* __restrict__ k0, const K* __restrict__ k1,
+    const uint32_t* __restrict__ v0, const uint32_t* __restrict__ v1, uint32_t n,
+    SortControl* __restrict__ ctl, uint64_t* __restrict__ tstat,
+    tds_traj_interval* __restrict__ out, uint64_t capacity) {
+    __shared__ K s_key[kWindow];
+    __shared__ double s_lo[kWindow], s_hi[kWindow];
+    __shared__ uint16_t s_beg[kWindow];  // first position of the run, kNoRun: not this tile's
+    __shared__ uint16_t s_end[kWindow];  // of a run's first position: its end
+    __shared__ uint8_t s_first[kWindow];  // an interval starts here
+    __shared__ uint32_t s_w[kTileThreads / kWave];
+    __shared__ uint32_t s_tile;
+    __shared__ uint64_t s_base;
+    const uint32_t tid = threadIdx.x, lane = __lane_id();
+    if (tid == 0) s_tile = atomicAdd(&ctl->merge_ticket, 1u);
+    __syncthreads();
+    const uint32_t tile = s_tile;
+    const uint64_t base = (uint64_t)tile * kTilePos;
+    const uint32_t cnt = (uint32_t)min((uint64_t)kWindow, (uint64_t)n - base);
+    const K* keys = ctl->side() ? k1 : k0;
+    const uint32_t* vals = ctl->side() ? v1 : v0;
+    for (uint32_t l = tid; l < cnt; l += kTileThreads) s_key[l] = keys[base + l];
+    const K prev = base ? keys[base - 1] : (K)0;
+    __syncthreads();
+    // run starts: thread t looks at positions [3t, 3t + 3)
+    {
+        const uint32_t l0 = tid * kPerThread;
+        uint32_t h[kPerThread], last = 0;  // position + 1 of a run start, 0: none
+        for (uint32_t j = 0; j < kPerThread; ++j) {
+            const uint32_t l = l0 + j;
+            bool head = false;
+            if (l < cnt) head = l ? s_key[l] != s_key[l - 1] : (base == 0 || s_key[0] != prev);
+            h[j] = head ? l + 1 : 0u;
+            last = max(last, h[j]);
+        }
+        uint32_t all;
+        uint32_t run = block_excl(last, 0u, [](uint32_t a, uint32_t b) { return max(a, b); }, s_w,
+                                  &all);
+        for (uint32_t j = 0; j < kPerThread; ++j) {
+            const uint32_t l = l0 + j;
+            if (h[j]) {
+                if (run) s_end[run - 1] = (uint16_t)l;
+                run = h[j];
+            }
+            // runs that start in the halo are the next tile's
+            s_beg[l] = (l < cnt && run && run <= kTilePos) ? (uint16_t)(run - 1) : kNoRun;
+            s_first[l] = 0;
+        }
+        if (tid == 0 && all) {
+            s_end[all - 1] = (uint16_t)cnt;
+            if (base + cnt < n && all <= kTilePos) atomicOr(&ctl->odd, kOddRun);
+        }
+    }
+    __syncthreads();
+    for (uint32_t l = tid; l < kWindow; l += kTileThreads)
+        if (s_beg[l] != kNoRun) {
+            const tds_result& r = recs[vals[base + l]];
+            s_lo[l] = r.t_lo;
+            s_hi[l] = r.t_hi;
+        }
+    __syncthreads();
+    // order every run by t_lo (records that start together stay in input order)
+    {
+        double lo[kPerThread], hi[kPerThread];
+        uint32_t to[kPerThread];
+#pragma unroll
+        for (uint32_t j = 0; j < kPerThread; ++j) {
+            const uint32_t l = tid + j * kTileThreads;
+            to[j] = kWindow;
+            const uint32_t b = s_beg[l];
+            if (b == kNoRun) continue;
+            const uint32_t e = s_end[b];
+            lo[j] = s_lo[l];
+            hi[j] = s_hi[l];
+            uint32_t r = b;
+            for (uint32_t m = b; m < e; ++m) {
+                const double x = s_lo[m];
+                r += (m < l ? x <= lo[j] : x < lo[j]) ? 1u : 0u;
+            }
+            to[j] = r;
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t j = 0; j < kPerThread; ++j)
+            if (to[j] < kWindow) {
+                s_lo[to[j]] = lo[j];
+                s_hi[to[j]] = hi[j];
+            }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < kPerThread; ++j) {
+        const uint32_t l = tid + j * kTileThreads;
+        const uint32_t b = s_beg[l];
+        if (b == kNoRun) continue;
+        const double lo = s_lo[l];
+        bool first = true;
+        for (uint32_t m = b; m < l; ++m) first = first && lo > s_hi[m];
+        s_first[l] = first ? 1 : 0;
+    }
+    __syncthreads();
+    const uint32_t l0 = tid * kPerThread;
+    uint32_t c = 0, all;
+    for (uint32_t j = 0; j < kPerThread; ++j) c += s_first[l0 + j];
+    uint32_t at = block_excl(c, 0u, [](uint32_t a, uint32_t b) { return a + b; }, s_w, &all);
+    // intervals of the tiles before this one: the first wave looks back, 64
+    // tiles at a time
+    if (tid < kWave) {
+        if (lane == 0)
+            __hip_atomic_store(tstat + tile, (tile ? kTileOwn : kTileSum) | all, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t sum = 0;
+        bool done = tile == 0;
+        int64_t p = (int64_t)tile - 1;
+        while (!done) {
+            const uint64_t w = p >= (int64_t)lane
+                                   ? __hip_atomic_load(tstat + (p - lane), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT)
+                                   : 0ull;
+            const uint64_t unready = __ballot((w >> 62) == 0), sums = __ballot((w >> 62) == 2);
+            const uint32_t ready = unready ? (uint32_t)__ffsll((unsigned long long)unready) - 1u
+                                           : (uint32_t)kWave;
+            uint32_t take = ready;  // leading words that are published
+            if (sums) {
+                const uint32_t s = (uint32_t)__ffsll((unsigned long long)sums) - 1u;
+                if (s < ready) {
+                    take = s + 1;
+                    done = true;
+                }
+            }
+            uint64_t x = lane < take ? w & kTileCount : 0ull;
+            for (int o = kWave / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
+            sum += x;
+            p -= take;
+        }
+        if (lane == 0) {
+            if (tile)
+                __hip_atomic_store(tstat + tile, kTileSum | (sum + all), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            s_base = sum;
+            if (base + kTilePos >= n) ctl->total = sum + all;
+        }
+    }
+    __syncthreads();
+    const PairPack pk = ctl->pack();
+    for (uint32_t j = 0; j < kPerThread; ++j) {
+        const uint32_t l = l0 + j;
+        if (!s_first[l]) continue;
+        const uint64_t pos = s_base + at;
+        ++at;
+        if (pos >= capacity) continue;
+        const uint32_t e = s_end[s_beg[l]];
+        double hi = s_hi[l];
+        for (uint32_t m = l + 1; m < e && !s_first[m]; ++m)
+            if (s_hi[m] > hi) hi = s_hi[m];
+        tds_traj_interval o;
+        o.q_traj = pk.high((uint64_t)s_key[l]);
+        o.e_traj = pk.low((uint64_t)s_key[l]);
+        o.t_lo = s_lo[l];
+        o.t_hi = hi;
+        out[pos] = o;
+    }
+}
+
+// ------------------------------------------------------------ general form
+
+__global__ __launch_bounds__(kMT) void k_keys_tlo(const tds_result* __restrict__ recs, uint32_t n,
+                                                  uint64_t* __restrict__ keys) {
+    const uint32_t i = blockIdx.x * kMT + threadIdx.x;
+    if (i < n) keys[i] = order_key_f64(recs[i].t_lo);
+}
+
+// The first sort's values to v, and the pair keys in that order (which sort
+// side holds it follows from the control block).
 __global__ __launch_bounds__(kMT) void k_keys_pair(const tds_result* __restrict__ recs, uint32_t n,
-                                                   const uint32_t* __restrict__ vals, uint32_t e_bits,
+                                                   const uint32_t* __restrict__ v0,
+                                                   const uint32_t* __restrict__ v1,
+                                                   const SortControl* __restrict__ ctl,
+                                                   uint32_t* __restrict__ v,
                                                    uint64_t* __restrict__ keys) {
     const uint32_t i = blockIdx.x * kMT + threadIdx.x;
     if (i >= n) return;
-    const tds_result r = recs[vals[i]];
-    keys[i] = ((uint64_t)r.q_traj << e_bits) | r.e_traj;
+    const uint32_t x = ctl->side() ? v1[i] : v0[i];
+    const tds_result r = recs[x];
+    v[i] = x;
+    keys[i] = ((uint64_t)r.q_traj << 32) | r.e_traj;
 }
 
 // head[i] = 1 where a new trajectory pair starts in sorted order.
-__global__ __launch_bounds__(kMT) void k_run_heads(const uint64_t* __restrict__ keys, uint32_t n,
+__global__ __launch_bounds__(kMT) void k_run_heads(const uint64_t* __restrict__ k0,
+                                                   const uint64_t* __restrict__ k1,
+                                                   const SortControl* __restrict__ ctl, uint32_t n,
                                                    uint32_t* __restrict__ head) {
+    const uint64_t* keys = ctl->side() ? k1 : k0;
     const uint32_t i = blockIdx.x * kMT + threadIdx.x;
     if (i >= n) return;
     head[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1u : 0u;
@@ -97,10 +326,13 @@ __global__ __launch_bounds__(kMT) void k_run_heads(const uint64_t* __restrict__ 
 
 // run_start[run index] = first sorted position of the run (from the
 // exclusive scan of the heads and the heads themselves).
-__global__ __launch_bounds__(kMT) void k_run_starts(const uint64_t* __restrict__ keys, uint32_t n,
+__global__ __launch_bounds__(kMT) void k_run_starts(const uint64_t* __restrict__ k0,
+                                                    const uint64_t* __restrict__ k1,
+                                                    const SortControl* __restrict__ ctl, uint32_t n,
                                                     const uint32_t* __restrict__ run_of,
                                                     uint32_t* __restrict__ run_start,
                                                     uint32_t n_runs) {
+    const uint64_t* keys = ctl->side() ? k1 : k0;
     const uint32_t i = blockIdx.x * kMT + threadIdx.x;
     if (i >= n) return;
     if (i == 0 || keys[i] != keys[i - 1]) run_start[run_of[i]] = i;
@@ -111,13 +343,16 @@ __global__ __launch_bounds__(kMT) void k_run_starts(const uint64_t* __restrict__
 // (kWrite false: cnt[r]) or written from offset cnt[r] (kWrite true).
 template <bool kWrite>
 __global__ __launch_bounds__(kMT) void k_merge_runs(const tds_result* __restrict__ recs,
-                                                    const uint32_t* __restrict__ order,
+                                                    const uint32_t* __restrict__ v0,
+                                                    const uint32_t* __restrict__ v1,
+                                                    const SortControl* __restrict__ ctl,
                                                     const uint32_t* __restrict__ run_start,
                                                     uint32_t n_runs, uint32_t* __restrict__ cnt,
                                                     tds_traj_interval* __restrict__ out,
                                                     uint64_t capacity) {
     const uint32_t r = blockIdx.x * kMT + threadIdx.x;
     if (r >= n_runs) return;
+    const uint32_t* order = ctl->side() ? v1 : v0;
     const uint32_t b = run_start[r], e = run_start[r + 1];
     uint64_t pos = kWrite ? cnt[r] : 0u;
     uint32_t c = 0;
@@ -157,65 +392,88 @@ __global__ __launch_bounds__(kMT) void k_merge_runs(const tds_result* __restrict
 // size; allocating and freeing per call cost more than the kernels).
 struct MergeScratch {
     std::mutex mu;
-    size_t cap = 0;  // records the buffers hold
-    tds_result* recs = nullptr;
-    uint64_t *k1 = nullptr, *k2 = nullptr;
-    uint32_t *v1 = nullptr, *v2 = nullptr, *runs = nullptr, *run_start = nullptr, *cnt = nullptr;
-    uint32_t *hist = nullptr, *part = nullptr;
-    tds_traj_interval* stage = nullptr;
-    unsigned long long* red = nullptr;
-    unsigned long long* red_host = nullptr;  // pinned
+    size_t cap = 0, rec_cap = 0, out_cap = 0, run_cap = 0;  // records each part holds
+    tds_result* recs = nullptr;          // host input
+    tds_traj_interval* stage = nullptr;  // host output
+    uint64_t *k1 = nullptr, *k2 = nullptr, *status = nullptr;
+    uint32_t *v1 = nullptr, *v2 = nullptr;
+    // general form
+    uint32_t *vfirst = nullptr, *runs = nullptr, *run_start = nullptr, *cnt = nullptr,
+             *part = nullptr;
+    SortControl* ctl = nullptr;
+    SortControl* ctl_host = nullptr;  // pinned; the fields before the counts
 
-    void release() {
-        dfree(recs);
-        dfree(k1);
-        dfree(k2);
-        dfree(v1);
-        dfree(v2);
-        dfree(runs);
-        dfree(run_start);
-        dfree(cnt);
-        dfree(hist);
-        dfree(part);
-        dfree(stage);
-        recs = nullptr;
-        k1 = k2 = nullptr;
-        v1 = v2 = runs = run_start = cnt = hist = part = nullptr;
-        stage = nullptr;
-        cap = 0;
+    template <class... P>
+    static void drop(size_t& c, P&... p) {
+        (dfree(p), ...);
+        ((p = nullptr), ...);
+        c = 0;
     }
 
     int reserve(size_t n) {
-        if (!red) {
-            TDS_TRY(dmalloc(&red, 4));
-            if (hipHostMalloc(reinterpret_cast<void**>(&red_host), 4 * sizeof(unsigned long long),
+        if (!ctl) TDS_TRY(dmalloc(&ctl, 1));
+        if (!ctl_host) {
+            if (hipHostMalloc(reinterpret_cast<void**>(&ctl_host), sizeof(SortControl),
                               hipHostMallocDefault) != hipSuccess) {
                 (void)hipGetLastError();
-                red_host = nullptr;
+                ctl_host = nullptr;
                 return TDS_E_NOMEM;
             }
         }
         if (n <= cap) return TDS_OK;
-        release();
+        drop(cap, k1, k2, status, v1, v2);
         const size_t c = std::max<size_t>(n, 1024);
-        const size_t parts = std::max(scan_part_len(radix_hist_len((uint32_t)c)), scan_part_len(c));
-        int st = TDS_OK;
-        if (st == TDS_OK) st = dmalloc(&recs, c);
-        if (st == TDS_OK) st = dmalloc(&k1, c);
+        int st = dmalloc(&k1, c);
         if (st == TDS_OK) st = dmalloc(&k2, c);
         if (st == TDS_OK) st = dmalloc(&v1, c);
         if (st == TDS_OK) st = dmalloc(&v2, c);
-        if (st == TDS_OK) st = dmalloc(&runs, c);
-        if (st == TDS_OK) st = dmalloc(&run_start, c + 1);
-        if (st == TDS_OK) st = dmalloc(&cnt, c);
-        if (st == TDS_OK) st = dmalloc(&hist, radix_hist_len((uint32_t)c));
-        if (st == TDS_OK) st = dmalloc(&part, parts);
-        if (st == TDS_OK) st = dmalloc(&stage, c);
+        if (st == TDS_OK)
+            st = dmalloc(&status, sort_status_len((uint32_t)c) + ceil_div(c, kTilePos) + 1);
         if (st != TDS_OK) {
-            release();
+            drop(cap, k1, k2, status, v1, v2);
             return st;
         }
         cap = c;
+        return TDS_OK;
+    }
+
+    int reserve_recs(size_t n) {
+        if (n <= rec_cap) return TDS_OK;
+        drop(rec_cap, recs);
+        TDS_TRY(dmalloc(&recs, n));
+        rec_cap = n;
+        return TDS_OK;
+    }
+
+    int reserve_out(size_t n) {
+        if (n <= out_cap) return TDS_OK;
+        drop(out_cap, stage);
+        TDS_TRY(dmalloc(&stage, n));
+        out_cap = n;
+        return TDS_OK;
+    }
+
+    int reserve_runs(size_t n) {
+        if (n <= run_cap) return TDS_OK;
+        drop(run_cap, vfirst, runs, run_start, cnt, part);
+        int st = dmalloc(&vfirst, n);
+        if (st == TDS_OK) st = dmalloc(&runs, n);
+        if (st == TDS_OK) st = dmalloc(&run_start, n + 1);
+        if (st == TDS_OK) st = dmalloc(&cnt, n);
+        if (st == TDS_OK) st = dmalloc(&part, scan_part_len(n));
+        if (st != TDS_OK) {
+            drop(run_cap, vfirst, runs, run_start, cnt, part);
+            return st;
+        }
+        run_cap = n;
+        return TDS_OK;
+    }
+
+    // the control block's fields before the digit counts, after the stream's work
+    int read_ctl(hipStream_t s) {
+        TDS_HIP(hipMemcpyAsync(ctl_host, ctl, offsetof(SortControl, hist), hipMemcpyDeviceToHost,
+                               s));
+        TDS_HIP(hipStreamSynchronize(s));
         return TDS_OK;
     }
 };
@@ -223,22 +481,47 @@ struct MergeScratch {
 constexpr int kMaxDevices = 64;
 MergeScratch g_scratch[kMaxDevices];
 
-// 8-bit digits in which some of the keys differ.
-uint32_t varying_digits(uint64_t ored, uint64_t anded) {
-    const uint64_t v = ored ^ anded;
-    uint32_t m = 0;
-    for (int p = 0; p < 8; ++p)
-        if ((v >> (8 * p)) & 0xFFull) m |= 1u << p;
-    return m;
-}
+// Records from which the host waits for the id ranges before the sort: then it
+// launches the passes that they need instead of all eight (a launch that has
+// nothing to do costs about 3 us; the wait about 40), and 32-bit keys are a
+// third less traffic per pass.
+constexpr uint32_t kHostPlanFrom = 1u << 20;
 
-uint32_t bit_width(uint64_t v) {
-    uint32_t b = 0;
-    while (v) {
-        ++b;
-        v >>= 1;
+// The general form; the records are on the device.  Leaves the first `keep` =
+// min(total, capacity) intervals in dst.
+int merge_general(MergeScratch& M, const tds_result* R, uint32_t nn, SortJob J,
+                  tds_traj_interval* dst, uint64_t capacity, uint32_t* total, hipStream_t s) {
+    TDS_TRY(M.reserve_runs(nn));
+    const uint32_t nb = ceil_div(nn, kMT);
+    TDS_TRY(sort_clear(J, s));
+    hipLaunchKernelGGL(k_keys_tlo, dim3(nb), dim3(kMT), 0, s, R, nn, M.k1);
+    TDS_TRY(sort_plan(J, 64, s));
+    TDS_TRY(sort_passes(J, 8, false, s));
+    hipLaunchKernelGGL(k_keys_pair, dim3(nb), dim3(kMT), 0, s, R, nn, M.v1, M.v2, M.ctl, M.vfirst,
+                       M.k1);
+    J.vinit = M.vfirst;
+    TDS_TRY(sort_clear(J, s));
+    TDS_TRY(sort_plan(J, 64, s));
+    TDS_TRY(sort_passes(J, 8, false, s));
+    // runs of equal pairs
+    hipLaunchKernelGGL(k_run_heads, dim3(nb), dim3(kMT), 0, s, M.k1, M.k2, M.ctl, nn, M.runs);
+    TDS_HIP(hipGetLastError());
+    uint32_t n_runs = 0;
+    TDS_TRY(exclusive_scan_u32_with(M.runs, nn, &n_runs, s, M.part));
+    hipLaunchKernelGGL(k_run_starts, dim3(nb), dim3(kMT), 0, s, M.k1, M.k2, M.ctl, nn, M.runs,
+                       M.run_start, n_runs);
+    const uint32_t rb = ceil_div(n_runs, kMT);
+    hipLaunchKernelGGL(k_merge_runs<false>, dim3(rb), dim3(kMT), 0, s, R, M.v1, M.v2, M.ctl,
+                       M.run_start, n_runs, M.cnt, nullptr, 0ull);
+    TDS_HIP(hipGetLastError());
+    TDS_TRY(exclusive_scan_u32_with(M.cnt, n_runs, total, s, M.part));
+    const uint64_t keep = std::min<uint64_t>(*total, capacity);
+    if (keep) {
+        hipLaunchKernelGGL(k_merge_runs<true>, dim3(rb), dim3(kMT), 0, s, R, M.v1, M.v2, M.ctl,
+                           M.run_start, n_runs, M.cnt, dst, keep);
+        TDS_HIP(hipGetLastError());
     }
-    return b;
+    return TDS_OK;
 }
 
 }  // namespace
@@ -258,55 +541,61 @@ int merge_impl(const tds_result* recs, uint64_t n, bool recs_dev, tds_traj_inter
     std::lock_guard<std::mutex> lock(M.mu);
     TDS_TRY(M.reserve(n));
     const uint32_t nn = (uint32_t)n;
-    const uint32_t nb = ceil_div(nn, kMT);
     const tds_result* R = recs;
     if (!recs_dev) {
+        TDS_TRY(M.reserve_recs(n));
         TDS_HIP(hipMemcpyAsync(M.recs, recs, n * sizeof(tds_result), hipMemcpyHostToDevice, s));
         R = M.recs;
     }
-    // keys, and which digits and id bits the sorts need
-    hipLaunchKernelGGL(k_red_init, dim3(1), dim3(1), 0, s, M.red);
-    hipLaunchKernelGGL(k_keys_tlo, dim3(nb), dim3(kMT), 0, s, R, nn, M.k1, M.v1, M.red);
-    TDS_HIP(hipGetLastError());
-    TDS_HIP(hipMemcpyAsync(M.red_host, M.red, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                           s));
-    TDS_HIP(hipStreamSynchronize(s));
-    const uint32_t t_digits = varying_digits(M.red_host[0], M.red_host[1]);
-    const uint32_t e_bits = std::max(1u, bit_width(M.red_host[3]));
-    const uint32_t pair_bits = bit_width(M.red_host[2]) + e_bits;
-    const uint32_t pair_digits = (pair_bits >= 64) ? 0xFFu : ((1u << ((pair_bits + 7) / 8)) - 1u);
-    // (q_traj, e_traj, t_lo) order: by t_lo, then stably by the pair
-    TDS_TRY(radix_sort_u64_digits(M.k1, M.v1, M.k2, M.v2, nn, t_digits, s, M.hist, M.part));
-    hipLaunchKernelGGL(k_keys_pair, dim3(nb), dim3(kMT), 0, s, R, nn, M.v1, e_bits, M.k1);
-    TDS_HIP(hipGetLastError());
-    TDS_TRY(radix_sort_u64_digits(M.k1, M.v1, M.k2, M.v2, nn, pair_digits, s, M.hist, M.part));
-    // runs of equal pairs
-    hipLaunchKernelGGL(k_run_heads, dim3(nb), dim3(kMT), 0, s, M.k1, nn, M.runs);
-    TDS_HIP(hipGetLastError());
-    uint32_t n_runs = 0;
-    TDS_TRY(exclusive_scan_u32_with(M.runs, nn, &n_runs, s, M.part));
-    hipLaunchKernelGGL(k_run_starts, dim3(nb), dim3(kMT), 0, s, M.k1, nn, M.runs, M.run_start,
-                       n_runs);
-    const uint32_t rb = ceil_div(n_runs, kMT);
-    hipLaunchKernelGGL(k_merge_runs<false>, dim3(rb), dim3(kMT), 0, s, R, M.v1, M.run_start, n_runs,
-                       M.cnt, nullptr, 0ull);
-    TDS_HIP(hipGetLastError());
-    uint32_t total = 0;
-    TDS_TRY(exclusive_scan_u32_with(M.cnt, n_runs, &total, s, M.part));
-    *n_out = total;
-    const uint64_t keep = std::min<uint64_t>(total, capacity);
-    if (keep) {
-        // at most one interval per record, so the staging buffer fits
-        tds_traj_interval* dst = out_dev ? out : M.stage;
-        hipLaunchKernelGGL(k_merge_runs<true>, dim3(rb), dim3(kMT), 0, s, R, M.v1, M.run_start,
-                           n_runs, M.cnt, dst, keep);
-        TDS_HIP(hipGetLastError());
-        if (!out_dev)
-            TDS_HIP(hipMemcpyAsync(out, M.stage, keep * sizeof(tds_traj_interval),
-                                   hipMemcpyDeviceToHost, s));
-        TDS_HIP(hipStreamSynchronize(s));
+    // at most one interval per record, so a staging buffer of n fits
+    tds_traj_interval* dst = out;
+    if (!out_dev && capacity) {
+        TDS_TRY(M.reserve_out(std::min<uint64_t>(n, capacity)));
+        dst = M.stage;
     }
-    return total > capacity ? TDS_E_OVERFLOW : TDS_OK;
+    const uint64_t cap = std::min<uint64_t>(n, capacity);
+    SortJob J{nn, M.k1, nullptr, M.k1, M.k2, M.v1, M.v2, M.ctl, M.status};
+    const uint32_t tiles = ceil_div(nn, kTilePos);
+    uint64_t* tstat = M.status + sort_status_used(nn);
+    TDS_TRY(sort_clear(J, s, tiles));
+    hipLaunchKernelGGL(k_pair_keys, dim3(std::min(ceil_div(nn, kMT), 2048u)), dim3(kMT), 0, s, R,
+                       nn, M.k1, M.ctl);
+    TDS_HIP(hipGetLastError());
+    int bits = 64;
+    bool narrow = false, one_pass = true;
+    if (nn >= kHostPlanFrom) {
+        TDS_TRY(M.read_ctl(s));
+        bits = (int)(bits_of(M.ctl_host->max_high) + bits_of(M.ctl_host->max_low));
+        narrow = bits <= 32;
+        one_pass = !M.ctl_host->odd;
+    }
+    if (one_pass) {
+        TDS_TRY(sort_plan(J, bits, s));
+        TDS_TRY(sort_passes(J, sort_npass(bits), narrow, s));
+        if (narrow) {
+            const uint32_t* a = reinterpret_cast<const uint32_t*>(M.k2);
+            hipLaunchKernelGGL(k_merge_tiles<uint32_t>, dim3(tiles), dim3(kTileThreads), 0, s, R,
+                               a + nn, a, M.v1, M.v2, nn, M.ctl, tstat, dst, cap);
+        } else {
+            hipLaunchKernelGGL(k_merge_tiles<uint64_t>, dim3(tiles), dim3(kTileThreads), 0, s, R,
+                               M.k1, M.k2, M.v1, M.v2, nn, M.ctl, tstat, dst, cap);
+        }
+        TDS_HIP(hipGetLastError());
+        TDS_TRY(M.read_ctl(s));
+        one_pass = !M.ctl_host->odd;
+        *n_out = M.ctl_host->total;
+    }
+    if (!one_pass) {
+        uint32_t total = 0;
+        TDS_TRY(merge_general(M, R, nn, J, dst, cap, &total, s));
+        *n_out = total;
+    }
+    const uint64_t keep = std::min<uint64_t>(*n_out, capacity);
+    if (keep && !out_dev)
+        TDS_HIP(hipMemcpyAsync(out, M.stage, keep * sizeof(tds_traj_interval),
+                               hipMemcpyDeviceToHost, s));
+    if (keep && (!out_dev || !one_pass)) TDS_HIP(hipStreamSynchronize(s));
+    return *n_out > capacity ? TDS_E_OVERFLOW : TDS_OK;
 }
 
 }  // namespace tds
