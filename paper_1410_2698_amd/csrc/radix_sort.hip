@@ -20,7 +20,7 @@
 // and a value once), launches for small ones (one per digit here).  Before, a
 // pass was five launches (count, three scan steps, scatter), read the keys
 // twice and wrote each key straight to its place from the lane that held it:
-// 2.1-3.1 ms per pass at 171e6 pairs, 5 x 4 us at 86,000.
+// 2.1-3.1 ms per pass at 171e6 pairs (now 1.1-1.3) and 40 us at 1e6 (now 22).
 //
 // Tiles are taken in order from a counter, so every tile before a waiting one
 // is held by a workgroup that is running and publishes its counts without
@@ -34,8 +34,7 @@ namespace tds {
 namespace {
 
 constexpr int kRadix = kSortRadix;
-constexpr int kThreads = kSortThreads;
-constexpr int kWaves = kThreads / kWave;
+constexpr int kHistThreads = 512;
 
 // Look-back status word of one (tile, digit): the pass it belongs to, whether
 // it is the tile's own count or the sum up to and including the tile, and the
@@ -64,18 +63,18 @@ __global__ __launch_bounds__(256) void rs_clear(uint32_t* __restrict__ ctl,
 // Digit counts of all passes.  A wave whose keys share a digit adds 64 to it
 // at once (keys that come sorted, or high digits that hardly vary, would
 // otherwise queue 64 atomics on one LDS address).
-__global__ __launch_bounds__(kThreads) void rs_hist(const uint64_t* __restrict__ keys, uint64_t n,
+__global__ __launch_bounds__(kHistThreads) void rs_hist(const uint64_t* __restrict__ keys, uint64_t n,
                                                     int npass, SortControl* __restrict__ ctl) {
     __shared__ uint32_t h[8][kRadix];
     const uint32_t tid = threadIdx.x;
     for (int p = 0; p < npass; ++p)
-        for (uint32_t d = tid; d < (uint32_t)kRadix; d += kThreads) h[p][d] = 0;
+        for (uint32_t d = tid; d < (uint32_t)kRadix; d += kHistThreads) h[p][d] = 0;
     __syncthreads();
     const PairPack pk = ctl->pack();
-    const uint64_t step = (uint64_t)gridDim.x * kThreads;
+    const uint64_t step = (uint64_t)gridDim.x * kHistThreads;
     const uint64_t rounds = (n + step - 1) / step;
     for (uint64_t r = 0; r < rounds; ++r) {
-        const uint64_t i = r * step + (uint64_t)blockIdx.x * kThreads + tid;
+        const uint64_t i = r * step + (uint64_t)blockIdx.x * kHistThreads + tid;
         const bool valid = i < n;
         const uint64_t key = valid ? pk.apply(keys[i]) : 0ull;
         const bool full = __ballot(valid) == ~0ull;
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(kThreads) void rs_hist(const uint64_t* __restrict__
     }
     __syncthreads();
     for (int p = 0; p < npass; ++p)
-        for (uint32_t d = tid; d < (uint32_t)kRadix; d += kThreads)
+        for (uint32_t d = tid; d < (uint32_t)kRadix; d += kHistThreads)
             if (h[p][d]) atomicAdd(&ctl->hist[p][d], h[p][d]);
 }
 
@@ -133,6 +132,42 @@ __global__ __launch_bounds__(kRadix) void rs_plan(SortControl* __restrict__ ctl,
     }
 }
 
+// One step back over kWide tiles from tile p on: adds the counts published so
+// far up to the first one that is not, or that is a sum (then true: done).
+template <int kWide>
+__device__ __forceinline__ bool look_back(const uint64_t* status, uint32_t digit, uint32_t pass,
+                                          int64_t& p, uint64_t& sum) {
+    uint64_t w[kWide];
+#pragma unroll
+    for (int q = 0; q < kWide; ++q)
+        w[q] = p >= q ? __hip_atomic_load(status + (uint64_t)(p - q) * kRadix + digit,
+                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                      : 0ull;
+    bool more = true, done = false;
+    int64_t back = 0;
+#pragma unroll
+    for (int q = 0; q < kWide; ++q) {
+        more = more && !done && (w[q] >> kEpochShift) == (uint64_t)(pass + 1);
+        if (more) {
+            sum += w[q] & kCount;
+            ++back;
+            done = (w[q] & kFlags) == kSum;
+        }
+    }
+    p -= back;
+    return done;
+}
+
+// What pass 0 reads are the 64-bit keys as given.
+template <class K, bool kFirst>
+struct SortRaw {
+    typedef K type;
+};
+template <class K>
+struct SortRaw<K, true> {
+    typedef uint64_t type;
+};
+
 // Pass number `pass` of the plan (a launch past the plan's end does nothing).
 // Passes alternate between the two buffer pairs (k0, v0) and (k1, v1); pass 0
 // reads its keys from `raw` (packed on the way) and its values from vinit or,
@@ -140,18 +175,19 @@ __global__ __launch_bounds__(kRadix) void rs_plan(SortControl* __restrict__ ctl,
 //
 // A tile is kThreads * kItems pairs, wave w holding its w-th contiguous part,
 // item k of the part's lanes consecutive.  The keys and then the values go
-// through one LDS buffer (half the LDS of two, so four workgroups share a
-// compute unit).  Keys past n are given digit 255: they come last in the last
-// tile, whose counts no other tile reads.
-template <class K, int kItems, bool kFirst>
+// through one LDS buffer.  Keys past n are given digit 255: they come last in
+// the last tile, whose counts no other tile reads.
+template <class K, int kThreads, int kItems, bool kFirst>
 __global__ __launch_bounds__(kThreads) void rs_pass(const uint64_t* __restrict__ raw,
                                                     const uint32_t* __restrict__ vinit, K* k0,
                                                     uint32_t* v0, K* k1, uint32_t* v1, uint32_t n,
                                                     uint32_t pass, SortControl* __restrict__ ctl,
                                                     uint64_t* __restrict__ status) {
     constexpr uint32_t kTile = kThreads * kItems;
+    constexpr int kWaves = kThreads / kWave;
+    static_assert(kThreads >= kRadix && kTile < 65536, "one thread per digit; 16-bit counts");
     __shared__ K s_buf[kTile];
-    __shared__ uint32_t s_cnt[kWaves][kRadix];
+    __shared__ uint16_t s_cnt[kWaves][kRadix];
     __shared__ uint32_t s_start[kRadix];  // first position of a digit in the tile
     __shared__ uint32_t s_dst[kRadix];    // its first position in the output, minus s_start
     __shared__ uint32_t s_wsum[kRadix / kWave];
@@ -173,19 +209,50 @@ __global__ __launch_bounds__(kThreads) void rs_pass(const uint64_t* __restrict__
     const uint32_t nvalid = (uint32_t)min((uint64_t)kTile, (uint64_t)n - base);
     K key[kItems];
     uint32_t val[kItems], rank[kItems];
-    const PairPack pk = ctl->pack();
+    // all loads of the tile are issued before the first is used
+    typename SortRaw<K, kFirst>::type in[kItems];
+    if (nvalid == kTile) {
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const uint64_t i = mine + (uint64_t)k * kWave;
-        if (i < n) key[k] = kFirst ? (K)pk.apply(raw[i]) : kin[i];
-        else key[k] = (K)~(K)0;
+        for (int k = 0; k < kItems; ++k) {
+            const uint64_t i = mine + (uint64_t)k * kWave;
+            if constexpr (kFirst) in[k] = raw[i];
+            else in[k] = kin[i];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const uint64_t i = mine + (uint64_t)k * kWave;
+            in[k] = 0;
+            if (i < n) {
+                if constexpr (kFirst) in[k] = raw[i];
+                else in[k] = kin[i];
+            }
+        }
     }
+    if (kFirst && !vinit) {
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const uint64_t i = mine + (uint64_t)k * kWave;
-        if (kFirst && !vinit) val[k] = (uint32_t)i;
-        else if (kFirst) val[k] = i < n ? vinit[i] : 0u;
-        else val[k] = i < n ? vin[i] : 0u;
+        for (int k = 0; k < kItems; ++k) val[k] = (uint32_t)mine + (uint32_t)k * kWave;
+    } else {
+        const uint32_t* vsrc = kFirst ? vinit : vin;
+        if (nvalid == kTile) {
+#pragma unroll
+            for (int k = 0; k < kItems; ++k) val[k] = vsrc[mine + (uint64_t)k * kWave];
+        } else {
+#pragma unroll
+            for (int k = 0; k < kItems; ++k) {
+                const uint64_t i = mine + (uint64_t)k * kWave;
+                val[k] = i < n ? vsrc[i] : 0u;
+            }
+        }
+    }
+    {
+        const PairPack pk = ctl->pack();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            if constexpr (kFirst) key[k] = (K)(pk.pairs ? pk.pack(in[k]) : in[k]);
+            else key[k] = in[k];
+            if (mine + (uint64_t)k * kWave >= n) key[k] = (K)~(K)0;
+        }
     }
     // rank among the wave's keys of the same digit
 #pragma unroll
@@ -201,7 +268,7 @@ __global__ __launch_bounds__(kThreads) void rs_pass(const uint64_t* __restrict__
         const uint32_t below = (uint32_t)__popcll(same & lanemask_lt());
         const uint32_t c = s_cnt[wv][d];
         wave_sync();
-        if (below == 0) s_cnt[wv][d] = c + (uint32_t)__popcll(same);
+        if (below == 0) s_cnt[wv][d] = (uint16_t)(c + (uint32_t)__popcll(same));
         wave_sync();
         rank[k] = c + below;
     }
@@ -210,7 +277,7 @@ __global__ __launch_bounds__(kThreads) void rs_pass(const uint64_t* __restrict__
     if (tid < (uint32_t)kRadix) {
         for (int w = 0; w < kWaves; ++w) {
             const uint32_t c = s_cnt[w][tid];
-            s_cnt[w][tid] = total;
+            s_cnt[w][tid] = (uint16_t)total;
             total += c;
         }
         const uint64_t epoch = (uint64_t)(pass + 1) << kEpochShift;
@@ -225,30 +292,14 @@ __global__ __launch_bounds__(kThreads) void rs_pass(const uint64_t* __restrict__
         }
         if (lane == kWave - 1) s_wsum[wv] = x;
         before = x - total;
-        // look back over the tiles before this one, four words at a time
+        // look back over the tiles before this one: a few words at first
+        // (enough once the tiles run staggered), then sixteen at a time (when
+        // all tiles start together, tile t needs about sqrt(t / 8) such steps)
         uint64_t sum = 0;
         if (tile) {
             int64_t p = (int64_t)tile - 1;
-            bool done = false;
-            while (!done) {
-                uint64_t w[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    w[q] = p >= q ? __hip_atomic_load(status + (uint64_t)(p - q) * kRadix + tid,
-                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                  : 0ull;
-                bool more = true;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const bool ready = (w[q] >> kEpochShift) == (uint64_t)(pass + 1);
-                    more = more && ready && !done;
-                    if (more) {
-                        sum += w[q] & kCount;
-                        --p;
-                        done = (w[q] & kFlags) == kSum;
-                    }
-                }
-            }
+            bool done = look_back<4>(status, tid, pass, p, sum);
+            while (!done) done = look_back<16>(status, tid, pass, p, sum);
             __hip_atomic_store(st, epoch | kSum | (sum + total), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -366,42 +417,56 @@ __global__ __launch_bounds__(kScanThreads) void rs_scan_down(uint32_t* __restric
     }
 }
 
-// Items per thread of a pass: tiles of 4,096 pairs once there are enough of
-// them for the 256 compute units, else tiles of 1,024.
-constexpr int kItemsLarge = 8, kItemsSmall = 2;
-constexpr uint32_t kLargeFrom = 1u << 20;
+// Tile shapes.  A tile's number comes from one counter, and a returning
+// atomic on one address takes the chip 30-48 ns, so large inputs take large
+// tiles (tiles of 4,096 pairs at 171e6 pairs: 41,700 atomics, 1.26 ms a pass,
+// whatever the bytes); small ones take tiles small enough to occupy the 256
+// compute units.
+struct TileShape {
+    int threads, items;
+};
+constexpr TileShape kSmall{512, 2}, kMedium{512, 8}, kLarge{1024, 16}, kLargeWide{1024, 8};
+constexpr uint32_t kMediumFrom = 1u << 18, kLargeFrom = 1u << 23;
 
-int items_of(uint32_t n) { return n >= kLargeFrom ? kItemsLarge : kItemsSmall; }
+TileShape shape_of(uint32_t n, bool narrow) {
+    if (n < kMediumFrom) return kSmall;
+    if (n < kLargeFrom) return kMedium;
+    return narrow ? kLarge : kLargeWide;
+}
 
-uint32_t tiles_of(uint32_t n) { return ceil_div(n, (uint64_t)kThreads * items_of(n)); }
+uint32_t tiles_of(uint32_t n, bool narrow) {
+    const TileShape t = shape_of(n, narrow);
+    return ceil_div(n, (uint64_t)t.threads * t.items);
+}
+
+template <class K, bool kFirst>
+auto pass_kernel(uint32_t n) {
+    constexpr bool narrow = sizeof(K) == 4;
+    constexpr TileShape L = narrow ? kLarge : kLargeWide;
+    if (n < kMediumFrom) return rs_pass<K, kSmall.threads, kSmall.items, kFirst>;
+    if (n < kLargeFrom) return rs_pass<K, kMedium.threads, kMedium.items, kFirst>;
+    return rs_pass<K, L.threads, L.items, kFirst>;
+}
 
 template <class K>
 void launch_pass(const SortJob& J, K* k0, K* k1, uint32_t p, hipStream_t s) {
-    const dim3 g(tiles_of(J.n)), b(kThreads);
-    const auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, g, b, 0, s, J.raw, J.vinit, k0, J.v0, k1, J.v1, J.n, p, J.ctl, J.status);
-    };
-    if (items_of(J.n) == kItemsLarge) {
-        if (p == 0) go(rs_pass<K, kItemsLarge, true>);
-        else go(rs_pass<K, kItemsLarge, false>);
-    } else {
-        if (p == 0) go(rs_pass<K, kItemsSmall, true>);
-        else go(rs_pass<K, kItemsSmall, false>);
-    }
+    const auto kern = p == 0 ? pass_kernel<K, true>(J.n) : pass_kernel<K, false>(J.n);
+    const bool narrow = sizeof(K) == 4;
+    hipLaunchKernelGGL(kern, dim3(tiles_of(J.n, narrow)), dim3(shape_of(J.n, narrow).threads), 0,
+                       s, J.raw, J.vinit, k0, J.v0, k1, J.v1, J.n, p, J.ctl, J.status);
 }
 
 }  // namespace
 
 size_t sort_status_len(uint32_t n) {
-    // tiles of either size, so that a buffer sized for n serves any smaller input
-    const uint32_t small = std::min(n, kLargeFrom - 1);
-    return (size_t)kSortRadix * std::max(tiles_of(n), tiles_of(small));
+    // the most tiles of any input up to n: each shape at its largest input
+    uint32_t t = tiles_of(n, false);
+    for (uint32_t top : {kMediumFrom - 1, kLargeFrom - 1}) t = std::max(t, tiles_of(std::min(n, top), false));
+    return (size_t)kSortRadix * t;
 }
 
-size_t sort_status_used(uint32_t n) { return (size_t)kSortRadix * tiles_of(n); }
-
-int sort_clear(const SortJob& J, hipStream_t s, size_t extra) {
-    const uint64_t words = sort_status_used(J.n) + extra;
+int sort_clear(const SortJob& J, hipStream_t s) {
+    const uint64_t words = (uint64_t)kSortRadix * tiles_of(J.n, false);  // the more of the two
     hipLaunchKernelGGL(rs_clear, dim3((uint32_t)std::min<uint64_t>((words + 255) / 256, 2048)),
                        dim3(256), 0, s, reinterpret_cast<uint32_t*>(J.ctl), J.status, words);
     TDS_HIP(hipGetLastError());
@@ -410,8 +475,8 @@ int sort_clear(const SortJob& J, hipStream_t s, size_t extra) {
 
 int sort_plan(const SortJob& J, int key_bits, hipStream_t s) {
     const int npass = (int)sort_npass(key_bits);
-    const uint32_t blocks = std::min(ceil_div(J.n, (uint64_t)kThreads * 4), 1024u);
-    hipLaunchKernelGGL(rs_hist, dim3(blocks), dim3(kThreads), 0, s, J.raw, (uint64_t)J.n, npass,
+    const uint32_t blocks = std::min(ceil_div(J.n, (uint64_t)kHistThreads * 4), 1024u);
+    hipLaunchKernelGGL(rs_hist, dim3(blocks), dim3(kHistThreads), 0, s, J.raw, (uint64_t)J.n, npass,
                        J.ctl);
     hipLaunchKernelGGL(rs_plan, dim3(1), dim3(kSortRadix), 0, s, J.ctl, npass, J.n);
     TDS_HIP(hipGetLastError());
@@ -432,6 +497,15 @@ int sort_passes(const SortJob& J, uint32_t npass, bool narrow, hipStream_t s) {
     return TDS_OK;
 }
 
+int scan_u32(uint32_t* v, uint32_t len, uint32_t* part, hipStream_t s) {
+    const uint32_t nparts = ceil_div(len, kScanTile);
+    hipLaunchKernelGGL(rs_scan_part, dim3(nparts), dim3(kScanThreads), 0, s, v, len, part);
+    hipLaunchKernelGGL(rs_scan_top, dim3(1), dim3(kScanThreads), 0, s, part, nparts);
+    hipLaunchKernelGGL(rs_scan_down, dim3(nparts), dim3(kScanThreads), 0, s, v, len, part);
+    TDS_HIP(hipGetLastError());
+    return TDS_OK;
+}
+
 size_t scan_part_len(size_t len) { return (size_t)ceil_div(len, kScanTile) + 1; }
 
 int exclusive_scan_u32(uint32_t* v, uint32_t len, uint32_t* total, hipStream_t stream) {
@@ -447,10 +521,7 @@ int exclusive_scan_u32_with(uint32_t* v, uint32_t len, uint32_t* total, hipStrea
     const uint32_t nparts = ceil_div(len, kScanTile);
     uint32_t* part = scratch;
     if (!part) TDS_TRY(dmalloc(&part, (size_t)nparts + 1));
-    hipLaunchKernelGGL(rs_scan_part, dim3(nparts), dim3(kScanThreads), 0, stream, v, len, part);
-    hipLaunchKernelGGL(rs_scan_top, dim3(1), dim3(kScanThreads), 0, stream, part, nparts);
-    hipLaunchKernelGGL(rs_scan_down, dim3(nparts), dim3(kScanThreads), 0, stream, v, len, part);
-    int st = (hipGetLastError() == hipSuccess) ? TDS_OK : TDS_E_DEVICE;
+    int st = scan_u32(v, len, part, stream);
     if (st == TDS_OK && total) {
         if (hipMemcpyAsync(total, part + nparts, sizeof(uint32_t), hipMemcpyDeviceToHost, stream) !=
                 hipSuccess ||

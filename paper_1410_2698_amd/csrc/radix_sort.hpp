@@ -7,7 +7,6 @@
 namespace tds {
 
 constexpr int kSortRadix = 256;
-constexpr int kSortThreads = 512;
 
 // Keys as the sort sees them: the 64-bit key itself, or, for pair keys
 // (first id << 32 | second id), the two ids next to each other with only as
@@ -15,7 +14,10 @@ constexpr int kSortThreads = 512;
 struct PairPack {
     uint32_t pairs, low_bits;
     __host__ __device__ uint64_t apply(uint64_t k) const {
-        return pairs ? ((k >> 32) << low_bits) | (uint32_t)k : k;
+        return pairs ? pack(k) : k;
+    }
+    __host__ __device__ uint64_t pack(uint64_t k) const {
+        return ((k >> 32) << low_bits) | (uint32_t)k;
     }
     __host__ __device__ uint32_t high(uint64_t packed) const {
         return (uint32_t)(packed >> low_bits);
@@ -41,9 +43,8 @@ struct SortControl {
     uint32_t max_high, max_low;
     // the trajectory merge
     uint32_t odd;              // why its one-pass form does not apply (kOdd*), 0: it does
-    uint32_t merge_ticket;     // next tile of that form
-    uint32_t pad[3];
-    uint64_t total;            // intervals found
+    uint32_t total;            // intervals found
+    uint32_t pad[5];
     uint32_t hist[8][kSortRadix];
     __host__ __device__ PairPack pack() const { return {pairs, bits_of(max_low)}; }
     // buffer (0 or 1) that holds the sorted data
@@ -61,19 +62,21 @@ struct SortJob {
     uint64_t *k0, *k1;
     uint32_t *v0, *v1;
     SortControl* ctl;
-    uint64_t* status;  // sort_status_len(n) words, and any `extra` words after those in use
+    uint64_t* status;  // sort_status_len(n) words
 };
 
-// Status words to allocate for sorts of up to n pairs, and the words that a
-// sort of exactly n uses (the first ones).
+// Status words to allocate for sorts of up to n pairs.
 size_t sort_status_len(uint32_t n);
-size_t sort_status_used(uint32_t n);
-// In this order, on one stream, nothing waiting: clear the control block, the
-// status words and `extra` words after them; (make the keys); count digits over key_bits low bits and
+// In this order, on one stream, nothing waiting: clear the control block and
+// the status words; (make the keys); count digits over key_bits low bits and
 // plan; up to npass passes (those past the plan's end do nothing).
-int sort_clear(const SortJob& J, hipStream_t s, size_t extra = 0);
+int sort_clear(const SortJob& J, hipStream_t s);
 int sort_plan(const SortJob& J, int key_bits, hipStream_t s);
 int sort_passes(const SortJob& J, uint32_t npass, bool narrow, hipStream_t s);
+
+// Exclusive scan of v in place, its sum to part[ceil(len / tile)] (part:
+// scan_part_len(len) entries); waits for nothing.
+int scan_u32(uint32_t* v, uint32_t len, uint32_t* part, hipStream_t s);
 
 inline uint32_t sort_npass(int key_bits) {
     return (uint32_t)(key_bits < 1 ? 1 : key_bits > 64 ? 8 : (key_bits + 7) / 8);

@@ -12,8 +12,9 @@
 //   3. k_merge_tiles: a workgroup takes the runs (records of one pair) that
 //      start in its tile of the sorted positions, reads their times once,
 //      orders each run by t_lo in LDS, finds where an interval starts (t_lo
-//      past every earlier t_hi of the run), learns the number of intervals
-//      before its own by look-back over the tiles, and writes its own.
+//      past every earlier t_hi of the run) and writes its intervals one after
+//      another to a scratch place of its own; k_merge_place puts the tiles'
+//      intervals together.
 // No step needs a number on the host before it is launched, except that a
 // large input (kHostPlanFrom) waits once for the id ranges, which pays for
 // itself in passes not made.
@@ -85,16 +86,15 @@ __global__ __launch_bounds__(kMT) void k_pair_keys(const tds_result* __restrict_
     }
 }
 
-// Tiles of the one-pass merge: kTilePos sorted positions, whose runs may
-// reach kHalo positions past the tile's end.  1,536 positions of times and
-// keys are 44 KB of LDS (38 with 32-bit keys): three or four workgroups of
-// eight waves per compute unit.  kHalo bounds the records per pair: a pair of
-// trajectories of 400 time steps has at most 400 or so.
+// Tiles of the one-pass merge: kPos sorted positions, whose runs may reach
+// kHalo positions past the tile's end.  kHalo bounds the records per pair: a
+// pair of trajectories of 400 time steps has at most 400 or so.  Tiles of
+// 1,024 need 38 KB of LDS with 32-bit keys: four workgroups of eight waves per
+// compute unit; small inputs take tiles of 256, for four times the workgroups.
 constexpr int kTileThreads = 512;
-constexpr uint32_t kTilePos = 1024, kHalo = 512, kWindow = kTilePos + kHalo;
-constexpr uint32_t kPerThread = kWindow / kTileThreads;
+constexpr uint32_t kHalo = 512, kPosLarge = 1024, kPosSmall = 256;
+constexpr uint32_t kSmallMerge = 1u << 18;  // records below which tiles are small
 constexpr uint16_t kNoRun = 0xFFFFu;
-constexpr uint64_t kTileOwn = 1ull << 62, kTileSum = 2ull << 62, kTileCount = (1ull << 62) - 1;
 
 // Exclusive prefix over the workgroup of one value per thread (op: max or +).
 template <class Op>
@@ -119,41 +119,57 @@ __device__ inline uint32_t block_excl(uint32_t v, uint32_t id, Op op, uint32_t* 
     return lane ? op(before, up) : before;
 }
 
+// Runs that start in the tile, ordered and merged; the intervals go to `tmp`
+// from the position of the tile's first run on (tiles own disjoint ranges of
+// positions, and a range holds at least as many records as intervals), their
+// number to cnt[tile].
+//
 // What bounds it: the gather of the records' times (16 bytes of a 32-byte
 // record, at the record's place in the input) and, for long runs, the LDS
-// reads of the ordering (each record compares itself with its run).  The walk
-// by one thread per run that this replaces read every record twice, each
-// thread one after another.
-template <class K>
+// reads of the ordering (each record compares itself with its run).  The
+// intervals take a second trip (k_merge_place) because the alternative, a
+// look-back over tiles numbered by a counter, made the counter's atomics the
+// bound: 48 ns for each of 167,000 tiles, 8.06 ms at 171e6 records.
+template <class K, uint32_t kPos>
 __global__ __launch_bounds__(kTileThreads) void k_merge_tiles(
     const tds_result* __restrict__ recs, const K* __restrict__ k0, const K* __restrict__ k1,
     const uint32_t* __restrict__ v0, const uint32_t* __restrict__ v1, uint32_t n,
-    SortControl* __restrict__ ctl, uint64_t* __restrict__ tstat,
-    tds_traj_interval* __restrict__ out, uint64_t capacity) {
+    SortControl* __restrict__ ctl, uint32_t* __restrict__ cnt_out, uint32_t* __restrict__ at_out,
+    tds_traj_interval* __restrict__ tmp) {
+    constexpr uint32_t kWindow = kPos + kHalo;
+    constexpr uint32_t kPer = (kWindow + kTileThreads - 1) / kTileThreads;
+    constexpr uint32_t kSlots = kPer * kTileThreads;  // positions, whole threads
     __shared__ K s_key[kWindow];
     __shared__ double s_lo[kWindow], s_hi[kWindow];
-    __shared__ uint16_t s_beg[kWindow];  // first position of the run, kNoRun: not this tile's
+    __shared__ uint16_t s_beg[kSlots];   // first position of the run, kNoRun: not this tile's
     __shared__ uint16_t s_end[kWindow];  // of a run's first position: its end
-    __shared__ uint8_t s_first[kWindow];  // an interval starts here
+    __shared__ uint8_t s_first[kSlots];  // an interval starts here
     __shared__ uint32_t s_w[kTileThreads / kWave];
-    __shared__ uint32_t s_tile;
-    __shared__ uint64_t s_base;
-    const uint32_t tid = threadIdx.x, lane = __lane_id();
-    if (tid == 0) s_tile = atomicAdd(&ctl->merge_ticket, 1u);
-    __syncthreads();
-    const uint32_t tile = s_tile;
-    const uint64_t base = (uint64_t)tile * kTilePos;
+    __shared__ uint32_t s_low;           // the tile's first run
+    const uint32_t tid = threadIdx.x;
+    const uint64_t base = (uint64_t)blockIdx.x * kPos;
     const uint32_t cnt = (uint32_t)min((uint64_t)kWindow, (uint64_t)n - base);
     const K* keys = ctl->side() ? k1 : k0;
     const uint32_t* vals = ctl->side() ? v1 : v0;
-    for (uint32_t l = tid; l < cnt; l += kTileThreads) s_key[l] = keys[base + l];
+    uint32_t v[kPer];
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        const uint32_t l = tid + j * kTileThreads;
+        v[j] = 0;
+        if (l < cnt) {
+            s_key[l] = keys[base + l];
+            v[j] = vals[base + l];
+        }
+    }
     const K prev = base ? keys[base - 1] : (K)0;
+    if (tid == 0) s_low = kWindow;
     __syncthreads();
-    // run starts: thread t looks at positions [3t, 3t + 3)
+    // run starts: thread t looks at kPer consecutive positions
     {
-        const uint32_t l0 = tid * kPerThread;
-        uint32_t h[kPerThread], last = 0;  // position + 1 of a run start, 0: none
-        for (uint32_t j = 0; j < kPerThread; ++j) {
+        const uint32_t l0 = tid * kPer;
+        uint32_t h[kPer], last = 0;  // position + 1 of a run start, 0: none
+#pragma unroll
+        for (uint32_t j = 0; j < kPer; ++j) {
             const uint32_t l = l0 + j;
             bool head = false;
             if (l < cnt) head = l ? s_key[l] != s_key[l - 1] : (base == 0 || s_key[0] != prev);
@@ -161,132 +177,137 @@ __global__ __launch_bounds__(kTileThreads) void k_merge_tiles(
             last = max(last, h[j]);
         }
         uint32_t all;
-        uint32_t run = block_excl(last, 0u, [](uint32_t a, uint32_t b) { return max(a, b); }, s_w,
-                                  &all);
-        for (uint32_t j = 0; j < kPerThread; ++j) {
+        const uint32_t before = block_excl(
+            last, 0u, [](uint32_t a, uint32_t b) { return max(a, b); }, s_w, &all);
+        uint32_t run = before;
+#pragma unroll
+        for (uint32_t j = 0; j < kPer; ++j) {
             const uint32_t l = l0 + j;
             if (h[j]) {
                 if (run) s_end[run - 1] = (uint16_t)l;
+                else s_low = l;  // one thread: the first run start of all
                 run = h[j];
             }
             // runs that start in the halo are the next tile's
-            s_beg[l] = (l < cnt && run && run <= kTilePos) ? (uint16_t)(run - 1) : kNoRun;
+            s_beg[l] = (l < cnt && run && run <= kPos) ? (uint16_t)(run - 1) : kNoRun;
             s_first[l] = 0;
         }
         if (tid == 0 && all) {
             s_end[all - 1] = (uint16_t)cnt;
-            if (base + cnt < n && all <= kTilePos) atomicOr(&ctl->odd, kOddRun);
+            if (base + cnt < n && all <= kPos) atomicOr(&ctl->odd, kOddRun);
         }
     }
     __syncthreads();
-    for (uint32_t l = tid; l < kWindow; l += kTileThreads)
-        if (s_beg[l] != kNoRun) {
-            const tds_result& r = recs[vals[base + l]];
-            s_lo[l] = r.t_lo;
-            s_hi[l] = r.t_hi;
+    double lo[kPer], hi[kPer];
+    uint32_t beg[kPer];
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        beg[j] = s_beg[tid + j * kTileThreads];
+        lo[j] = hi[j] = 0.0;
+        if (beg[j] != kNoRun) {
+            const tds_result& r = recs[v[j]];
+            lo[j] = r.t_lo;
+            hi[j] = r.t_hi;
         }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j)
+        if (beg[j] != kNoRun) s_lo[tid + j * kTileThreads] = lo[j];
     __syncthreads();
     // order every run by t_lo (records that start together stay in input order)
-    {
-        double lo[kPerThread], hi[kPerThread];
-        uint32_t to[kPerThread];
+    uint32_t to[kPer];
 #pragma unroll
-        for (uint32_t j = 0; j < kPerThread; ++j) {
-            const uint32_t l = tid + j * kTileThreads;
-            to[j] = kWindow;
-            const uint32_t b = s_beg[l];
-            if (b == kNoRun) continue;
-            const uint32_t e = s_end[b];
-            lo[j] = s_lo[l];
-            hi[j] = s_hi[l];
-            uint32_t r = b;
-            for (uint32_t m = b; m < e; ++m) {
-                const double x = s_lo[m];
-                r += (m < l ? x <= lo[j] : x < lo[j]) ? 1u : 0u;
-            }
-            to[j] = r;
-        }
-        __syncthreads();
-#pragma unroll
-        for (uint32_t j = 0; j < kPerThread; ++j)
-            if (to[j] < kWindow) {
-                s_lo[to[j]] = lo[j];
-                s_hi[to[j]] = hi[j];
-            }
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t j = 0; j < kPerThread; ++j) {
+    for (uint32_t j = 0; j < kPer; ++j) {
         const uint32_t l = tid + j * kTileThreads;
-        const uint32_t b = s_beg[l];
-        if (b == kNoRun) continue;
-        const double lo = s_lo[l];
-        bool first = true;
-        for (uint32_t m = b; m < l; ++m) first = first && lo > s_hi[m];
-        s_first[l] = first ? 1 : 0;
+        to[j] = l;
+        if (beg[j] == kNoRun) continue;
+        const uint32_t e = s_end[beg[j]];
+        uint32_t r = beg[j];
+#pragma unroll 4
+        for (uint32_t m = beg[j]; m < l; ++m) r += s_lo[m] <= lo[j] ? 1u : 0u;
+#pragma unroll 4
+        for (uint32_t m = l + 1; m < e; ++m) r += s_lo[m] < lo[j] ? 1u : 0u;
+        to[j] = r;
     }
     __syncthreads();
-    const uint32_t l0 = tid * kPerThread;
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j)
+        if (beg[j] != kNoRun) {
+            s_lo[to[j]] = lo[j];
+            s_hi[to[j]] = hi[j];
+        }
+    __syncthreads();
+    // a record starts an interval if it starts past all earlier ends of its run
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        if (beg[j] == kNoRun) continue;
+        double most = -INFINITY;
+#pragma unroll 4
+        for (uint32_t m = beg[j]; m < to[j]; ++m) most = fmax(most, s_hi[m]);
+        s_first[to[j]] = (to[j] == beg[j] || lo[j] > most) ? 1 : 0;
+    }
+    __syncthreads();
+    const uint32_t l0 = tid * kPer;
     uint32_t c = 0, all;
-    for (uint32_t j = 0; j < kPerThread; ++j) c += s_first[l0 + j];
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) c += s_first[l0 + j];
     uint32_t at = block_excl(c, 0u, [](uint32_t a, uint32_t b) { return a + b; }, s_w, &all);
-    // intervals of the tiles before this one: the first wave looks back, 64
-    // tiles at a time
-    if (tid < kWave) {
-        if (lane == 0)
-            __hip_atomic_store(tstat + tile, (tile ? kTileOwn : kTileSum) | all, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        uint64_t sum = 0;
-        bool done = tile == 0;
-        int64_t p = (int64_t)tile - 1;
-        while (!done) {
-            const uint64_t w = p >= (int64_t)lane
-                                   ? __hip_atomic_load(tstat + (p - lane), __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT)
-                                   : 0ull;
-            const uint64_t unready = __ballot((w >> 62) == 0), sums = __ballot((w >> 62) == 2);
-            const uint32_t ready = unready ? (uint32_t)__ffsll((unsigned long long)unready) - 1u
-                                           : (uint32_t)kWave;
-            uint32_t take = ready;  // leading words that are published
-            if (sums) {
-                const uint32_t s = (uint32_t)__ffsll((unsigned long long)sums) - 1u;
-                if (s < ready) {
-                    take = s + 1;
-                    done = true;
-                }
-            }
-            uint64_t x = lane < take ? w & kTileCount : 0ull;
-            for (int o = kWave / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
-            sum += x;
-            p -= take;
-        }
-        if (lane == 0) {
-            if (tile)
-                __hip_atomic_store(tstat + tile, kTileSum | (sum + all), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            s_base = sum;
-            if (base + kTilePos >= n) ctl->total = sum + all;
-        }
+    const uint32_t low = s_low < kPos ? s_low : 0u;
+    if (tid == 0) {
+        cnt_out[blockIdx.x] = all;
+        at_out[blockIdx.x] = (uint32_t)(base + low);
     }
-    __syncthreads();
     const PairPack pk = ctl->pack();
-    for (uint32_t j = 0; j < kPerThread; ++j) {
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
         const uint32_t l = l0 + j;
         if (!s_first[l]) continue;
-        const uint64_t pos = s_base + at;
-        ++at;
-        if (pos >= capacity) continue;
         const uint32_t e = s_end[s_beg[l]];
-        double hi = s_hi[l];
+        double end = s_hi[l];
         for (uint32_t m = l + 1; m < e && !s_first[m]; ++m)
-            if (s_hi[m] > hi) hi = s_hi[m];
+            if (s_hi[m] > end) end = s_hi[m];
         tds_traj_interval o;
         o.q_traj = pk.high((uint64_t)s_key[l]);
         o.e_traj = pk.low((uint64_t)s_key[l]);
         o.t_lo = s_lo[l];
-        o.t_hi = hi;
-        out[pos] = o;
+        o.t_hi = end;
+        tmp[base + low + at] = o;
+        ++at;
     }
+}
+
+// The tiles' intervals one after another in `out` (those below the capacity).
+// pre: exclusive sums of the tiles' counts with the total at [tiles], or, for
+// inputs of few tiles (kSum), the counts themselves, which each workgroup adds
+// up to its tile.  One workgroup per tile; bound by HBM (24 bytes in and out
+// per interval, in 8-byte words next to each other).
+template <bool kSum>
+__global__ __launch_bounds__(256) void k_merge_place(const uint32_t* __restrict__ pre,
+                                                     const uint32_t* __restrict__ from,
+                                                     uint32_t tiles,
+                                                     const uint64_t* __restrict__ tmp,
+                                                     uint64_t* __restrict__ out, uint64_t capacity,
+                                                     SortControl* __restrict__ ctl) {
+    const uint32_t t = blockIdx.x;
+    uint32_t first, n;
+    if (kSum) {
+        __shared__ uint32_t s_w[256 / kWave];
+        uint32_t x = 0;
+        for (uint32_t i = threadIdx.x; i < t; i += 256) x += pre[i];
+        for (int o = kWave / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        if (__lane_id() == 0) s_w[threadIdx.x / kWave] = x;
+        __syncthreads();
+        first = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        n = pre[t];
+    } else {
+        first = pre[t];
+        n = pre[t + 1] - first;
+    }
+    if (t == tiles - 1 && threadIdx.x == 0) ctl->total = first + n;
+    if (first >= capacity) return;
+    const uint32_t words = 3 * (uint32_t)min((uint64_t)n, capacity - first);
+    const uint64_t src = 3 * (uint64_t)from[t], dst = 3 * (uint64_t)first;
+    for (uint32_t i = threadIdx.x; i < words; i += 256) out[dst + i] = tmp[src + i];
 }
 
 // ------------------------------------------------------------ general form
@@ -387,6 +408,11 @@ __global__ __launch_bounds__(kMT) void k_merge_runs(const tds_result* __restrict
     if (!kWrite) cnt[r] = c;
 }
 
+uint32_t merge_tiles(uint32_t n) { return ceil_div(n, n < kSmallMerge ? kPosSmall : kPosLarge); }
+
+// Tiles up to which k_merge_place adds up the counts itself.
+constexpr uint32_t kSumTiles = 1024;
+
 // Device scratch of the merge, per device, grown on demand and kept until the
 // process ends (the merge is called repeatedly on result sets of similar
 // size; allocating and freeing per call cost more than the kernels).
@@ -395,8 +421,10 @@ struct MergeScratch {
     size_t cap = 0, rec_cap = 0, out_cap = 0, run_cap = 0;  // records each part holds
     tds_result* recs = nullptr;          // host input
     tds_traj_interval* stage = nullptr;  // host output
+    tds_traj_interval* tmp = nullptr;    // the tiles' intervals, before they are put together
     uint64_t *k1 = nullptr, *k2 = nullptr, *status = nullptr;
     uint32_t *v1 = nullptr, *v2 = nullptr;
+    uint32_t *tcnt = nullptr, *tfrom = nullptr, *tpart = nullptr;  // per tile
     // general form
     uint32_t *vfirst = nullptr, *runs = nullptr, *run_start = nullptr, *cnt = nullptr,
              *part = nullptr;
@@ -421,16 +449,22 @@ struct MergeScratch {
             }
         }
         if (n <= cap) return TDS_OK;
-        drop(cap, k1, k2, status, v1, v2);
+        drop(cap, k1, k2, status, v1, v2, tmp, tcnt, tfrom, tpart);
         const size_t c = std::max<size_t>(n, 1024);
         int st = dmalloc(&k1, c);
         if (st == TDS_OK) st = dmalloc(&k2, c);
         if (st == TDS_OK) st = dmalloc(&v1, c);
         if (st == TDS_OK) st = dmalloc(&v2, c);
-        if (st == TDS_OK)
-            st = dmalloc(&status, sort_status_len((uint32_t)c) + ceil_div(c, kTilePos) + 1);
+        if (st == TDS_OK) st = dmalloc(&status, sort_status_len((uint32_t)c));
+        if (st == TDS_OK) st = dmalloc(&tmp, c);
+        // tiles of either size
+        const size_t t = std::max<size_t>(merge_tiles((uint32_t)c),
+                                          merge_tiles((uint32_t)std::min<size_t>(c, kSmallMerge - 1)));
+        if (st == TDS_OK) st = dmalloc(&tcnt, t + 1);
+        if (st == TDS_OK) st = dmalloc(&tfrom, t);
+        if (st == TDS_OK) st = dmalloc(&tpart, scan_part_len(t + 1));
         if (st != TDS_OK) {
-            drop(cap, k1, k2, status, v1, v2);
+            drop(cap, k1, k2, status, v1, v2, tmp, tcnt, tfrom, tpart);
             return st;
         }
         cap = c;
@@ -486,6 +520,34 @@ MergeScratch g_scratch[kMaxDevices];
 // nothing to do costs about 3 us; the wait about 40), and 32-bit keys are a
 // third less traffic per pass.
 constexpr uint32_t kHostPlanFrom = 1u << 20;
+
+// The one-pass form on the sorted positions.
+int merge_one_pass(MergeScratch& M, const tds_result* R, uint32_t nn, bool narrow,
+                   tds_traj_interval* dst, uint64_t capacity, hipStream_t s) {
+    const uint32_t tiles = merge_tiles(nn);
+    const auto go = [&](auto kern, const auto* k0, const auto* k1) {
+        hipLaunchKernelGGL(kern, dim3(tiles), dim3(kTileThreads), 0, s, R, k0, k1, M.v1, M.v2, nn,
+                           M.ctl, M.tcnt, M.tfrom, M.tmp);
+    };
+    const uint32_t* a = reinterpret_cast<const uint32_t*>(M.k2);
+    const uint64_t *w0 = M.k1, *w1 = M.k2;
+    if (narrow) go(k_merge_tiles<uint32_t, kPosLarge>, a + nn, a);
+    else if (nn < kSmallMerge) go(k_merge_tiles<uint64_t, kPosSmall>, w0, w1);
+    else go(k_merge_tiles<uint64_t, kPosLarge>, w0, w1);
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(M.tmp);
+    uint64_t* out = reinterpret_cast<uint64_t*>(dst);
+    if (tiles <= kSumTiles) {
+        hipLaunchKernelGGL(k_merge_place<true>, dim3(tiles), dim3(256), 0, s, M.tcnt, M.tfrom,
+                           tiles, src, out, capacity, M.ctl);
+    } else {
+        // one entry more than tiles, so that the total ends up after the sums
+        TDS_TRY(scan_u32(M.tcnt, tiles + 1, M.tpart, s));
+        hipLaunchKernelGGL(k_merge_place<false>, dim3(tiles), dim3(256), 0, s, M.tcnt, M.tfrom,
+                           tiles, src, out, capacity, M.ctl);
+    }
+    TDS_HIP(hipGetLastError());
+    return TDS_OK;
+}
 
 // The general form; the records are on the device.  Leaves the first `keep` =
 // min(total, capacity) intervals in dst.
@@ -555,9 +617,7 @@ int merge_impl(const tds_result* recs, uint64_t n, bool recs_dev, tds_traj_inter
     }
     const uint64_t cap = std::min<uint64_t>(n, capacity);
     SortJob J{nn, M.k1, nullptr, M.k1, M.k2, M.v1, M.v2, M.ctl, M.status};
-    const uint32_t tiles = ceil_div(nn, kTilePos);
-    uint64_t* tstat = M.status + sort_status_used(nn);
-    TDS_TRY(sort_clear(J, s, tiles));
+    TDS_TRY(sort_clear(J, s));
     hipLaunchKernelGGL(k_pair_keys, dim3(std::min(ceil_div(nn, kMT), 2048u)), dim3(kMT), 0, s, R,
                        nn, M.k1, M.ctl);
     TDS_HIP(hipGetLastError());
@@ -572,15 +632,7 @@ int merge_impl(const tds_result* recs, uint64_t n, bool recs_dev, tds_traj_inter
     if (one_pass) {
         TDS_TRY(sort_plan(J, bits, s));
         TDS_TRY(sort_passes(J, sort_npass(bits), narrow, s));
-        if (narrow) {
-            const uint32_t* a = reinterpret_cast<const uint32_t*>(M.k2);
-            hipLaunchKernelGGL(k_merge_tiles<uint32_t>, dim3(tiles), dim3(kTileThreads), 0, s, R,
-                               a + nn, a, M.v1, M.v2, nn, M.ctl, tstat, dst, cap);
-        } else {
-            hipLaunchKernelGGL(k_merge_tiles<uint64_t>, dim3(tiles), dim3(kTileThreads), 0, s, R,
-                               M.k1, M.k2, M.v1, M.v2, nn, M.ctl, tstat, dst, cap);
-        }
-        TDS_HIP(hipGetLastError());
+        TDS_TRY(merge_one_pass(M, R, nn, narrow, dst, cap, s));
         TDS_TRY(M.read_ctl(s));
         one_pass = !M.ctl_host->odd;
         *n_out = M.ctl_host->total;
