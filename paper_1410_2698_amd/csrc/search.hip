@@ -1550,8 +1550,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // taken dynamically from the part's counter, and a wave whose part is
     // used up takes from the next parts: item costs vary by orders of
     // magnitude where results cluster (a static deal left some XCDs idle for
-    // more than half of a galaxy search).  A part's counter is read before
-    // it is incremented, so exhausted parts cost loads, not contended atomics.
+    // more than half of a galaxy search).  The next item is asked for before
+    // the current one's last evaluations, which hide most of the atomic's
+    // latency (asked for at the item's start, it is bound to a wave that may
+    // be busy for long: 8.6 against 6.4 ms on galaxy), and the counters are read before an increment only by a wave that looks
+    // for another part: reading all eight per item, next to the atomics, took
+    // the whole chip 30 ns per item (1.9e6 items of 64 candidates: 57 ms).
+    // The 9,600 items of three uniform1m searches: 279 us that way, 197 asked
+    // ahead, 145 with the line that says all parts are used up, 137 dealt
+    // statically.
     const uint64_t n_it = item_end > A.item_begin ? item_end - A.item_begin : 0u;
     // this wave's result stage
     const uint64_t sbase =
@@ -1573,14 +1580,34 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint64_t k = part_lo(grp) + gw;
     bool have = k < part_lo(grp + 1);
     uint32_t xs = grp;  // the part dynamic items are taken from
+    uint64_t ahead = 0;  // lane 0: its next number, asked for during the current item
+    bool asked = false;
     for (;;) {
         if (!have) {
             if (!dyn) break;
+            if (asked) {
+                asked = false;
+                const uint64_t v = lane0_64(ahead);
+                const uint64_t ps = part_lo(xs) + waves_of(xs), pe = part_lo(xs + 1);
+                if (ps + v < pe) {
+                    k = ps + v;
+                    have = true;
+                }
+            }
             // the next dynamic item: the parts' counters are read at once,
             // one part per lane in rotation from part xs, and the first part
             // with items left past its static round is taken from; losing
             // the race for a part's last items exhausts that part, so this
             // ends after at most ng + 1 rounds
+            // (a wave that finds all parts used up says so on a line of its
+            // own, which the other waves look at first)
+            unsigned long long* done = A.dyn_ctr + (size_t)kCtrDone * kCtrStride;
+            if (!have) {
+                uint64_t over = 0;
+                if (lane == 0)
+                    over = __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (lane0_64(over)) break;
+            }
             for (uint32_t round = 0; round <= ng && !have; ++round) {
                 bool avail = false;
                 if (lane < ng) {
@@ -1594,7 +1621,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     }
                 }
                 const uint64_t am = ballot(avail);
-                if (!am) break;  // every part is used up
+                if (!am) {  // every part is used up
+                    if (lane == 0)
+                        __hip_atomic_store(done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
                 xs = (xs + (uint32_t)__ffsll((unsigned long long)am) - 1u) % ng;
                 uint64_t v = 0;
                 if (lane == 0) v = atomicAdd(A.dyn_ctr + (size_t)xs * kCtrStride, 1ull);
@@ -1650,6 +1681,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         } else {
             if (all_cover) scan_chunk_fp64<true>(L, A, S);
             else scan_chunk_fp64<false>(L, A, S);
+        }
+        if (dyn) {
+            if (lane == 0) ahead = atomicAdd(A.dyn_ctr + (size_t)xs * kCtrStride, 1ull);
+            asked = true;
         }
         drain_rest(L, S, A);
         // the item's results get their positions (the next item's group has
@@ -2010,7 +2045,7 @@ DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q,
                    ? 1u
                    : 0u;
     A.dir_chunk = A.stage_cap;
-    A.dir_ctr = w->dyn_ctr + (size_t)kXcds * kCtrStride;
+    A.dir_ctr = w->dyn_ctr + (size_t)kCtrDirect * kCtrStride;
     A.dscratch = w->stage;
     A.dscratch_cap = (uint64_t)waves * A.stage_cap;
     A.dlast = w->dlast;

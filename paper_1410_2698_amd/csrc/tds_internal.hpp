@@ -19,10 +19,10 @@ constexpr int kWave = 64;               // CDNA wavefront width
 constexpr int kBlock = 256;             // threads per block of the search kernels
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr uint32_t kXcds = 8;            // accelerator complex dies (own L2 each)
-constexpr uint32_t kCtrStride = 8;       // 64-bit counters 64 bytes apart (own cache lines)
-// counters of the distance kernel: one dynamic item counter per XCD part, and
-// the reservation counter of direct output (the last slot)
-constexpr uint32_t kCtrSlots = kXcds + 1;
+constexpr uint32_t kCtrStride = 32;      // 64-bit counters 256 bytes apart (own lines and channels)
+// counters of the distance kernel: one dynamic item counter per XCD part, the
+// reservation counter of direct output, and whether every part is used up
+constexpr uint32_t kCtrDirect = kXcds, kCtrDone = kXcds + 1, kCtrSlots = kXcds + 2;
 constexpr uint32_t kMaxBins = 65535;
 constexpr uint32_t kMaxBuckets = 65536; // query buckets of one search
 constexpr uint32_t kSpanClasses = 4;    // bin-span classes per first bin
