@@ -106,11 +106,11 @@ enum {
 };
 
 /* Place of the FP32 form's closest-approach refinement: a pair that passes
-   the bounding-sphere test is dropped when FP32 lower bounds on the smallest
-   distance of the two moving points exceed d by more than the rounding of
+   the bounding-sphere test is dropped when an FP32 lower bound on the smallest
+   distance of the two moving points exceeds d by more than the rounding of
    the FP32 data and arithmetic; the rest are decided in FP64. */
 enum {
-    TDS_REFINE_DEFAULT = 0, /* currently TDS_REFINE_QUEUED */
+    TDS_REFINE_DEFAULT = 0, /* currently TDS_REFINE_INLINE */
     /* A stage of the pair queue, 64 pairs at a time (least register pressure
        in the filter; best where few pairs pass the sphere test). */
     TDS_REFINE_QUEUED = 1,
@@ -175,7 +175,7 @@ typedef struct tds_result {
 typedef struct tds_search_params {
     int32_t precision;     /* TDS_PREC_* */
     int32_t out_on_device; /* 1: `out` is device memory, else host memory */
-    uint32_t chunk;        /* candidates per work item; 0 = auto */
+    uint32_t chunk;        /* candidates per work item; 0 = auto (by the number of items) */
     uint32_t grid_waves;   /* waves of the persistent distance kernel; 0 = auto */
     /* Host output only: size, in records, of the device result buffer
        (the paper's fixed result buffer, Sec. 5.2).  When the results exceed
@@ -183,7 +183,7 @@ typedef struct tds_search_params {
        0 = min(capacity, 2^24). */
     uint64_t device_capacity;
     /* FP32 form: candidates each lane holds per tile of the distance kernel
-       (the tile is 64 x this); 2 or 4, 0 = 4. */
+       (the tile is 64 x this); 2 or 4, 0 = 2. */
     uint32_t tile;
     /* FP32 form: where the closest-approach refinement of the filter runs
        (TDS_REFINE_*).  Both places drop the same pairs. */

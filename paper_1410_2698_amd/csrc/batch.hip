@@ -106,7 +106,7 @@ int Batcher::init(tds_index* idx, uint64_t max_q, uint32_t max_r, uint64_t res_c
     TDS_TRY(ws_init(w_));
     TDS_TRY(ws_reserve(w_, max_q, max_r));
     TDS_TRY(ws_reserve_stage(w_, cfg_.grid_waves));
-    item_cap_ = std::min<uint64_t>(item_table_bound(idx, max_q, cfg_.chunk), 1ull << 28);
+    item_cap_ = std::min<uint64_t>(item_table_bound(idx, max_q, cfg_), 1ull << 28);
     TDS_TRY(dmalloc(&w_->item_bucket, std::max<uint64_t>(item_cap_, 1)));
     w_->item_bucket_cap = std::max<uint64_t>(item_cap_, 1);
     TDS_TRY(dmalloc(&w_->item_count, std::max<uint64_t>(item_cap_, 1)));
@@ -268,7 +268,7 @@ int Batcher::run(const tds_segments* Q, const tds_request* reqs, uint32_t nreq, 
         tds_search_params P;
         tds_search_params_default(&P);
         P.precision = cfg_.prec;
-        P.chunk = cfg_.chunk;
+        P.chunk = cfg_.chunk & kChunkAuto ? 0u : cfg_.chunk;
         P.grid_waves = cfg_.grid_waves;
         return batch_impl(idx_, Q, reqs, nreq, out, res_cap_, counts, &P, stream_, stats);
     }

@@ -18,6 +18,14 @@ struct QCanon {
     double x, y, z, vx, vy, vz, ts, aq, bq, d;
 };
 
+// A query segment as the distance kernel's FP64 evaluation needs it (written
+// by the query preparation): its canonical data and the ids of its records.
+struct QEval {
+    QCanon c;
+    uint32_t qid, qtraj;
+};
+static_assert(sizeof(QEval) == 88, "QEval layout");
+
 // Membership and interval of one (query, entry) pair in the fixed FP64
 // operation order: positions at the ends of the common extent, squared
 // distances minus d^2 there (C0, C1), relative velocity W, A = |W|^2,

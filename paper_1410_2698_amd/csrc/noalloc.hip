@@ -8,6 +8,7 @@
 #include <cmath>
 #include <mutex>
 
+#include "canon.hpp"
 #include "tds_internal.hpp"
 
 namespace tds {
@@ -25,9 +26,9 @@ constexpr size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 // Byte offsets of the carved buffers.
 struct Carve {
-    size_t qfu, qreq, qkey, qslot, qsorted, qf;
+    size_t qkey, qslot, qsorted, qf, qev;
     size_t b_count, b_hi, b_start, b_nch, binfo;
-    size_t item_bucket, item_count, bstats;
+    size_t item_bucket, bstats;
     size_t stage, stage_meta;
     size_t desc, req, hdr, ctr, dyn;
     size_t total;
@@ -41,19 +42,17 @@ constexpr Carve carve() {
         o = up(o + bytes);
         return at;
     };
-    c.qfu = take(kNaMaxQuery * sizeof(QF32));
-    c.qreq = take(kNaMaxQuery * sizeof(uint32_t));
     c.qkey = take(kNaMaxQuery * sizeof(uint32_t));
     c.qslot = take(kNaMaxQuery * sizeof(uint32_t));
     c.qsorted = take(kNaMaxQuery * sizeof(uint32_t));
-    c.qf = take((kNaMaxQuery + kQfPad) * sizeof(QF32));
+    c.qf = take(kNaMaxQuery * sizeof(QF32));
+    c.qev = take(kNaMaxQuery * sizeof(QEval));
     c.b_count = take(kMaxBuckets * sizeof(uint32_t));
     c.b_hi = take(kMaxBuckets * sizeof(uint32_t));
     c.b_start = take(kMaxBuckets * sizeof(uint32_t));
     c.b_nch = take(kMaxBuckets * sizeof(uint32_t));
     c.binfo = take(kMaxBuckets * sizeof(BucketInfo));
     c.item_bucket = take(kNaItems * sizeof(uint32_t));
-    c.item_count = take(kNaItems * sizeof(uint32_t));
     c.bstats = take((kNaGridWaves / kWavesPerBlock) * sizeof(BlockStats));
     c.stage = take((size_t)kNaGridWaves * kNaStagePerWave * sizeof(tds_result));
     c.stage_meta = take((size_t)kNaGridWaves * kNaStagePerWave * sizeof(uint32_t));
@@ -113,12 +112,11 @@ struct ScratchWorkspace : Workspace {
         device = dev;
         q_cap = kNaMaxQuery;
         r_cap = 1;
-        qfu = reinterpret_cast<QF32*>(base + kCarve.qfu);
-        qreq = reinterpret_cast<uint32_t*>(base + kCarve.qreq);
         qkey = reinterpret_cast<uint32_t*>(base + kCarve.qkey);
         qslot = reinterpret_cast<uint32_t*>(base + kCarve.qslot);
         qsorted = reinterpret_cast<uint32_t*>(base + kCarve.qsorted);
         qf = reinterpret_cast<QF32*>(base + kCarve.qf);
+        qev = reinterpret_cast<QEval*>(base + kCarve.qev);
         b_count = reinterpret_cast<uint32_t*>(base + kCarve.b_count);
         b_hi = reinterpret_cast<uint32_t*>(base + kCarve.b_hi);
         b_start = reinterpret_cast<uint32_t*>(base + kCarve.b_start);
@@ -126,8 +124,6 @@ struct ScratchWorkspace : Workspace {
         binfo = reinterpret_cast<BucketInfo*>(base + kCarve.binfo);
         item_bucket = reinterpret_cast<uint32_t*>(base + kCarve.item_bucket);
         item_bucket_cap = kNaItems;
-        item_count = reinterpret_cast<uint32_t*>(base + kCarve.item_count);
-        item_cap = kNaItems;
         bstats = reinterpret_cast<BlockStats*>(base + kCarve.bstats);
         stage = reinterpret_cast<tds_result*>(base + kCarve.stage);
         stage_meta = reinterpret_cast<uint32_t*>(base + kCarve.stage_meta);
@@ -140,11 +136,12 @@ struct ScratchWorkspace : Workspace {
     }
     ~ScratchWorkspace() {
         // views only: leave nothing for ~Workspace to free
-        qfu = qf = nullptr;
-        qreq = qkey = qslot = qsorted = nullptr;
+        qf = nullptr;
+        qev = nullptr;
+        qkey = qslot = qsorted = nullptr;
         b_count = b_hi = b_start = b_nch = nullptr;
         binfo = nullptr;
-        item_bucket = item_count = nullptr;
+        item_bucket = nullptr;
         bstats = nullptr;
         stage = nullptr;
         stage_meta = nullptr;

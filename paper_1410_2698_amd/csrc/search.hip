@@ -58,6 +58,8 @@ uint32_t count_parts(uint32_t nb) {
 
 constexpr uint32_t kPartedBuckets = kMaxBuckets / kCountParts;  // most buckets with parts
 
+constexpr uint32_t kChunkLevels = 4;  // chunk sizes k_bucket_scan chooses from
+
 // Maximum over the kCountParts parts of bucket b (nb buckets).
 __device__ __forceinline__ uint32_t parts_max(const uint32_t* c, uint32_t b, uint32_t nb) {
     uint32_t v[kCountParts];
@@ -139,6 +141,25 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
+
+// Where the lanes meet again after a branch that only some of them took.  It
+// emits nothing, but gives the meeting point a place of its own: without it
+// the compiler merges it with a following loop latch, takes the loop's state
+// (queue lengths, masks, counters) to differ between lanes, keeps it in
+// vector registers and runs every loop around it under lane masks.  In the
+// distance kernel that was all of them: 128 VGPRs with 20-90 spilled.
+__device__ inline void rejoin() { __builtin_amdgcn_wave_barrier(); }
+
+// The lane number, computed anew: what is derived from it (masks, addresses)
+// is then not kept in registers from the kernel's start on.
+__device__ inline uint32_t fresh_lane() {
+    uint32_t l = __lane_id();
+#if defined(__AMDGCN__)
+    asm volatile("" : "+v"(l));
+#endif
+    return l;
+}
+__device__ inline uint64_t below(uint32_t lane) { return (1ull << lane) - 1ull; }
 
 __device__ inline uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -356,10 +377,28 @@ __device__ inline void query_canon(const QueryView& Q, const Request& R, uint64_
     q.d = R.d;
 }
 
+// One record per lane, the 64 of a wave consecutive in dst (cnt of them
+// within the buffer): through LDS, so that each store
+// of the wave is one run of 512 bytes.  Straight from the lanes, 88 or 64
+// bytes apart, the two records' stores were most of the kernel.
+template <class T>
+__device__ inline void store_records(T* __restrict__ dst, const T& v, uint64_t* lds, uint32_t cnt) {
+    static_assert(sizeof(T) % 8 == 0, "");
+    constexpr uint32_t kW = sizeof(T) / 8;
+    const uint32_t lane = __lane_id();
+    wave_sync();
+    __builtin_memcpy(lds + lane * kW, &v, sizeof(T));
+    wave_sync();
+    uint64_t* d = (uint64_t*)dst;
+#pragma unroll
+    for (uint32_t i = 0; i < kW; ++i)
+        if (i * kWave + lane < cnt * kW) d[i * kWave + lane] = lds[i * kWave + lane];
+}
+
 __global__ __launch_bounds__(kBlock) void k_qprep(QueryView Q, const BatchDesc* __restrict__ desc,
                                                   const Request* __restrict__ req, IndexView I,
-                                                  QF32* __restrict__ qfu,
-                                                  uint32_t* __restrict__ qreq,
+                                                  QF32* __restrict__ qf,
+                                                  QEval* __restrict__ qev,
                                                   uint32_t* __restrict__ qkey,
                                                   uint32_t* __restrict__ qslot, uint32_t* b_count,
                                                   uint32_t* b_hi, uint32_t shift, uint32_t nb,
@@ -367,6 +406,8 @@ __global__ __launch_bounds__(kBlock) void k_qprep(QueryView Q, const BatchDesc* 
     // the first requests' starts in LDS: the request of a query segment is
     // then found without a chain of dependent global loads
     __shared__ uint64_t s_begin[kBlock];
+    __shared__ uint64_t s_rec[kWavesPerBlock][kWave * sizeof(QEval) / 8];
+    static_assert(sizeof(QF32) <= sizeof(QEval), "");
     const uint32_t nreq = desc->nreq;
     if (threadIdx.x < nreq) s_begin[threadIdx.x] = req[threadIdx.x].q_begin;
     __syncthreads();
@@ -376,6 +417,8 @@ __global__ __launch_bounds__(kBlock) void k_qprep(QueryView Q, const BatchDesc* 
     const uint32_t part = blockIdx.x / bpp;
     bool act = false;  // the segment gets a bucket slot
     uint32_t key = 0;
+    QF32 f = {};
+    QEval e = {};
     if (k < desc->nq) {
         uint32_t r;
         if (nreq <= kBlock) {
@@ -415,10 +458,10 @@ __global__ __launch_bounds__(kBlock) void k_qprep(QueryView Q, const BatchDesc* 
                                  paz = p.z + p.vz * (p.aq - ts);
                     const double pbx = p.x + p.vx * (p.bq - ts), pby = p.y + p.vy * (p.bq - ts),
                                  pbz = p.z + p.vz * (p.bq - ts);
-                    QF32 f;
                     sphere32(pax, pay, paz, pbx, pby, pbz, p.d, f.cx, f.cy, f.cz, f.R);
                     f.box = seg_box32(pax, pay, paz, pbx, pby, pbz, p.d);
-                    f.pad[0] = f.pad[1] = 0.f;
+                    f.req = r;
+                    f.pad = 0.f;
                     f.a32 = __double2float_rd(p.aq);
                     f.b32 = __double2float_ru(p.bq);
                     f.lo = lo;
@@ -430,11 +473,24 @@ __global__ __launch_bounds__(kBlock) void k_qprep(QueryView Q, const BatchDesc* 
                     // the bucket's range follows from its key unless it merges
                     // several first bins or spans an open number of bins
                     if (shift || span == kSpanClasses - 1) atomicMax(&b_hi[part * nb + key], hi);
-                    qfu[k] = f;
-                    qreq[k] = r;
+                    e.c = p;
+                    if (Q.ent) {
+                        e.qid = Q.ent_id[k];
+                        e.qtraj = Q.ent_traj[k];
+                    } else {
+                        e.qid = (uint32_t)(k - req[r].q_begin);
+                        e.qtraj = Q.traj ? Q.traj[k] : 0u;
+                    }
                 }
             }
         }
+    }
+    const uint32_t wv = threadIdx.x / kWave;
+    const uint64_t k0 = k - __lane_id(), nq = desc->nq;
+    if (ballot(act)) {
+        const uint32_t cnt = (uint32_t)(nq - k0 < kWave ? nq - k0 : kWave);
+        store_records(qf + k0, f, s_rec[wv], cnt);
+        store_records(qev + k0, e, s_rec[wv], cnt);
     }
     // bucket slots: one atomic per run of equal keys in consecutive lanes
     // (neighbouring query segments often share a bucket, e.g. in the
@@ -479,8 +535,39 @@ __global__ __launch_bounds__(kBlock) void k_schedule(QueryView Q, double t_start
     hi_out[k] = hi;
 }
 
+// Inclusive sum of v over the wave's lanes up to this one.
+__device__ inline uint32_t wave_scan(uint32_t v) {
+    const uint32_t lane = __lane_id();
+#pragma unroll
+    for (uint32_t off = 1; off < (uint32_t)kWave; off <<= 1) {
+        const uint32_t t = __shfl_up(v, off);
+        if (lane >= off) v += t;
+    }
+    return v;
+}
+
+// Candidate range [lo, hi) of bucket b (not empty): first entry of its
+// smallest first bin to the end of its last bin (from the key, or the
+// members' maximum hi_max where the bucket merges several first bins or spans
+// an open number of bins).
+__device__ inline void bucket_range(uint32_t b, uint32_t shift, uint32_t m,
+                                    const uint32_t* __restrict__ bin_first, uint32_t hi_max,
+                                    uint32_t* lo, uint32_t* hi) {
+    const uint32_t code = b << shift;  // smallest (j0 * classes + span) of the bucket
+    const uint32_t j0 = code / kSpanClasses, span = code % kSpanClasses;
+    *lo = bin_first[j0];
+    *hi = (shift == 0 && span < kSpanClasses - 1) ? bin_first[min(j0 + span + 1, m)] : hi_max;
+}
+
 // Bucket offsets, groups and the work-item table, one block.  The parts of
 // each bucket's slot counter become the parts' offsets within the bucket.
+//
+// Candidates per work item: with levels == 1, `chunk`.  Otherwise the largest
+// of chunk, chunk / 2, ... chunk / 2^(levels - 1) that makes at least `target`
+// items (about; the count is that of the unrounded chunks), or the smallest of
+// them if none does: a search of few items leaves most waves idle while each
+// of the others walks its whole chunk.  Each halving at most doubles that
+// count, so a smaller chunk than the first never makes 2 target items or more.
 __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_count,
                                                       const uint32_t* __restrict__ b_hi,
                                                       const uint32_t* __restrict__ bin_first,
@@ -488,13 +575,16 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
                                                       const double* __restrict__ max_ts,
                                                       uint32_t m, uint32_t shift,
                                                       uint32_t nb, uint32_t nparts, uint32_t chunk,
+                                                      uint32_t levels, uint32_t target,
                                                       uint32_t* __restrict__ b_start,
                                                       uint32_t* __restrict__ b_nch,
                                                       BucketInfo* __restrict__ binfo,
                                                       SearchHeader* hdr) {
-    __shared__ uint32_t pc[1024], pi[1024];
     __shared__ uint32_t s_cnt[kPartedBuckets], s_hi[kPartedBuckets];
-    const uint32_t tid = threadIdx.x;
+    __shared__ uint32_t s_n0[kChunkLevels];
+    __shared__ uint32_t s_c[1024 / kWave], s_i[1024 / kWave];
+    const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = tid / kWave;
+    if (tid < kChunkLevels) s_n0[tid] = 0;
     if (nparts == kCountParts) {
         // bucket totals and range maxima of the parts (nb <= kPartedBuckets),
         // each part's count replaced by its first slot in the bucket;
@@ -515,13 +605,43 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
                           ? parts_max(b_hi, b, nb)
                           : 0u;
         }
-        __syncthreads();
     }
-    // each thread's consecutive buckets: the record of each (all but its
-    // offsets), then the offsets after the scan.  Items per bucket are kept
-    // in s_hi (parts) or b_nch for the second pass.
+    __syncthreads();
+    // each thread's consecutive buckets
     const uint32_t per = (nb + 1023) / 1024;
     const uint32_t b0 = tid * per, b1 = min(nb, b0 + per);
+    if (levels > 1) {
+        // chunk is a power of two; sums capped at the target, so that the
+        // block's total fits 32 bits
+        const uint32_t lg = (uint32_t)__builtin_ctz(chunk);
+        uint32_t n0[kChunkLevels] = {};
+        for (uint32_t b = b0; b < b1; ++b) {
+            const uint32_t cnt = nparts == kCountParts ? s_cnt[b] : b_count[b];
+            if (!cnt) continue;
+            uint32_t lo, hi;
+            bucket_range(b, shift, m, bin_first, nparts == kCountParts ? s_hi[b] : b_hi[b], &lo,
+                         &hi);
+            const uint64_t len = hi - (lo & ~(uint32_t)(kWave - 1));
+#pragma unroll
+            for (uint32_t l = 0; l < kChunkLevels; ++l) {
+                const uint64_t n = (uint64_t)((cnt + kWave - 1) / kWave) *
+                                   ((len + (chunk >> l) - 1) >> (lg - l));
+                n0[l] = (uint32_t)min(n0[l] + n, (uint64_t)target);
+            }
+        }
+#pragma unroll
+        for (uint32_t l = 0; l < kChunkLevels; ++l) {
+            const uint32_t sum = wave_scan(n0[l]);
+            if (lane == kWave - 1 && sum) atomicAdd(&s_n0[l], sum);
+        }
+        __syncthreads();
+        uint32_t l = 0;
+        while (l + 1 < levels && s_n0[l] < target) ++l;
+        chunk >>= l;
+    }
+    // the record of each bucket (all but its offsets), then the offsets after
+    // the scan.  Items per bucket are kept in s_hi (parts) or b_nch for the
+    // second pass.
     uint32_t sc = 0, si = 0;
     for (uint32_t b = b0; b < b1; ++b) {
         const uint32_t cnt = nparts == kCountParts ? s_cnt[b] : b_count[b];
@@ -538,16 +658,11 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
         bi.tmax_ts = INFINITY;
         bi.pad2[0] = bi.pad2[1] = 0.0;
         if (cnt) {
-            // range of the bucket: first entry of its smallest first bin to
-            // the end of its last bin (from the key, or the members' maximum)
-            const uint32_t code = b << shift;  // smallest (j0 * classes + span) of the bucket
+            const uint32_t code = b << shift;
             const uint32_t j0 = code / kSpanClasses, span = code % kSpanClasses;
-            const uint32_t lo = bin_first[j0];
-            uint32_t hi;
-            if (shift == 0 && span < kSpanClasses - 1)
-                hi = bin_first[min(j0 + span + 1, m)];
-            else
-                hi = nparts == kCountParts ? s_hi[b] : b_hi[b];
+            uint32_t lo, hi;
+            bucket_range(b, shift, m, bin_first, nparts == kCountParts ? s_hi[b] : b_hi[b], &lo,
+                         &hi);
             if (shift == 0 && span < kSpanClasses - 1) {
                 // time bounds of the bins the bucket's range covers
                 const uint32_t j1 = min(j0 + span, m - 1);
@@ -580,18 +695,24 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
         sc += cnt;
         si += items;
     }
-    pc[tid] = sc;
-    pi[tid] = si;
-    __syncthreads();
-    for (uint32_t off = 1; off < 1024; off <<= 1) {
-        const uint32_t tc = (tid >= off) ? pc[tid - off] : 0u;
-        const uint32_t ti = (tid >= off) ? pi[tid - off] : 0u;
-        __syncthreads();
-        pc[tid] += tc;
-        pi[tid] += ti;
-        __syncthreads();
+    // sums over the threads before this one: within the wave, then the waves'
+    // totals (two barriers)
+    const uint32_t ic = wave_scan(sc), ii = wave_scan(si);
+    if (lane == kWave - 1) {
+        s_c[wv] = ic;
+        s_i[wv] = ii;
     }
-    uint32_t rc = pc[tid] - sc, ri = pi[tid] - si;
+    __syncthreads();
+    uint32_t rc = ic - sc, ri = ii - si;
+    for (uint32_t w = 0; w < wv; ++w) {
+        rc += s_c[w];
+        ri += s_i[w];
+    }
+    if (tid == 1023) {
+        hdr->n_items = ri + si;
+        hdr->n_buckets = nb;
+        hdr->active = rc + sc;  // every active query segment has a bucket slot
+    }
     for (uint32_t b = b0; b < b1; ++b) {
         uint32_t cnt, items;
         if (nparts == kCountParts) {
@@ -608,26 +729,22 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
         rc += cnt;
         ri += items;
     }
-    if (tid == 1023) {
-        hdr->n_items = pi[1023];
-        hdr->n_buckets = nb;
-        hdr->active = pc[1023];  // every active query segment has a bucket slot
-    }
 }
 
-// Workgroups [0, qblocks): one thread per query segment, which goes to its
-// bucket position (bucket start + its counter part's offset + its slot in
-// the part).  Workgroups [qblocks, qblocks + nb): item_bucket[i] = bucket of
-// work item i, one workgroup per bucket.
+// Workgroups [0, qblocks): one thread per query segment, whose number goes to
+// its bucket position (bucket start + its counter part's offset + its slot in
+// the part).  Only the number: copying the records along (64 to 152 bytes to
+// scattered places) cost 15-50 us more than the distance kernel saves by not
+// following the number.
+// Workgroups [qblocks, qblocks + nb): item_bucket[i] = bucket of work item i,
+// one workgroup per bucket.
 __global__ __launch_bounds__(kBlock) void k_scatter(const BatchDesc* __restrict__ desc,
                                                     const uint32_t* __restrict__ qkey,
                                                     const uint32_t* __restrict__ qslot,
                                                     const uint32_t* __restrict__ b_start,
                                                     const uint32_t* __restrict__ b_part,
                                                     uint32_t nb, uint32_t bpp, uint32_t qblocks,
-                                                    const QF32* __restrict__ qfu,
                                                     uint32_t* __restrict__ qsorted,
-                                                    QF32* __restrict__ qf,
                                                     const BucketInfo* __restrict__ binfo,
                                                     uint32_t* __restrict__ item_bucket,
                                                     SearchHeader* hdr) {
@@ -637,9 +754,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const BatchDesc* __restrict_
         const uint32_t s = qslot[k];
         if (s == kInactive) return;
         const uint32_t key = qkey[k];
-        const uint32_t pos = b_start[key] + b_part[(blockIdx.x / bpp) * nb + key] + s;
-        qsorted[pos] = (uint32_t)k;
-        qf[pos] = qfu[k];
+        qsorted[b_start[key] + b_part[(blockIdx.x / bpp) * nb + key] + s] = (uint32_t)k;
         return;
     }
     const uint32_t b = blockIdx.x - qblocks;
@@ -815,12 +930,16 @@ __global__ __launch_bounds__(256) void k_fill_copy(const uint64_t* __restrict__ 
     }
 }
 
+// The distance kernel's arguments.  Steps off the filter's walk take them from
+// the kernel's argument block anew (cold_args), so that they are not held in
+// scalar registers, which spilled by the dozen, across the walk.
 struct DistArgs {
     IndexView I;
-    QueryView Q;             // query arrays (FP64 data of rechecked pairs)
-    const uint32_t* qreq;    // request of each query segment
-    const QF32* qf;
-    const uint32_t* qsorted;
+    uint32_t self;           // self-join (see QueryView)
+    uint32_t one;            // one request
+    const uint32_t* qsorted; // query segments in bucket order
+    const QF32* qf;          // their records in query order
+    const QEval* qev;
     const BucketInfo* binfo;
     const uint32_t* item_bucket;
     const BatchDesc* desc;
@@ -840,7 +959,7 @@ struct DistArgs {
     uint32_t by_order;      // 1: a single-request item run whose results go to
                             // their order in the item (minus win_lo), no stage
     uint32_t cpl;           // FP32 form: candidates per lane per tile (2 or 4)
-    uint32_t inline_refine; // FP32 form: refinement in the filter walk, not the queue
+    uint32_t refine;        // FP32 form: TDS_REFINE_QUEUED or TDS_REFINE_INLINE
     uint32_t deal;          // TDS_DEAL_STATIC or TDS_DEAL_DYNAMIC
     // direct output (one request, not by_order): results go straight to the
     // request's output through per-wave reservations of dir_chunk positions
@@ -852,16 +971,25 @@ struct DistArgs {
     uint64_t* dlast;        // per wave: last reservation (chunk << 16 | used), ~0: none
 };
 
+#if defined(__AMDGCN__)
+typedef const __attribute__((address_space(4))) DistArgs* ArgsPtr;
+__device__ __forceinline__ ArgsPtr cold_args(const DistArgs&) {
+    ArgsPtr p = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+#else
+typedef const DistArgs* ArgsPtr;
+inline ArgsPtr cold_args(const DistArgs& A) { return &A; }
+#endif
+
 // FP32 data of a query segment for the closest-approach refinement (one per
-// group lane): its velocity and the time of its sphere centre (the mid time
-// of its clipped extent), each rounded to nearest; d rounded up; and the
-// query's parts of the refinement's error scale.
+// group lane, refine32).
 struct QRef {
-    float vx, vy, vz, tq;
-    float d;
-    float sc;  // |cx| + |cy| + |cz| of the sphere centre
-    float sv;  // |vx| + |vy| + |vz|
-    float st;  // |a| + |b| + |tq| + 1, [a, b] the clipped extent rounded outwards
+    float ox, oy, oz;  // the sphere centre moved to time 0 (c - v t, t its time)
+    float vx, vy, vz;  // velocity
+    float d;           // d + 2^-17 times the query's part of the position scale
+    float st;          // |a| + |b| + |t| + 1, [a, b] the clipped extent rounded outwards
 };
 static_assert(sizeof(QRef) == 32, "QRef layout");
 
@@ -887,35 +1015,34 @@ static_assert(sizeof(QRef) == 32, "QRef layout");
 // fill pass (k_fill_plan, k_fill_copy) then moves the results found past the
 // final count (or the capacity) into the unused tails below it, so that the
 // output is dense again.  No result takes the round trip through a stage.
-// Filter record of a query segment as the wave keeps it in LDS: the sphere
-// and the clipped extent of its QF32 record (the candidate range stays in the
-// registers of the query's lane).
-struct QF24 {
+// Filter data of a query segment as the wave keeps it in LDS: the sphere and
+// the clipped extent of its QF32 record, apart, since most slots need only the
+// sphere (the candidate range stays in the registers of the query's lane).
+struct alignas(16) QSphere {
     float cx, cy, cz, R;
-    float a32, b32;
 };
-static_assert(sizeof(QF24) == 24, "QF24 layout");
+struct alignas(8) QTime {
+    float a, b;
+};
 
 // The wave's LDS: 10,240 bytes, so that four workgroups of four waves fit in a
 // compute unit's 160 KB.  Per-lane values of the group (the request of query
 // j, its request slot, the staged results of a slot) live in the registers of
 // lane j (ItemState) and are read across lanes by shuffles.
 struct alignas(64) WaveLDS {
-    uint32_t queue[2 * kWave];  // < 64 left over + one pair per lane
-    uint32_t rq[2 * kWave];     // FP32 form: refined pairs awaiting the FP64 evaluation
-    QF24 qrec[kWave];           // filter records of the item's query group
+    uint32_t queue[2 * kWave];  // sphere survivors to refine: < 64 left over + one per lane
+    uint32_t rq[2 * kWave];     // pairs awaiting the FP64 evaluation, likewise
+    QSphere qs[kWave];          // filter data of the item's query group
+    QTime qt[kWave];
     QRef qref[kWave];           // FP32 form: refinement data of the group's queries
-    QCanon qc[kWave];           // canonical FP64 data of the group's queries
-    uint32_t qid[kWave];        // group lane j -> q_seg of its records
-    uint32_t qtraj[kWave];      // group lane j -> its trajectory
+    QEval qe[kWave];            // FP64 data of the group's queries
 };
 static_assert(sizeof(WaveLDS) == 10240, "WaveLDS size");
 
 struct ItemState {
     uint32_t c0, c1, qbase, nq;
-    uint32_t qn, evals;
-    uint32_t rqn;     // pairs in the refined queue (FP32 form)
-    bool refine;      // FP32 form: queued pairs go through the refinement first
+    uint32_t qn, rqn;  // pairs in the two queues
+    uint32_t evals;
     uint32_t found;   // results of the item so far (their order in the item)
     uint32_t nst;     // results in the wave's stage
     uint64_t sbase;   // the wave's stage: records [sbase, sbase + stage_cap)
@@ -941,7 +1068,7 @@ __device__ inline void wave_sync_mem() {
 
 // Staged records each lane copies per round of a flush (their loads in
 // flight together).
-constexpr int kFlushUnroll = 4;
+constexpr int kFlushUnroll = 2;
 
 // Reserves the staged results of every request slot (one atomic each) and
 // copies them from the stage to their positions; the stage is then empty.
@@ -950,19 +1077,20 @@ constexpr int kFlushUnroll = 4;
 // in the window [win_lo, win_lo + out_capacity), at out[dst + k].  The copy
 // then reads kFlushUnroll records per lane before it writes any, so a flush
 // waits for about one memory round trip per 256 records.
-__device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A, ItemState& S) {
-    const uint32_t lane = __lane_id();
+__device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A0, ItemState& S) {
+    const uint32_t lane = fresh_lane();
+    const ArgsPtr A = cold_args(A0);
     wave_sync_mem();
     int64_t dst = 0;
     uint32_t klo = 0, khi = 0;  // kept staged results of slot `lane`: [klo, khi)
     if (S.rcnt) {
         const uint64_t base =
-            (uint64_t)atomicAdd(&A.rc[S.qr].count, (unsigned long long)S.rcnt);
-        const Request& R = A.req[S.qr];
-        const uint64_t w0 = A.win_lo, w1 = A.win_lo + R.out_capacity, n = S.rcnt;
+            (uint64_t)atomicAdd(&A->rc[S.qr].count, (unsigned long long)S.rcnt);
+        const Request& R = A->req[S.qr];
+        const uint64_t w0 = A->win_lo, w1 = A->win_lo + R.out_capacity, n = S.rcnt;
         klo = (uint32_t)min(max(w0, base) - base, n);
         khi = (uint32_t)min(max(w1, base) - base, n);
-        dst = (int64_t)R.out_offset + (int64_t)base - (int64_t)A.win_lo;
+        dst = (int64_t)R.out_offset + (int64_t)base - (int64_t)A->win_lo;
     }
     S.rcnt = 0;
     for (uint32_t p0 = 0; p0 < S.nst; p0 += kFlushUnroll * kWave) {
@@ -974,8 +1102,8 @@ __device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A, ItemS
             meta[u] = 0xFFFFFFFFu;  // no record (a real one is below 2^17)
             ra[u] = rb[u] = make_uint4(0u, 0u, 0u, 0u);
             if (p < S.nst) {
-                meta[u] = A.stage_meta[S.sbase + p];
-                const uint4* src = reinterpret_cast<const uint4*>(A.stage + S.sbase + p);
+                meta[u] = A->stage_meta[S.sbase + p];
+                const uint4* src = reinterpret_cast<const uint4*>(A->stage + S.sbase + p);
                 ra[u] = src[0];
                 rb[u] = src[1];
             }
@@ -990,23 +1118,28 @@ __device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A, ItemS
             const uint32_t lo = (uint32_t)__shfl((int)klo, (int)slot);
             const uint32_t hi = (uint32_t)__shfl((int)khi, (int)slot);
             if (meta[u] != 0xFFFFFFFFu && k >= lo && k < hi) {
-                uint4* o = reinterpret_cast<uint4*>(A.out + (d + (int64_t)k));
+                uint4* o = reinterpret_cast<uint4*>(A->out + (d + (int64_t)k));
                 o[0] = ra[u];
                 o[1] = rb[u];
             }
+            rejoin();
         }
     }
     S.nst = 0;
     wave_sync_mem();
 }
 
-// Evaluates `cnt` <= 64 queued pairs from position `head` (one per lane) with
-// the canonical FP64 code and stages the results (or, by order, writes them).
-__device__ __forceinline__ void drain(WaveLDS& L, const uint32_t* queue, uint32_t head,
-                                      uint32_t cnt, ItemState& S, const DistArgs& A) {
-    const uint32_t lane = __lane_id();
+// Evaluates the last min(rqn, 64) pairs of the refined queue (one per lane)
+// with the canonical FP64 code and writes or stages the results.
+__device__ __forceinline__ void drain(WaveLDS& L, ItemState& S, const DistArgs& A0) {
+    const uint32_t lane = fresh_lane();
+    const ArgsPtr A = cold_args(A0);
+    const uint32_t cnt = min(S.rqn, (uint32_t)kWave);
+    wave_sync();
+    S.rqn -= cnt;
     const bool act = lane < cnt;
-    const uint32_t pk = act ? queue[head + lane] : 0u;
+    const uint32_t pk = act ? L.rq[S.rqn + lane] : 0u;
+    wave_sync();
     const uint32_t ql = pk & (kWave - 1);
     const uint32_t i = S.c0 + (pk >> 6);
     const uint32_t slot = (uint32_t)__shfl((int)S.rslot, (int)ql);  // every lane takes part
@@ -1014,14 +1147,14 @@ __device__ __forceinline__ void drain(WaveLDS& L, const uint32_t* queue, uint32_
     bool hit = false;
     uint32_t qid = 0, qtraj = 0, eid = 0, etraj = 0;
     if (act) {
-        const EntryF64 e = A.I.e64[i];
-        eid = A.I.seg_id[i];
-        etraj = A.I.traj[i];
-        const QCanon q = L.qc[ql];
-        qid = L.qid[ql];
-        qtraj = L.qtraj[ql];
+        const EntryF64 e = A->I.e64[i];
+        eid = A->I.seg_id[i];
+        etraj = A->I.traj[i];
+        const QCanon& q = L.qe[ql].c;
+        qid = L.qe[ql].qid;
+        qtraj = L.qe[ql].qtraj;
         hit = canon_eval<true>(q, e.x, e.y, e.z, e.vx, e.vy, e.vz, e.ts, e.te, &t_lo, &t_hi);
-        if (A.Q.ent) {
+        if (A->self) {
             // self-join: pairs of one trajectory are not results, and a record
             // names the lower segment id first (its interval is symmetric)
             hit = hit && qtraj != etraj;
@@ -1043,42 +1176,44 @@ __device__ __forceinline__ void drain(WaveLDS& L, const uint32_t* queue, uint32_
     rec.t_hi = t_hi;
     const uint64_t hm = ballot(hit);
     const uint32_t nhit = (uint32_t)__popcll(hm);
-    const uint32_t rank = (uint32_t)__popcll(hm & lanemask_lt());
+    const uint32_t rank = (uint32_t)__popcll(hm & below(lane));
     S.evals += cnt;
-    if (A.by_order) {
+    if (A->by_order) {
         const uint64_t pos = (uint64_t)S.found + rank;
-        const Request& R = A.req[0];
-        if (hit && pos >= A.win_lo && pos - A.win_lo < R.out_capacity)
-            A.out[R.out_offset + (pos - A.win_lo)] = rec;
+        const Request& R = A->req[0];
+        if (hit && pos >= A->win_lo && pos - A->win_lo < R.out_capacity)
+            A->out[R.out_offset + (pos - A->win_lo)] = rec;
+        rejoin();
         S.found += nhit;
         return;
     }
-    if (A.direct) {
+    if (A->direct) {
         if (!nhit) return;
         // nhit <= 64 <= dir_chunk: at most one new reservation
         const uint64_t room = S.dend - S.dpos;
         uint64_t pos = S.dpos + rank;
         if (nhit > room) {
             unsigned long long nb = 0;
-            if (lane == 0) nb = atomicAdd(A.dir_ctr, (unsigned long long)A.dir_chunk);
+            if (lane == 0) nb = atomicAdd(A->dir_ctr, (unsigned long long)A->dir_chunk);
             const uint64_t b = lane0_64(nb);
             if (rank >= room) pos = b + (rank - room);
             S.dpos = b + (nhit - room);
-            S.dend = b + A.dir_chunk;
+            S.dend = b + A->dir_chunk;
             ++S.nres;
         } else {
             S.dpos += nhit;
         }
         if (hit) {
-            const Request& R = A.req[0];
-            if (pos < R.out_capacity) A.out[R.out_offset + pos] = rec;
-            else if (pos - R.out_capacity < A.dscratch_cap) A.dscratch[pos - R.out_capacity] = rec;
+            const Request& R = A->req[0];
+            if (pos < R.out_capacity) A->out[R.out_offset + pos] = rec;
+            else if (pos - R.out_capacity < A->dscratch_cap) A->dscratch[pos - R.out_capacity] = rec;
         }
+        rejoin();
         S.found += nhit;
         return;
     }
     if (!nhit) return;
-    if (S.nst + nhit > A.stage_cap) stage_flush(L, A, S);
+    if (S.nst + nhit > A->stage_cap) stage_flush(L, A0, S);
     // index of each result among the staged results of its request slot
     uint32_t idx = 0;
     uint64_t rem = hm;
@@ -1087,94 +1222,112 @@ __device__ __forceinline__ void drain(WaveLDS& L, const uint32_t* queue, uint32_
         const uint32_t sl = uniform((uint32_t)__shfl((int)slot, (int)leader));
         const uint64_t mm = ballot(hit && slot == sl);
         const uint32_t c = uniform((uint32_t)__builtin_amdgcn_readlane((int)S.rcnt, (int)sl));
-        if (hit && slot == sl) idx = c + (uint32_t)__popcll(mm & lanemask_lt());
+        if (hit && slot == sl) idx = c + (uint32_t)__popcll(mm & below(lane));
         if (lane == sl) S.rcnt = c + (uint32_t)__popcll(mm);
         rem &= ~mm;
     }
     if (hit) {
-        A.stage[S.sbase + S.nst + rank] = rec;
-        A.stage_meta[S.sbase + S.nst + rank] = ql | (idx << 6);
+        A->stage[S.sbase + S.nst + rank] = rec;
+        A->stage_meta[S.sbase + S.nst + rank] = ql | (idx << 6);
     }
+    rejoin();
     S.nst += nhit;
     S.found += nhit;
 }
 
-// Appends the lanes of mask m (candidate i) to the wave's pair queue.
-__device__ __forceinline__ void enqueue(WaveLDS& L, uint64_t m, bool pass, uint32_t i, uint32_t c0,
-                                        uint32_t& qn) {
-    if (pass) L.queue[qn + (uint32_t)__popcll(m & lanemask_lt())] = ((i - c0) << 6) | __lane_id();
-    qn += (uint32_t)__popcll(m);
+// Is this lane's bit set in m?
+__device__ __forceinline__ bool in_mask(uint64_t m) {
+    return __builtin_amdgcn_inverse_ballot_w64(m);
+}
+
+// Appends the pairs of the lanes of mask m to a queue.
+__device__ __forceinline__ void enqueue(uint32_t* queue, uint32_t& n, uint64_t m, uint32_t pk) {
+    if (in_mask(m)) queue[n + (uint32_t)__popcll(m & lanemask_lt())] = pk;
+    rejoin();
+    n += (uint32_t)__popcll(m);
+}
+
+// fmaxf / fminf as the one instruction they are: the compiler precedes it by
+// one per operand that quiets signalling NaNs, of which none are made here.
+__device__ __forceinline__ float max1(float a, float b) {
+#if defined(__AMDGCN__)
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+#else
+    return fmaxf(a, b);
+#endif
+}
+__device__ __forceinline__ float min1(float a, float b) {
+#if defined(__AMDGCN__)
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+#else
+    return fminf(a, b);
+#endif
 }
 
 // Closest-approach refinement of the FP32 filter, for a pair that passed the
-// sphere and time tests: lower bounds, in FP32, on the smallest distance of
+// sphere and time tests: a lower bound, in FP32, on the smallest distance of
 // the two moving points over their common extent.  The pair is dropped only
-// when one of them exceeds d by more than the FP32 data and arithmetic can
-// account for, so every pair the canonical FP64 evaluation accepts is kept.
+// when it exceeds d by more than the FP32 data and arithmetic can account
+// for, so every pair the canonical FP64 evaluation accepts is kept.
 //
-// Query: centre cq = its position at tq (mid time of its clipped extent),
-// velocity vq, clipped extent [qa, qb] rounded outwards; entry likewise (cl,
-// vl, tl, [la, lb]).  On the common extent [a, b] (rounded outwards, so it
-// contains the exact one), with tm = (a + b) / 2 and h = (b - a) / 2, the
-// relative position is D(tau) = Dm + W tau for |tau| <= h, Dm = (cq - cl) +
-// (vq (tm - tq) - vl (tm - tl)), W = vq - vl.  Its distance from the origin is
-// at least
-//   (1) |Dm| - h |W|                    (triangle inequality),
-//   (2) |Dm x W| / |W|                  (distance to the line of motion),
-//   (3) min(|Dm - h W|, |Dm + h W|)     when the vertex -Dm.W / |W|^2 lies
-//                                       outside [-h, h] for certain.
-// Error budget (u = 2^-24): rounding of the FP32 data to nearest and the
-// operations forming Dm and W move D(tau) by at most about 10 u S0, S0 =
-// |cq|1 + |cl|1 + (|vq|1 + |vl|1)(|a| + |b| + |tq| + |tl| + 1) (L1 norms; this
-// also covers the FP64 rounding of the canonical evaluation, about 1e-15 S0).
-// The scale used is S = (sc_q + sc_l) + (sv_q + sv_l)(st_q + st_l) >= S0 (the
-// parts of each side are precomputed, QRef and the candidate's registers;
-// |a| + |b| <= |qa| + |qb| + |la| + |lb| since a is qa or la and b is qb or
-// lb), and E = 2^-17 S.  The squared forms below are evaluated with errors
-// below 10 u (|Dm|1 + h|W|1)^2 and 20 u |Dm|1^2 |W|1^2, bounded by 2^-17 and
-// 2^-16 times those magnitudes.  |W| comes from the hardware square root
-// (within 1 ulp; its operand is kept normal by adding 2^-100, which only
-// raises it) and is inflated by 2^-18.  Every test is "value > bound", so
-// overflow to infinity or NaN never drops a pair.
-__device__ __forceinline__ bool refine32(const QF24& f, const QRef& r, float clx, float cly,
-                                         float clz, float vlx, float vly, float vlz, float tl,
-                                         float la, float lb, float scl, float svl, float stl) {
+// Query: position cq at time tq, velocity vq, clipped extent [qa, qb] rounded
+// outwards; entry likewise (cl, vl, tl, [la, lb]).  Both positions moved to
+// time 0 (oq = cq - vq tq, ol = cl - vl tl), on the common extent [a, b]
+// (rounded outwards, so it contains the exact one), with tm = (a + b) / 2 and
+// h = (b - a) / 2, the relative position is D(tau) = Dm + W tau for
+// |tau| <= h, Dm = (oq - ol) + W tm, W = vq - vl.  Its distance from the
+// origin is smallest at tau* = clamp(-Dm.W / |W|^2, -h, h); the pair is
+// dropped when |D(tau)|^2 > R^2 for the computed tau, R = d + E.
+//
+// Error budget (u = 2^-24), with S0 = |cq|1 + |cl|1 + (|vq|1 + |vl|1)(|a| +
+// |b| + |tq| + |tl| + 1) (L1 norms):
+//  - rounding of the FP32 data to nearest (centres, velocities, mid times,
+//    the positions moved to time 0) and the operations forming Dm, W, tm and h
+//    move D(tau) by at most about 12 u S0, which also covers the FP64 rounding
+//    of the canonical evaluation (its vertex clause accepts distances past d
+//    by at most 0.7 u S0);
+//  - the computed tau lies in [-h, h] whatever its error, so D(tau) is a
+//    distance of the segment; that it is not the smallest one costs
+//    |W|^2 (tau - tau*)^2 <= (9 u |Dm|)^2 (|tau - tau*| <= 9 u |Dm| / |W|
+//    from the products' rounding, the reciprocal's 1 ulp and |tau*| <=
+//    |Dm| / |W|), i.e. at most 9 u S0 of distance;
+//  - |W|^2 may underflow when |W| < 2^-50; then D moves by at most 2 h |W|
+//    over the whole extent, below the 2^-48 st that the query's part of E
+//    always holds (qref_of).
+// E = 2^-17 S = 128 u S with S = (sc_q + sc_l) + (sv_q + sv_l)(st_q + st_l) >=
+// S0 (sc = |c|1, sv = |v|1, st = |a| + |b| + |t|, each side's own extent: |a| +
+// |b| <= |qa| + |qb| + |la| + |lb| since a is qa or la and b is qb or lb), so
+// E is at least six times the sum.  The relative rounding of R^2 and of
+// |D|^2 (below 8 u each) is covered by the factor 1 + 2^-19.  The test is
+// "value > bound", and an undefined tau (0 times infinity) becomes an end of
+// the extent, so overflow to infinity or NaN never drops a pair.
+//
+// One reciprocal and about 45 operations; the three separate bounds used
+// before (triangle inequality, distance to the line of motion, the ends) took
+// 75 and a square root for the same pairs kept.
+__device__ __forceinline__ bool refine32(const QTime& f, const QRef& r, float olx, float oly,
+                                         float olz, float vlx, float vly, float vlz, float la,
+                                         float lb, float scl, float svl, float stl) {
     // sums of products are fused (fmaf): each has at most the rounding error
     // of the separate multiply and add it replaces
-    const float a = fmaxf(f.a32, la), b = fminf(f.b32, lb);
+    const float a = max1(f.a, la), b = min1(f.b, lb);
     const float tm = 0.5f * (a + b), h = 0.5f * (b - a);
-    const float dq = tm - r.tq, dl = tm - tl;
-    const float dx = (f.cx - clx) + fmaf(r.vx, dq, -(vlx * dl));
-    const float dy = (f.cy - cly) + fmaf(r.vy, dq, -(vly * dl));
-    const float dz = (f.cz - clz) + fmaf(r.vz, dq, -(vlz * dl));
     const float wx = r.vx - vlx, wy = r.vy - vly, wz = r.vz - vlz;
-    const float S = fmaf(r.sv + svl, r.st + stl, r.sc + scl);
-    const float R = fmaf(0x1p-17f, S, r.d) * (1.0f + 0x1p-20f);
-    const float R2 = (R * R) * (1.0f + 0x1p-20f);
-    const float dm1 = fabsf(dx) + fabsf(dy) + fabsf(dz);
-    const float w1 = fabsf(wx) + fabsf(wy) + fabsf(wz);
-    const float Dm2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+    const float dx = fmaf(wx, tm, r.ox - olx);
+    const float dy = fmaf(wy, tm, r.oy - oly);
+    const float dz = fmaf(wz, tm, r.oz - olz);
+    const float svq = (fabsf(r.vx) + fabsf(r.vy)) + fabsf(r.vz);
+    const float R = fmaf(0x1p-17f, fmaf(svq + svl, r.st + stl, scl), r.d);
+    const float R2 = (R * R) * (1.0f + 0x1p-19f);
     const float WW = fmaf(wz, wz, fmaf(wy, wy, wx * wx));
     const float DW = fmaf(dz, wz, fmaf(dy, wy, dx * wx));
-    const float span = fmaf(h, w1, dm1);
-    const float errA = 0x1p-17f * (span * span);
-    // (1)
-    const float hw = (h * __builtin_amdgcn_sqrtf(WW + 0x1p-100f)) * (1.0f + 0x1p-18f);
-    const float Rh = R + hw;
-    if (Dm2 - errA > (Rh * Rh) * (1.0f + 0x1p-20f)) return false;
-    // (2), multiplied through by |W|^2
-    const float cross = dm1 * w1;
-    if (fmaf(-DW, DW, Dm2 * WW) - 0x1p-16f * (cross * cross) > (R2 * WW) * (1.0f + 0x1p-18f))
-        return false;
-    // (3)
-    if (fabsf(DW) > fmaf(h, WW, 0x1p-17f * fmaf(h, w1 * w1, cross))) {
-        const float ax = fmaf(-h, wx, dx), ay = fmaf(-h, wy, dy), az = fmaf(-h, wz, dz);
-        const float bx = fmaf(h, wx, dx), by = fmaf(h, wy, dy), bz = fmaf(h, wz, dz);
-        const float D0 = fmaf(az, az, fmaf(ay, ay, ax * ax));
-        const float D1 = fmaf(bz, bz, fmaf(by, by, bx * bx));
-        if (fminf(D0, D1) - errA > R2) return false;
-    }
-    return true;
+    const float tau = min1(max1(-DW * __builtin_amdgcn_rcpf(WW), -h), h);
+    const float px = fmaf(wx, tau, dx), py = fmaf(wy, tau, dy), pz = fmaf(wz, tau, dz);
+    return !(fmaf(pz, pz, fmaf(py, py, px * px)) > R2);
 }
 
 // The query's refinement data, from its canonical data and filter record.
@@ -1183,134 +1336,69 @@ __device__ __forceinline__ QRef qref_of(const QCanon& q, const QF32& f) {
     r.vx = __double2float_rn(q.vx);
     r.vy = __double2float_rn(q.vy);
     r.vz = __double2float_rn(q.vz);
-    r.tq = __double2float_rn(0.5 * (q.aq + q.bq));
-    r.d = __double2float_ru(q.d);
-    r.sc = (fabsf(f.cx) + fabsf(f.cy)) + fabsf(f.cz);
-    r.sv = (fabsf(r.vx) + fabsf(r.vy)) + fabsf(r.vz);
-    r.st = ((fabsf(f.a32) + fabsf(f.b32)) + fabsf(r.tq)) + 1.0f;
+    const float tq = __double2float_rn(0.5 * (q.aq + q.bq));
+    r.ox = fmaf(-r.vx, tq, f.cx);
+    r.oy = fmaf(-r.vy, tq, f.cy);
+    r.oz = fmaf(-r.vz, tq, f.cz);
+    r.st = ((fabsf(f.a32) + fabsf(f.b32)) + fabsf(tq)) + 1.0f;
+    const float sc = (fabsf(f.cx) + fabsf(f.cy)) + fabsf(f.cz);
+    // an unbounded sphere (stored centre 0): nothing is dropped
+    r.d = f.R < INFINITY ? fmaf(0x1p-17f, fmaf(0x1p-30f, r.st, sc), __double2float_ru(q.d))
+                         : INFINITY;
     return r;
 }
 
-// The candidate's parts of the refinement's error scale (see refine32).
+// The candidate's side of the refinement: its position moved to time 0 and
+// its parts of the error scale (see refine32).
 struct ERef {
+    float ox, oy, oz, vx, vy, vz;
     float sc, sv, st;
 };
-__device__ __forceinline__ ERef eref_of(float cx, float cy, float cz, const EntryV32& v, float ts,
-                                        float te) {
+__device__ __forceinline__ ERef eref_of(float cx, float cy, float cz, float rad,
+                                        const EntryV32& v, float ts, float te) {
     ERef e;
-    e.sc = (fabsf(cx) + fabsf(cy)) + fabsf(cz);
+    e.vx = v.vx;
+    e.vy = v.vy;
+    e.vz = v.vz;
+    e.ox = fmaf(-v.vx, v.tm, cx);
+    e.oy = fmaf(-v.vy, v.tm, cy);
+    e.oz = fmaf(-v.vz, v.tm, cz);
+    // an unbounded sphere (stored centre 0): nothing is dropped
+    e.sc = rad < INFINITY ? (fabsf(cx) + fabsf(cy)) + fabsf(cz) : INFINITY;
     e.sv = (fabsf(v.vx) + fabsf(v.vy)) + fabsf(v.vz);
     e.st = (fabsf(ts) + fabsf(te)) + fabsf(v.tm);
     return e;
 }
 
-// FP32 form: the closest-approach refinement (refine32) of `cnt` <= 64 queued
-// sphere survivors from position `head`, one per lane; the pairs it keeps go
-// to the refined queue.  A stage of its own, so that its registers are not
-// held across the filter's walk and searches with few survivors seldom run it.
-__device__ __forceinline__ void refine_step(WaveLDS& L, uint32_t head, uint32_t cnt,
-                                            ItemState& S, const DistArgs& A) {
-    const uint32_t lane = __lane_id();
+// FP32 form: the closest-approach refinement (refine32) of the last
+// min(qn, 64) queued sphere survivors, one per lane; the pairs it keeps go to
+// the refined queue, which is evaluated when it holds 64.
+__device__ __forceinline__ void refine_step(WaveLDS& L, ItemState& S, const DistArgs& A0) {
+    const uint32_t lane = fresh_lane();
+    const ArgsPtr A = cold_args(A0);
+    const uint32_t cnt = min(S.qn, (uint32_t)kWave);
+    wave_sync();
+    S.qn -= cnt;
     const bool act = lane < cnt;
-    const uint32_t pk = act ? L.queue[head + lane] : 0u;
+    const uint32_t pk = act ? L.queue[S.qn + lane] : 0u;
+    wave_sync();
     bool keep = false;
     if (act) {
         const uint32_t ql = pk & (kWave - 1);
         const uint32_t i = S.c0 + (pk >> 6);
-        const EntryF32 e = A.I.e32[i];
-        const EntryV32 v = A.I.ev32[i];
-        const QF24 f = L.qrec[ql];
-        keep = true;
-        // an unbounded sphere (stored centre 0) passes unrefined
-        if (e.r < INFINITY && f.R < INFINITY) {
-            const ERef x = eref_of(e.cx, e.cy, e.cz, v, e.ts, e.te);
-            keep = refine32(f, L.qref[ql], e.cx, e.cy, e.cz, v.vx, v.vy, v.vz, v.tm, e.ts, e.te,
-                            x.sc, x.sv, x.st);
-        }
+        const EntryF32 e = A->I.e32[i];
+        const EntryV32 v = A->I.ev32[i];
+        const ERef x = eref_of(e.cx, e.cy, e.cz, e.r, v, e.ts, e.te);
+        keep = refine32(L.qt[ql], L.qref[ql], x.ox, x.oy, x.oz, x.vx, x.vy, x.vz, e.ts, e.te, x.sc,
+                        x.sv, x.st);
     }
-    const uint64_t m = ballot(keep);
-    if (keep) L.rq[S.rqn + (uint32_t)__popcll(m & lanemask_lt())] = pk;
-    S.rqn += (uint32_t)__popcll(m);
-    wave_sync();
+    enqueue(L.rq, S.rqn, ballot(keep), pk);
 }
 
-// Moves entries [from, n) of a queue to its front.
-__device__ __forceinline__ void queue_shift(uint32_t* queue, uint32_t from, uint32_t n) {
+// The request slot of each query of the group: the first lane of the group
+// with the same request.
+__device__ __forceinline__ uint32_t request_slots(bool has, uint32_t r) {
     const uint32_t lane = __lane_id();
-    const uint32_t rest = n - from;  // < 64
-    wave_sync();
-    uint32_t v = 0;
-    if (lane < rest) v = queue[from + lane];
-    wave_sync();
-    if (lane < rest) queue[lane] = v;
-    wave_sync();
-}
-
-// Evaluates full batches of 64 queued pairs (FP32 form: refined first, then
-// evaluated 64 refined pairs at a time); keeps the remainders queued.
-__device__ __forceinline__ void drain_full(WaveLDS& L, ItemState& S, const DistArgs& A) {
-    uint32_t head = 0;
-    wave_sync();
-    while (S.qn - head >= kWave) {
-        if (S.refine) {
-            refine_step(L, head, kWave, S, A);
-            if (S.rqn >= kWave) {
-                drain(L, L.rq, 0, kWave, S, A);
-                queue_shift(L.rq, kWave, S.rqn);
-                S.rqn -= kWave;
-            }
-        } else {
-            drain(L, L.queue, head, kWave, S, A);
-        }
-        head += kWave;
-    }
-    if (head) {
-        queue_shift(L.queue, head, S.qn);
-        S.qn -= head;
-    }
-    wave_sync();
-}
-
-// Evaluates everything still queued (end of a work item).
-__device__ __forceinline__ void drain_rest(WaveLDS& L, ItemState& S, const DistArgs& A) {
-    wave_sync();
-    if (S.qn) {
-        if (S.refine) refine_step(L, 0, S.qn, S, A);
-        else drain(L, L.queue, 0, S.qn, S, A);
-        S.qn = 0;
-    }
-    uint32_t head = 0;
-    while (S.rqn - head > 0) {
-        const uint32_t c = min(S.rqn - head, (uint32_t)kWave);
-        drain(L, L.rq, head, c, S, A);
-        head += c;
-    }
-    S.rqn = 0;
-    wave_sync();
-}
-
-// Start of a work item: the canonical data, record ids and request of each
-// query segment of the group, and its request slot (the first lane of the
-// group with the same request).
-__device__ __forceinline__ void item_begin(WaveLDS& L, const DistArgs& A, ItemState& S) {
-    const uint32_t lane = __lane_id();
-    const bool has = lane < S.nq;
-    uint32_t r = 0;
-    QCanon q = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0};  // empty window: never a member
-    uint32_t qid = 0, qtraj = 0;
-    if (has) {
-        const uint32_t k = A.qsorted[S.qbase + lane];
-        r = A.qreq[k];
-        const Request& R = A.req[r];
-        query_canon(A.Q, R, k, q);
-        if (A.Q.ent) {
-            qid = A.Q.ent_id[k];
-            qtraj = A.Q.ent_traj[k];
-        } else {
-            qid = (uint32_t)(k - R.q_begin);
-            qtraj = A.Q.traj ? A.Q.traj[k] : 0u;
-        }
-    }
     uint32_t slot = lane;
     uint64_t rem = ballot(has);
     while (rem) {
@@ -1320,218 +1408,189 @@ __device__ __forceinline__ void item_begin(WaveLDS& L, const DistArgs& A, ItemSt
         if ((mm >> lane) & 1ull) slot = leader;
         rem &= ~mm;
     }
-    wave_sync();
-    L.qc[lane] = q;
-    L.qid[lane] = qid;
-    L.qtraj[lane] = qtraj;
-    S.qr = r;
-    S.rslot = slot;
-    S.rcnt = 0;
-    wave_sync();
+    return slot;
 }
-
-// FP32 filter record of the query segment held by a lane (its QF32 record).
-struct QReg {
-    Box32 box;        // box of the clipped segment grown by d (seg_box32)
-    float a, b;       // clipped window rounded outwards
-    uint32_t lo, hi;  // candidate range
-};
 
 // Value of v in lane j (wave-uniform j): a register read, no memory access.
 __device__ __forceinline__ float lane_val(float v, uint32_t j) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), (int)j));
 }
 
-// FP32 filter of one query (its record q, read from LDS at a wave-uniform
-// address, i.e. broadcast to every lane) against the candidate held in this
-// lane.  A pair can only be a result if the two bounding spheres come within
-// d (the error margins are folded into R and r) and the outward-rounded time
-// extents overlap strictly.  With kTime false the caller has established
-// that every pair of the slot overlaps in time.
-template <bool kTime>
-__device__ __forceinline__ bool pass32(const QF24& q, float ecx, float ecy, float ecz, float er,
-                                       float ets, float ete) {
-    bool p = sphere_pass(q.cx, q.cy, q.cz, q.R, ecx, ecy, ecz, er);
-    if (kTime) p = p & (q.a32 < ete) & (ets < q.b32);
-    return p;
+// A candidate as a lane holds it; its motion with kRef other than queued.
+struct Cand {
+    float cx, cy, cz, r, ts, te;
+    EntryV32 v;
+};
+
+// Candidate `lane` of a block; one outside the chunk gets an empty time extent
+// (it never passes).
+template <bool kMotion>
+__device__ __forceinline__ Cand load_cand(const DistArgs& A, const ItemState& S, uint32_t blk) {
+    const uint32_t cand = (blk << kBoxShift) + __lane_id();
+    const bool valid = cand >= S.c0 && cand < S.c1;
+    const uint32_t i = valid ? cand : S.c1 - 1;
+    const EntryF32 e = A.I.e32[i];
+    EntryV32 v = {0.f, 0.f, 0.f, 0.f};
+    if (kMotion) v = A.I.ev32[i];
+    return {e.cx, e.cy, e.cz, e.r, valid ? e.ts : INFINITY, valid ? e.te : -INFINITY, v};
 }
 
-// One 64-candidate slot (candidate `cand` in the lane) against the queries of
-// mask mk, in ascending order.  For each query, the sphere and time test of
-// every lane's candidate, then, with kInline, the closest-approach refinement
-// of the pairs that passed (the candidate's motion is loaded at the slot's
-// first survivor); the pairs kept are queued, and full batches of 64 go on to
-// the FP64 evaluation.  Without kInline the sphere survivors are queued and
-// the refinement is a stage of the queue (refine_step).  mk is wave uniform:
-// the walk over its bits is scalar, and the query records are read from LDS
-// at wave-uniform addresses.  With kUniform false, the queries of `part`
-// have candidate ranges that cover the slot only in part: their bounds are
-// read from the registers of their lanes (qlo, qhi) and checked per pair.
-template <bool kUniform, bool kTime, bool kInline>
-__device__ __forceinline__ void slot_fp32(WaveLDS& L, const DistArgs& A, ItemState& S,
-                                          uint64_t mk, uint64_t part, uint32_t qlo, uint32_t qhi,
-                                          uint32_t cand, float ecx, float ecy, float ecz,
-                                          float er, float ets, float ete) {
-    const uint32_t code = (cand - S.c0) << 6;  // used in lanes whose candidate is in the chunk
-    bool motion = false;
-    EntryV32 ev = {0.f, 0.f, 0.f, 0.f};
-    ERef ex = {0.f, 0.f, 0.f};
-    while (mk) {
-        const uint32_t j = (uint32_t)__builtin_ctzll(mk);
-        mk &= mk - 1u;
-        const QF24 q = L.qrec[j];
-        bool p = pass32<kTime>(q, ecx, ecy, ecz, er, ets, ete);
-        if (!kUniform && ((part >> j) & 1ull)) {
-            const uint32_t lo = uniform((uint32_t)__builtin_amdgcn_readlane((int)qlo, (int)j));
-            const uint32_t hi = uniform((uint32_t)__builtin_amdgcn_readlane((int)qhi, (int)j));
-            p = p & (cand >= lo) & (cand < hi);
-        }
-        uint64_t m = ballot(p);
-        if (!m) continue;
-        if (kInline) {
-            if (!motion) {
-                motion = true;
-                // lanes outside the chunk load its last entry (they never pass)
-                const uint32_t i = (cand >= S.c0 && cand < S.c1) ? cand : S.c1 - 1u;
-                ev = A.I.ev32[i];
-                ex = eref_of(ecx, ecy, ecz, ev, ets, ete);
-            }
-            // an unbounded sphere (stored centre 0) passes unrefined
-            if (p && er < INFINITY && q.R < INFINITY)
-                p = refine32(q, L.qref[j], ecx, ecy, ecz, ev.vx, ev.vy, ev.vz, ev.tm, ets, ete,
-                             ex.sc, ex.sv, ex.st);
-            m = ballot(p);
-        }
-        if (p) L.queue[S.qn + (uint32_t)__popcll(m & lanemask_lt())] = code | j;
-        S.qn += (uint32_t)__popcll(m);
-        if (S.qn >= kWave) drain_full(L, S, A);
+// Takes queued pairs on while a queue holds at least `from` of them (64 inside
+// an item, 1 at its end): refinement, then FP64 evaluation.
+__device__ __forceinline__ void take_queued(WaveLDS& L, ItemState& S, const DistArgs& A,
+                                            uint32_t from) {
+    while (S.qn >= from || S.rqn >= from) {
+        if (S.qn >= from && S.rqn < kWave) refine_step(L, S, A);
+        if (S.rqn >= from) drain(L, S, A);
     }
 }
 
 // FP32 form: the wave takes the chunk kCpl * 64 candidates at a time (kCpl
-// per lane, coalesced vector loads, tiles aligned to the 64-entry blocks).
-// Lane j holds query j of the group and, with the spatial layout, the box of
-// one of the next 64 blocks (broadcast from its registers by readlane, so the
-// loop over blocks makes no memory access).  Each block's box is first tested
-// against every query (one lane per query), and only the queries that pass
-// are tested against the block's entries, their records read from the wave's
-// LDS copy of the group.  When every
-// candidate of the bucket overlaps every query of the group in time, the
-// per-pair time test is skipped: exact, since the outward-rounded FP32 times
-// then overlap as well.
-template <bool kUniform, int kCpl, bool kInline>
+// per lane, coalesced vector loads issued together, tiles aligned to the
+// 64-entry blocks).  Lane j holds the box of query j and the box of one of the
+// next 64 blocks (broadcast from its registers by readlane; read by scalar
+// loads, every read of LDS waited for them as well).  Each block's box is
+// first tested against every query, and only the queries that pass are tested
+// against the block's entries, one after another (a scalar walk over the
+// mask), their records read from the wave's LDS copy of the group at
+// wave-uniform addresses: the sphere and time test of every lane's candidate,
+// then the closest-approach refinement of the pairs that passed, here or later
+// from the queue (kRef); pairs that stay go on to the FP64 evaluation 64 at a
+// time.  (The candidates' motion loaded only at a block's first refinement
+// cost twelve register copies per query; candidates read again after an
+// evaluation instead of held, a stall each.)  Queries whose candidate range
+// covers a block only in part (`part`, from the lanes' qlo and qhi; none when
+// `uni`) have their bounds checked per pair.  When every candidate of the bucket overlaps every
+// query of the group in time (all_overlap), the per-pair time test is skipped:
+// exact, since the outward-rounded FP32 times then overlap as well.
+//
+// One copy of each step per block of the tile, with the item's end as part of
+// the last block: a copy per combination of partial ranges, skipped time test
+// and item end made 70 KB of code and 22 to 103 spilled registers.
+//
+// Bound by instructions issued (about 23 vector and 26 scalar ones per query
+// and block, 66 and 33 where pairs are refined), not by memory.  The kernel,
+// before (queued refinement with three bounds, tile 4) and with this walk (one
+// bound, in the walk, tile 2): two particle sets close by, 4.4 million
+// evaluations, 1577 -> 904 us; the same overlapping, 171 million, 6507 -> 4438;
+// 1 M uniform segments in a batch 145 -> 148; 89 k evaluations of a self-join
+// of 1 M, 240 -> 231; 8000 items of dense walks 165 -> 143.
+template <int kCpl, int kRef>
 __device__ __forceinline__ void scan_chunk_fp32(WaveLDS& L, const DistArgs& A, ItemState& S,
-                                                const BucketInfo& bi) {
-    constexpr uint32_t kStep = kCpl * kWave;  // candidates per tile
+                                                const Box32& qbox, uint32_t qlo, uint32_t qhi,
+                                                bool uni, bool all_overlap) {
     const uint32_t lane = __lane_id();
-    const bool has = lane < S.nq;
     const bool cull = A.I.bbox != nullptr;
-    // a lane without a query: an empty box (it never passes a block) and an
-    // unbounded window (it never blocks the whole-overlap shortcut)
-    QReg q = {{INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY},
-              -INFINITY, INFINITY, 0u, 0u};
-    if (has) {
-        const QF32 f = A.qf[S.qbase + lane];
-        q.box = f.box;
-        q.a = f.a32;
-        q.b = f.b32;
-        q.lo = f.lo;
-        q.hi = f.hi;
-        L.qrec[lane] = QF24{f.cx, f.cy, f.cz, f.R, f.a32, f.b32};
-        if (kInline || S.refine) L.qref[lane] = qref_of(L.qc[lane], f);
-    }
-    wave_sync();
-    const bool all_overlap =
-        ballot(((double)q.a < bi.tmin_te) && (bi.tmax_ts < (double)q.b)) == ~0ull;
-    const uint64_t has_mask = ballot(has);
-    const uint32_t last_blk = (S.c1 - 1) >> kBoxShift;
-    uint32_t wb = 0xFFFFFFFFu;  // first block of the box window held in the lanes
-    Box32 wbox;
-    for (uint32_t tile = S.c0 & ~(uint32_t)(kWave - 1); tile < S.c1; tile += kStep) {
-        uint32_t cand[kCpl];
-        float ecx[kCpl], ecy[kCpl], ecz[kCpl], er[kCpl], ets[kCpl], ete[kCpl];
-        bool valid[kCpl];
+    const uint64_t has_mask = ~0ull >> (kWave - S.nq);
+    const uint32_t blk0 = S.c0 >> kBoxShift, blk1 = (S.c1 - 1) >> kBoxShift;
+    Box32 wbox = {};  // box of block wb + lane
+    uint32_t wb = blk0 - kWave;
+    for (uint32_t tile = blk0; tile <= blk1; tile += kCpl) {
+        Cand tc[kCpl];
 #pragma unroll
-        for (int k = 0; k < kCpl; ++k) {
-            cand[k] = tile + k * kWave + lane;
-            valid[k] = cand[k] >= S.c0 && cand[k] < S.c1;
-            const EntryF32 e = A.I.e32[valid[k] ? cand[k] : S.c1 - 1];
-            ecx[k] = e.cx;
-            ecy[k] = e.cy;
-            ecz[k] = e.cz;
-            er[k] = e.r;
-            // a slot outside the chunk gets an empty time extent: it never passes
-            ets[k] = valid[k] ? e.ts : INFINITY;
-            ete[k] = valid[k] ? e.te : -INFINITY;
-        }
-        const uint32_t tb = tile >> kBoxShift;
-        if (cull && (wb == 0xFFFFFFFFu || tb + kCpl > wb + kWave)) {
-            // lane l takes the box of block wb + l (the last block of the
-            // chunk repeated past the end)
-            wb = tb;
-            wbox = A.I.bbox[min(wb + lane, last_blk)].b;
+        for (int k = 0; k < kCpl; ++k)
+            tc[k] = load_cand<kRef != TDS_REFINE_QUEUED>(A, S, tile + k);
+        if (cull && tile + kCpl - 1 - wb >= kWave) {
+            wb = tile;
+            wbox = A.I.bbox[min(wb + lane, blk1)].b;
         }
 #pragma unroll
         for (int k = 0; k < kCpl; ++k) {
-            const uint32_t b0 = tile + k * kWave;  // first entry of the block
-            if (b0 >= S.c1) break;
+            const uint32_t blk = tile + k;
+            if (blk > blk1) break;
+            const uint32_t b0 = blk << kBoxShift;  // first entry of the block
             uint64_t mk = has_mask, part = 0;
-            if (!kUniform) {
-                mk &= ballot(q.lo < b0 + kWave && q.hi > b0);
-                part = mk & ~ballot(q.lo <= b0 && q.hi >= b0 + kWave);
+            if (!uni) {
+                mk &= ballot(qlo < b0 + kWave) & ballot(qhi > b0);
+                part = mk & ~(ballot(qlo <= b0) & ballot(qhi >= b0 + kWave));
             }
             if (cull && mk) {
-                const uint32_t bl = tb + k - wb;
-                const Box32 box = {lane_val(wbox.lx, bl), lane_val(wbox.ly, bl),
-                                   lane_val(wbox.lz, bl), lane_val(wbox.hx, bl),
-                                   lane_val(wbox.hy, bl), lane_val(wbox.hz, bl)};
-                mk &= ballot(box_overlap(box, q.box));
+                const uint32_t l = blk - wb;
+                const Box32 box = {lane_val(wbox.lx, l), lane_val(wbox.ly, l),
+                                   lane_val(wbox.lz, l), lane_val(wbox.hx, l),
+                                   lane_val(wbox.hy, l), lane_val(wbox.hz, l)};
+                // box_overlap, a mask per comparison
+                mk &= ballot(box.lx <= qbox.hx) & ballot(qbox.lx <= box.hx) &
+                      ballot(box.ly <= qbox.hy) & ballot(qbox.ly <= box.hy) &
+                      ballot(box.lz <= qbox.hz) & ballot(qbox.lz <= box.hz);
                 S.btests += S.nq;
             }
-            if (!mk) continue;
-            const uint64_t vm = ballot(valid[k]);
-            S.ftests += (uint64_t)__popcll(mk) * (uint64_t)__popcll(vm);
+            // at the item's end what is queued is taken on to the last pair
+            const uint32_t from = blk == blk1 ? 1u : (uint32_t)kWave;
+            if (!mk && from == kWave) continue;
+            const uint32_t nv = min(S.c1, b0 + kWave) - max(S.c0, b0);
+            S.ftests += (uint64_t)__popcll(mk) * (uint64_t)nv;
+            const uint32_t cand = b0 + lane;
+            const uint32_t code = (cand - S.c0) << 6;  // used where the candidate is in the chunk
             // the time test can be dropped only on full slots
-            if (all_overlap && vm == ~0ull)
-                slot_fp32<kUniform, false, kInline>(L, A, S, mk, part, q.lo, q.hi, cand[k], ecx[k],
-                                                    ecy[k], ecz[k], er[k], ets[k], ete[k]);
-            else
-                slot_fp32<kUniform, true, kInline>(L, A, S, mk, part, q.lo, q.hi, cand[k], ecx[k],
-                                                   ecy[k], ecz[k], er[k], ets[k], ete[k]);
+            const bool timed = !all_overlap || nv < kWave;
+            const Cand c = tc[k];
+            const ERef ex = eref_of(c.cx, c.cy, c.cz, c.r, c.v, c.ts, c.te);
+            for (;;) {
+                while (mk && max(S.qn, S.rqn) < kWave) {
+                    const uint32_t j = (uint32_t)__builtin_ctzll(mk);
+                    mk &= mk - 1u;
+                    const QSphere q = L.qs[j];
+                    uint64_t m = ballot(sphere_pass(q.cx, q.cy, q.cz, q.R, c.cx, c.cy, c.cz, c.r));
+                    if (timed) {
+                        const QTime t = L.qt[j];
+                        m &= ballot(t.a < c.te) & ballot(c.ts < t.b);
+                    }
+                    if ((part >> j) & 1ull) {
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)qlo, (int)j);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)qhi, (int)j);
+                        m &= ballot(cand >= lo) & ballot(cand < hi);
+                    }
+                    if (!m) continue;
+                    if (kRef == TDS_REFINE_QUEUED) {
+                        enqueue(L.queue, S.qn, m, code | j);
+                        continue;
+                    }
+                    const bool keep = refine32(L.qt[j], L.qref[j], ex.ox, ex.oy, ex.oz, ex.vx,
+                                               ex.vy, ex.vz, c.ts, c.te, ex.sc, ex.sv, ex.st);
+                    enqueue(L.rq, S.rqn, m & ballot(keep), code | j);
+                }
+                take_queued(L, S, A, mk ? (uint32_t)kWave : from);
+                if (!mk) break;
+            }
         }
     }
+    wave_sync();
 }
 
 // Plain FP64 form: one query segment per lane, every candidate of the chunk
-// streamed through scalar loads and tested with the canonical predicate.
-template <bool kUniform>
-__device__ __forceinline__ void scan_chunk_fp64(WaveLDS& L, const DistArgs& A, ItemState& S) {
-    const uint32_t lane = __lane_id();
-    const bool has = lane < S.nq;
+// streamed through scalar loads, each asked for one candidate ahead, and
+// tested with the canonical predicate.
+__device__ __forceinline__ void scan_chunk_fp64(WaveLDS& L, const DistArgs& A, ItemState& S,
+                                                const QCanon& q, uint32_t qlo, uint32_t qhi,
+                                                bool uni) {
     ConstE64 ce = (ConstE64)(A.I.e64);
-    const QCanon q = L.qc[lane];  // an empty window past the group's end
-    uint32_t qlo = 0, qhi = 0;
-    if (has) {
-        const QF32 f = A.qf[S.qbase + lane];
-        qlo = f.lo;
-        qhi = f.hi;
+    f64x4 n0 = ce[2 * S.c0], n1 = ce[2 * S.c0 + 1];
+    for (uint32_t i = S.c0; i <= S.c1; ++i) {
+        uint32_t from = 1;
+        if (i < S.c1) {
+            from = kWave;
+            const f64x4 e0 = n0, e1 = n1;  // x, y, z, vx | vy, vz, ts, te
+            const uint32_t i1 = min(i + 1, S.c1 - 1);
+            n0 = ce[2 * i1];
+            n1 = ce[2 * i1 + 1];
+            bool pass = canon_eval<false>(q, e0[0], e0[1], e0[2], e0[3], e1[0], e1[1], e1[2],
+                                          e1[3], nullptr, nullptr);
+            if (!uni) pass = pass & (i >= qlo) & (i < qhi);
+            const uint64_t m = ballot(pass);
+            if (!m) continue;
+            enqueue(L.rq, S.rqn, m, ((i - S.c0) << 6) | __lane_id());
+        }
+        if (S.rqn >= from) take_queued(L, S, A, from);
     }
-    for (uint32_t i = S.c0; i < S.c1; ++i) {
-        const f64x4 e0 = ce[2 * i], e1 = ce[2 * i + 1];  // x, y, z, vx | vy, vz, ts, te
-        bool pass = canon_eval<false>(q, e0[0], e0[1], e0[2], e0[3], e1[0], e1[1], e1[2], e1[3],
-                                      nullptr, nullptr);
-        if (!kUniform) pass = pass & (i >= qlo) & (i < qhi);
-        const uint64_t m = ballot(pass);
-        if (!m) continue;
-        enqueue(L, m, pass, i, S.c0, S.qn);
-        if (S.qn >= kWave) drain_full(L, S, A);
-    }
+    wave_sync();
 }
 
-template <int kPrec, int kCplT, bool kInline>
+template <int kPrec, int kCplT, int kRef>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_distance(DistArgs A) {
     __shared__ WaveLDS wl[kWavesPerBlock];
-    WaveLDS& L = wl[threadIdx.x / kWave];
+    const uint32_t wid = uniform(threadIdx.x / kWave);
+    WaveLDS& L = wl[wid];
     const uint32_t lane = __lane_id();
     uint64_t tests = 0, evals_total = 0, ftests = 0, btests = 0;
     uint32_t flushes = 0;  // stage flushes at the end of an item (direct output: reservations)
@@ -1562,10 +1621,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const uint64_t n_it = item_end > A.item_begin ? item_end - A.item_begin : 0u;
     // this wave's result stage
     const uint64_t sbase =
-        (uint64_t)(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave) * A.stage_cap;
+        (uint64_t)(blockIdx.x * kWavesPerBlock + wid) * A.stage_cap;
     const uint32_t ng = min(gridDim.x, kXcds);
     const uint32_t grp = blockIdx.x % ng;
-    const uint32_t gw = uniform((blockIdx.x / ng) * kWavesPerBlock + threadIdx.x / kWave);
+    const uint32_t gw = (blockIdx.x / ng) * kWavesPerBlock + wid;
     // waves of the workgroups on XCD x
     auto waves_of = [&](uint32_t x) {
         return ((gridDim.x - x + ng - 1) / ng) * (uint32_t)kWavesPerBlock;
@@ -1621,9 +1680,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     }
                 }
                 const uint64_t am = ballot(avail);
-                if (!am) {  // every part is used up
-                    if (lane == 0)
-                        __hip_atomic_store(done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!am) {  // every part is used up (every lane stores the same)
+                    __hip_atomic_store(done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
                 xs = (xs + (uint32_t)__ffsll((unsigned long long)am) - 1u) % ng;
@@ -1658,7 +1716,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         S.qbase = uniform(bi.start + g * kWave);
         S.qn = 0;
         S.rqn = 0;
-        S.refine = kPrec == TDS_PREC_FP32_RECHECK && !kInline;
         S.evals = 0;
         S.found = 0;
         S.nst = 0;
@@ -1667,26 +1724,42 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         S.dpos = dpos;
         S.dend = dend;
         S.nres = 0;
+        // the group's data.  A lane without a query: an empty box (it never
+        // passes a block), an unbounded window and range (it never stands in
+        // the way of the whole-group shortcuts) and, in FP64, an empty extent
+        // (never a member)
+        const bool has = lane < S.nq;
+        QF32 f = {0.f, 0.f, 0.f, 0.f, -INFINITY, INFINITY, 0u, 0xFFFFFFFFu,
+                  {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY}, 0u, 0.f};
+        QEval e = {{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0}, 0u, 0u};
+        if (has) {
+            const uint32_t q = A.qsorted[S.qbase + lane];
+            f = A.qf[q];
+            e = A.qev[q];
+        }
         // does every query of the group cover the whole chunk?
-        bool cover = true;
-        if (lane < S.nq) {
-            const QF32 f = A.qf[S.qbase + lane];
-            cover = f.lo <= S.c0 && f.hi >= S.c1;
-        }
-        const bool all_cover = ballot(cover) == ~0ull;
-        item_begin(L, A, S);
+        const bool all_cover = ballot(f.lo <= S.c0 && f.hi >= S.c1) == ~0ull;
+        S.qr = f.req;
+        S.rslot = A.one ? 0u : request_slots(has, f.req);
+        S.rcnt = 0;
+        wave_sync();
+        L.qe[lane] = e;
         if (kPrec == TDS_PREC_FP32_RECHECK) {
-            if (all_cover) scan_chunk_fp32<true, kCplT, kInline>(L, A, S, bi);
-            else scan_chunk_fp32<false, kCplT, kInline>(L, A, S, bi);
-        } else {
-            if (all_cover) scan_chunk_fp64<true>(L, A, S);
-            else scan_chunk_fp64<false>(L, A, S);
+            L.qs[lane] = QSphere{f.cx, f.cy, f.cz, f.R};
+            L.qt[lane] = QTime{f.a32, f.b32};
+            L.qref[lane] = qref_of(e.c, f);
         }
+        wave_sync();
+        if (kPrec == TDS_PREC_FP32_RECHECK)
+            scan_chunk_fp32<kCplT, kRef>(
+                L, A, S, f.box, f.lo, f.hi, all_cover,
+                (ballot((double)f.a32 < bi.tmin_te) & ballot(bi.tmax_ts < (double)f.b32)) == ~0ull);
+        else scan_chunk_fp64(L, A, S, e.c, f.lo, f.hi, all_cover);
         if (dyn) {
             if (lane == 0) ahead = atomicAdd(A.dyn_ctr + (size_t)xs * kCtrStride, 1ull);
+            rejoin();
             asked = true;
         }
-        drain_rest(L, S, A);
         // the item's results get their positions (the next item's group has
         // other request slots)
         if (S.nst) {
@@ -1702,13 +1775,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         btests += S.btests;
         evals_total += S.evals;
         if (A.item_count && lane == 0) A.item_count[it] = S.found;
+        rejoin();
         if (stat) {
             // the wave's next item of its part
             k += waves_of(grp);
             have = k < part_lo(grp + 1);
         }
     }
-    const uint32_t wid = threadIdx.x / kWave;
     if (A.direct && lane == 0) {
         // the wave's results and its last reservation (chunk, positions used)
         if (found_total) atomicAdd(&A.rc[0].count, (unsigned long long)found_total);
@@ -1758,7 +1831,7 @@ int grow(T** p, size_t* cap, size_t need) {
 }  // namespace
 
 Workspace::~Workspace() {
-    for (void* p : {(void*)qfu, (void*)qreq, (void*)qkey, (void*)qslot, (void*)qsorted, (void*)qf, (void*)qstage,
+    for (void* p : {(void*)qsorted, (void*)qkey, (void*)qslot, (void*)qf, (void*)qev, (void*)qstage,
                     (void*)qtraj_stage, (void*)ctl, (void*)b_count,
                     (void*)b_hi, (void*)b_start, (void*)b_nch,
                     (void*)binfo, (void*)item_bucket, (void*)item_count, (void*)res,
@@ -1820,21 +1893,19 @@ int ws_download(Workspace* w, uint32_t nreq, hipStream_t s) {
 }
 
 int ws_reserve(Workspace* w, size_t nq, size_t nreq) {
-    if (w->q_cap < nq || !w->qfu) {
-        for (void* p : {(void*)w->qfu, (void*)w->qreq, (void*)w->qkey, (void*)w->qslot,
-                        (void*)w->qsorted, (void*)w->qf})
+    if (w->q_cap < nq || !w->qf) {
+        for (void* p : {(void*)w->qsorted, (void*)w->qkey, (void*)w->qslot, (void*)w->qf,
+                        (void*)w->qev})
             dfree(p);
-        w->qfu = nullptr;
-        w->qreq = nullptr;
         w->qf = nullptr;
+        w->qev = nullptr;
         w->qkey = w->qslot = w->qsorted = nullptr;
         w->q_cap = 0;
-        TDS_TRY(dmalloc(&w->qfu, nq));
-        TDS_TRY(dmalloc(&w->qreq, nq));
+        TDS_TRY(dmalloc(&w->qsorted, nq));
         TDS_TRY(dmalloc(&w->qkey, nq));
         TDS_TRY(dmalloc(&w->qslot, nq));
-        TDS_TRY(dmalloc(&w->qsorted, nq));
-        TDS_TRY(dmalloc(&w->qf, nq + kQfPad));
+        TDS_TRY(dmalloc(&w->qf, nq));
+        TDS_TRY(dmalloc(&w->qev, nq));
         w->q_cap = nq;
     }
     if (w->r_cap < nreq || !w->ctl) {
@@ -1912,13 +1983,32 @@ uint32_t bucket_count(uint32_t m) {
     return (uint32_t)((((uint64_t)m * kSpanClasses - 1) >> bucket_shift(m)) + 1);
 }
 
+// Candidates per work item, chosen by the item count (k_bucket_scan): from
+// 4096 down to 512 (FP32 form) or 512 down to 128 (FP64 form), until there
+// are 3 / 2 items per wave.  Small searches are bound by the longest item:
+// with 4096 -> 512 the kernel takes 22 -> 12 us (201 -> 1005 items), 63 -> 26
+// (98 -> 392), 95 -> 32 (ragged, 2806 items), FP64 with 512 -> 128 240 -> 200
+// (2000 -> 8000).  With enough items each costs its own start, 8 to 10 us of
+// latency: 512 instead of 4096 takes 225 instead of 148 us at 9600 items and
+// 306 instead of 231 at 16000; 4800 items are better split (159 -> 143).
+uint32_t chunk_levels(int prec, uint32_t chunk) {
+    if (!(chunk & kChunkAuto)) return 1;
+    return prec == TDS_PREC_FP64 ? 3 : 4;
+}
+uint32_t item_target(uint32_t grid_waves) {
+    return launch_blocks(grid_waves) * kWavesPerBlock * 3 / 2;
+}
+
 // Upper bound of the work items of a batch of nq query segments: every
 // non-empty bucket contributes ceil(count / 64) groups, each split into at
 // most ceil((n + 63) / chunk) chunks (chunks count from a 64-entry block).
-uint64_t item_bound(uint64_t nq, uint32_t nb, uint64_t n, uint32_t chunk) {
+// With the chunk picked by the item count, twice the count aimed at bounds
+// the items of the smaller chunks.
+uint64_t item_bound(uint64_t nq, uint32_t nb, uint64_t n, uint32_t chunk, uint32_t grid_waves) {
     const uint64_t groups = (nq + kWave - 1) / kWave + std::min<uint64_t>(nq, nb);
-    const uint64_t nch = std::max<uint64_t>((n + kWave - 1 + chunk - 1) / chunk, 1);
-    return groups * nch;
+    const uint64_t c = chunk & ~kChunkAuto;
+    const uint64_t bound = groups * std::max<uint64_t>((n + kWave - 1 + c - 1) / c, 1);
+    return chunk & kChunkAuto ? std::max<uint64_t>(bound, 2ull * item_target(grid_waves)) : bound;
 }
 
 constexpr uint64_t kMaxItemTable = 1ull << 26;  // entries (256 MiB) kept without an exact count
@@ -1931,7 +2021,7 @@ static_assert((uint64_t)kMaxChunk + 2 * kTile < (1ull << 26), "packed queue entr
 
 uint32_t resolve_chunk(int prec, uint32_t chunk) {
     if (chunk) return std::min(std::max(chunk, 64u), kMaxChunk);
-    return prec == TDS_PREC_FP64 ? 512u : 4096u;
+    return kChunkAuto | (prec == TDS_PREC_FP64 ? 512u : 4096u);
 }
 
 // Default: 4 waves per SIMD on all 256 CUs (the occupancy the distance
@@ -1962,15 +2052,15 @@ uint32_t stage_per_wave(size_t recs, uint32_t blocks) {
 }
 
 // Kernel variant and dealing of a launch, packed: candidates per lane per
-// tile of the FP32 form (0 selects 4; 2 and 4 are built) in the low byte,
+// tile of the FP32 form (0 selects 2; 2 and 4 are built) in the low byte,
 // the place of the closest-approach refinement (TDS_REFINE_*, 0 selects the
-// queue stage) in the next, the dealing of the work items (TDS_DEAL_*, 0
+// walk) in the next, the dealing of the work items (TDS_DEAL_*, 0
 // selects the dynamic tail) above; 0 if any of them is unknown.
 uint32_t resolve_tile(uint32_t t, uint32_t refine = 0, uint32_t deal = 0) {
-    if (t == 0) t = 4;
+    if (t == 0) t = 2;
     if (t != 2 && t != 4) return 0;
-    if (refine == TDS_REFINE_DEFAULT) refine = TDS_REFINE_QUEUED;
-    if (refine != TDS_REFINE_QUEUED && refine != TDS_REFINE_INLINE) return 0;
+    if (refine > TDS_REFINE_INLINE) return 0;
+    if (refine == TDS_REFINE_DEFAULT) refine = TDS_REFINE_INLINE;
     if (deal == TDS_DEAL_DEFAULT) deal = TDS_DEAL_DYNAMIC;
     if (deal != TDS_DEAL_DYNAMIC && deal != TDS_DEAL_STATIC) return 0;
     return t | (refine << 8) | (deal << 16);
@@ -2010,10 +2100,11 @@ int stage_queries(const tds_segments* Q, QueryView* V, hipStream_t s, double** s
 
 DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q, tds_result* out,
                    uint64_t win_lo, uint32_t item_begin, uint32_t item_end, uint32_t* item_count,
-                   uint32_t grid_waves, bool by_order, uint32_t cpl, bool direct = false) {
+                   uint32_t grid_waves, bool by_order, uint32_t cpl, bool one,
+                   bool direct = false) {
     DistArgs A;
     A.cpl = cpl & 0xFFu;
-    A.inline_refine = ((cpl >> 8) & 0xFFu) == TDS_REFINE_INLINE ? 1u : 0u;
+    A.refine = (cpl >> 8) & 0xFFu;
     A.deal = cpl >> 16;
     A.dyn_ctr = w->dyn_ctr;
     A.stage = w->stage;
@@ -2021,10 +2112,11 @@ DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q,
     A.stage_cap = stage_per_wave(w->stage_recs, launch_blocks(grid_waves));
     A.by_order = by_order ? 1u : 0u;
     A.I = view_of(idx);
-    A.Q = Q;
-    A.qreq = w->qreq;
+    A.self = Q.ent ? 1u : 0u;
+    A.one = one ? 1u : 0u;
     A.qsorted = w->qsorted;
     A.qf = w->qf;
+    A.qev = w->qev;
     A.binfo = w->binfo;
     A.item_bucket = w->item_bucket;
     A.desc = w->desc;
@@ -2059,14 +2151,12 @@ int launch_distance(int prec, const DistArgs& A, uint32_t grid_waves, hipStream_
     const uint32_t blocks = launch_blocks(grid_waves);
     // every wave must be able to stage a full batch of 64 evaluations
     if (!A.stage || A.stage_cap < (uint32_t)kWave) return TDS_E_DEVICE;
+    constexpr int F32 = TDS_PREC_FP32_RECHECK, Q = TDS_REFINE_QUEUED, N = TDS_REFINE_INLINE;
     void (*kern)(DistArgs);
-    if (A.inline_refine)
-        kern = (A.cpl == 2) ? k_distance<TDS_PREC_FP32_RECHECK, 2, true>
-                            : k_distance<TDS_PREC_FP32_RECHECK, 4, true>;
-    else
-        kern = (A.cpl == 2) ? k_distance<TDS_PREC_FP32_RECHECK, 2, false>
-                            : k_distance<TDS_PREC_FP32_RECHECK, 4, false>;
-    if (prec == TDS_PREC_FP64) kern = k_distance<TDS_PREC_FP64, 4, false>;
+    const bool t2 = A.cpl == 2;
+    if (prec == TDS_PREC_FP64) kern = k_distance<TDS_PREC_FP64, 2, Q>;
+    else if (A.refine == Q) kern = t2 ? k_distance<F32, 2, Q> : k_distance<F32, 4, Q>;
+    else kern = t2 ? k_distance<F32, 2, N> : k_distance<F32, 4, N>;
     if (ev_begin && ev_end) {
         // the events take the dispatch's own start and end times (no marker
         // packets around the kernel, so no bubbles before and after it)
@@ -2108,17 +2198,18 @@ int enqueue_pipeline(const tds_index* idx, Workspace* w, const QueryView& Q, siz
                        w->b_hi, nb, nparts, w->req_ctr, r_cap, w->dyn_ctr);
     const uint32_t qblocks = std::max(1u, ceil_div(q_grid, kBlock));
     const uint32_t bpp = ceil_div(qblocks, nparts);  // workgroup b counts in part b / bpp < nparts
-    hipLaunchKernelGGL(k_qprep, dim3(qblocks), dim3(kBlock), 0, s, Q, w->desc, w->req, I, w->qfu,
-                       w->qreq, w->qkey, w->qslot, w->b_count, w->b_hi, shift, nb, bpp, w->hdr);
+    hipLaunchKernelGGL(k_qprep, dim3(qblocks), dim3(kBlock), 0, s, Q, w->desc, w->req, I, w->qf,
+                       w->qev, w->qkey, w->qslot, w->b_count, w->b_hi, shift, nb, bpp, w->hdr);
     hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, s, w->b_count, w->b_hi,
-                       idx->bin_first, idx->min_te, idx->max_ts, idx->m, shift, nb, nparts, chunk,
+                       idx->bin_first, idx->min_te, idx->max_ts, idx->m, shift, nb, nparts,
+                       chunk & ~kChunkAuto, chunk_levels(prec, chunk), item_target(grid_waves),
                        w->b_start, w->b_nch, w->binfo, w->hdr);
     hipLaunchKernelGGL(k_scatter, dim3(qblocks + nb), dim3(kBlock), 0, s, w->desc, w->qkey,
-                       w->qslot, w->b_start, w->b_count, nb, bpp, qblocks, w->qfu, w->qsorted,
-                       w->qf, w->binfo, w->item_bucket, w->hdr);
+                       w->qslot, w->b_start, w->b_count, nb, bpp, qblocks, w->qsorted, w->binfo,
+                       w->item_bucket, w->hdr);
     TDS_HIP(hipGetLastError());
     const DistArgs A = dist_args(idx, w, Q, out, 0, 0, 0xFFFFFFFFu, item_count, grid_waves, false,
-                                 cpl, direct);
+                                 cpl, r_cap == 1, direct);
     TDS_TRY(launch_distance(prec, A, grid_waves, s, ev_begin, ev_end));
     return A.direct ? launch_fill(A, w, grid_waves, s) : TDS_OK;
 }
@@ -2136,7 +2227,7 @@ int enqueue_range(const tds_index* idx, Workspace* w, const QueryView& Q, int pr
     TDS_HIP(hipGetLastError());
     return launch_distance(prec,
                            dist_args(idx, w, Q, out, win_lo, i0, i1, nullptr, grid_waves, by_order,
-                                     cpl),
+                                     cpl, r_cap == 1),
                            grid_waves, s, ev_begin, ev_end);
 }
 
@@ -2179,8 +2270,8 @@ bool valid_window(double d, double t0, double t1) {
 // Sizes the item table for the batch: from the bound when it is small enough,
 // else from the exact count after the preparation launches (one extra sync).
 int reserve_items(const tds_index* idx, Workspace* w, uint64_t nq, uint32_t chunk,
-                  uint64_t* cap_out) {
-    const uint64_t bound = item_bound(nq, bucket_count(idx->m), idx->n, chunk);
+                  uint32_t grid_waves, uint64_t* cap_out) {
+    const uint64_t bound = item_bound(nq, bucket_count(idx->m), idx->n, chunk, grid_waves);
     const uint64_t cap = std::min<uint64_t>(bound, kMaxItemTable);
     TDS_TRY(grow(&w->item_bucket, &w->item_bucket_cap, std::max<size_t>(cap, 1)));
     TDS_TRY(grow(&w->item_count, &w->item_cap, std::max<size_t>(cap, 1)));
@@ -2233,7 +2324,7 @@ int run_batch(const tds_index* idx, Workspace* w, const QueryView& V, uint32_t n
               uint32_t chunk, uint32_t grid_waves, uint32_t cpl, uint32_t output, tds_result* out,
               hipStream_t s, tds_stats* st, SearchHeader* h_out) {
     uint64_t cap = 0;
-    TDS_TRY(reserve_items(idx, w, V.n, chunk, &cap));
+    TDS_TRY(reserve_items(idx, w, V.n, chunk, grid_waves, &cap));
     TDS_TRY(ws_reserve_stage(w, grid_waves));
     for (int attempt = 0; attempt < 2; ++attempt) {
         TDS_TRY(enqueue_attempt(idx, w, V, nreq, prec, chunk, grid_waves, cpl, output, out, s,
@@ -2261,8 +2352,8 @@ int resolve_config(const tds_search_params* params, PipelineConfig* cfg) {
     return TDS_OK;
 }
 
-uint64_t item_table_bound(const tds_index* idx, uint64_t nq, uint32_t chunk) {
-    return item_bound(nq, bucket_count(idx->m), idx->n, chunk);
+uint64_t item_table_bound(const tds_index* idx, uint64_t nq, const PipelineConfig& cfg) {
+    return item_bound(nq, bucket_count(idx->m), idx->n, cfg.chunk, cfg.grid_waves);
 }
 
 int enqueue_search(const tds_index* idx, Workspace* w, const double* const* qarrays,
@@ -2540,7 +2631,7 @@ int search_begin_impl(tds_index* idx, const tds_segments* Q, double d, double t_
         R.out_offset = 0;
         R.out_capacity = capacity;
         *w->req_host = R;
-        if ((st = reserve_items(idx, w, Q->n, ps->chunk, &ps->cap_items))) break;
+        if ((st = reserve_items(idx, w, Q->n, ps->chunk, ps->grid_waves, &ps->cap_items))) break;
         if ((st = ws_reserve_stage(w, ps->grid_waves))) break;
         if (hipEventCreateWithFlags(&ps->done, hipEventDisableTiming) != hipSuccess) {
             ps->done = nullptr;

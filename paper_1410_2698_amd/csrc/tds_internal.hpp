@@ -27,7 +27,6 @@ constexpr uint32_t kMaxBins = 65535;
 constexpr uint32_t kMaxBuckets = 65536; // query buckets of one search
 constexpr uint32_t kSpanClasses = 4;    // bin-span classes per first bin
 constexpr uint64_t kDefaultDevCap = 1ull << 24;
-constexpr uint32_t kQfPad = 4;          // query records read past a group's end
 
 // ---------------------------------------------------------------- records
 
@@ -75,17 +74,15 @@ struct alignas(32) BlockBox {
 static_assert(sizeof(BlockBox) == 32, "BlockBox layout");
 constexpr uint32_t kBoxShift = 6;  // log2 of the entries per box (one wave)
 
-// FP32 filter record of a query segment (32 bytes: one wave-uniform scalar
-// load), written by the preparation kernel in query order and copied into
-// bucket order.  The FP64 data of a query segment is not stored: where it is
-// needed (recheck, plain form) it is derived again from the query arrays by
-// the same operations.
+// FP32 filter record of a query segment, written by the preparation kernel in
+// query order, as is its FP64 data (QEval).
 struct alignas(64) QF32 {
     float cx, cy, cz, R;  // sphere of the clipped segment, R >= r + d + margins
     float a32, b32;       // clipped window rounded outwards
     uint32_t lo, hi;      // candidate range
     Box32 box;            // box of the clipped segment grown by d (seg_box32)
-    float pad[2];
+    uint32_t req;         // request of the query segment
+    float pad;
 };
 static_assert(sizeof(QF32) == 64, "QF32 layout");
 
@@ -155,16 +152,17 @@ struct alignas(16) ReqCounter {
 
 // ---------------------------------------------------------------- host objects
 
+struct QEval;  // canon.hpp
+
 struct Workspace {
     int device = 0;
     // query-side buffers, sized for `q_cap` query segments and `r_cap` requests
     size_t q_cap = 0, r_cap = 0, item_cap = 0, res_cap = 0;
-    QF32* qfu = nullptr;            // filter records in query order
-    uint32_t* qreq = nullptr;       // request of each query segment
     uint32_t* qkey = nullptr;
     uint32_t* qslot = nullptr;
-    uint32_t* qsorted = nullptr;
-    QF32* qf = nullptr;             // q_cap + kQfPad records
+    uint32_t* qsorted = nullptr;    // query segments in bucket order
+    QF32* qf = nullptr;             // filter records in query order
+    QEval* qev = nullptr;           // FP64 data in query order
     double* qstage = nullptr;       // staging of host query arrays (8 * stage_cap doubles)
     uint32_t* qtraj_stage = nullptr;
     size_t stage_cap = 0, traj_cap = 0;
@@ -464,14 +462,15 @@ int batch_impl(tds_index* idx, const tds_segments* Q, const tds_request* reqs, u
 int validate_requests(const tds_request* reqs, uint32_t nreq, uint64_t nq, uint64_t out_cap);
 
 // Pieces of the search pipeline used by the batcher (search.hip).
+constexpr uint32_t kChunkAuto = 1u << 31;  // chunk: at most this, by the number of work items
 struct PipelineConfig {
     int prec;
-    uint32_t chunk;
+    uint32_t chunk;  // candidates per work item, | kChunkAuto
     uint32_t grid_waves;
     uint32_t cpl;  // FP32 form: candidates per lane per tile
 };
 int resolve_config(const tds_search_params* params, PipelineConfig* cfg);
-uint64_t item_table_bound(const tds_index* idx, uint64_t nq, uint32_t chunk);
+uint64_t item_table_bound(const tds_index* idx, uint64_t nq, const PipelineConfig& cfg);
 // Enqueues the fixed-shape launch sequence for the batch described by the
 // workspace's descriptor and requests; query arrays at qarrays[0..7] (stride
 // q_grid doubles apart is not required: any device pointers), traj may be

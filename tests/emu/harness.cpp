@@ -31,8 +31,8 @@
 // and d from 1e-3 to 1e9, separations of d (1 + eps) with eps down to 0) and
 // counts the pairs that the canonical evaluation accepts but the FP32
 // filter (sphere32 spheres and sphere_pass, the outward-rounded time
-// extents, seg_box32 boxes and box_overlap, built as the kernels build them)
-// would drop: "misses", which must be 0.  "naive" counts the accepted pairs
+// extents, seg_box32 boxes and box_overlap, the closest-approach refinement,
+// built as the kernels build them) would drop: "misses", which must be 0.  "naive" counts the accepted pairs
 // that boxes without margins (end points rounded to nearest, grown by d in
 // FP32) would drop, which shows that the pairs are close enough to the
 // boundary to matter.
@@ -336,6 +336,27 @@ int run_fill(char** argv) {
     return 0;
 }
 
+// The closest-approach refinement, from the data the kernels keep.
+bool refine_keeps(const tds::QCanon& q, float qcx, float qcy, float qcz, float qR, float ecx,
+                  float ecy, float ecz, float er, double evx, double evy, double evz, double ets,
+                  double ete) {
+    tds::QF32 f = {};
+    f.cx = qcx;
+    f.cy = qcy;
+    f.cz = qcz;
+    f.R = qR;
+    f.a32 = tds::f32_rd(q.aq);
+    f.b32 = tds::f32_ru(q.bq);
+    tds::QTime t = {};
+    t.a = f.a32;
+    t.b = f.b32;
+    const tds::EntryV32 v = {(float)evx, (float)evy, (float)evz, (float)(0.5 * (ets + ete))};
+    const float la = tds::f32_rd(ets), lb = tds::f32_ru(ete);
+    const tds::ERef x = tds::eref_of(ecx, ecy, ecz, er, v, la, lb);
+    return tds::refine32(t, tds::qref_of(q, f), x.ox, x.oy, x.oz, x.vx, x.vy, x.vz, la, lb, x.sc,
+                         x.sv, x.st);
+}
+
 int run_filtercheck(char** argv) {
     using tds::Box32;
     using tds::QCanon;
@@ -412,7 +433,8 @@ int run_filtercheck(char** argv) {
         const Box32 qb = tds::seg_box32(pa[0], pa[1], pa[2], pb[0], pb[1], pb[2], d);
         const bool time_ok = tds::f32_rd(q.aq) < tds::f32_ru(ete) && tds::f32_rd(ets) < tds::f32_ru(q.bq);
         if (!(tds::sphere_pass(qcx, qcy, qcz, qR, ecx, ecy, ecz, er) && time_ok &&
-              tds::box_overlap(eb, qb)))
+              tds::box_overlap(eb, qb)) ||
+            !refine_keeps(q, qcx, qcy, qcz, qR, ecx, ecy, ecz, er, evx, evy, evz, ets, ete))
             ++misses;
         const float df = (float)d;
         const Box32 nb = {(float)std::min(e0[0], e1[0]), (float)std::min(e0[1], e1[1]),

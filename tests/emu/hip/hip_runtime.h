@@ -114,6 +114,9 @@ template <class T> inline T __shfl_up(T v, unsigned d, int = 64) {
 }
 // AMDGCN builtins the sources call directly
 inline unsigned long long __builtin_amdgcn_ballot_w64(bool p) { return __ballot(p); }
+inline bool __builtin_amdgcn_inverse_ballot_w64(unsigned long long m) {
+    return (m >> __lane_id()) & 1ull;
+}
 inline int __builtin_amdgcn_readlane(int v, int l) { return emu_xchg(v, (unsigned)l); }
 // the sources apply it to wave-uniform values only, which every lane holds
 inline int __builtin_amdgcn_readfirstlane(int v) { return v; }
@@ -123,6 +126,11 @@ inline void __builtin_amdgcn_wave_barrier() { emu_wave().bar->arrive_and_wait();
 inline float __builtin_amdgcn_sqrtf(float x) {
     const float r = std::sqrt(x);
     return (r > 0.f && r < INFINITY) ? std::nextafter(r, 0.f) : r;
+}
+// likewise the hardware reciprocal (1 ulp), on the side away from zero
+inline float __builtin_amdgcn_rcpf(float x) {
+    const float r = 1.0f / x;
+    return std::isfinite(r) ? std::nextafter(r, r > 0.f ? INFINITY : -INFINITY) : r;
 }
 #define __builtin_amdgcn_fence(order, scope) std::atomic_thread_fence(std::memory_order_seq_cst)
 #define __HIP_MEMORY_SCOPE_AGENT 3
