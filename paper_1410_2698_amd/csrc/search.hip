@@ -313,9 +313,11 @@ __device__ inline uint32_t request_of(const Request* req, uint32_t nreq, uint64_
 __global__ __launch_bounds__(kBlock) void k_zero(SearchHeader* hdr, uint32_t* b_count,
                                                  uint32_t* b_hi, uint32_t nb,
                                                  uint32_t nparts, ReqCounter* rc, uint32_t nreq,
-                                                 unsigned long long* dyn_ctr) {
+                                                 unsigned long long* dyn_ctr,
+                                                 unsigned long long dir_first) {
     // nreq: capacity of the request counters (all of them are cleared);
-    // b_count and b_hi hold nparts parts for each of the nb buckets
+    // b_count and b_hi hold nparts parts for each of the nb buckets;
+    // dir_first: first position of the direct output not given to a wave yet
     const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i == 0) {
         SearchHeader h = {};
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(kBlock) void k_zero(SearchHeader* hdr, uint32_t* b_
         rc[i].count = 0;
         rc[i].pad = 0;
     }
-    if (i < kCtrSlots * kCtrStride) dyn_ctr[i] = 0;
+    if (i < kCtrSlots * kCtrStride) dyn_ctr[i] = i == kCtrDirect * kCtrStride ? dir_first : 0ull;
 }
 
 // Canonical FP64 data of query segment k of request r, from the query
@@ -775,12 +777,13 @@ __global__ void k_reset_pass(ReqCounter* rc, uint32_t nreq, unsigned long long* 
 }
 
 // Adds the per-workgroup counters of one distance-kernel launch to the
-// header (one block).
-__global__ __launch_bounds__(256) void k_stats_fold(const BlockStats* __restrict__ bs, uint32_t nb,
-                                                    SearchHeader* hdr) {
-    __shared__ uint64_t red[5][256];
+// header (one block of kThreads).
+template <uint32_t kThreads>
+__device__ inline void fold_stats(const BlockStats* __restrict__ bs, uint32_t nb,
+                                  SearchHeader* hdr) {
+    __shared__ uint64_t red[5][kThreads / kWave];
     uint64_t v[5] = {0, 0, 0, 0, 0};
-    for (uint32_t i = threadIdx.x; i < nb; i += 256) {
+    for (uint32_t i = threadIdx.x; i < nb; i += kThreads) {
         const BlockStats b = bs[i];
         v[0] += b.tests;
         v[1] += b.evals;
@@ -788,20 +791,26 @@ __global__ __launch_bounds__(256) void k_stats_fold(const BlockStats* __restrict
         v[3] += b.btests;
         v[4] += b.flushes;
     }
-    for (int k = 0; k < 5; ++k) red[k][threadIdx.x] = v[k];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        for (uint32_t off = kWave / 2; off; off >>= 1) v[k] += __shfl_xor(v[k], (int)off);
+        if (__lane_id() == 0) red[k][threadIdx.x / kWave] = v[k];
+    }
     __syncthreads();
-    for (uint32_t off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off)
-            for (int k = 0; k < 5; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + off];
-        __syncthreads();
-    }
     if (threadIdx.x == 0) {
-        hdr->tests += red[0][0];
-        hdr->evals += red[1][0];
-        hdr->ftests += red[2][0];
-        hdr->btests += red[3][0];
-        hdr->flushes += (uint32_t)red[4][0];
+        for (int k = 0; k < 5; ++k) v[k] = 0;
+        for (uint32_t w = 0; w < kThreads / kWave; ++w)
+            for (int k = 0; k < 5; ++k) v[k] += red[k][w];
+        hdr->tests += v[0];
+        hdr->evals += v[1];
+        hdr->ftests += v[2];
+        hdr->btests += v[3];
+        hdr->flushes += (uint32_t)v[4];
     }
+}
+__global__ __launch_bounds__(256) void k_stats_fold(const BlockStats* __restrict__ bs, uint32_t nb,
+                                                    SearchHeader* hdr) {
+    fold_stats<256>(bs, nb, hdr);
 }
 
 // Waves of a distance-kernel launch that may use direct output (the fill
@@ -930,6 +939,159 @@ __global__ __launch_bounds__(256) void k_fill_copy(const uint64_t* __restrict__ 
     }
 }
 
+// A wave's last reservation in dlast: g chunks of C positions of which it used
+// the first `used`, as (g - 1) << 56 | first chunk << 16 | used.
+__device__ inline uint64_t pack_last(uint64_t first, uint32_t g, uint32_t used) {
+    return (uint64_t)(g - 1) << 56 | first << 16 | used;
+}
+struct LastRes {
+    uint64_t first;   // chunk
+    uint64_t a, e;    // its unused positions [a, e)
+};
+__device__ inline LastRes unpack_last(uint64_t v, uint32_t C) {
+    LastRes l;
+    l.first = v >> 16 & ((1ull << 40) - 1);
+    l.a = l.first * C + (v & 0xFFFFu);
+    l.e = (l.first + (v >> 56) + 1) * C;
+    return l;
+}
+
+// Direct output of a launch of up to kFillWaves waves, after the distance
+// kernel: the number of results (positions reserved less the unused ones), the
+// fill (see k_fill_plan: holes below T = min(count, capacity), sources at or
+// past T) and, by the last workgroup, the fold of the launch's counters.
+// Between T and the last source that is moved lie no more positions than all
+// the unused ones together, U, so the chunks T / C .. T / C + U / C + 1 are
+// enough, and positions past the capacity within U of it are in the scratch
+// buffer.
+//
+// Bound by the latency of the chain launch, load of the waves' words, prefix
+// sums, load of the records, store, at about 2 us for each access that comes
+// from memory.  So every workgroup makes the plan for itself, in LDS: as two
+// kernels (one workgroup's plan in memory, then the copy) and the fold it was
+// three launches and 25 us for a small search, now 12.5 (dense walks, 8000
+// items: 53 -> 16.5).  The sums fit 32 bits: U is
+// at most the stage buffer's 2^23 records.
+constexpr uint32_t kFillWaves = 4096;
+constexpr uint32_t kFillBlocks = 128;  // and one for the fold
+constexpr uint32_t kFillChunks = 4 * kFillWaves;  // most chunks of the waves' last reservations
+__global__ __launch_bounds__(1024) void k_fill(const Request* __restrict__ req,
+                                               ReqCounter* __restrict__ rc,
+                                               const unsigned long long* __restrict__ dir_ctr,
+                                               const uint64_t* __restrict__ dlast, uint32_t nw,
+                                               uint32_t C, tds_result* __restrict__ out,
+                                               const tds_result* __restrict__ scratch,
+                                               const BlockStats* __restrict__ bs, uint32_t nb,
+                                               SearchHeader* __restrict__ hdr) {
+    __shared__ uint64_t last[kFillWaves];
+    __shared__ uint32_t hpre[kFillWaves];       // hole positions before wave w's
+    __shared__ uint32_t src[kFillChunks + 2];   // positions used of chunk c0 + i at or past T,
+                                                // then the sources before them
+    __shared__ uint32_t s_u[1024 / kWave], s_s[1024 / kWave], s_d[1024 / kWave];
+    if (blockIdx.x == gridDim.x - 1) {
+        fold_stats<1024>(bs, nb, hdr);
+        return;
+    }
+    const uint32_t t = threadIdx.x, lane = __lane_id(), wv = t / kWave;
+    const Request Rq = req[0];
+    const uint64_t R = *dir_ctr;
+    for (uint32_t w = t; w < nw; w += 1024) last[w] = dlast[w];
+    __syncthreads();
+    // consecutive waves, and below consecutive chunks, per thread: a prefix sum
+    // is one step within the waves and one over them
+    const uint32_t pw = (nw + 1023) / 1024, w0 = min(nw, t * pw), w1 = min(nw, w0 + pw);
+    const auto over_c = [&](uint64_t v) {
+        return C & (C - 1) ? v / C : v >> (uint32_t)__builtin_ctz(C);
+    };
+    uint32_t u = 0;
+#pragma unroll 1
+    for (uint32_t w = w0; w < w1; ++w) {
+        const LastRes l = unpack_last(last[w], C);
+        u += (uint32_t)(l.e - l.a);
+    }
+    u = wave_scan(u);
+    if (lane == kWave - 1) s_u[wv] = u;
+    __syncthreads();
+    uint32_t unused = 0;
+#pragma unroll 1
+    for (uint32_t k = 0; k < 1024 / kWave; ++k) unused += s_u[k];
+    const uint64_t count = R - unused, T = min(count, Rq.out_capacity);
+    const uint64_t c0 = over_c(T), nch = over_c(R);
+    const uint32_t skip = (uint32_t)(T - c0 * C);  // chunk c0's positions below T
+    const uint32_t ns =
+        nch > c0 ? (uint32_t)min(min(nch - c0, over_c(unused) + 2), (uint64_t)kFillChunks + 2)
+                 : 0u;
+    // full unless a wave's last
+    for (uint32_t i = t; i < ns; i += 1024) src[i] = C - (i ? 0u : skip);
+    __syncthreads();
+    uint32_t dsum = 0;
+#pragma unroll 1
+    for (uint32_t w = w0; w < w1; ++w) {
+        const LastRes l = unpack_last(last[w], C);
+        const uint64_t e = min(l.e, T);
+        if (e > l.a) dsum += (uint32_t)(e - l.a);
+        uint64_t p = l.first * C;
+        for (uint64_t k = l.first; p < l.e; ++k, p += C)
+            if (p + C > l.a && k >= c0 && k - c0 < ns) {
+                const uint64_t f = max(p, T);
+                src[k - c0] = l.a > f ? (uint32_t)(l.a - f) : 0u;
+            }
+    }
+    __syncthreads();
+    const uint32_t ps = (ns + 1023) / 1024, i0 = min(ns, t * ps), i1 = min(ns, i0 + ps);
+    uint32_t ssum = 0;
+#pragma unroll 1
+    for (uint32_t i = i0; i < i1; ++i) ssum += src[i];
+    const uint32_t is = wave_scan(ssum), id = wave_scan(dsum);
+    if (lane == kWave - 1) {
+        s_s[wv] = is;
+        s_d[wv] = id;
+    }
+    __syncthreads();
+    uint32_t sp = is - ssum, dp = id - dsum, total = 0;
+#pragma unroll 1
+    for (uint32_t k = 0; k < 1024 / kWave; ++k) {
+        if (k < wv) {
+            sp += s_s[k];
+            dp += s_d[k];
+        }
+        total += s_d[k];
+    }
+#pragma unroll 1
+    for (uint32_t i = i0; i < i1; ++i) {
+        const uint32_t n = src[i];
+        src[i] = sp;
+        sp += n;
+    }
+#pragma unroll 1
+    for (uint32_t w = w0; w < w1; ++w) {
+        const LastRes l = unpack_last(last[w], C);
+        const uint64_t e = min(l.e, T);
+        hpre[w] = dp;
+        if (e > l.a) dp += (uint32_t)(e - l.a);
+    }
+    if (blockIdx.x == 0 && t == 0) rc[0].count = count;
+    __syncthreads();
+    // last entry of p[0 .. n) that is at most x (p[0] is 0)
+    const auto find = [](const uint32_t* p, uint32_t n, uint32_t x) {
+        uint32_t a = 0;
+        while (n > 1) {
+            const uint32_t h = n >> 1;
+            if (p[a + h] <= x) a += h;
+            n -= h;
+        }
+        return a;
+    };
+    for (uint32_t x = blockIdx.x * 1024 + t; x < total; x += (gridDim.x - 1) * 1024) {
+        const uint32_t w = find(hpre, nw, x), a = find(src, ns, x);
+        const uint64_t dst = unpack_last(last[w], C).a + (x - hpre[w]);
+        const uint64_t from = max((c0 + a) * C, T) + (x - src[a]);
+        const tds_result v =
+            from < Rq.out_capacity ? out[Rq.out_offset + from] : scratch[from - Rq.out_capacity];
+        out[Rq.out_offset + dst] = v;
+    }
+}
+
 // The distance kernel's arguments.  Steps off the filter's walk take them from
 // the kernel's argument block anew (cold_args), so that they are not held in
 // scalar registers, which spilled by the dozen, across the walk.
@@ -965,10 +1127,12 @@ struct DistArgs {
     // request's output through per-wave reservations of dir_chunk positions
     uint32_t direct;
     uint32_t dir_chunk;
+    uint32_t dir_max;       // most chunks of one reservation
+    uint32_t dir_count;     // the waves add their results to the request's counter
     unsigned long long* dir_ctr;  // next free position (reservation counter)
     tds_result* dscratch;   // positions [cap, cap + dscratch_cap) (the stage buffer)
     uint64_t dscratch_cap;
-    uint64_t* dlast;        // per wave: last reservation (chunk << 16 | used), ~0: none
+    uint64_t* dlast;        // per wave: last reservation (pack_last)
 };
 
 #if defined(__AMDGCN__)
@@ -1050,6 +1214,7 @@ struct ItemState {
     // direct output: the wave's open reservation [dpos, dend) (kept across
     // items) and its reservations so far
     uint64_t dpos, dend;
+    uint32_t dg;      // chunks of the open reservation
     uint32_t nres;
     // per lane j of the group
     uint32_t qr;      // request of query j
@@ -1189,16 +1354,19 @@ __device__ __forceinline__ void drain(WaveLDS& L, ItemState& S, const DistArgs& 
     }
     if (A->direct) {
         if (!nhit) return;
-        // nhit <= 64 <= dir_chunk: at most one new reservation
+        // nhit <= 64 <= dir_chunk: at most one new reservation, of twice the
+        // last one's chunks
         const uint64_t room = S.dend - S.dpos;
         uint64_t pos = S.dpos + rank;
         if (nhit > room) {
             unsigned long long nb = 0;
-            if (lane == 0) nb = atomicAdd(A->dir_ctr, (unsigned long long)A->dir_chunk);
+            S.dg = min(2 * S.dg, A->dir_max);
+            const uint32_t size = S.dg * A->dir_chunk;
+            if (lane == 0) nb = atomicAdd(A->dir_ctr, (unsigned long long)size);
             const uint64_t b = lane0_64(nb);
             if (rank >= room) pos = b + (rank - room);
             S.dpos = b + (nhit - room);
-            S.dend = b + A->dir_chunk;
+            S.dend = b + size;
             ++S.nres;
         } else {
             S.dpos += nhit;
@@ -1594,7 +1762,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const uint32_t lane = __lane_id();
     uint64_t tests = 0, evals_total = 0, ftests = 0, btests = 0;
     uint32_t flushes = 0;  // stage flushes at the end of an item (direct output: reservations)
-    uint64_t dpos = 0, dend = 0, found_total = 0;  // direct output (see DistArgs)
+    // direct output (see DistArgs): the wave's open reservation, at first the
+    // chunk of its number
+    const uint64_t dfirst = (uint64_t)(blockIdx.x * kWavesPerBlock + wid) * A.dir_chunk;
+    uint64_t dpos = dfirst, dend = dfirst + A.dir_chunk;
+    uint32_t dg = 1;
+    uint64_t found_total = 0;
     // all items of the search, unless a range is given (incremental passes)
     const uint32_t item_end = (A.item_end == 0xFFFFFFFFu)
                                   ? uniform(min(A.hdr->n_items, A.desc->item_cap))
@@ -1723,6 +1896,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         S.btests = 0;
         S.dpos = dpos;
         S.dend = dend;
+        S.dg = dg;
         S.nres = 0;
         // the group's data.  A lane without a query: an empty box (it never
         // passes a block), an unbounded window and range (it never stands in
@@ -1768,6 +1942,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
         dpos = S.dpos;
         dend = S.dend;
+        dg = S.dg;
         flushes += S.nres;
         found_total += S.found;
         tests += (uint64_t)(S.c1 - S.c0) * S.nq;
@@ -1783,11 +1958,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
     }
     if (A.direct && lane == 0) {
-        // the wave's results and its last reservation (chunk, positions used)
-        if (found_total) atomicAdd(&A.rc[0].count, (unsigned long long)found_total);
+        // the wave's last reservation and, where the fill does not count them,
+        // its results
+        const uint32_t size = dg * A.dir_chunk;
         A.dlast[blockIdx.x * kWavesPerBlock + wid] =
-            dend ? ((dend / A.dir_chunk - 1) << 16) | (A.dir_chunk - (dend - dpos)) : ~0ull;
+            pack_last((dend - size) / A.dir_chunk, dg, size - (uint32_t)(dend - dpos));
+        if (A.dir_count && found_total)
+            atomicAdd(&A.rc[0].count, (unsigned long long)found_total);
     }
+    // the first reservation counts as one that was made, once it holds a result
+    if (A.direct && !(dpos == dfirst)) ++flushes;
     // per-workgroup counters (folded into the header by k_stats_fold), each
     // wave's in the front of its own LDS, which it no longer uses
     wave_sync();
@@ -2098,6 +2278,19 @@ int stage_queries(const tds_segments* Q, QueryView* V, hipStream_t s, double** s
     return TDS_OK;
 }
 
+// Positions per chunk of the direct output (a whole number of 64): a quarter
+// of a wave's stage.  A wave's first chunk is given to it, the next
+// reservations are of 2, 4, 4 ... chunks.  A returning atomic on one counter
+// takes 30 ns of the chip's time: with reservations of 128, 256, 512 or 2048
+// positions 71 million results take 16.7, 8.9, 5.0 or 4.4 ms, so they have to
+// be large, but the holes that large first ones leave cost the fill 40 to 74 us
+// where a wave has few results, and the first atomic of every wave at the
+// search's end as much again (8000 items of dense walks: kernel 143 -> 114 us
+// without it and without the waves' atomics on the number of results).
+uint32_t direct_chunk(uint32_t stage_cap) {
+    return std::max((uint32_t)kWave, stage_cap / 4 / kWave * kWave);
+}
+
 DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q, tds_result* out,
                    uint64_t win_lo, uint32_t item_begin, uint32_t item_end, uint32_t* item_count,
                    uint32_t grid_waves, bool by_order, uint32_t cpl, bool one,
@@ -2129,14 +2322,17 @@ DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q,
     A.item_begin = item_begin;
     A.item_end = item_end;
     A.item_count = item_count;
-    // direct output: chunks of a wave's stage size, the stage buffer as the
-    // scratch for positions past the capacity (W C records, within it)
+    // direct output: reservations of up to a wave's stage size, the stage
+    // buffer as the scratch for positions past the capacity
     const uint32_t waves = launch_blocks(grid_waves) * kWavesPerBlock;
     A.direct = (direct && !by_order && win_lo == 0 && waves <= kMaxDirectWaves &&
                 waves <= w->stage_waves && A.stage_cap >= (uint32_t)kWave)
                    ? 1u
                    : 0u;
-    A.dir_chunk = A.stage_cap;
+    const bool small = waves <= kFillWaves;
+    A.dir_chunk = small ? direct_chunk(A.stage_cap) : A.stage_cap;
+    A.dir_max = small ? std::min(A.stage_cap / A.dir_chunk, kFillChunks / waves) : 1u;
+    A.dir_count = small ? 0u : 1u;
     A.dir_ctr = w->dyn_ctr + (size_t)kCtrDirect * kCtrStride;
     A.dscratch = w->stage;
     A.dscratch_cap = (uint64_t)waves * A.stage_cap;
@@ -2144,8 +2340,7 @@ DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q,
     return A;
 }
 
-// The distance kernel, timed by the two events when both are given, then the
-// fold of its per-workgroup counters into the header.
+// The distance kernel, timed by the two events when both are given.
 int launch_distance(int prec, const DistArgs& A, uint32_t grid_waves, hipStream_t s,
                     hipEvent_t ev_begin, hipEvent_t ev_end) {
     const uint32_t blocks = launch_blocks(grid_waves);
@@ -2164,18 +2359,28 @@ int launch_distance(int prec, const DistArgs& A, uint32_t grid_waves, hipStream_
     } else {
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, s, A);
     }
-    hipLaunchKernelGGL(k_stats_fold, dim3(1), dim3(256), 0, s, A.bstats, blocks, A.hdr);
     TDS_HIP(hipGetLastError());
     return TDS_OK;
 }
 
-// Direct output: the fill of the holes left by the waves' last reservations.
-int launch_fill(const DistArgs& A, const Workspace* w, uint32_t grid_waves, hipStream_t s) {
-    const uint32_t nw = launch_blocks(grid_waves) * kWavesPerBlock;
-    hipLaunchKernelGGL(k_fill_plan, dim3(1), dim3(1024), 0, s, A.req, A.rc, A.dir_ctr, A.dlast,
-                       nw, A.dir_chunk, w->fill_s, w->fill_d, w->fill_dstart, w->fill_plan);
-    hipLaunchKernelGGL(k_fill_copy, dim3(1024), dim3(256), 0, s, w->fill_plan, w->fill_s,
-                       w->fill_d, w->fill_dstart, nw, A.dir_chunk, A.req, A.out, A.dscratch);
+// After the distance kernel: the fold of its counters and, with direct output,
+// the fill of the holes left by the waves' last reservations.
+int launch_finish(const DistArgs& A, const Workspace* w, uint32_t grid_waves, hipStream_t s) {
+    const uint32_t blocks = launch_blocks(grid_waves), nw = blocks * kWavesPerBlock;
+    if (A.direct && !A.dir_count) {
+        hipLaunchKernelGGL(k_fill, dim3(kFillBlocks + 1), dim3(1024), 0, s, A.req, A.rc, A.dir_ctr,
+                           A.dlast, nw, A.dir_chunk, A.out, A.dscratch, A.bstats, blocks, A.hdr);
+        TDS_HIP(hipGetLastError());
+        return TDS_OK;
+    }
+    hipLaunchKernelGGL(k_stats_fold, dim3(1), dim3(256), 0, s, A.bstats, blocks, A.hdr);
+    if (A.direct) {
+        hipLaunchKernelGGL(k_fill_plan, dim3(1), dim3(1024), 0, s, A.req, A.rc, A.dir_ctr,
+                           A.dlast, nw, A.dir_chunk, w->fill_s, w->fill_d, w->fill_dstart,
+                           w->fill_plan);
+        hipLaunchKernelGGL(k_fill_copy, dim3(1024), dim3(256), 0, s, w->fill_plan, w->fill_s,
+                           w->fill_d, w->fill_dstart, nw, A.dir_chunk, A.req, A.out, A.dscratch);
+    }
     TDS_HIP(hipGetLastError());
     return TDS_OK;
 }
@@ -2193,9 +2398,12 @@ int enqueue_pipeline(const tds_index* idx, Workspace* w, const QueryView& Q, siz
     const uint32_t nb = bucket_count(idx->m);
     const uint32_t nparts = count_parts(nb);
     const uint32_t zn = std::max(std::max(nb * nparts, r_cap), kCtrSlots * kCtrStride);
+    const DistArgs A = dist_args(idx, w, Q, out, 0, 0, 0xFFFFFFFFu, item_count, grid_waves, false,
+                                 cpl, r_cap == 1, direct);
     // k_zero also clears the request counters the distance kernel appends with
     hipLaunchKernelGGL(k_zero, dim3(ceil_div(zn, kBlock)), dim3(kBlock), 0, s, w->hdr, w->b_count,
-                       w->b_hi, nb, nparts, w->req_ctr, r_cap, w->dyn_ctr);
+                       w->b_hi, nb, nparts, w->req_ctr, r_cap, w->dyn_ctr,
+                       (unsigned long long)launch_blocks(grid_waves) * kWavesPerBlock * A.dir_chunk);
     const uint32_t qblocks = std::max(1u, ceil_div(q_grid, kBlock));
     const uint32_t bpp = ceil_div(qblocks, nparts);  // workgroup b counts in part b / bpp < nparts
     hipLaunchKernelGGL(k_qprep, dim3(qblocks), dim3(kBlock), 0, s, Q, w->desc, w->req, I, w->qf,
@@ -2208,10 +2416,8 @@ int enqueue_pipeline(const tds_index* idx, Workspace* w, const QueryView& Q, siz
                        w->qslot, w->b_start, w->b_count, nb, bpp, qblocks, w->qsorted, w->binfo,
                        w->item_bucket, w->hdr);
     TDS_HIP(hipGetLastError());
-    const DistArgs A = dist_args(idx, w, Q, out, 0, 0, 0xFFFFFFFFu, item_count, grid_waves, false,
-                                 cpl, r_cap == 1, direct);
     TDS_TRY(launch_distance(prec, A, grid_waves, s, ev_begin, ev_end));
-    return A.direct ? launch_fill(A, w, grid_waves, s) : TDS_OK;
+    return launch_finish(A, w, grid_waves, s);
 }
 
 // Re-runs the distance kernel over work items [i0, i1) keeping result
@@ -2225,10 +2431,10 @@ int enqueue_range(const tds_index* idx, Workspace* w, const QueryView& Q, int pr
     hipLaunchKernelGGL(k_reset_pass, dim3(ceil_div(std::max(r_cap, kCtrSlots * kCtrStride), 256)),
                        dim3(256), 0, s, w->req_ctr, r_cap, w->dyn_ctr);
     TDS_HIP(hipGetLastError());
-    return launch_distance(prec,
-                           dist_args(idx, w, Q, out, win_lo, i0, i1, nullptr, grid_waves, by_order,
-                                     cpl, r_cap == 1),
-                           grid_waves, s, ev_begin, ev_end);
+    const DistArgs A = dist_args(idx, w, Q, out, win_lo, i0, i1, nullptr, grid_waves, by_order,
+                                 cpl, r_cap == 1);
+    TDS_TRY(launch_distance(prec, A, grid_waves, s, ev_begin, ev_end));
+    return launch_finish(A, w, grid_waves, s);
 }
 
 Workspace* acquire(tds_index* idx) {

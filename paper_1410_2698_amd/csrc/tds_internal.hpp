@@ -195,7 +195,7 @@ struct Workspace {
     // direct output (one-request searches): each wave's last reservation and
     // the plan of the pass that fills the holes (sized for stage_waves waves)
     uint64_t* dlast = nullptr;
-    uint64_t* fill_s = nullptr;      // stage_waves + 2 source prefix sums
+    uint64_t* fill_s = nullptr;      // source prefix sums of the chunks
     uint64_t* fill_d = nullptr;      // stage_waves + 1 hole prefix sums
     uint64_t* fill_dstart = nullptr; // stage_waves hole starts
     uint64_t* fill_plan = nullptr;   // T, c0, ns, total
