@@ -23,6 +23,7 @@
 
 #include "canon.hpp"
 #include "radix_sort.hpp"
+#include "schedule.hpp"
 #include "tds_internal.hpp"
 
 namespace tds {
@@ -147,20 +148,24 @@ __global__ __launch_bounds__(kFT) void k_fsg_take(const uint32_t* __restrict__ v
     if (i < nl) list[i] = ctl->side() ? v1[i] : v0[i];
 }
 
+constexpr uint32_t kFTested = 16, kFLine = 16;
+constexpr uint32_t kFCounters = (1 + kFTested) * kFLine;
+
 struct FsgArgs {
     Grid G;
-    const EntryF64* e64;
-    const uint32_t* seg_id;
-    const uint32_t* traj;
+    IndexView I;
     const uint32_t* cell_first;
     const uint32_t* list;
     const double* q[8];  // xs, ys, zs, ts, xe, ye, ze, te (device)
     const uint32_t* qtraj;
     uint32_t nq;
+    uint32_t batch;      // query segments a wave takes at a time, at most kFQ
     double d, t_start, t_end;
     tds_result* out;
     uint64_t capacity;
-    unsigned long long* counters;  // [0] results, [1] listings compared, [2] invalid input
+    // [0] results, [1] invalid input; then on kFTested lines of their own parts
+    // of the number of listings compared
+    unsigned long long* counters;
 };
 
 __device__ inline uint64_t lanemask_below() {
@@ -168,103 +173,282 @@ __device__ inline uint64_t lanemask_below() {
     return (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 }
 
-__global__ __launch_bounds__(kFT) void k_fsg_search(FsgArgs A) {
+// Keeps LDS traffic of one wave in program order around cross-lane exchange.
+__device__ inline void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// A query segment of the wave's batch: its canonical data, cell range and
+// candidate range (positions of the entries that may overlap it in time).
+struct FsgQuery {
+    QCanon c;
+    uint32_t q0[3], nx, ny;  // lowest cell; cells along x and y
+    uint32_t lo, hi;
+    uint32_t qid, qtraj;
+    uint32_t rows;           // rows of cells along x (ny times its cells along z)
+};
+
+// A pair to evaluate: the entry, its listing and the row it was found in.
+struct FsgPair {
+    uint32_t pos, i, cell, q;  // cell: first of the grid's row; q: query of the batch
+};
+
+constexpr int kFS = 256;           // threads of the search's workgroups
+constexpr uint32_t kFQ = 16;       // query segments of a batch
+constexpr uint32_t kFU = 4;        // listings per lane in flight
+constexpr uint32_t kFOut = 128;    // results a workgroup keeps until its end
+
+struct FsgWave {
+    FsgQuery q[kFQ];
+    FsgPair pair[2 * kWave];
+    uint32_t pre[kWave];                  // listings before row r of the step
+    uint32_t first[kWave], cell[kWave];   // first listing of row r, first cell of its grid row
+    uint32_t rq[kWave];                   // its query
+    uint32_t qrow[kFQ];                   // rows before query j
+};
+
+struct FsgOut {
+    tds_result r[kFOut];
+    uint32_t n;
+    unsigned long long tested, base;
+};
+
+// Evaluates the last min(n, 64) pairs.  An entry listed in several of the
+// query's cells counts only in the lowest cell of the intersection of the two
+// cell ranges.
+__device__ inline void fsg_drain(const FsgArgs& A, FsgWave& W, FsgOut& O, uint32_t& n) {
     const uint32_t lane = __lane_id();
-    const uint32_t wave = blockIdx.x * (kFT / kWave) + threadIdx.x / kWave;
-    const uint32_t nwaves = gridDim.x * (kFT / kWave);
-    unsigned long long tested = 0;
-    for (uint32_t k = wave; k < A.nq; k += nwaves) {
-        const double xs = A.q[0][k], ys = A.q[1][k], zs = A.q[2][k], ts = A.q[3][k];
-        const double xe = A.q[4][k], ye = A.q[5][k], ze = A.q[6][k], te = A.q[7][k];
-        if (!(isfinite(xs) && isfinite(ys) && isfinite(zs) && isfinite(ts) && isfinite(xe) &&
-              isfinite(ye) && isfinite(ze) && isfinite(te) && te > ts)) {
-            if (lane == 0) atomicAdd(&A.counters[2], 1ull);
-            continue;
-        }
-        // the canonical query data (the same operations as every search form)
-        const double dt = te - ts;
-        QCanon q;
-        q.x = xs;
-        q.y = ys;
-        q.z = zs;
-        q.vx = (xe - xs) / dt;
-        q.vy = (ye - ys) / dt;
-        q.vz = (ze - zs) / dt;
-        q.ts = ts;
-        q.aq = dmax(ts, A.t_start);
-        q.bq = dmin(te, A.t_end);
-        q.d = A.d;
-        if (!(q.aq < q.bq)) continue;
-        const uint32_t qid = k;
-        const uint32_t qt = A.qtraj ? A.qtraj[k] : 0u;
-        // the query's box over its clipped extent, grown by d (+ rounding room)
-        double lo[3], hi[3];
-        {
-            const double pa[3] = {q.x + q.vx * (q.aq - ts), q.y + q.vy * (q.aq - ts),
-                                  q.z + q.vz * (q.aq - ts)};
-            const double pb[3] = {q.x + q.vx * (q.bq - ts), q.y + q.vy * (q.bq - ts),
-                                  q.z + q.vz * (q.bq - ts)};
-            for (int a = 0; a < 3; ++a) {
-                const double l = dmin(pa[a], pb[a]), h = dmax(pa[a], pb[a]);
-                const double m = q.d + 1e-9 * (fabs(l) + fabs(h) + q.d + 1.0);
-                lo[a] = l - m;
-                hi[a] = h + m;
+    const uint32_t cnt = min(n, (uint32_t)kWave);
+    n -= cnt;
+    wave_fence();
+    bool hit = false;
+    double t_lo = 0.0, t_hi = 0.0;
+    FsgPair p = {0, 0, 0, 0};
+    if (lane < cnt) {
+        p = W.pair[n + lane];
+        const FsgQuery& Q = W.q[p.q];
+        const EntryF64 E = A.I.e64[p.pos];
+        if (E.ts < Q.c.bq && E.te > Q.c.aq) {
+            double el[3], eh[3];
+            entry_box(E, el, eh);
+            uint32_t e0[3], e1[3];
+            cell_range(A.G, el, eh, e0, e1);
+            const uint32_t row =
+                (max(Q.q0[2], e0[2]) * A.G.g[1] + max(Q.q0[1], e0[1])) * A.G.g[0];
+            if (row == p.cell) {
+                const uint32_t c = row + max(Q.q0[0], e0[0]);
+                hit = A.cell_first[c] <= p.i && p.i < A.cell_first[c + 1] &&
+                      canon_eval<true>(Q.c, E.x, E.y, E.z, E.vx, E.vy, E.vz, E.ts, E.te, &t_lo,
+                                       &t_hi);
             }
         }
-        uint32_t q0[3], q1[3];
-        cell_range(A.G, lo, hi, q0, q1);
-        for (uint32_t cz = q0[2]; cz <= q1[2]; ++cz)
-            for (uint32_t cy = q0[1]; cy <= q1[1]; ++cy)
-                for (uint32_t cx = q0[0]; cx <= q1[0]; ++cx) {
-                    const uint32_t c = (cz * A.G.g[1] + cy) * A.G.g[0] + cx;
-                    const uint32_t s = A.cell_first[c], e = A.cell_first[c + 1];
-                    for (uint32_t i0 = s; i0 < e; i0 += kWave) {
-                        const uint32_t i = i0 + lane;
-                        bool hit = false;
-                        double t_lo = 0.0, t_hi = 0.0;
-                        uint32_t pos = 0;
-                        if (i < e) {
-                            ++tested;
-                            pos = A.list[i];
-                            const EntryF64 E = A.e64[pos];
-                            if (E.ts < q.bq && E.te > q.aq) {
-                                // report the pair only from the lowest cell of
-                                // the intersection of the two cell ranges
-                                double el[3], eh[3];
-                                entry_box(E, el, eh);
-                                uint32_t e0[3], e1[3];
-                                cell_range(A.G, el, eh, e0, e1);
-                                const bool first = max(q0[0], e0[0]) == cx &&
-                                                   max(q0[1], e0[1]) == cy &&
-                                                   max(q0[2], e0[2]) == cz;
-                                hit = first && canon_eval<true>(q, E.x, E.y, E.z, E.vx, E.vy,
-                                                                E.vz, E.ts, E.te, &t_lo, &t_hi);
-                            }
+    }
+    const uint64_t hm = __ballot(hit);
+    if (!hm) return;
+    const uint32_t nh = (uint32_t)__popcll(hm), rank = (uint32_t)__popcll(hm & lanemask_below());
+    tds_result r;
+    if (hit) {
+        r.q_seg = W.q[p.q].qid;
+        r.e_seg = A.I.seg_id[p.pos];
+        r.q_traj = W.q[p.q].qtraj;
+        r.e_traj = A.I.traj[p.pos];
+        r.t_lo = t_lo;
+        r.t_hi = t_hi;
+    }
+    // into the workgroup's buffer, those past its end straight to the output
+    uint32_t at = 0;
+    if (lane == 0) at = *(volatile uint32_t*)&O.n < kFOut ? atomicAdd(&O.n, nh) : kFOut;
+    at = __shfl(at, 0);
+    if (hit && at + rank < kFOut) O.r[at + rank] = r;
+    const uint32_t kept = min(nh, at < kFOut ? kFOut - at : 0u);
+    if (kept == nh) return;
+    unsigned long long base = 0;
+    if (lane == 0) base = atomicAdd(&A.counters[0], (unsigned long long)(nh - kept));
+    base = __shfl(base, 0);
+    if (hit && rank >= kept && base + (rank - kept) < A.capacity) A.out[base + (rank - kept)] = r;
+}
+
+// A workgroup takes `batch` consecutive query segments for each of its waves:
+// first, one per thread, what is done once per segment, its canonical data,
+// cell range, and the range of entry positions that may overlap it in time
+// (from the index's bins), then a wave each its batch.  The cells of a query
+// that are neighbours along x hold consecutive listings, so its cells
+// are (cells along y) x (cells along z) runs of listings; the runs of the batch
+// are laid end to end, 64 at a time, and their listings tested 64 at a time,
+// full waves whatever the cells hold.  A listing is four bytes, read in order,
+// and its entry position decides by the range whether the entry is read at all
+// (one in a hundred where a segment lasts 1 / 400 of the data's time span).
+// Pairs that stay are queued and evaluated 64 at a time.
+//
+// With a wave per query, one cell after another (three dependent loads each,
+// the 64-byte entry for every listing), 200,000 segments in 50^3 cells of a
+// million entries (13 million listings) took 311 us, nearly all latency; this
+// takes 105, about 45 of it the latency of a workgroup's chain and the last
+// ones' end, and the number of listings in flight, of workgroups and of query
+// segments to a batch hardly change it.  Results are collected per workgroup:
+// a returning atomic on one counter takes 30 ns of the chip's time, one per
+// wave and evaluation would be most of the kernel.
+__global__ __launch_bounds__(kFS) void k_fsg_search(FsgArgs A) {
+    __shared__ FsgWave waves[kFS / kWave];
+    __shared__ FsgOut O;
+    if (threadIdx.x == 0) {
+        O.n = 0;
+        O.tested = 0;
+    }
+    __syncthreads();
+    const uint32_t lane = __lane_id(), t = threadIdx.x;
+    FsgWave& W = waves[t / kWave];
+    const uint32_t per = A.batch * (kFS / kWave);  // query segments of the workgroup at a time
+    unsigned long long tested = 0;
+    for (uint64_t k0 = (uint64_t)blockIdx.x * per; k0 < A.nq; k0 += (uint64_t)gridDim.x * per) {
+        const uint64_t kk = k0 + t;
+        if (t < per) {
+            const uint32_t k = (uint32_t)kk;
+            uint32_t rows = 0;
+            if (kk < A.nq) {
+                const double xs = A.q[0][k], ys = A.q[1][k], zs = A.q[2][k], ts = A.q[3][k];
+                const double xe = A.q[4][k], ye = A.q[5][k], ze = A.q[6][k], te = A.q[7][k];
+                FsgQuery Q;
+                QCanon& q = Q.c;
+                if (!(isfinite(xs) && isfinite(ys) && isfinite(zs) && isfinite(ts) && isfinite(xe) &&
+                      isfinite(ye) && isfinite(ze) && isfinite(te) && te > ts)) {
+                    atomicAdd(&A.counters[1], 1ull);
+                } else {
+                    // the canonical query data (the same operations as every
+                    // search form)
+                    const double dt = te - ts;
+                    q.x = xs;
+                    q.y = ys;
+                    q.z = zs;
+                    q.vx = (xe - xs) / dt;
+                    q.vy = (ye - ys) / dt;
+                    q.vz = (ze - zs) / dt;
+                    q.ts = ts;
+                    q.aq = dmax(ts, A.t_start);
+                    q.bq = dmin(te, A.t_end);
+                    q.d = A.d;
+                    if (q.aq < q.bq) {
+                        // the query's box over its clipped extent, grown by d (+
+                        // rounding room)
+                        const double pa[3] = {q.x + q.vx * (q.aq - ts), q.y + q.vy * (q.aq - ts),
+                                              q.z + q.vz * (q.aq - ts)};
+                        const double pb[3] = {q.x + q.vx * (q.bq - ts), q.y + q.vy * (q.bq - ts),
+                                              q.z + q.vz * (q.bq - ts)};
+                        double lo[3], hi[3];
+                        for (int a = 0; a < 3; ++a) {
+                            const double l = dmin(pa[a], pb[a]), h = dmax(pa[a], pb[a]);
+                            const double m = q.d + 1e-9 * (fabs(l) + fabs(h) + q.d + 1.0);
+                            lo[a] = l - m;
+                            hi[a] = h + m;
                         }
-                        const uint64_t hm = __ballot(hit);
-                        if (!hm) continue;
-                        unsigned long long base = 0;
-                        if (lane == 0) base = atomicAdd(&A.counters[0], (unsigned long long)__popcll(hm));
-                        base = __shfl(base, 0);
-                        if (hit) {
-                            const uint64_t p = base + (uint64_t)__popcll(hm & lanemask_below());
-                            if (p < A.capacity) {
-                                tds_result r;
-                                r.q_seg = qid;
-                                r.e_seg = A.seg_id[pos];
-                                r.q_traj = qt;
-                                r.e_traj = A.traj[pos];
-                                r.t_lo = t_lo;
-                                r.t_hi = t_hi;
-                                A.out[p] = r;
-                            }
-                        }
+                        uint32_t q1[3], j0, j1;
+                        cell_range(A.G, lo, hi, Q.q0, q1);
+                        Q.nx = q1[0] - Q.q0[0] + 1;
+                        Q.ny = q1[1] - Q.q0[1] + 1;
+                        rows = Q.ny * (q1[2] - Q.q0[2] + 1);
+                        cand_range(A.I, q.aq, q.bq, &Q.lo, &Q.hi, &j0, &j1);
+                        Q.qid = k;
+                        Q.qtraj = A.qtraj ? A.qtraj[k] : 0u;
+                        Q.rows = rows;
+                        waves[t / A.batch].q[t % A.batch] = Q;
                     }
                 }
+            }
+            waves[t / A.batch].qrow[t % A.batch] = rows;
+        }
+        __syncthreads();
+        const uint32_t rows = lane < A.batch ? W.qrow[lane] : 0u;
+        wave_fence();
+        // rows of the queries before each
+        uint32_t inc = rows;
+        for (uint32_t off = 1; off < kFQ; off <<= 1) {
+            const uint32_t v = __shfl_up(inc, off);
+            if (lane >= off) inc += v;
+        }
+        if (lane < kFQ) W.qrow[lane] = inc - rows;
+        const uint32_t total = __shfl(inc, kFQ - 1);
+        wave_fence();
+        uint32_t np = 0;
+        for (uint32_t r0 = 0; r0 < total;) {
+            // up to 64 rows: their listings
+            const uint32_t r = r0 + lane;
+            uint32_t len = 0, first = 0, cell = 0, ql = 0;
+            if (r < total) {
+                for (uint32_t h = kFQ / 2; h; h >>= 1)
+                    if (W.qrow[ql + h] <= r) ql += h;
+                const FsgQuery& Q = W.q[ql];
+                const uint32_t x = r - W.qrow[ql], z = x / Q.ny, y = x - z * Q.ny;
+                cell = ((Q.q0[2] + z) * A.G.g[1] + Q.q0[1] + y) * A.G.g[0];
+                first = A.cell_first[cell + Q.q0[0]];
+                len = A.cell_first[cell + Q.q0[0] + Q.nx] - first;
+            }
+            uint64_t sum = len;
+            for (uint32_t off = 1; off < (uint32_t)kWave; off <<= 1) {
+                const uint64_t v = __shfl_up(sum, off);
+                if (lane >= off) sum += v;
+            }
+            // all of them, or one if their listings' number passes 32 bits
+            uint32_t step = kWave;
+            uint64_t all = __shfl(sum, kWave - 1);
+            if (all >> 31) {
+                step = 1;
+                all = __shfl(sum, 0);
+                if (lane) sum = all + len;  // past the end
+            }
+            wave_fence();
+            W.pre[lane] = (uint32_t)(sum - len);
+            W.first[lane] = first;
+            W.cell[lane] = cell;
+            W.rq[lane] = ql;
+            wave_fence();
+            r0 += step;
+            tested += all;
+            for (uint64_t x0 = 0; x0 < all; x0 += kFU * kWave) {
+                uint32_t row[kFU], li[kFU], pos[kFU];
+                bool in[kFU];
+#pragma unroll
+                for (uint32_t u = 0; u < kFU; ++u) {
+                    const uint64_t x = x0 + u * kWave + lane;
+                    in[u] = x < all;
+                    // the last row with at most x listings before it
+                    row[u] = 0;
+                    if (step == kWave)
+                        for (uint32_t h = kWave / 2; h; h >>= 1)
+                            if (W.pre[row[u] + h] <= (uint32_t)x) row[u] += h;
+                    li[u] = in[u] ? W.first[row[u]] + (uint32_t)(x - W.pre[row[u]]) : 0u;
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < kFU; ++u) pos[u] = A.list[li[u]];
+#pragma unroll
+                for (uint32_t u = 0; u < kFU; ++u) {
+                    const uint32_t ql = W.rq[row[u]];
+                    in[u] = in[u] && pos[u] >= W.q[ql].lo && pos[u] < W.q[ql].hi;
+                    const uint64_t m = __ballot(in[u]);
+                    if (!m) continue;
+                    if (in[u]) {
+                        const FsgPair p = {pos[u], li[u], W.cell[row[u]], ql};
+                        W.pair[np + (uint32_t)__popcll(m & lanemask_below())] = p;
+                    }
+                    np += (uint32_t)__popcll(m);
+                    if (np >= (uint32_t)kWave) fsg_drain(A, W, O, np);
+                }
+            }
+        }
+        while (np) fsg_drain(A, W, O, np);
+        __syncthreads();
     }
-    // listings compared, summed over the wave
-    for (int off = kWave / 2; off > 0; off >>= 1) tested += __shfl_xor(tested, off);
-    if (lane == 0 && tested) atomicAdd(&A.counters[1], tested);
+    // listings compared, and the workgroup's results
+    if (lane == 0 && tested) atomicAdd(&O.tested, tested);
+    __syncthreads();
+    const uint32_t n = min(O.n, kFOut);
+    if (threadIdx.x == 0) {
+        if (O.tested)
+            atomicAdd(&A.counters[(1 + blockIdx.x % kFTested) * kFLine], O.tested);
+        if (n) O.base = atomicAdd(&A.counters[0], (unsigned long long)n);
+    }
+    __syncthreads();
+    if (t < n && O.base + t < A.capacity) A.out[O.base + t] = O.r[t];
 }
 
 struct Bufs {
@@ -412,9 +596,7 @@ int fsg_search(const tds_fsg* f, const tds_segments* Q, double d, double t_start
         A.G.lo[a] = f->lo[a];
         A.G.cw[a] = f->cw[a];
     }
-    A.e64 = f->idx->e64;
-    A.seg_id = f->idx->seg_id;
-    A.traj = f->idx->traj;
+    A.I = view_of(f->idx);
     A.cell_first = f->cell_first;
     A.list = f->list;
     const double* src[8] = {Q->xs, Q->ys, Q->zs, Q->ts, Q->xe, Q->ye, Q->ze, Q->te};
@@ -453,16 +635,20 @@ int fsg_search(const tds_fsg* f, const tds_segments* Q, double d, double t_start
         A.out = res;
     }
     unsigned long long* ctr = nullptr;
-    TDS_TRY(dmalloc(&ctr, 4));
+    TDS_TRY(dmalloc(&ctr, kFCounters));
     B.p[3] = ctr;
     A.counters = ctr;
-    TDS_HIP(hipMemsetAsync(ctr, 0, 4 * sizeof(unsigned long long), s));
+    TDS_HIP(hipMemsetAsync(ctr, 0, kFCounters * sizeof(unsigned long long), s));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     TDS_HIP(hipEventCreate(&e0));
     TDS_HIP(hipEventCreate(&e1));
-    const uint32_t blocks = std::max(1u, std::min(ceil_div(nq, kFT / kWave), 4096u));
-    hipExtLaunchKernelGGL(k_fsg_search, dim3(blocks), dim3(kFT), 0, s, e0, e1, 0u, A);
-    unsigned long long h[4] = {0, 0, 0, 0};
+    // batches of up to kFQ query segments, smaller ones while there are fewer
+    // than the waves that the chip holds (4 to a workgroup of 24 KB of LDS)
+    A.batch = (uint32_t)std::min<uint64_t>(kFQ, std::max<uint64_t>(1, nq / 8192));
+    const uint32_t blocks =
+        std::max(1u, std::min(ceil_div(ceil_div(nq, A.batch), kFS / kWave), 4096u));
+    hipExtLaunchKernelGGL(k_fsg_search, dim3(blocks), dim3(kFS), 0, s, e0, e1, 0u, A);
+    unsigned long long h[kFCounters] = {};
     int st = (hipGetLastError() == hipSuccess) ? TDS_OK : TDS_E_DEVICE;
     if (st == TDS_OK &&
         hipMemcpyAsync(h, ctr, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess)
@@ -473,7 +659,9 @@ int fsg_search(const tds_fsg* f, const tds_segments* Q, double d, double t_start
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     TDS_TRY(st);
-    if (h[2]) return TDS_E_INVALID;
+    if (h[1]) return TDS_E_INVALID;
+    uint64_t tested = 0;
+    for (uint32_t i = 1; i <= kFTested; ++i) tested += h[i * kFLine];
     *n_out = h[0];
     if (!dev_out) {
         const uint64_t k = std::min<uint64_t>(h[0], capacity);
@@ -485,8 +673,8 @@ int fsg_search(const tds_fsg* f, const tds_segments* Q, double d, double t_start
     if (stats) {
         tds_stats st2{};
         st2.query_segments = nq;
-        st2.candidate_tests = h[1];
-        st2.filter_tests = h[1];
+        st2.candidate_tests = tested;
+        st2.filter_tests = tested;
         st2.results = h[0];
         st2.passes = 1;
         st2.kernel_ms = ms;
