@@ -27,6 +27,9 @@ namespace tds {
 constexpr uint32_t kHostRouteThreads = 4;
 constexpr uint32_t kHostRouteQueue = 2 * kHostRouteThreads;
 
+// Records of a batch that go to the caller through pinned memory (2 MB).
+constexpr uint64_t kPinnedRecords = 1u << 16;
+
 namespace {
 
 // Copies the counted records of each request of a batch (at most its
@@ -196,7 +199,11 @@ int Batcher::launch(uint64_t nq, const tds_request* reqs, uint32_t nreq) {
     TDS_HIP(hipGraphLaunch(exec_, stream_));
     ++replays_;
     TDS_TRY(ws_download(w_, nreq, stream_));
-    if (copy_all_ && used_) {
+    // the counted records to pinned memory behind the search: always for the
+    // serving loop, else while they are few (a copy of pageable memory per
+    // request takes 30 us each; of many records the copies are the faster)
+    pinned_ = copy_all_ || used_ <= kPinnedRecords;
+    if (pinned_ && used_) {
         hipLaunchKernelGGL(k_copy_counted, dim3(std::min<uint32_t>(nreq, 1024u)), dim3(256), 0,
                            stream_, w_->req, w_->req_ctr, nreq, dres_, hres_dev_);
         TDS_HIP(hipGetLastError());
@@ -240,10 +247,23 @@ int Batcher::finish(uint64_t* counts, tds_stats* stats, bool* table_overflow) {
 }
 
 int Batcher::copy_out(tds_result* out, const uint64_t* counts) {
+    if (!pinned_) {
+        // more records reserved than kPinnedRecords, but perhaps not found
+        uint64_t total = 0;
+        for (uint32_t r = 0; r < nreq_; ++r)
+            total += std::min<uint64_t>(counts[r], hreq_[r].out_capacity);
+        if (total && total <= kPinnedRecords && nreq_ > 1) {
+            hipLaunchKernelGGL(k_copy_counted, dim3(std::min<uint32_t>(nreq_, 1024u)), dim3(256), 0,
+                               stream_, w_->req, w_->req_ctr, nreq_, dres_, hres_dev_);
+            TDS_HIP(hipGetLastError());
+            TDS_HIP(hipStreamSynchronize(stream_));
+            pinned_ = true;
+        }
+    }
     for (uint32_t r = 0; r < nreq_; ++r) {
         const uint64_t k = std::min<uint64_t>(counts[r], hreq_[r].out_capacity);
         if (!k) continue;
-        if (copy_all_) {
+        if (pinned_) {
             std::memcpy(out + hreq_[r].out_offset, hres_ + hreq_[r].out_offset,
                         k * sizeof(tds_result));
         } else {
@@ -251,7 +271,7 @@ int Batcher::copy_out(tds_result* out, const uint64_t* counts) {
                                    k * sizeof(tds_result), hipMemcpyDeviceToHost, stream_));
         }
     }
-    if (!copy_all_) TDS_HIP(hipStreamSynchronize(stream_));
+    if (!pinned_) TDS_HIP(hipStreamSynchronize(stream_));
     return TDS_OK;
 }
 

@@ -64,6 +64,7 @@ private:
     tds_result* hres_dev_ = nullptr;  // hres_ as the device sees it
     bool staged_on_device_ = false;
     bool copy_all_ = false;
+    bool pinned_ = false;         // the batch's records are in hres_
     hipGraph_t graph_ = nullptr;
     hipGraphExec_t exec_ = nullptr;
     std::chrono::steady_clock::time_point t0_;

@@ -451,6 +451,48 @@ __global__ __launch_bounds__(kFS) void k_fsg_search(FsgArgs A) {
     if (t < n && O.base + t < A.capacity) A.out[O.base + t] = O.r[t];
 }
 
+constexpr size_t kFsgPool = 16;
+
+void free_scratch(FsgScratch& x) {
+    dfree(x.ctr);
+    if (x.ctr_host) (void)hipHostFree(x.ctr_host);
+    if (x.e0) (void)hipEventDestroy(x.e0);
+    if (x.e1) (void)hipEventDestroy(x.e1);
+    x = {};
+}
+
+// A search's counters and events, from the grid's pool or new, given back (or
+// freed, past kFsgPool) at the end.
+struct ScratchLease {
+    const tds_fsg* f;
+    FsgScratch x;
+    explicit ScratchLease(const tds_fsg* g) : f(g) {
+        std::lock_guard<std::mutex> l(f->mu);
+        if (f->pool.empty()) return;
+        x = f->pool.back();
+        f->pool.pop_back();
+    }
+    int ready() {
+        if (x.e1) return TDS_OK;
+        TDS_TRY(dmalloc(&x.ctr, kFCounters));
+        TDS_HIP(hipHostMalloc((void**)&x.ctr_host, kFCounters * sizeof(unsigned long long),
+                              hipHostMallocDefault));
+        TDS_HIP(hipEventCreate(&x.e0));
+        TDS_HIP(hipEventCreate(&x.e1));
+        return TDS_OK;
+    }
+    ~ScratchLease() {
+        {
+            std::lock_guard<std::mutex> l(f->mu);
+            if (x.e1 && f->pool.size() < kFsgPool) {
+                f->pool.push_back(x);
+                return;
+            }
+        }
+        free_scratch(x);
+    }
+};
+
 struct Bufs {
     void* p[8] = {};
     ~Bufs() {
@@ -568,6 +610,7 @@ int fsg_build(const tds_index* idx, uint32_t gx, uint32_t gy, uint32_t gz, hipSt
 
 void fsg_destroy(tds_fsg* f) {
     if (!f) return;
+    for (FsgScratch& x : f->pool) free_scratch(x);
     dfree(f->cell_first);
     dfree(f->list);
     delete f;
@@ -634,30 +677,26 @@ int fsg_search(const tds_fsg* f, const tds_segments* Q, double d, double t_start
         B.p[2] = res;
         A.out = res;
     }
-    unsigned long long* ctr = nullptr;
-    TDS_TRY(dmalloc(&ctr, kFCounters));
-    B.p[3] = ctr;
-    A.counters = ctr;
-    TDS_HIP(hipMemsetAsync(ctr, 0, kFCounters * sizeof(unsigned long long), s));
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    TDS_HIP(hipEventCreate(&e0));
-    TDS_HIP(hipEventCreate(&e1));
+    ScratchLease lease(f);
+    TDS_TRY(lease.ready());
+    A.counters = lease.x.ctr;
+    TDS_HIP(hipMemsetAsync(A.counters, 0, kFCounters * sizeof(unsigned long long), s));
     // batches of up to kFQ query segments, smaller ones while there are fewer
     // than the waves that the chip holds (4 to a workgroup of 24 KB of LDS)
     A.batch = (uint32_t)std::min<uint64_t>(kFQ, std::max<uint64_t>(1, nq / 8192));
     const uint32_t blocks =
         std::max(1u, std::min(ceil_div(ceil_div(nq, A.batch), kFS / kWave), 4096u));
-    hipExtLaunchKernelGGL(k_fsg_search, dim3(blocks), dim3(kFS), 0, s, e0, e1, 0u, A);
-    unsigned long long h[kFCounters] = {};
+    hipExtLaunchKernelGGL(k_fsg_search, dim3(blocks), dim3(kFS), 0, s, lease.x.e0,
+                          lease.x.e1, 0u, A);
+    const unsigned long long* h = lease.x.ctr_host;
     int st = (hipGetLastError() == hipSuccess) ? TDS_OK : TDS_E_DEVICE;
     if (st == TDS_OK &&
-        hipMemcpyAsync(h, ctr, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess)
+        hipMemcpyAsync(lease.x.ctr_host, A.counters, kFCounters * sizeof(unsigned long long),
+                       hipMemcpyDeviceToHost, s) != hipSuccess)
         st = TDS_E_DEVICE;
     if (st == TDS_OK && hipStreamSynchronize(s) != hipSuccess) st = TDS_E_DEVICE;
     float ms = 0.f;
-    if (st == TDS_OK) (void)hipEventElapsedTime(&ms, e0, e1);
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
+    if (st == TDS_OK) (void)hipEventElapsedTime(&ms, lease.x.e0, lease.x.e1);
     TDS_TRY(st);
     if (h[1]) return TDS_E_INVALID;
     uint64_t tested = 0;

@@ -276,13 +276,96 @@ __global__ __launch_bounds__(kBT) void k_block_box(uint64_t n, const EntryF64* _
 }
 
 struct Scratch {
-    void* p[12] = {};
-    ~Scratch() {
-        for (void* q : p) dfree(q);
-    }
+    DeviceBlock block;
+    ~Scratch() { release_block(&block); }
 };
 
+struct BlockPool {
+    std::mutex mu;
+    std::vector<DeviceBlock> idle;  // in the order of their release
+};
+// never destroyed: at the program's end the runtime may be gone first
+BlockPool& block_pool() {
+    static BlockPool* pool = new BlockPool();
+    return *pool;
+}
+
 }  // namespace
+
+int acquire_block(size_t bytes, DeviceBlock* b) {
+    // whole 2 MB, so that about the same sizes fit
+    bytes = (std::max<size_t>(bytes, 1) + (size_t(2) << 20) - 1) >> 21 << 21;
+    int dev = 0;
+    TDS_HIP(hipGetDevice(&dev));
+    BlockPool& P = block_pool();
+    {
+        // the smallest idle block that holds it, unless most would lie idle
+        std::lock_guard<std::mutex> l(P.mu);
+        size_t best = P.idle.size();
+        for (size_t i = 0; i < P.idle.size(); ++i) {
+            const DeviceBlock& x = P.idle[i];
+            if (x.device == dev && x.bytes >= bytes && x.bytes / 2 <= bytes &&
+                (best == P.idle.size() || x.bytes < P.idle[best].bytes))
+                best = i;
+        }
+        if (best < P.idle.size()) {
+            *b = P.idle[best];
+            P.idle.erase(P.idle.begin() + (std::ptrdiff_t)best);
+            return TDS_OK;
+        }
+    }
+    TDS_TRY(dmalloc(&b->p, bytes));
+    b->bytes = bytes;
+    b->device = dev;
+    return TDS_OK;
+}
+
+void release_block(DeviceBlock* b) {
+    if (!b->p) return;
+    std::vector<DeviceBlock> out;  // to free
+    int cur = 0;
+    (void)hipGetDevice(&cur);
+    (void)hipSetDevice(b->device);
+    const bool idle = b->bytes <= kPoolBytes && hipDeviceSynchronize() == hipSuccess;
+    (void)hipSetDevice(cur);
+    if (!idle) {
+        (void)hipGetLastError();
+        out.push_back(*b);
+    } else {
+        BlockPool& P = block_pool();
+        std::lock_guard<std::mutex> l(P.mu);
+        P.idle.push_back(*b);
+        size_t sum = 0;
+        for (size_t i = P.idle.size(); i-- > 0;) {
+            if (P.idle[i].device != b->device) continue;
+            sum += P.idle[i].bytes;
+            if (sum > kPoolBytes) {
+                sum -= P.idle[i].bytes;
+                out.push_back(P.idle[i]);
+                P.idle.erase(P.idle.begin() + (std::ptrdiff_t)i);
+            }
+        }
+    }
+    for (const DeviceBlock& x : out) dfree(x.p);
+    *b = DeviceBlock();
+}
+
+bool trim_blocks() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::vector<DeviceBlock> out;
+    {
+        BlockPool& P = block_pool();
+        std::lock_guard<std::mutex> l(P.mu);
+        for (size_t i = P.idle.size(); i-- > 0;)
+            if (P.idle[i].device == dev) {
+                out.push_back(P.idle[i]);
+                P.idle.erase(P.idle.begin() + (std::ptrdiff_t)i);
+            }
+    }
+    for (const DeviceBlock& x : out) dfree(x.p);
+    return !out.empty();
+}
 
 int validate_segments_args(const tds_segments* S) {
     if (!S) return TDS_E_INVALID;
@@ -299,19 +382,7 @@ void destroy_index(tds_index* idx) {
     (void)hipSetDevice(idx->device);
     for (Workspace* w : idx->pool) delete w;
     idx->pool.clear();
-    dfree(idx->e64);
-    dfree(idx->e32);
-    dfree(idx->ev32);
-    dfree(idx->seg_id);
-    dfree(idx->traj);
-    dfree(idx->bin_first);
-    dfree(idx->min_ts);
-    dfree(idx->max_te);
-    dfree(idx->min_te);
-    dfree(idx->cmax_te);
-    dfree(idx->lo_ts);
-    dfree(idx->max_ts);
-    dfree(idx->bbox);
+    release_block(&idx->block);
     (void)hipSetDevice(cur);
     delete idx;
 }
@@ -330,7 +401,33 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
 
     int dev = 0;
     TDS_HIP(hipGetDevice(&dev));
+    // ---- everything that the build alone needs
+    const uint32_t nb = ceil_div(n, kBT);
+    double *stage = nullptr, *part = nullptr;
+    EntryF64* tmp64 = nullptr;
+    EntryF32* tmp32 = nullptr;
+    uint64_t *keys = nullptr, *keys2 = nullptr, *status = nullptr;
+    uint32_t *tr = nullptr, *vals = nullptr, *vals2 = nullptr, *err = nullptr;
+    SortControl* ctl = nullptr;
     Scratch sc;
+    {
+        DeviceArena a;
+        if (!D->on_device) {
+            a.add(&stage, 8 * n);
+            if (D->traj_id) a.add(&tr, n);
+        }
+        a.add(&tmp64, n);
+        a.add(&tmp32, n);
+        a.add(&keys, n);
+        a.add(&keys2, n);
+        a.add(&vals, n);
+        a.add(&vals2, n);
+        a.add(&part, kPart * (size_t)nb);
+        a.add(&err, 1);
+        a.add(&ctl, 1);
+        a.add(&status, sort_status_len((uint32_t)n));
+        TDS_TRY(a.alloc(&sc.block));
+    }
     // ---- stage the input on the device
     SegView S{};
     S.n = n;
@@ -339,9 +436,6 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
         for (int k = 0; k < 8; ++k) S.a[k] = src[k];
         S.traj = D->traj_id;
     } else {
-        double* stage = nullptr;
-        TDS_TRY(dmalloc(&stage, 8 * n));
-        sc.p[0] = stage;
         for (int k = 0; k < 8; ++k) {
             TDS_HIP(hipMemcpyAsync(stage + k * n, src[k], n * sizeof(double), hipMemcpyHostToDevice,
                                    stream));
@@ -349,37 +443,12 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
         }
         S.traj = nullptr;
         if (D->traj_id) {
-            uint32_t* tr = nullptr;
-            TDS_TRY(dmalloc(&tr, n));
-            sc.p[1] = tr;
             TDS_HIP(hipMemcpyAsync(tr, D->traj_id, n * sizeof(uint32_t), hipMemcpyHostToDevice,
                                    stream));
             S.traj = tr;
         }
     }
     // ---- per-segment preparation
-    const uint32_t nb = ceil_div(n, kBT);
-    EntryF64* tmp64 = nullptr;
-    EntryF32* tmp32 = nullptr;
-    uint64_t *keys = nullptr, *keys2 = nullptr;
-    uint32_t *vals = nullptr, *vals2 = nullptr, *err = nullptr;
-    double* part = nullptr;
-    TDS_TRY(dmalloc(&tmp64, n));
-    sc.p[2] = tmp64;
-    TDS_TRY(dmalloc(&tmp32, n));
-    sc.p[3] = tmp32;
-    TDS_TRY(dmalloc(&keys, n));
-    sc.p[4] = keys;
-    TDS_TRY(dmalloc(&keys2, n));
-    sc.p[5] = keys2;
-    TDS_TRY(dmalloc(&vals, n));
-    sc.p[6] = vals;
-    TDS_TRY(dmalloc(&vals2, n));
-    sc.p[7] = vals2;
-    TDS_TRY(dmalloc(&part, kPart * (size_t)nb));
-    sc.p[8] = part;
-    TDS_TRY(dmalloc(&err, 1));
-    sc.p[9] = err;
     TDS_HIP(hipMemsetAsync(err, 0, sizeof(uint32_t), stream));
     hipLaunchKernelGGL(k_seg_prep, dim3(nb), dim3(kBT), 0, stream, S, tmp64, tmp32, keys,
                        part, err);
@@ -429,12 +498,6 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
         while ((1u << bin_bits) < m) ++bin_bits;
         key_bits = 30 + bin_bits;
     }
-    SortControl* ctl = nullptr;
-    uint64_t* status = nullptr;
-    TDS_TRY(dmalloc(&ctl, 1));
-    sc.p[10] = ctl;
-    TDS_TRY(dmalloc(&status, sort_status_len((uint32_t)n)));
-    sc.p[11] = status;
     const SortJob sort{(uint32_t)n, keys, nullptr, keys, keys2, vals, vals2, ctl, status};
     TDS_TRY(sort_clear(sort, stream));
     TDS_TRY(sort_plan(sort, key_bits, stream));
@@ -451,22 +514,21 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
     idx->bw = bw;
     idx->layout = layout;
     const uint32_t nblk = ceil_div(n, 1u << kBoxShift);
-    int st = TDS_OK;
-    do {
-        if ((st = dmalloc(&idx->e64, n))) break;
-        if ((st = dmalloc(&idx->e32, n))) break;
-        if ((st = dmalloc(&idx->ev32, n))) break;
-        if ((st = dmalloc(&idx->seg_id, n))) break;
-        if ((st = dmalloc(&idx->traj, n))) break;
-        if ((st = dmalloc(&idx->bin_first, (size_t)m + 1))) break;
-        if ((st = dmalloc(&idx->min_ts, m))) break;
-        if ((st = dmalloc(&idx->max_te, m))) break;
-        if ((st = dmalloc(&idx->min_te, m))) break;
-        if ((st = dmalloc(&idx->cmax_te, m))) break;
-        if ((st = dmalloc(&idx->lo_ts, m))) break;
-        if ((st = dmalloc(&idx->max_ts, m))) break;
-        if (layout == TDS_LAYOUT_SPATIAL && (st = dmalloc(&idx->bbox, nblk))) break;
-    } while (0);
+    DeviceArena arrays;
+    arrays.add(&idx->e64, n);
+    arrays.add(&idx->e32, n);
+    arrays.add(&idx->ev32, n);
+    arrays.add(&idx->seg_id, n);
+    arrays.add(&idx->traj, n);
+    arrays.add(&idx->bin_first, (size_t)m + 1);
+    arrays.add(&idx->min_ts, m);
+    arrays.add(&idx->max_te, m);
+    arrays.add(&idx->min_te, m);
+    arrays.add(&idx->cmax_te, m);
+    arrays.add(&idx->lo_ts, m);
+    arrays.add(&idx->max_ts, m);
+    if (layout == TDS_LAYOUT_SPATIAL) arrays.add(&idx->bbox, nblk);
+    const int st = arrays.alloc(&idx->block);
     if (st != TDS_OK) {
         destroy_index(idx);
         return st;

@@ -1855,16 +1855,60 @@ int grow(T** p, size_t* cap, size_t need) {
 
 }  // namespace
 
+namespace {
+struct PinPool {
+    std::mutex mu;
+    std::vector<PinBlock*> idle;
+};
+// never destroyed: at the program's end the runtime may be gone first
+PinPool& pin_pool() {
+    static PinPool* pool = new PinPool();
+    return *pool;
+}
+}  // namespace
+
+int acquire_pin(PinBlock** b) {
+    if (*b) return TDS_OK;
+    {
+        PinPool& P = pin_pool();
+        std::lock_guard<std::mutex> l(P.mu);
+        if (!P.idle.empty()) {
+            *b = P.idle.back();
+            P.idle.pop_back();
+            return TDS_OK;
+        }
+    }
+    void* p = nullptr;
+    TDS_HIP(hipHostMalloc(&p, sizeof(PinBlock), hipHostMallocPortable));
+    *b = static_cast<PinBlock*>(p);
+    return TDS_OK;
+}
+
+void release_pin(PinBlock* b) {
+    if (!b) return;
+    {
+        PinPool& P = pin_pool();
+        std::lock_guard<std::mutex> l(P.mu);
+        if (P.idle.size() < kPinPool) {
+            P.idle.push_back(b);
+            return;
+        }
+    }
+    (void)hipHostFree(b);
+}
+
 Workspace::~Workspace() {
     for (void* p : {(void*)qsorted, (void*)qkey, (void*)qslot, (void*)qf, (void*)qev, (void*)qstage,
                     (void*)qtraj_stage, (void*)ctl, (void*)b_count,
                     (void*)b_hi, (void*)b_start, (void*)b_nch,
                     (void*)binfo, (void*)item_bucket, (void*)item_count, (void*)res,
-                    (void*)bstats, (void*)stage, (void*)stage_meta, (void*)dyn_ctr,
+                    (void*)bstats, (void*)dyn_ctr,
                     (void*)dlast, (void*)fill_s, (void*)fill_d, (void*)fill_dstart,
                     (void*)fill_plan})
         dfree(p);
     if (ctl_host) (void)hipHostFree(ctl_host);
+    release_block(&stage_block);
+    release_pin(pin);  // nothing uses it: the releases above waited for the device
     if (ev0) (void)hipEventDestroy(ev0);
     if (ev1) (void)hipEventDestroy(ev1);
 }
@@ -1985,13 +2029,14 @@ int ws_reserve_stage(Workspace* w, uint32_t grid_waves) {
         w->stage_waves = waves;
     }
     if (w->stage_recs >= need && w->stage) return TDS_OK;
-    dfree(w->stage);
-    dfree(w->stage_meta);
+    release_block(&w->stage_block);
     w->stage = nullptr;
     w->stage_meta = nullptr;
     w->stage_recs = 0;
-    TDS_TRY(dmalloc(&w->stage, need));
-    TDS_TRY(dmalloc(&w->stage_meta, need));
+    DeviceArena a;
+    a.add(&w->stage, need);
+    a.add(&w->stage_meta, need);
+    TDS_TRY(a.alloc(&w->stage_block));
     w->stage_recs = need;
     return TDS_OK;
 }
@@ -2098,17 +2143,32 @@ int resolve_prec(int p) {
 }
 
 // Device view of the query arrays; host arrays are copied into the staging
-// buffers first.
+// buffers first, through the workspace's pinned block (`pin`, taken at its
+// first use) where they fit.
 int stage_queries(const tds_segments* Q, QueryView* V, hipStream_t s, double** stage_buf,
-                  size_t* stage_cap, uint32_t** traj_buf, size_t* traj_cap, bool force_copy) {
+                  size_t* stage_cap, uint32_t** traj_buf, size_t* traj_cap, PinBlock** block) {
     V->n = Q->n;
     const double* src[8] = {Q->xs, Q->ys, Q->zs, Q->ts, Q->xe, Q->ye, Q->ze, Q->te};
-    if (Q->on_device && !force_copy) {
+    if (Q->on_device) {
         for (int k = 0; k < 8; ++k) V->a[k] = src[k];
         V->traj = Q->traj_id;
         return TDS_OK;
     }
-    const hipMemcpyKind kind = Q->on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+    const hipMemcpyKind kind = hipMemcpyHostToDevice;
+    if (block && Q->n <= kPinSegs) {
+        TDS_TRY(acquire_pin(block));
+        char* pin = (*block)->segs;
+        const size_t col = Q->n * sizeof(double);
+        for (int k = 0; k < 8; ++k) std::memcpy(pin + k * col, src[k], col);
+        if (Q->traj_id) std::memcpy(pin + 8 * col, Q->traj_id, Q->n * sizeof(uint32_t));
+        const size_t bytes = 8 * col + (Q->traj_id ? Q->n * sizeof(uint32_t) : 0);
+        // the ids after the columns, in whole doubles
+        TDS_TRY(grow(stage_buf, stage_cap, (bytes + sizeof(double) - 1) / sizeof(double)));
+        TDS_HIP(hipMemcpyAsync(*stage_buf, pin, bytes, kind, s));
+        for (int k = 0; k < 8; ++k) V->a[k] = *stage_buf + k * Q->n;
+        V->traj = Q->traj_id ? reinterpret_cast<uint32_t*>(*stage_buf + 8 * Q->n) : nullptr;
+        return TDS_OK;
+    }
     TDS_TRY(grow(stage_buf, stage_cap, 8 * (size_t)Q->n));
     for (int k = 0; k < 8; ++k) {
         TDS_HIP(hipMemcpyAsync(*stage_buf + k * Q->n, src[k], Q->n * sizeof(double), kind, s));
@@ -2339,7 +2399,7 @@ int reserve_items(const tds_index* idx, Workspace* w, uint64_t nq, uint32_t chun
 // counters come back into pinned memory.  Returns without waiting.
 int enqueue_attempt(const tds_index* idx, Workspace* w, const QueryView& V, uint32_t nreq,
                     int prec, uint32_t chunk, uint32_t grid_waves, uint32_t cpl, uint32_t output,
-                    tds_result* out, hipStream_t s, uint64_t cap) {
+                    tds_result* out, hipStream_t s, uint64_t cap, uint32_t peek = 0) {
     w->desc_host->nq = V.n;
     w->desc_host->nreq = nreq;
     w->desc_host->item_cap = (uint32_t)std::min<uint64_t>(cap, 0xFFFFFFFFull);
@@ -2348,6 +2408,8 @@ int enqueue_attempt(const tds_index* idx, Workspace* w, const QueryView& V, uint
     TDS_TRY(enqueue_pipeline(idx, w, V, V.n, nreq, prec, chunk, grid_waves, cpl, out,
                              w->item_count, s, w->ev0, w->ev1,
                              nreq == 1 && output != TDS_OUTPUT_STAGED));
+    if (peek)
+        TDS_HIP(hipMemcpyAsync(w->pin->peek, out, peek * sizeof(tds_result), hipMemcpyDeviceToHost, s));
     return ws_download(w, nreq, s);
 }
 
@@ -2373,13 +2435,13 @@ int finish_attempt(Workspace* w, tds_stats* st, SearchHeader* h_out, uint64_t* c
 // item table and re-running if the bound was too small.
 int run_batch(const tds_index* idx, Workspace* w, const QueryView& V, uint32_t nreq, int prec,
               uint32_t chunk, uint32_t grid_waves, uint32_t cpl, uint32_t output, tds_result* out,
-              hipStream_t s, tds_stats* st, SearchHeader* h_out) {
+              hipStream_t s, tds_stats* st, SearchHeader* h_out, uint32_t peek = 0) {
     uint64_t cap = 0;
     TDS_TRY(reserve_items(idx, w, V.n, chunk, grid_waves, &cap));
     TDS_TRY(ws_reserve_stage(w, grid_waves));
     for (int attempt = 0; attempt < 2; ++attempt) {
         TDS_TRY(enqueue_attempt(idx, w, V, nreq, prec, chunk, grid_waves, cpl, output, out, s,
-                                cap));
+                                cap, peek));
         TDS_HIP(hipStreamSynchronize(s));
         const int r = finish_attempt(w, st, h_out, &cap);
         if (r != 1) return r;
@@ -2432,7 +2494,7 @@ int schedule_impl(tds_index* idx, const tds_segments* Q, double t_start, double 
     int st = TDS_OK;
     QueryView V{};
     do {
-        if ((st = stage_queries(Q, &V, s, &stage, &scap, &tstage, &tcap, false))) break;
+        if ((st = stage_queries(Q, &V, s, &stage, &scap, &tstage, &tcap, nullptr))) break;
         if ((st = dmalloc(&dlo, nq))) break;
         if ((st = dmalloc(&dhi, nq))) break;
         if ((st = dmalloc(&err, 1))) break;
@@ -2514,7 +2576,7 @@ int search_core(tds_index* idx, const tds_segments* Q, bool self_join, double d,
         V.ent_traj = idx->traj;
     } else {
         TDS_TRY(stage_queries(Q, &V, s, &w->qstage, &w->stage_cap, &w->qtraj_stage, &w->traj_cap,
-                              false));
+                              &w->pin));
     }
 
     // result buffer
@@ -2543,7 +2605,12 @@ int search_core(tds_index* idx, const tds_segments* Q, bool self_join, double d,
     st.query_segments = nq;
     SearchHeader h{};
     // pass 1: every item, result window [0, dev_cap)
-    TDS_TRY(run_batch(idx, w, V, 1, prec, chunk, grid_waves, cpl, P.output, res, s, &st, &h));
+    uint32_t peek = 0;
+    if (!dev_out && capacity) {
+        TDS_TRY(acquire_pin(&w->pin));
+        peek = (uint32_t)std::min<uint64_t>(kPeek, dev_cap);
+    }
+    TDS_TRY(run_batch(idx, w, V, 1, prec, chunk, grid_waves, cpl, P.output, res, s, &st, &h, peek));
     const ReqCounter rc = w->rc_host[0];
     const uint32_t n_items = h.n_items;
     st.active_segments = h.active;
@@ -2560,8 +2627,12 @@ int search_core(tds_index* idx, const tds_segments* Q, bool self_join, double d,
         status = (total > capacity) ? TDS_E_OVERFLOW : TDS_OK;
     } else if (total <= dev_cap) {
         const uint64_t k = std::min(total, capacity);
-        if (k) TDS_HIP(hipMemcpyAsync(out, res, k * sizeof(tds_result), hipMemcpyDeviceToHost, s));
-        TDS_HIP(hipStreamSynchronize(s));
+        if (k && k <= peek) {
+            std::memcpy(out, w->pin->peek, k * sizeof(tds_result));
+        } else if (k) {
+            TDS_HIP(hipMemcpyAsync(out, res, k * sizeof(tds_result), hipMemcpyDeviceToHost, s));
+            TDS_HIP(hipStreamSynchronize(s));
+        }
         status = (total > capacity) ? TDS_E_OVERFLOW : TDS_OK;
     } else if (total > capacity) {
         const uint64_t k = std::min(dev_cap, capacity);
@@ -2671,7 +2742,7 @@ int search_begin_impl(tds_index* idx, const tds_segments* Q, double d, double t_
         Workspace* w = ps->w;
         if ((st = ws_reserve(w, Q->n, 1))) break;
         if ((st = stage_queries(Q, &ps->V, s, &w->qstage, &w->stage_cap, &w->qtraj_stage,
-                                &w->traj_cap, false)))
+                                &w->traj_cap, &w->pin)))
             break;
         Request R{};
         R.q_begin = 0;
@@ -2792,7 +2863,8 @@ int batch_impl(tds_index* idx, const tds_segments* Q, const tds_request* reqs, u
     WsGuard guard{idx, w};
     TDS_TRY(ws_reserve(w, Q->n, nreq));
     QueryView V{};
-    TDS_TRY(stage_queries(Q, &V, s, &w->qstage, &w->stage_cap, &w->qtraj_stage, &w->traj_cap, false));
+    TDS_TRY(stage_queries(Q, &V, s, &w->qstage, &w->stage_cap, &w->qtraj_stage, &w->traj_cap,
+                          &w->pin));
     tds_result* res = out;
     if (!dev_out) {
         TDS_TRY(grow(&w->res, &w->res_cap, (size_t)std::max<uint64_t>(out_capacity, 1)));

@@ -4,9 +4,11 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "tds.h"
@@ -152,7 +154,31 @@ struct alignas(16) ReqCounter {
 
 // ---------------------------------------------------------------- host objects
 
+// A block of device memory (see acquire_block).
+struct DeviceBlock {
+    char* p = nullptr;
+    size_t bytes = 0;
+    int device = 0;
+};
+
 struct QEval;  // canon.hpp
+
+// Pinned memory of a workspace that serves host arrays.  Query arrays of up to
+// kPinSegs segments are packed into it and sent with one copy (nine copies of
+// pageable memory take about 5 us each, whatever their size); the first kPeek
+// results come back with a search's counters, before their number is known, so
+// that a search of few results waits once.  Pinning 32 KB or more takes 0.3 ms,
+// a good part of a new index's first search, so that the blocks outlive their
+// workspaces, at most kPinPool of them.
+constexpr size_t kPinSegs = 1024;
+constexpr uint32_t kPeek = 512;
+constexpr size_t kPinPool = 32;
+struct PinBlock {
+    tds_result peek[kPeek];
+    char segs[kPinSegs * (8 * sizeof(double) + sizeof(uint32_t))];
+};
+int acquire_pin(PinBlock** b);  // leaves a block that is there
+void release_pin(PinBlock* b);  // after the device has finished with it
 
 struct Workspace {
     int device = 0;
@@ -166,6 +192,7 @@ struct Workspace {
     double* qstage = nullptr;       // staging of host query arrays (8 * stage_cap doubles)
     uint32_t* qtraj_stage = nullptr;
     size_t stage_cap = 0, traj_cap = 0;
+    PinBlock* pin = nullptr;
     // control block, one device allocation and its pinned host mirror, laid
     // out as [desc | req x r_cap | hdr | req_ctr x r_cap]: the batch goes to
     // the device with one copy (desc and requests) and its counters come back
@@ -191,6 +218,7 @@ struct Workspace {
     tds_result* stage = nullptr;
     uint32_t* stage_meta = nullptr;
     size_t stage_recs = 0;
+    DeviceBlock stage_block;        // holds both
     unsigned long long* dyn_ctr = nullptr;  // kCtrSlots counters, kCtrStride apart
     // direct output (one-request searches): each wave's last reservation and
     // the plan of the pass that fills the holes (sized for stage_waves waves)
@@ -229,12 +257,21 @@ struct tds_index {
     double* lo_ts = nullptr;       // m: min t_start over bins >= j (+inf when none)
     double* max_ts = nullptr;      // m: max t_start per bin (-inf when empty)
     tds::BlockBox* bbox = nullptr; // ceil(n / 64) block boxes (spatial layout)
+    tds::DeviceBlock block;        // holds the arrays above
     uint32_t layout = TDS_LAYOUT_TEMPORAL;
     uint64_t device_bytes = 0;
     std::mutex mu;
     std::vector<tds::Workspace*> pool;
     tds_stats last{};
 };
+
+namespace tds {
+struct FsgScratch {
+    unsigned long long* ctr = nullptr;       // the search kernel's counters
+    unsigned long long* ctr_host = nullptr;  // pinned
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+};
+}  // namespace tds
 
 // Fixed spatial grid over the entries of an index (fsg.hip).
 struct tds_fsg {
@@ -246,6 +283,10 @@ struct tds_fsg {
     uint32_t* cell_first = nullptr;  // ncells + 1
     uint32_t* list = nullptr;        // entry positions grouped by cell
     uint64_t nlist = 0;
+    // what a search needs besides its arrays, kept for the next ones (one per
+    // search at a time; at most kFsgPool are kept)
+    mutable std::mutex mu;
+    mutable std::vector<tds::FsgScratch> pool;
 };
 
 namespace tds {
@@ -287,11 +328,27 @@ struct DeviceGuard {
         if (s_ != TDS_OK) return s_; \
     } while (0)
 
+// Blocks of device memory that outlive what they were allocated for
+// (index_build.hip): an index, its build and a workspace's result stages each
+// take one.  An allocation of 128 MB and more takes up to 0.3 ms and a release of
+// 64 MB and more 0.3 ms, 3 ms once a program has released some hundreds: most of
+// a build of a million entries.  At most kPoolBytes of a
+// device stay allocated while nothing uses them, the most recently released
+// ones, and all of them go back when an allocation of the library finds no
+// memory.  Safe with several threads and streams: a block is only offered again
+// after the device has finished all work, as with hipFree.
+constexpr size_t kPoolBytes = size_t(1) << 30;
+int acquire_block(size_t bytes, DeviceBlock* b);  // on the current device
+void release_block(DeviceBlock* b);
+bool trim_blocks();  // the current device's idle blocks; true if there were any
+
 template <typename T>
 int dmalloc(T** p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
     hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
+    if (e == hipErrorOutOfMemory && trim_blocks())
+        e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         *p = nullptr;
@@ -303,6 +360,25 @@ int dmalloc(T** p, size_t count) {
 inline void dfree(void* p) {
     if (p) (void)hipFree(p);
 }
+
+// Device arrays that live and die together, as one block of the pool.
+struct DeviceArena {
+    static constexpr size_t kAlign = 256;
+    std::vector<std::pair<void**, size_t>> parts;  // pointer to set, byte offset
+    size_t bytes = 0;
+    template <class T>
+    void add(T** p, size_t count) {
+        *p = nullptr;
+        parts.push_back({reinterpret_cast<void**>(p), bytes});
+        bytes += (std::max<size_t>(count, 1) * sizeof(T) + kAlign - 1) / kAlign * kAlign;
+    }
+    // Sets the pointers; the block is to be given back with release_block.
+    int alloc(DeviceBlock* block) {
+        TDS_TRY(acquire_block(bytes, block));
+        for (const auto& p : parts) *p.first = block->p + p.second;
+        return TDS_OK;
+    }
+};
 
 inline uint32_t ceil_div(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 
