@@ -20,7 +20,7 @@
 // and a value once), launches for small ones (one per digit here).  Before, a
 // pass was five launches (count, three scan steps, scatter), read the keys
 // twice and wrote each key straight to its place from the lane that held it:
-// 2.1-3.1 ms per pass at 171e6 pairs (now 1.1-1.3) and 40 us at 1e6 (now 22).
+// 2.1-3.1 ms per pass at 171e6 pairs (now 0.9-1.0) and 40 us at 1e6 (now 22).
 //
 // Tiles are taken in order from a counter, so every tile before a waiting one
 // is held by a workgroup that is running and publishes its counts without
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kHistThreads) void rs_hist(const uint64_t* __restri
         const bool full = __ballot(valid) == ~0ull;
         for (int p = 0; p < npass; ++p) {
             const uint32_t d = (uint32_t)(key >> (8 * p)) & (kRadix - 1);
-            const uint32_t d0 = (uint32_t)__shfl((int)d, 0);
+            const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, 0);
             const bool same = __ballot(d == d0) == ~0ull;
             if (full && same) {
                 if (__lane_id() == 0) atomicAdd(&h[p][d], (uint32_t)kWave);
@@ -298,8 +298,11 @@ __global__ __launch_bounds__(kThreads) void rs_pass(const uint64_t* __restrict__
         uint64_t sum = 0;
         if (tile) {
             int64_t p = (int64_t)tile - 1;
-            bool done = look_back<4>(status, tid, pass, p, sum);
-            while (!done) done = look_back<16>(status, tid, pass, p, sum);
+            // the largest tile holds so many registers that sixteen more
+            // spilled (171e6 pairs: 1.1 ms a pass, 0.9 with two and four)
+            constexpr bool kFew = kItems >= 16;
+            bool done = look_back<kFew ? 2 : 4>(status, tid, pass, p, sum);
+            while (!done) done = look_back<kFew ? 4 : 16>(status, tid, pass, p, sum);
             __hip_atomic_store(st, epoch | kSum | (sum + total), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
