@@ -207,7 +207,7 @@ typedef struct tds_stats {
     uint32_t stage_flushes;   /* first pass, staged output: work items whose results
                                  were reserved and written at the item's end (one
                                  device-scope atomic per request in the item); direct
-                                 output: chunk reservations */
+                                 output: reservations that hold results */
     double kernel_ms;         /* distance kernel(s), measured with HIP events */
     double total_ms;          /* whole call, host wall clock */
     uint64_t filter_tests;    /* pairs put through the FP32 filter (FP32 form) or the

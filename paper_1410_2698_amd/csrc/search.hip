@@ -5,14 +5,14 @@
 //   k_qprep      one thread per query segment: validate, velocity, clip to the
 //                window, candidate range [lo, hi) by bisection of the bin
 //                tables (the schedule S of Sec. 4.2.2, computed on the GPU),
-//                FP32 filter sphere, bucket key = (first bin, bin span);
+//                FP32 filter sphere, bucket key = (first bin, bin span); its
+//                filter record and its FP64 data, in query order;
 //   k_bucket_scan  one block: bucket offsets, 64-segment groups per bucket,
-//                candidate chunks per bucket and the work-item table;
-//   k_scatter    order the query segments by bucket, and fill the work-item
-//                table (item -> bucket);
-//   k_distance   persistent waves take work items round-robin (64 query
-//                segments of one bucket x one chunk of their common candidate
-//                range).  FP32 form: the lanes hold the chunk's candidates
+//                the size of the candidate chunks and the work-item table;
+//   k_scatter    the numbers of the query segments by bucket, and the
+//                work-item table (item -> bucket);
+//   k_distance   persistent waves take work items (64 query segments of one
+//                bucket x one chunk of their common candidate range).  FP32 form: the lanes hold the chunk's candidates
 //                (coalesced loads) and the boxes of its 64-entry blocks; each
 //                block's box is tested against every query of the group (one
 //                lane per query) and only the surviving queries are tested
@@ -20,7 +20,10 @@
 //                segment per lane, candidates streamed through wave-uniform
 //                scalar loads.  Pairs that pass are queued in LDS and
 //                evaluated 64 at a time by the canonical FP64 code; results
-//                are appended with one atomic per request per 64 evaluations.
+//                of one request go to positions that the wave reserved, those
+//                of several through a stage per wave;
+//   k_fill       after one request: the results' positions made dense, and the
+//                counters folded (k_stats_fold alone after several).
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -1015,15 +1018,16 @@ static_assert(sizeof(QRef) == 32, "QRef layout");
 // windows of the host's buffer), a result's position is instead its order
 // among the item's results, which a wave computes the same way on every run.
 //
-// Direct output (a one-request search's first pass): a wave reserves
-// dir_chunk consecutive positions of the request at a time (one atomic per
-// reservation, aligned chunks since every reservation has that size) and
-// writes its results straight to them, keeping its last reservation open from
-// one item to the next.  At the end each wave's last chunk may be partly
-// used; positions at or past the output capacity go to a scratch buffer.  A
-// fill pass (k_fill_plan, k_fill_copy) then moves the results found past the
-// final count (or the capacity) into the unused tails below it, so that the
-// output is dense again.  No result takes the round trip through a stage.
+// Direct output (a one-request search's first pass): a wave writes its results
+// straight to consecutive positions of the request that it reserved, first the
+// dir_chunk positions of its own number, then twice as many chunks as the last
+// time, up to dir_max (one atomic per reservation; whole aligned chunks),
+// keeping its last reservation open from one item to the next.  At the end it
+// may be partly used; positions at or past the output capacity go to a scratch
+// buffer.  A fill pass (k_fill, or k_fill_plan and k_fill_copy) then moves the
+// results found past the final count (or the capacity) into the unused tails
+// below it, so that the output is dense again.  No result takes the round trip
+// through a stage.
 // Filter data of a query segment as the wave keeps it in LDS: the sphere and
 // the clipped extent of its QF32 record, apart, since most slots need only the
 // sphere (the candidate range stays in the registers of the query's lane).
