@@ -137,7 +137,9 @@ enum {
    requests, the batcher and the server always stage.  Both modes give the
    same records; positions within a request are in no fixed order. */
 enum {
-    TDS_OUTPUT_DEFAULT = 0, /* currently TDS_OUTPUT_DIRECT */
+    /* TDS_OUTPUT_STAGED for a capacity of at most 32 records per wave of the
+       launch (131,072 at the default grid), else TDS_OUTPUT_DIRECT. */
+    TDS_OUTPUT_DEFAULT = 0,
     /* Each wave reserves a chunk of output positions at a time (one
        device-scope atomic per chunk) and writes its results straight to it;
        a short pass after the distance kernel moves the results found past the

@@ -1107,7 +1107,9 @@ __device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A0, Item
         dst = (int64_t)R.out_offset + (int64_t)base - (int64_t)A->win_lo;
     }
     S.rcnt = 0;
-    for (uint32_t p0 = 0; p0 < S.nst; p0 += kFlushUnroll * kWave) {
+    // (nothing to copy once the output is full)
+    const uint32_t nst = ballot(klo < khi) ? S.nst : 0u;
+    for (uint32_t p0 = 0; p0 < nst; p0 += kFlushUnroll * kWave) {
         uint32_t meta[kFlushUnroll];
         uint4 ra[kFlushUnroll], rb[kFlushUnroll];
 #pragma unroll
@@ -2397,6 +2399,18 @@ int reserve_items(const tds_index* idx, Workspace* w, uint64_t nq, uint32_t chun
 // Runs the pipeline once for the batch whose requests the caller staged in
 // w->req_host (sent to the device here, with the descriptor), growing the
 // item table and re-running if the bound was too small.
+// Largest output that a one-request search stages unless told otherwise: 32
+// records per wave, 4 MB in all at the default grid, so that the second trip of
+// the records that are kept costs 2 us.  Small outputs are those of small
+// searches, which are latency: staged they end with the last item, direct with
+// one more kernel of 12.5 us (4,900 query segments, 6,000 records: the call 97
+// against 86 us; 400 query segments 135 against 125; but 100,000 with 472,000
+// records 189 against 202, and 71 million 4.7 against 6.9 ms, each result
+// written twice).
+uint64_t staged_room(uint32_t grid_waves) {
+    return 32ull * launch_blocks(grid_waves) * kWavesPerBlock;
+}
+
 // One run of the pipeline for the batch whose requests the caller staged in
 // w->req_host with an item table of `cap` entries: the descriptor and the
 // requests go up, the launches are ordered on `s`, and the header and request
@@ -2408,10 +2422,12 @@ int enqueue_attempt(const tds_index* idx, Workspace* w, const QueryView& V, uint
     w->desc_host->nreq = nreq;
     w->desc_host->item_cap = (uint32_t)std::min<uint64_t>(cap, 0xFFFFFFFFull);
     TDS_TRY(ws_upload(w, nreq, s));
-    // one request: direct output unless staging is asked for
+    const bool direct =
+        nreq == 1 && (output == TDS_OUTPUT_DIRECT ||
+                      (output == TDS_OUTPUT_DEFAULT &&
+                       w->req_host->out_capacity > staged_room(grid_waves)));
     TDS_TRY(enqueue_pipeline(idx, w, V, V.n, nreq, prec, chunk, grid_waves, cpl, out,
-                             w->item_count, s, w->ev0, w->ev1,
-                             nreq == 1 && output != TDS_OUTPUT_STAGED));
+                             w->item_count, s, w->ev0, w->ev1, direct));
     if (peek)
         TDS_HIP(hipMemcpyAsync(w->pin->peek, out, peek * sizeof(tds_result), hipMemcpyDeviceToHost, s));
     return ws_download(w, nreq, s);

@@ -43,3 +43,23 @@ def test_fill_edges(walks, grid_waves, room):
     same = want[np.searchsorted(key(want), key(got))] if k else want[:0]
     for f in ("q_seg", "e_seg", "q_traj", "e_traj", "t_lo", "t_hi"):
         assert np.array_equal(got[f], same[f]), f
+
+
+@pytest.mark.parametrize("cap", [0, 1, 2047, 2048, 2049, 4096])
+@pytest.mark.parametrize("refine", ["default", "queued"])
+def test_default_output_by_capacity(walks, cap, refine):
+    """Staged up to 32 records per wave (2048 for 64 waves), direct beyond: a
+    full output of distinct results and the whole count on either side."""
+    w, idx, want = walks
+    buf = torch.full(((cap + 64) * 32,), 0xAB, dtype=torch.uint8, device="cuda")
+    st, m, _ = idx.search_raw(w.Q, 12.0, *w.window, out_ptr=buf.data_ptr(), capacity=cap,
+                              out_on_device=True, grid_waves=64, refine=refine)
+    assert m == want.size and st == tds.TDS_E_OVERFLOW
+    raw = buf.cpu().numpy()
+    assert np.all(raw[32 * cap:] == 0xAB)
+    got = tds.sort_records(raw[:32 * cap].view(want.dtype))
+    key = lambda r: r["q_seg"].astype(np.uint64) << np.uint64(32) | r["e_seg"]  # noqa: E731
+    assert np.unique(key(got)).size == cap
+    same = want[np.searchsorted(key(want), key(got))] if cap else want[:0]
+    for f in ("q_seg", "e_seg", "q_traj", "e_traj", "t_lo", "t_hi"):
+        assert np.array_equal(got[f], same[f]), f
