@@ -154,12 +154,7 @@ __global__ __launch_bounds__(kBT) void k_gather(uint64_t n, const uint32_t* __re
     const EntryF64 e = tmp64[src];
     e64[i] = e;
     e32[i] = tmp32[src];
-    EntryV32 v;
-    v.vx = __double2float_rn(e.vx);
-    v.vy = __double2float_rn(e.vy);
-    v.vz = __double2float_rn(e.vz);
-    v.tm = __double2float_rn(0.5 * (e.ts + e.te));
-    ev32[i] = v;
+    ev32[i] = motion32(e.vx, e.vy, e.vz, 0.5 * (e.ts + e.te));
     seg_id[i] = src;
     traj[i] = traj_in ? traj_in[src] : 0u;
 }

@@ -308,7 +308,8 @@ __global__ __launch_bounds__(kBlock) void k_qprep(QueryView Q, const BatchDesc* 
                                  paz = p.z + p.vz * (p.aq - ts);
                     const double pbx = p.x + p.vx * (p.bq - ts), pby = p.y + p.vy * (p.bq - ts),
                                  pbz = p.z + p.vz * (p.bq - ts);
-                    sphere32(pax, pay, paz, pbx, pby, pbz, p.d, f.cx, f.cy, f.cz, f.R);
+                    query_sphere32(pax, pay, paz, pbx, pby, pbz, p.vx, p.vy, p.vz, p.d, f.cx, f.cy,
+                                   f.cz, f.R);
                     f.box = seg_box32(pax, pay, paz, pbx, pby, pbz, p.d);
                     f.req = r;
                     f.pad = 0.f;
@@ -1321,9 +1322,18 @@ __device__ __forceinline__ float min1(float a, float b) {
 // S0 (sc = |c|1, sv = |v|1, st = |a| + |b| + |t|, each side's own extent: |a| +
 // |b| <= |qa| + |qb| + |la| + |lb| since a is qa or la and b is qb or lb), so
 // E is at least six times the sum.  The relative rounding of R^2 and of
-// |D|^2 (below 8 u each) is covered by the factor 1 + 2^-19.  The test is
-// "value > bound", and an undefined tau (0 times infinity) becomes an end of
-// the extent, so overflow to infinity or NaN never drops a pair.
+// |D|^2 (below 8 u each) is covered by the factor 1 + 2^-19.
+//
+// Range: tau is only as good as said while |W|^2 and its reciprocal are normal
+// numbers and Dm.W is finite.  So a side whose speed sv reaches 2^60 (kFastest)
+// has R infinite: a query's sphere is made unbounded (query_sphere32), which
+// those past 1e18 < 2^60 are already, an entry's velocity infinite (motion32).
+// Otherwise |W| < 2^61, hence |W|^2 < 2^122; each segment lies within 2^61 of
+// the origin at all of the common extent, hence |Dm| < 2^63 up to its rounding
+// of u S, which is small beside that where R^2 is finite (S < 2^81), so Dm.W and
+// |D|^2 are finite too.  Where R is infinite nothing is dropped: the test is
+// "value > bound", and an undefined tau (0 times infinity) becomes an end of the
+// extent.
 //
 // One reciprocal and about 45 operations; the three separate bounds used
 // before (triangle inequality, distance to the line of motion, the ends) took
@@ -1382,7 +1392,8 @@ __device__ __forceinline__ ERef eref_of(float cx, float cy, float cz, float rad,
     e.ox = fmaf(-v.vx, v.tm, cx);
     e.oy = fmaf(-v.vy, v.tm, cy);
     e.oz = fmaf(-v.vz, v.tm, cz);
-    // an unbounded sphere (stored centre 0): nothing is dropped
+    // an unbounded sphere (stored centre 0): nothing is dropped, nor where the
+    // velocity is infinite (motion32)
     e.sc = rad < INFINITY ? (fabsf(cx) + fabsf(cy)) + fabsf(cz) : INFINITY;
     e.sv = (fabsf(v.vx) + fabsf(v.vy)) + fabsf(v.vz);
     e.st = (fabsf(ts) + fabsf(te)) + fabsf(v.tm);

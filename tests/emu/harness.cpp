@@ -12,6 +12,7 @@
 //   harness fill seed W C K frac add align prefix                 -> "status count cap T holes R"
 //   harness filtercheck seed n                                    -> "status accepted misses naive"
 //   harness cvt in.bin out.bin                                    -> "status n"
+//   harness fastpairs seed n                         -> "status accepted misses past dropped"
 //
 // D.bin / Q.bin: 9 float64 columns (xs ys zs ts xe ye ze te traj), column
 // after column.  recs.bin: tds_result records.  out.bin: the records or
@@ -36,6 +37,13 @@
 // that boxes without margins (end points rounded to nearest, grown by d in
 // FP32) would drop, which shows that the pairs are close enough to the
 // boundary to matter.
+//
+// "fastpairs" does the same with n pairs of fast movers that meet inside their
+// common extent (speeds from 1e12 to 1e24, durations from 1e-6 to 1, positions
+// to 1e18, d from 1e-6 of the position scale up): "past" counts those accepted
+// whose squared relative speed is past FP32's normal reciprocals, "dropped" the
+// pairs that the canonical evaluation does not accept and the filter drops (a
+// filter that keeps everything would drop none).
 //
 // "cvt" converts the float64 values of in.bin to float32 rounded downwards
 // and upwards (f32_rd, f32_ru) and writes them as pairs.
@@ -350,7 +358,7 @@ bool refine_keeps(const tds::QCanon& q, float qcx, float qcy, float qcz, float q
     tds::QTime t = {};
     t.a = f.a32;
     t.b = f.b32;
-    const tds::EntryV32 v = {(float)evx, (float)evy, (float)evz, (float)(0.5 * (ets + ete))};
+    const tds::EntryV32 v = tds::motion32(evx, evy, evz, 0.5 * (ets + ete));
     const float la = tds::f32_rd(ets), lb = tds::f32_ru(ete);
     const tds::ERef x = tds::eref_of(ecx, ecy, ecz, er, v, la, lb);
     return tds::refine32(t, tds::qref_of(q, f), x.ox, x.oy, x.oz, x.vx, x.vy, x.vz, la, lb, x.sc,
@@ -450,6 +458,74 @@ int run_filtercheck(char** argv) {
     return 0;
 }
 
+// Pairs of fast movers (see the head of this file).
+int run_fastpairs(char** argv) {
+    std::mt19937_64 rng(strtoull(argv[2], nullptr, 10));
+    const uint64_t n = strtoull(argv[3], nullptr, 10);
+    std::uniform_real_distribution<double> U(0.0, 1.0);
+    std::normal_distribution<double> N(0.0, 1.0);
+    uint64_t accepted = 0, misses = 0, past = 0, dropped = 0;
+    for (uint64_t k = 0; k < n; ++k) {
+        const double dt = std::pow(10.0, -6.0 + 6.0 * U(rng));
+        const double speed = std::min(std::pow(10.0, 12.0 + 12.0 * U(rng)), 5e17 / dt);
+        const double at = std::pow(10.0, 6.0 + 11.0 * U(rng));  // where they meet
+        const double ets = k % 3 ? 100.0 * (U(rng) - 0.5) : 0.0, ete = ets + dt;
+        const double qts = ets + 0.4 * dt * (U(rng) - 0.5), qte = qts + dt;
+        const double tau = std::max(ets, qts) + 0.9 * dt * (0.1 + 0.8 * U(rng)) * 0.8;
+        const double d = std::max(1.0, (at + speed * dt) * std::pow(10.0, -6.0 * U(rng)));
+        const bool line = k % 4 == 0;      // head-on along x, from the same point
+        const bool slow = k % 5 == 0;      // a query at rest
+        double e[3], ev[3], q[3], qv[3];
+        for (int a = 0; a < 3; ++a) {
+            const bool on = !line || a == 0;
+            e[a] = on ? at * (2.0 * U(rng) - 1.0) : 0.0;
+            ev[a] = on ? speed * N(rng) : 0.0;
+            qv[a] = on && !slow ? -speed * std::fabs(N(rng)) * (ev[a] > 0 ? 1.0 : -1.0) : 0.0;
+            // half of the pairs pass within d, half up to a few d away
+            q[a] = e[a] + (line && a ? 0.0 : d * (k % 2 ? 0.5 : 4.0) * (2.0 * U(rng) - 1.0));
+        }
+        const auto pos = [](const double* p, const double* v, double t, int a) { return p[a] + v[a] * t; };
+        tds::QCanon c;
+        double e0[3], e1[3], q0[3], q1[3];
+        for (int a = 0; a < 3; ++a) {
+            e0[a] = pos(e, ev, ets - tau, a);
+            e1[a] = pos(e, ev, ete - tau, a);
+            q0[a] = pos(q, qv, qts - tau, a);
+            q1[a] = pos(q, qv, qte - tau, a);
+        }
+        c.x = q0[0];
+        c.y = q0[1];
+        c.z = q0[2];
+        c.vx = (q1[0] - q0[0]) / (qte - qts);
+        c.vy = (q1[1] - q0[1]) / (qte - qts);
+        c.vz = (q1[2] - q0[2]) / (qte - qts);
+        c.ts = c.aq = qts;
+        c.bq = qte;
+        c.d = d;
+        const double edt = ete - ets;
+        const double vx = (e1[0] - e0[0]) / edt, vy = (e1[1] - e0[1]) / edt, vz = (e1[2] - e0[2]) / edt;
+        float ecx, ecy, ecz, er, qcx, qcy, qcz, qR;
+        tds::sphere32(e0[0], e0[1], e0[2], e1[0], e1[1], e1[2], 0.0, ecx, ecy, ecz, er);
+        tds::query_sphere32(q0[0], q0[1], q0[2], c.x + c.vx * (qte - qts),
+                            c.y + c.vy * (qte - qts), c.z + c.vz * (qte - qts), c.vx, c.vy, c.vz,
+                            d, qcx, qcy, qcz, qR);
+        const bool kept = tds::sphere_pass(qcx, qcy, qcz, qR, ecx, ecy, ecz, er) &&
+                          refine_keeps(c, qcx, qcy, qcz, qR, ecx, ecy, ecz, er, vx, vy, vz, ets, ete);
+        double t_lo, t_hi;
+        if (!tds::canon_eval<false>(c, e0[0], e0[1], e0[2], vx, vy, vz, ets, ete, &t_lo, &t_hi)) {
+            dropped += !kept;
+            continue;
+        }
+        ++accepted;
+        misses += !kept;
+        const double wx = c.vx - vx, wy = c.vy - vy, wz = c.vz - vz;
+        past += wx * wx + wy * wy + wz * wz > 0x1p126;
+    }
+    printf("%d %llu %llu %llu %llu\n", TDS_OK, (unsigned long long)accepted,
+           (unsigned long long)misses, (unsigned long long)past, (unsigned long long)dropped);
+    return 0;
+}
+
 int run_cvt(char** argv) {
     const std::vector<char> raw = read_file(argv[2]);
     const size_t n = raw.size() / sizeof(double);
@@ -494,6 +570,7 @@ int main(int argc, char** argv) {
     if (argc >= 10 && std::string(argv[1]) == "fill") return run_fill(argv);
     if (argc >= 4 && std::string(argv[1]) == "filtercheck") return run_filtercheck(argv);
     if (argc >= 4 && std::string(argv[1]) == "cvt") return run_cvt(argv);
+    if (argc >= 4 && std::string(argv[1]) == "fastpairs") return run_fastpairs(argv);
     fprintf(stderr, "usage: harness fsg ... | harness merge ...\n");
     return 2;
 }

@@ -128,9 +128,11 @@ inline float __builtin_amdgcn_sqrtf(float x) {
     const float r = std::sqrt(x);
     return (r > 0.f && r < INFINITY) ? std::nextafter(r, 0.f) : r;
 }
-// likewise the hardware reciprocal (1 ulp), on the side away from zero
+// likewise the hardware reciprocal (1 ulp), on the side away from zero; it
+// returns no subnormals
 inline float __builtin_amdgcn_rcpf(float x) {
     const float r = 1.0f / x;
+    if (std::fabs(r) < 0x1p-126f) return std::copysign(0.0f, r);
     return std::isfinite(r) ? std::nextafter(r, r > 0.f ? INFINITY : -INFINITY) : r;
 }
 #define __builtin_amdgcn_fence(order, scope) std::atomic_thread_fence(std::memory_order_seq_cst)
