@@ -2383,11 +2383,18 @@ void release(tds_index* idx, Workspace* w) {
     idx->pool.push_back(w);
 }
 
+// Gives a call's workspace back.  Unless the call has waited for all it queued
+// on its stream (`idle`: it has returned its results), that is done first: the
+// next call may be on another stream, and the copy of the query arrays reads the
+// workspace's pinned memory and writes its device memory.
 struct WsGuard {
     tds_index* idx;
     Workspace* w;
+    hipStream_t s;
+    bool idle = false;
     ~WsGuard() {
-        if (w) release(idx, w);
+        if (!idle) (void)hipStreamSynchronize(s);
+        release(idx, w);
     }
 };
 
@@ -2596,7 +2603,7 @@ int search_core(tds_index* idx, const tds_segments* Q, bool self_join, double d,
 
     Workspace* w = acquire(idx);
     if (!w) return TDS_E_NOMEM;
-    WsGuard guard{idx, w};
+    WsGuard guard{idx, w, s};
     const uint64_t nq = self_join ? idx->n : Q->n;
     TDS_TRY(ws_reserve(w, nq, 1));
     QueryView V{};
@@ -2710,6 +2717,7 @@ int search_core(tds_index* idx, const tds_segments* Q, bool self_join, double d,
         }
         if (written != total) return TDS_E_DEVICE;
     }
+    guard.idle = true;
     *n_out = total;
     st.results = total;
     st.total_ms =
@@ -2797,11 +2805,11 @@ int search_begin_impl(tds_index* idx, const tds_segments* Q, double d, double t_
         if (hipEventRecord(ps->done, s) != hipSuccess) { st = TDS_E_DEVICE; break; }
     } while (0);
     if (st != TDS_OK) {
-        if (ps->done) {
+        if (ps->done) (void)hipEventDestroy(ps->done);
+        if (ps->w) {
             (void)hipStreamSynchronize(s);  // nothing of it may still run
-            (void)hipEventDestroy(ps->done);
+            release(idx, ps->w);
         }
-        if (ps->w) release(idx, ps->w);
         delete ps;
         return st;
     }
@@ -2833,6 +2841,7 @@ int search_end_impl(void* pending, uint64_t* n_out, tds_stats* stats) {
         }
         status = r;
     }
+    if (status != TDS_OK) (void)hipStreamSynchronize(ps->s);  // a second attempt may still run
     if (status == TDS_OK) {
         const uint64_t total = w->rc_host[0].count;
         if (n_out) *n_out = total;
@@ -2891,7 +2900,7 @@ int batch_impl(tds_index* idx, const tds_segments* Q, const tds_request* reqs, u
 
     Workspace* w = acquire(idx);
     if (!w) return TDS_E_NOMEM;
-    WsGuard guard{idx, w};
+    WsGuard guard{idx, w, s};
     TDS_TRY(ws_reserve(w, Q->n, nreq));
     QueryView V{};
     TDS_TRY(stage_queries(Q, &V, s, &w->qstage, &w->stage_cap, &w->qtraj_stage, &w->traj_cap,
@@ -2932,6 +2941,7 @@ int batch_impl(tds_index* idx, const tds_segments* Q, const tds_request* reqs, u
         }
     }
     if (!dev_out) TDS_HIP(hipStreamSynchronize(s));
+    guard.idle = true;
     st.active_segments = h.active;
     st.work_items = h.n_items;
     st.candidate_tests = h.tests;

@@ -1,0 +1,125 @@
+// The library's host paths on the CPU emulation of its kernels, with allocations
+// that fail (see faults.hpp):
+//
+//   faults waits search|batch|begin   each allocation of a call without a
+//       workspace fails in turn: "calls that failed, failures after something was queued,
+//       calls that returned with work queued"
+#include <cstdio>
+#include <string>
+#include <vector>
+
+#include "tds_internal.hpp"
+
+long emu_launches = 0;
+
+// As in the C ABI (capi.hip, not linked here).
+extern "C" void tds_search_params_default(tds_search_params* p) {
+    std::memset(p, 0, sizeof(*p));
+    p->precision = TDS_PREC_FP32_RECHECK;
+}
+
+namespace {
+
+struct Segs {
+    std::vector<double> a[8];
+    std::vector<uint32_t> traj;
+    tds_segments s{};
+    explicit Segs(size_t n, unsigned seed) {
+        unsigned x = seed;
+        const auto u = [&] { return (x = x * 1664525u + 1013904223u) / 4294967296.0; };
+        for (auto& v : a) v.resize(n);
+        for (size_t i = 0; i < n; ++i) {
+            for (int k = 0; k < 3; ++k) a[k][i] = 10 * u(), a[4 + k][i] = a[k][i] + u();
+            a[3][i] = 4 * u();
+            a[7][i] = a[3][i] + 1;
+            traj.push_back((uint32_t)i);
+        }
+        s.xs = a[0].data();
+        s.ys = a[1].data();
+        s.zs = a[2].data();
+        s.ts = a[3].data();
+        s.xe = a[4].data();
+        s.ye = a[5].data();
+        s.ze = a[6].data();
+        s.te = a[7].data();
+        s.traj_id = traj.data();
+        s.n = n;
+    }
+};
+
+tds_index* build(const Segs& D) {
+    tds_build_params bp{};
+    bp.num_bins = 2;
+    tds_index* idx = nullptr;
+    if (tds::build_impl(&D.s, &bp, nullptr, &idx) != TDS_OK) exit(3);
+    return idx;
+}
+
+tds_search_params params() {
+    tds_search_params p;
+    tds_search_params_default(&p);
+    p.grid_waves = 4;
+    p.output = TDS_OUTPUT_STAGED;
+    return p;
+}
+
+// One call of `entry`; what it returned.
+int call(const std::string& entry, tds_index* idx, const Segs& Q, std::vector<tds_result>& out,
+         uint64_t* n) {
+    tds_search_params p = params();
+    if (entry == "search")
+        return tds::search_impl(idx, &Q.s, 2.0, -1e9, 1e9, out.data(), out.size(), n, &p, nullptr,
+                                nullptr);
+    if (entry == "batch") {
+        const uint64_t h = Q.s.n / 2, room = out.size() / 2;
+        const tds_request r[2] = {{0, h, 2.0, -1e9, 1e9, 0, room},
+                                  {h, Q.s.n - h, 1.0, -1e9, 1e9, room, room}};
+        uint64_t c[2] = {};
+        const int st = tds::batch_impl(idx, &Q.s, r, 2, out.data(), out.size(), c, &p, nullptr, nullptr);
+        *n = c[0] + c[1];
+        return st;
+    }
+    p.out_on_device = 1;
+    void* pending = nullptr;
+    const int st = tds::search_begin_impl(idx, &Q.s, 2.0, -1e9, 1e9, out.data(), out.size(), &p,
+                                          nullptr, &pending);
+    return st == TDS_OK ? tds::search_end_impl(pending, n, nullptr) : st;
+}
+
+int run_waits(const std::string& entry) {
+    const Segs D(200, 1), Q(70, 2);
+    std::vector<tds_result> out(20000);
+    int failed = 0, late = 0, unwaited = 0;
+    tds_index* idx = build(D);
+    for (int pinned = 0; pinned < 2; ++pinned)
+        for (long k = 0;; ++k) {
+            emu_faults.queued = emu_faults.failed = 0;
+            const long launches = emu_launches;
+            (pinned ? emu_faults.pinned : emu_faults.mallocs) = k;
+            emu_faults.copies = 0;
+            uint64_t n = 0;
+            const int st = call(entry, idx, Q, out, &n);
+            emu_faults.pinned = emu_faults.mallocs = -1;
+            if (st != TDS_OK) {
+                ++failed;
+                late += emu_faults.copies > 0;
+                unwaited += emu_faults.queued > 0;
+            }
+            const bool done = emu_faults.failed == 0;
+            if (done && (st != TDS_OK || n == 0 || emu_launches == launches)) return 4;
+            for (tds::Workspace* w : idx->pool) delete w;
+            idx->pool.clear();
+            if (done) break;
+        }
+    tds::destroy_index(idx);
+    printf("%d %d %d\n", failed, late, unwaited);
+    return 0;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+    const std::string mode = argc > 1 ? argv[1] : "";
+    if (mode == "waits" && argc > 2) return run_waits(argv[2]);
+    return 2;
+}
