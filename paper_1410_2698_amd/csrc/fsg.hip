@@ -462,11 +462,14 @@ void free_scratch(FsgScratch& x) {
 }
 
 // A search's counters and events, from the grid's pool or new, given back (or
-// freed, past kFsgPool) at the end.
+// freed, past kFsgPool) at the end: once the search has waited for its stream
+// (`idle`), or after that wait here.
 struct ScratchLease {
     const tds_fsg* f;
+    hipStream_t s;
     FsgScratch x;
-    explicit ScratchLease(const tds_fsg* g) : f(g) {
+    bool idle = false;
+    ScratchLease(const tds_fsg* g, hipStream_t stream) : f(g), s(stream) {
         std::lock_guard<std::mutex> l(f->mu);
         if (f->pool.empty()) return;
         x = f->pool.back();
@@ -482,6 +485,7 @@ struct ScratchLease {
         return TDS_OK;
     }
     ~ScratchLease() {
+        if (!idle) (void)hipStreamSynchronize(s);
         {
             std::lock_guard<std::mutex> l(f->mu);
             if (x.e1 && f->pool.size() < kFsgPool) {
@@ -677,7 +681,7 @@ int fsg_search(const tds_fsg* f, const tds_segments* Q, double d, double t_start
         B.p[2] = res;
         A.out = res;
     }
-    ScratchLease lease(f);
+    ScratchLease lease(f, s);
     TDS_TRY(lease.ready());
     A.counters = lease.x.ctr;
     TDS_HIP(hipMemsetAsync(A.counters, 0, kFCounters * sizeof(unsigned long long), s));
@@ -695,6 +699,7 @@ int fsg_search(const tds_fsg* f, const tds_segments* Q, double d, double t_start
                        hipMemcpyDeviceToHost, s) != hipSuccess)
         st = TDS_E_DEVICE;
     if (st == TDS_OK && hipStreamSynchronize(s) != hipSuccess) st = TDS_E_DEVICE;
+    lease.idle = st == TDS_OK;
     float ms = 0.f;
     if (st == TDS_OK) (void)hipEventElapsedTime(&ms, lease.x.e0, lease.x.e1);
     TDS_TRY(st);

@@ -4,6 +4,8 @@
 //   faults waits search|batch|begin   each allocation of a call without a
 //       workspace fails in turn: "calls that failed, failures after something was queued,
 //       calls that returned with work queued"
+//   faults grid    each copy of a grid search of device arrays fails in turn: the
+//       same three numbers
 #include <cstdio>
 #include <string>
 #include <vector>
@@ -116,10 +118,44 @@ int run_waits(const std::string& entry) {
     return 0;
 }
 
+int run_grid() {
+    const Segs D(200, 1);
+    Segs Q(70, 2);
+    Q.s.on_device = 1;
+    std::vector<tds_result> out(20000);
+    tds_index* idx = build(D);
+    tds_fsg* f = nullptr;
+    if (tds::fsg_build(idx, 3, 3, 3, nullptr, &f) != TDS_OK) return 3;
+    tds_search_params p = params();
+    p.out_on_device = 1;
+    int failed = 0, late = 0, unwaited = 0;
+    for (long k = 0;; ++k) {
+        emu_faults.queued = emu_faults.failed = 0;
+        emu_faults.copies_left = k;
+        const long launches = emu_launches;
+        uint64_t n = 0;
+        const int st = tds::fsg_search(f, &Q.s, 2.0, -1e9, 1e9, out.data(), out.size(), &n, &p,
+                                       nullptr, nullptr);
+        emu_faults.copies_left = -1;
+        if (emu_faults.failed == 0) {
+            if (st != TDS_OK || n == 0) return 4;
+            break;
+        }
+        failed += st != TDS_OK;
+        late += emu_launches > launches;
+        unwaited += emu_faults.queued > 0;
+    }
+    tds::fsg_destroy(f);
+    tds::destroy_index(idx);
+    printf("%d %d %d\n", failed, late, unwaited);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string mode = argc > 1 ? argv[1] : "";
     if (mode == "waits" && argc > 2) return run_waits(argv[2]);
+    if (mode == "grid") return run_grid();
     return 2;
 }

@@ -1,5 +1,5 @@
 // Included ahead of the library's sources (-include) in the build of
-// tests/emu/faults.cpp: allocations that fail when they are told to, and a count
+// tests/emu/faults.cpp: allocations and copies that fail when they are told to, and a count
 // of what has been queued on a stream since a host thread last waited for it
 // (the emulation itself runs everything at once).
 #pragma once
@@ -8,7 +8,8 @@
 
 struct EmuFaults {
     long mallocs = -1, pinned = -1;  // that many more succeed, the rest fail; < 0: all do
-    long failed = 0;                 // allocations that failed
+    long copies_left = -1;           // likewise, of the copies
+    long failed = 0;                 // allocations and copies that failed
     long queued = 0;                 // copies and launches not waited for
     long copies = 0;                 // copies queued
     long live = 0;                   // device allocations not freed
@@ -44,6 +45,7 @@ inline hipError_t emu_hipHostMalloc(void** p, size_t n, unsigned flags) {
     return hipHostMalloc(p, n, flags);
 }
 inline hipError_t emu_hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t t) {
+    if (emu_fails(emu_faults.copies_left)) return hipErrorInvalidValue;
     ++emu_faults.queued;
     ++emu_faults.copies;
     return hipMemcpyAsync(d, s, n, k, t);

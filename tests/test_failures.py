@@ -43,3 +43,10 @@ def test_failed_call_leaves_no_work_behind(faults, entry):
     failed, late, unwaited = faults("waits", entry)
     assert failed > 10 and late > 0
     assert unwaited == 0
+
+
+def test_failed_grid_search_leaves_no_work_behind(faults):
+    """The counters go back to the grid's pool when a search fails."""
+    failed, late, unwaited = faults("grid")
+    assert failed == late == 1
+    assert unwaited == 0
