@@ -512,6 +512,17 @@ struct MergeScratch {
     }
 };
 
+// Waits for the stream at a merge's end unless it has (`idle`): parts of the
+// scratch are reserved after work was queued on it, and when that fails the next
+// merge, perhaps on another stream, must not find that work running.
+struct MergeWait {
+    hipStream_t s;
+    bool idle = false;
+    ~MergeWait() {
+        if (!idle) (void)hipStreamSynchronize(s);
+    }
+};
+
 constexpr int kMaxDevices = 64;
 MergeScratch g_scratch[kMaxDevices];
 
@@ -602,6 +613,7 @@ int merge_impl(const tds_result* recs, uint64_t n, bool recs_dev, tds_traj_inter
     // before it returns, so the next call finds the scratch free
     std::lock_guard<std::mutex> lock(M.mu);
     TDS_TRY(M.reserve(n));
+    MergeWait wait{s};
     const uint32_t nn = (uint32_t)n;
     const tds_result* R = recs;
     if (!recs_dev) {
@@ -647,6 +659,7 @@ int merge_impl(const tds_result* recs, uint64_t n, bool recs_dev, tds_traj_inter
         TDS_HIP(hipMemcpyAsync(out, M.stage, keep * sizeof(tds_traj_interval),
                                hipMemcpyDeviceToHost, s));
     if (keep && (!out_dev || !one_pass)) TDS_HIP(hipStreamSynchronize(s));
+    wait.idle = true;
     return *n_out > capacity ? TDS_E_OVERFLOW : TDS_OK;
 }
 

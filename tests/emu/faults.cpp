@@ -4,6 +4,8 @@
 //   faults waits search|batch|begin   each allocation of a call without a
 //       workspace fails in turn: "calls that failed, failures after something was queued,
 //       calls that returned with work queued"
+//   faults merge   each allocation of a merge of host records fails in turn: the
+//       same three numbers
 //   faults grid    each copy of a grid search of device arrays fails in turn: the
 //       same three numbers
 #include <cstdio>
@@ -118,6 +120,37 @@ int run_waits(const std::string& entry) {
     return 0;
 }
 
+int run_merge() {
+    std::vector<tds_result> r(40);
+    for (size_t i = 0; i < r.size(); ++i) {
+        r[i] = {};
+        r[i].q_traj = (uint32_t)i % 3;
+        r[i].t_lo = (double)(i % 7);
+        r[i].t_hi = r[i].t_lo + (i == 9 ? -1 : 2);  // one is no interval: the general form
+    }
+    std::vector<tds_traj_interval> out(r.size());
+    int failed = 0, late = 0, unwaited = 0;
+    for (long k = 0;; ++k) {
+        emu_faults.queued = emu_faults.failed = emu_faults.copies = 0;
+        emu_faults.mallocs = k;
+        const long live = emu_faults.live;
+        uint64_t n = 0;
+        const int st = tds::merge_impl(r.data(), r.size(), false, out.data(), out.size(), false, &n,
+                                       nullptr);
+        emu_faults.mallocs = -1;
+        if (emu_faults.failed == 0) {
+            if (st != TDS_OK || n == 0) return 4;
+            break;
+        }
+        failed += st != TDS_OK;
+        late += emu_faults.copies > 0;
+        unwaited += emu_faults.queued > 0;
+        if (emu_faults.live > live) k = -1;  // a part of the scratch stays: on from the next
+    }
+    printf("%d %d %d\n", failed, late, unwaited);
+    return 0;
+}
+
 int run_grid() {
     const Segs D(200, 1);
     Segs Q(70, 2);
@@ -156,6 +189,7 @@ int run_grid() {
 int main(int argc, char** argv) {
     const std::string mode = argc > 1 ? argv[1] : "";
     if (mode == "waits" && argc > 2) return run_waits(argv[2]);
+    if (mode == "merge") return run_merge();
     if (mode == "grid") return run_grid();
     return 2;
 }

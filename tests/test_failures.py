@@ -50,3 +50,10 @@ def test_failed_grid_search_leaves_no_work_behind(faults):
     failed, late, unwaited = faults("grid")
     assert failed == late == 1
     assert unwaited == 0
+
+
+def test_failed_merge_leaves_no_work_behind(faults):
+    """The merge's scratch is the next merge's, on whatever stream."""
+    failed, late, unwaited = faults("merge")
+    assert failed > 5 and late > 1
+    assert unwaited == 0
