@@ -280,7 +280,8 @@ __global__ __launch_bounds__(kTileThreads) void k_merge_tiles(
 // pre: exclusive sums of the tiles' counts with the total at [tiles], or, for
 // inputs of few tiles (kSum), the counts themselves, which each workgroup adds
 // up to its tile.  One workgroup per tile; bound by HBM (24 bytes in and out
-// per interval, in 8-byte words next to each other).
+// per interval, in 8-byte words next to each other).  Nothing is written where
+// the general form takes over: it may find fewer intervals.
 template <bool kSum>
 __global__ __launch_bounds__(256) void k_merge_place(const uint32_t* __restrict__ pre,
                                                      const uint32_t* __restrict__ from,
@@ -288,6 +289,7 @@ __global__ __launch_bounds__(256) void k_merge_place(const uint32_t* __restrict_
                                                      const uint64_t* __restrict__ tmp,
                                                      uint64_t* __restrict__ out, uint64_t capacity,
                                                      SortControl* __restrict__ ctl) {
+    if (ctl->odd) return;
     const uint32_t t = blockIdx.x;
     uint32_t first, n;
     if (kSum) {
@@ -647,7 +649,7 @@ int merge_impl(const tds_result* recs, uint64_t n, bool recs_dev, tds_traj_inter
         TDS_TRY(merge_one_pass(M, R, nn, narrow, dst, cap, s));
         TDS_TRY(M.read_ctl(s));
         one_pass = !M.ctl_host->odd;
-        *n_out = M.ctl_host->total;
+        if (one_pass) *n_out = M.ctl_host->total;
     }
     if (!one_pass) {
         uint32_t total = 0;

@@ -5,7 +5,7 @@
 //       workspace fails in turn: "calls that failed, failures after something was queued,
 //       calls that returned with work queued"
 //   faults merge   each allocation of a merge of host records fails in turn: the
-//       same three numbers
+//       same three numbers, and the failed calls that gave a number of intervals
 //   faults grid    each copy of a grid search of device arrays fails in turn: the
 //       same three numbers
 #include <cstdio>
@@ -129,7 +129,7 @@ int run_merge() {
         r[i].t_hi = r[i].t_lo + (i == 9 ? -1 : 2);  // one is no interval: the general form
     }
     std::vector<tds_traj_interval> out(r.size());
-    int failed = 0, late = 0, unwaited = 0;
+    int failed = 0, late = 0, unwaited = 0, counted = 0;
     for (long k = 0;; ++k) {
         emu_faults.queued = emu_faults.failed = emu_faults.copies = 0;
         emu_faults.mallocs = k;
@@ -145,9 +145,10 @@ int run_merge() {
         failed += st != TDS_OK;
         late += emu_faults.copies > 0;
         unwaited += emu_faults.queued > 0;
+        counted += n != 0;
         if (emu_faults.live > live) k = -1;  // a part of the scratch stays: on from the next
     }
-    printf("%d %d %d\n", failed, late, unwaited);
+    printf("%d %d %d %d\n", failed, late, unwaited, counted);
     return 0;
 }
 

@@ -8,6 +8,7 @@
 //   harness search D.bin Q.bin layout prec d t0 t1 cap out.bin [bins] -> "status n ftests"
 //   harness selfjoin D.bin layout prec d t0 t1 cap out.bin        -> "status n ftests"
 //   harness merge recs.bin capacity out.bin                       -> "status n"
+//   harness mergefull recs.bin capacity out.bin                   -> "status n"
 //   harness hostsearch D.bin Q.bin d t0 t1 out.bin                -> "status n candidates"
 //   harness fill seed W C K frac add align prefix                 -> "status count cap T holes R"
 //   harness filtercheck seed n                                    -> "status accepted misses naive"
@@ -16,7 +17,8 @@
 //
 // D.bin / Q.bin: 9 float64 columns (xs ys zs ts xe ye ze te traj), column
 // after column.  recs.bin: tds_result records.  out.bin: the records or
-// intervals written.
+// intervals written; with "mergefull" (records and output in device memory) the
+// whole output, whose bytes were 0xAB.
 //
 // "fill" runs the direct-output fill pass (k_fill_plan, k_fill_copy) alone on
 // a synthetic reservation pattern: W waves append random runs of 1..64
@@ -559,6 +561,23 @@ int run_merge(char** argv) {
     return 0;
 }
 
+int run_mergefull(char** argv) {
+    const std::vector<char> raw = read_file(argv[2]);
+    const size_t n = raw.size() / sizeof(tds_result);
+    std::vector<tds_result> recs(n);
+    if (n) std::memcpy(recs.data(), raw.data(), n * sizeof(tds_result));
+    const uint64_t cap = strtoull(argv[3], nullptr, 10);
+    std::vector<tds_traj_interval> out(std::max<uint64_t>(cap, 1));
+    std::memset(static_cast<void*>(out.data()), 0xAB, out.size() * sizeof(tds_traj_interval));
+    uint64_t m = 0;
+    const int st = tds::merge_impl(recs.data(), n, true, out.data(), cap, true, &m, nullptr);
+    FILE* fo = fopen(argv[4], "wb");
+    fwrite(out.data(), sizeof(tds_traj_interval), cap, fo);
+    fclose(fo);
+    printf("%d %llu\n", st, (unsigned long long)m);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -566,6 +585,7 @@ int main(int argc, char** argv) {
     if (argc >= 11 && std::string(argv[1]) == "search") return run_search(argc, argv, false);
     if (argc >= 10 && std::string(argv[1]) == "selfjoin") return run_search(argc, argv, true);
     if (argc >= 5 && std::string(argv[1]) == "merge") return run_merge(argv);
+    if (argc >= 5 && std::string(argv[1]) == "mergefull") return run_mergefull(argv);
     if (argc >= 8 && std::string(argv[1]) == "hostsearch") return run_hostsearch(argv);
     if (argc >= 10 && std::string(argv[1]) == "fill") return run_fill(argv);
     if (argc >= 4 && std::string(argv[1]) == "filtercheck") return run_filtercheck(argv);
