@@ -48,6 +48,24 @@ def test_nothing_past_the_result_emulated(tmp_path):
 
 
 @pytest.mark.gpu
+def test_lengths_of_the_walk():
+    """Runs of every length around the eight records that the general form's walk
+    reads ahead, behind a run that makes it the form taken."""
+    import paper_1410_2698_amd as tds
+    rng = np.random.default_rng(3)
+    runs = np.concatenate([[1600], np.arange(1, 35).repeat(3)])
+    pair = np.repeat(np.arange(runs.size), runs)
+    r = np.zeros(pair.size, RESULT_DTYPE)
+    r["q_traj"], r["e_traj"] = pair // 9, pair % 9
+    r["t_lo"] = rng.integers(0, 160, pair.size) / 4.0
+    r["t_hi"] = r["t_lo"] + rng.integers(0, 6, pair.size) / 4.0
+    r = r[rng.permutation(r.size)]
+    want = oracle.merge_trajectories(r)
+    got = tds.merge_trajectories(r)
+    assert got.tobytes() == want.tobytes()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["long", "odd"])
 def test_nothing_past_the_result_gpu(kind):
     import torch
