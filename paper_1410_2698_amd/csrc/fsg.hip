@@ -451,8 +451,6 @@ __global__ __launch_bounds__(kFS) void k_fsg_search(FsgArgs A) {
     if (t < n && O.base + t < A.capacity) A.out[O.base + t] = O.r[t];
 }
 
-constexpr size_t kFsgPool = 16;
-
 void free_scratch(FsgScratch& x) {
     dfree(x.ctr);
     if (x.ctr_host) (void)hipHostFree(x.ctr_host);
@@ -471,9 +469,7 @@ struct ScratchLease {
     bool idle = false;
     ScratchLease(const tds_fsg* g, hipStream_t stream) : f(g), s(stream) {
         std::lock_guard<std::mutex> l(f->mu);
-        if (f->pool.empty()) return;
-        x = f->pool.back();
-        f->pool.pop_back();
+        if (f->npool) x = f->pool[--f->npool];
     }
     int ready() {
         if (x.e1) return TDS_OK;
@@ -488,8 +484,8 @@ struct ScratchLease {
         if (!idle) (void)hipStreamSynchronize(s);
         {
             std::lock_guard<std::mutex> l(f->mu);
-            if (x.e1 && f->pool.size() < kFsgPool) {
-                f->pool.push_back(x);
+            if (x.e1 && f->npool < kFsgPool) {
+                f->pool[f->npool++] = x;
                 return;
             }
         }
@@ -614,7 +610,7 @@ int fsg_build(const tds_index* idx, uint32_t gx, uint32_t gy, uint32_t gz, hipSt
 
 void fsg_destroy(tds_fsg* f) {
     if (!f) return;
-    for (FsgScratch& x : f->pool) free_scratch(x);
+    for (size_t i = 0; i < f->npool; ++i) free_scratch(f->pool[i]);
     dfree(f->cell_first);
     dfree(f->list);
     delete f;

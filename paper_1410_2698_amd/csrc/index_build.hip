@@ -18,6 +18,7 @@
 //   k_block_box   (spatial layout) box of the segments of every aligned
 //                 block of 64 entries.
 #include <cmath>
+#include <new>
 #include <utility>
 
 #include "hilbert.hpp"
@@ -277,11 +278,34 @@ struct Scratch {
 
 struct BlockPool {
     std::mutex mu;
-    std::vector<DeviceBlock> idle;  // in the order of their release
+    DeviceBlock idle[kPoolBlocks];  // in the order of their release
+    size_t n = 0;
+    DeviceBlock take(size_t i) {
+        const DeviceBlock b = idle[i];
+        std::copy(idle + i + 1, idle + n, idle + i);
+        --n;
+        return b;
+    }
+    // Takes the most recently released of the device's blocks with which, from
+    // the newest on, they hold more than `keep` bytes.
+    bool take_past(int device, size_t keep, DeviceBlock* b) {
+        std::lock_guard<std::mutex> l(mu);
+        size_t sum = 0;
+        for (size_t i = n; i-- > 0;) {
+            if (idle[i].device != device) continue;
+            sum += idle[i].bytes;
+            if (sum > keep) {
+                *b = take(i);
+                return true;
+            }
+        }
+        return false;
+    }
 };
 // never destroyed: at the program's end the runtime may be gone first
 BlockPool& block_pool() {
-    static BlockPool* pool = new BlockPool();
+    alignas(BlockPool) static unsigned char mem[sizeof(BlockPool)];
+    static BlockPool* pool = new (mem) BlockPool();
     return *pool;
 }
 
@@ -296,16 +320,15 @@ int acquire_block(size_t bytes, DeviceBlock* b) {
     {
         // the smallest idle block that holds it, unless most would lie idle
         std::lock_guard<std::mutex> l(P.mu);
-        size_t best = P.idle.size();
-        for (size_t i = 0; i < P.idle.size(); ++i) {
+        size_t best = P.n;
+        for (size_t i = 0; i < P.n; ++i) {
             const DeviceBlock& x = P.idle[i];
             if (x.device == dev && x.bytes >= bytes && x.bytes / 2 <= bytes &&
-                (best == P.idle.size() || x.bytes < P.idle[best].bytes))
+                (best == P.n || x.bytes < P.idle[best].bytes))
                 best = i;
         }
-        if (best < P.idle.size()) {
-            *b = P.idle[best];
-            P.idle.erase(P.idle.begin() + (std::ptrdiff_t)best);
+        if (best < P.n) {
+            *b = P.take(best);
             return TDS_OK;
         }
     }
@@ -317,49 +340,36 @@ int acquire_block(size_t bytes, DeviceBlock* b) {
 
 void release_block(DeviceBlock* b) {
     if (!b->p) return;
-    std::vector<DeviceBlock> out;  // to free
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(b->device);
     const bool idle = b->bytes <= kPoolBytes && hipDeviceSynchronize() == hipSuccess;
     (void)hipSetDevice(cur);
+    DeviceBlock out;  // to free
     if (!idle) {
         (void)hipGetLastError();
-        out.push_back(*b);
+        out = *b;
     } else {
         BlockPool& P = block_pool();
         std::lock_guard<std::mutex> l(P.mu);
-        P.idle.push_back(*b);
-        size_t sum = 0;
-        for (size_t i = P.idle.size(); i-- > 0;) {
-            if (P.idle[i].device != b->device) continue;
-            sum += P.idle[i].bytes;
-            if (sum > kPoolBytes) {
-                sum -= P.idle[i].bytes;
-                out.push_back(P.idle[i]);
-                P.idle.erase(P.idle.begin() + (std::ptrdiff_t)i);
-            }
-        }
+        if (P.n == kPoolBlocks) out = P.take(0);
+        P.idle[P.n++] = *b;
     }
-    for (const DeviceBlock& x : out) dfree(x.p);
+    dfree(out.p);
+    while (idle && block_pool().take_past(b->device, kPoolBytes, &out)) dfree(out.p);
     *b = DeviceBlock();
 }
 
 bool trim_blocks() {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return false;
-    std::vector<DeviceBlock> out;
-    {
-        BlockPool& P = block_pool();
-        std::lock_guard<std::mutex> l(P.mu);
-        for (size_t i = P.idle.size(); i-- > 0;)
-            if (P.idle[i].device == dev) {
-                out.push_back(P.idle[i]);
-                P.idle.erase(P.idle.begin() + (std::ptrdiff_t)i);
-            }
+    DeviceBlock out;
+    bool any = false;
+    while (block_pool().take_past(dev, 0, &out)) {
+        dfree(out.p);
+        any = true;
     }
-    for (const DeviceBlock& x : out) dfree(x.p);
-    return !out.empty();
+    return any;
 }
 
 int validate_segments_args(const tds_segments* S) {

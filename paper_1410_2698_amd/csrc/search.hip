@@ -28,6 +28,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <new>
 
 #include <hip/hip_ext.h>
 
@@ -1875,11 +1876,13 @@ int grow(T** p, size_t* cap, size_t need) {
 namespace {
 struct PinPool {
     std::mutex mu;
-    std::vector<PinBlock*> idle;
+    PinBlock* idle[kPinPool];
+    size_t n = 0;
 };
 // never destroyed: at the program's end the runtime may be gone first
 PinPool& pin_pool() {
-    static PinPool* pool = new PinPool();
+    alignas(PinPool) static unsigned char mem[sizeof(PinPool)];
+    static PinPool* pool = new (mem) PinPool();
     return *pool;
 }
 }  // namespace
@@ -1889,9 +1892,8 @@ int acquire_pin(PinBlock** b) {
     {
         PinPool& P = pin_pool();
         std::lock_guard<std::mutex> l(P.mu);
-        if (!P.idle.empty()) {
-            *b = P.idle.back();
-            P.idle.pop_back();
+        if (P.n) {
+            *b = P.idle[--P.n];
             return TDS_OK;
         }
     }
@@ -1906,8 +1908,8 @@ void release_pin(PinBlock* b) {
     {
         PinPool& P = pin_pool();
         std::lock_guard<std::mutex> l(P.mu);
-        if (P.idle.size() < kPinPool) {
-            P.idle.push_back(b);
+        if (P.n < kPinPool) {
+            P.idle[P.n++] = b;
             return;
         }
     }

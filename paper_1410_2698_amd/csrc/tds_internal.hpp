@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cassert>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -266,6 +267,7 @@ struct tds_index {
 };
 
 namespace tds {
+constexpr size_t kFsgPool = 16;
 struct FsgScratch {
     unsigned long long* ctr = nullptr;       // the search kernel's counters
     unsigned long long* ctr_host = nullptr;  // pinned
@@ -286,7 +288,8 @@ struct tds_fsg {
     // what a search needs besides its arrays, kept for the next ones (one per
     // search at a time; at most kFsgPool are kept)
     mutable std::mutex mu;
-    mutable std::vector<tds::FsgScratch> pool;
+    mutable tds::FsgScratch pool[tds::kFsgPool];
+    mutable size_t npool = 0;
 };
 
 namespace tds {
@@ -337,7 +340,11 @@ struct DeviceGuard {
 // ones, and all of them go back when an allocation of the library finds no
 // memory.  Safe with several threads and streams: a block is only offered again
 // after the device has finished all work, as with hipFree.
+// The list of idle blocks has kPoolBlocks places (of all devices), so that
+// giving one back needs no host memory: it happens in destructors and in C
+// entries.
 constexpr size_t kPoolBytes = size_t(1) << 30;
+constexpr size_t kPoolBlocks = 256;
 int acquire_block(size_t bytes, DeviceBlock* b);  // on the current device
 void release_block(DeviceBlock* b);
 bool trim_blocks();  // the current device's idle blocks; true if there were any
@@ -363,19 +370,23 @@ inline void dfree(void* p) {
 
 // Device arrays that live and die together, as one block of the pool.
 struct DeviceArena {
-    static constexpr size_t kAlign = 256;
-    std::vector<std::pair<void**, size_t>> parts;  // pointer to set, byte offset
-    size_t bytes = 0;
+    static constexpr size_t kAlign = 256, kParts = 16;
+    struct Part {
+        void** p;
+        size_t at;
+    } parts[kParts];  // pointer to set, byte offset
+    size_t n = 0, bytes = 0;
     template <class T>
     void add(T** p, size_t count) {
         *p = nullptr;
-        parts.push_back({reinterpret_cast<void**>(p), bytes});
+        assert(n < kParts);
+        parts[n++] = {reinterpret_cast<void**>(p), bytes};
         bytes += (std::max<size_t>(count, 1) * sizeof(T) + kAlign - 1) / kAlign * kAlign;
     }
     // Sets the pointers; the block is to be given back with release_block.
     int alloc(DeviceBlock* block) {
         TDS_TRY(acquire_block(bytes, block));
-        for (const auto& p : parts) *p.first = block->p + p.second;
+        for (size_t i = 0; i < n; ++i) *parts[i].p = block->p + parts[i].at;
         return TDS_OK;
     }
 };

@@ -6,9 +6,12 @@
 //       calls that returned with work queued"
 //   faults merge   each allocation of a merge of host records fails in turn: the
 //       same three numbers, and the failed calls that gave a number of intervals
+//   faults pools   device and pinned blocks are given back, and a grid search ends,
+//       with no host memory to be had: 0 (an exception ends the program)
 //   faults grid    each copy of a grid search of device arrays fails in turn: the
 //       same three numbers
 #include <cstdio>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -21,6 +24,17 @@ extern "C" void tds_search_params_default(tds_search_params* p) {
     std::memset(p, 0, sizeof(*p));
     p->precision = TDS_PREC_FP32_RECHECK;
 }
+
+void* operator new(size_t n) {
+    void* p = emu_faults.news ? nullptr : malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void* operator new(size_t n, const std::nothrow_t&) noexcept {
+    return emu_faults.news ? nullptr : malloc(n);
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
 
 namespace {
 
@@ -120,6 +134,40 @@ int run_waits(const std::string& entry) {
     return 0;
 }
 
+int run_pools() {
+    constexpr int kBlocks = 200;
+    static tds::DeviceBlock b[kBlocks];
+    static tds::PinBlock* pins[40];
+    for (int i = 0; i < kBlocks; ++i)
+        if (tds::acquire_block((size_t)(1 + i % 7) << 21, &b[i]) != TDS_OK) return 3;
+    for (auto& p : pins)
+        if (tds::acquire_pin(&p) != TDS_OK) return 3;
+    emu_faults.news = true;
+    for (auto& x : b) tds::release_block(&x);
+    tds::DeviceBlock again;
+    if (tds::acquire_block(3 << 20, &again) != TDS_OK) return 4;
+    tds::release_block(&again);
+    tds::trim_blocks();
+    for (auto* p : pins) tds::release_pin(p);
+    emu_faults.news = false;
+    if (emu_faults.live != 0) return 5;  // all blocks were freed
+    const Segs D(200, 1), Q(70, 2);
+    std::vector<tds_result> out(20000);
+    tds_index* idx = build(D);
+    tds_fsg* f = nullptr;
+    if (tds::fsg_build(idx, 3, 3, 3, nullptr, &f) != TDS_OK) return 3;
+    uint64_t n = 0;
+    emu_faults.news_after_wait = true;
+    const int st = tds::fsg_search(f, &Q.s, 2.0, -1e9, 1e9, out.data(), out.size(), &n, nullptr,
+                                   nullptr, nullptr);
+    emu_faults.news_after_wait = emu_faults.news = false;
+    if (st != TDS_OK || n == 0) return 4;
+    tds::fsg_destroy(f);
+    tds::destroy_index(idx);
+    printf("0\n");
+    return 0;
+}
+
 int run_merge() {
     std::vector<tds_result> r(40);
     for (size_t i = 0; i < r.size(); ++i) {
@@ -190,6 +238,7 @@ int run_grid() {
 int main(int argc, char** argv) {
     const std::string mode = argc > 1 ? argv[1] : "";
     if (mode == "waits" && argc > 2) return run_waits(argv[2]);
+    if (mode == "pools") return run_pools();
     if (mode == "merge") return run_merge();
     if (mode == "grid") return run_grid();
     return 2;

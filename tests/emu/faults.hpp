@@ -12,6 +12,8 @@ struct EmuFaults {
     long failed = 0;                 // allocations and copies that failed
     long queued = 0;                 // copies and launches not waited for
     long copies = 0;                 // copies queued
+    bool news = false;               // operator new fails
+    bool news_after_wait = false;    // from the next wait for a stream on
     long live = 0;                   // device allocations not freed
 };
 inline EmuFaults emu_faults;
@@ -52,6 +54,7 @@ inline hipError_t emu_hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpy
 }
 inline hipError_t emu_hipStreamSynchronize(hipStream_t s) {
     emu_faults.queued = 0;
+    if (emu_faults.news_after_wait) emu_faults.news = true;
     return hipStreamSynchronize(s);
 }
 inline hipError_t emu_hipDeviceSynchronize() {

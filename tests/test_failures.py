@@ -57,3 +57,9 @@ def test_failed_merge_leaves_no_work_behind(faults):
     failed, late, unwaited, counted = faults("merge")
     assert failed > 5 and late > 1
     assert unwaited == 0 and counted == 0
+
+
+def test_pools_need_no_host_memory(faults):
+    """Giving a block back allocates nothing: it happens in destructors and at the
+    end of C entries, where an exception ends the program."""
+    assert faults("pools") == [0]
