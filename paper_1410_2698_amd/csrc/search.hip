@@ -2163,7 +2163,7 @@ int resolve_prec(int p) {
 
 // Device view of the query arrays; host arrays are copied into the staging
 // buffers first, through the workspace's pinned block (`pin`, taken at its
-// first use) where they fit.
+// first use) where they fit and there is one.
 int stage_queries(const tds_segments* Q, QueryView* V, hipStream_t s, double** stage_buf,
                   size_t* stage_cap, uint32_t** traj_buf, size_t* traj_cap, PinBlock** block) {
     V->n = Q->n;
@@ -2174,8 +2174,7 @@ int stage_queries(const tds_segments* Q, QueryView* V, hipStream_t s, double** s
         return TDS_OK;
     }
     const hipMemcpyKind kind = hipMemcpyHostToDevice;
-    if (block && Q->n <= kPinSegs) {
-        TDS_TRY(acquire_pin(block));
+    if (block && Q->n <= kPinSegs && acquire_pin(block) == TDS_OK) {
         char* pin = (*block)->segs;
         const size_t col = Q->n * sizeof(double);
         for (int k = 0; k < 8; ++k) std::memcpy(pin + k * col, src[k], col);
@@ -2646,10 +2645,8 @@ int search_core(tds_index* idx, const tds_segments* Q, bool self_join, double d,
     SearchHeader h{};
     // pass 1: every item, result window [0, dev_cap)
     uint32_t peek = 0;
-    if (!dev_out && capacity) {
-        TDS_TRY(acquire_pin(&w->pin));
+    if (!dev_out && capacity && acquire_pin(&w->pin) == TDS_OK)
         peek = (uint32_t)std::min<uint64_t>(kPeek, dev_cap);
-    }
     TDS_TRY(run_batch(idx, w, V, 1, prec, chunk, grid_waves, cpl, P.output, res, s, &st, &h, peek));
     const ReqCounter rc = w->rc_host[0];
     const uint32_t n_items = h.n_items;

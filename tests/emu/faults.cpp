@@ -8,6 +8,9 @@
 //       same three numbers, and the failed calls that gave a number of intervals
 //   faults pools   device and pinned blocks are given back, and a grid search ends,
 //       with no host memory to be had: 0 (an exception ends the program)
+//   faults pinned  a search, a batch and a begun search of host arrays where the
+//       index has a workspace and there is no more pinned memory: their statuses and
+//       whether each found what it finds with it
 //   faults grid    each copy of a grid search of device arrays fails in turn: the
 //       same three numbers
 #include <cstdio>
@@ -168,6 +171,39 @@ int run_pools() {
     return 0;
 }
 
+int run_pinned() {
+    const Segs D(200, 1), Q(70, 2);
+    Segs dq(70, 3);
+    dq.s.on_device = 1;
+    std::vector<tds_result> out(20000);
+    tds_index* idx = build(D);
+    tds_search_params p = params();
+    p.out_on_device = 1;
+    const std::string entry[3] = {"search", "batch", "begin"};
+    uint64_t want[3] = {}, n = 0;
+    for (int i = 0; i < 3; ++i)
+        if (call(entry[i], idx, Q, out, &want[i]) != TDS_OK || want[i] == 0) return 3;
+    for (int i = 0; i < 3; ++i) {
+        // a workspace as a search from and to device memory leaves it
+        for (tds::Workspace* w : idx->pool) delete w;
+        idx->pool.clear();
+        if (tds::search_impl(idx, &dq.s, 2.0, -1e9, 1e9, out.data(), out.size(), &n, &p, nullptr,
+                             nullptr) != TDS_OK)
+            return 3;
+        tds::PinBlock* idle[tds::kPinPool] = {};  // none in the pool either
+        for (auto& x : idle) (void)tds::acquire_pin(&x);
+        emu_faults.pinned = 0;
+        n = 0;
+        const int st = call(entry[i], idx, Q, out, &n);
+        emu_faults.pinned = -1;
+        for (auto* x : idle) tds::release_pin(x);
+        printf("%d %d ", st, n == want[i]);
+    }
+    tds::destroy_index(idx);
+    printf("\n");
+    return 0;
+}
+
 int run_merge() {
     std::vector<tds_result> r(40);
     for (size_t i = 0; i < r.size(); ++i) {
@@ -239,6 +275,7 @@ int main(int argc, char** argv) {
     const std::string mode = argc > 1 ? argv[1] : "";
     if (mode == "waits" && argc > 2) return run_waits(argv[2]);
     if (mode == "pools") return run_pools();
+    if (mode == "pinned") return run_pinned();
     if (mode == "merge") return run_merge();
     if (mode == "grid") return run_grid();
     return 2;

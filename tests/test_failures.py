@@ -63,3 +63,9 @@ def test_pools_need_no_host_memory(faults):
     """Giving a block back allocates nothing: it happens in destructors and at the
     end of C entries, where an exception ends the program."""
     assert faults("pools") == [0]
+
+
+def test_searches_without_pinned_memory(faults):
+    """The pinned block only saves copies: without one the arrays are copied as
+    they are."""
+    assert faults("pinned") == [0, 1] * 3
