@@ -253,9 +253,19 @@ const char* tds_status_str(int status);
 int tds_build_index(const tds_segments* D, const tds_build_params* params,
                     void* stream, tds_index** out);
 
-/* Free the index and its device memory.  NULL is accepted.  The caller must
-   ensure no search on it is still running. */
+/* Free the index.  NULL is accepted.  The caller must ensure no search on it is
+   still running.  Up to 1 GiB of a device's memory that indexes, their builds and
+   their searches no longer need stays with the library for the next ones; it
+   goes back when an allocation of the library finds no memory, or with
+   tds_release_idle. */
 int tds_index_destroy(tds_index* index);
+
+/* Give the memory of the current device that the library holds for later use
+   (see tds_index_destroy) back to the system, for another allocator in the
+   process.  *bytes (if not NULL) is how much that was.  Safe beside calls of
+   other threads: memory in use is not touched.
+   Errors: TDS_E_DEVICE. */
+int tds_release_idle(uint64_t* bytes);
 
 /* Describe the index.  Errors: TDS_E_INVALID (NULL pointers). */
 int tds_index_info_get(const tds_index* index, tds_index_info* info);

@@ -573,6 +573,15 @@ class Server:
             pass
 
 
+def release_idle_memory() -> int:
+    """Give the current device's memory that the library keeps from closed
+    indexes for later ones (at most 1 GiB) back, e.g. for torch; the bytes."""
+    _current_stream()  # the device is torch's
+    n = ctypes.c_uint64()
+    check(load().tds_release_idle(ctypes.byref(n)), "tds_release_idle")
+    return int(n.value)
+
+
 def abi_version() -> int:
     return int(load().tds_abi_version())
 

@@ -94,6 +94,7 @@ SIGNATURES = {
     "tds_build_index": (ctypes.c_int, [ctypes.POINTER(tds_segments), ctypes.POINTER(tds_build_params),
                                        ctypes.c_void_p, ctypes.POINTER(ctypes.c_void_p)]),
     "tds_index_destroy": (ctypes.c_int, [ctypes.c_void_p]),
+    "tds_release_idle": (ctypes.c_int, [c_u64_p]),
     "tds_index_info_get": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(tds_index_info)]),
     "tds_index_export": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                         ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),

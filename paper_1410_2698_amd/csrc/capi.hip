@@ -43,6 +43,14 @@ int tds_index_destroy(tds_index* index) {
     return TDS_OK;
 }
 
+int tds_release_idle(uint64_t* bytes) {
+    if (bytes) *bytes = 0;
+    size_t n = 0;
+    const int st = tds::trim_blocks(&n);
+    if (st == TDS_OK && bytes) *bytes = n;
+    return st;
+}
+
 int tds_index_info_get(const tds_index* index, tds_index_info* info) {
     if (!index || !info) return TDS_E_INVALID;
     info->n = index->n;

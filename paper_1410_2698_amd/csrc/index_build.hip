@@ -360,16 +360,16 @@ void release_block(DeviceBlock* b) {
     *b = DeviceBlock();
 }
 
-bool trim_blocks() {
+int trim_blocks(size_t* bytes) {
+    *bytes = 0;
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
+    TDS_HIP(hipGetDevice(&dev));
     DeviceBlock out;
-    bool any = false;
     while (block_pool().take_past(dev, 0, &out)) {
         dfree(out.p);
-        any = true;
+        *bytes += out.bytes;
     }
-    return any;
+    return TDS_OK;
 }
 
 int validate_segments_args(const tds_segments* S) {

@@ -338,7 +338,7 @@ struct DeviceGuard {
 // a build of a million entries.  At most kPoolBytes of a
 // device stay allocated while nothing uses them, the most recently released
 // ones, and all of them go back when an allocation of the library finds no
-// memory.  Safe with several threads and streams: a block is only offered again
+// memory or the caller asks for it (tds_release_idle).  Safe with several threads and streams: a block is only offered again
 // after the device has finished all work, as with hipFree.
 // The list of idle blocks has kPoolBlocks places (of all devices), so that
 // giving one back needs no host memory: it happens in destructors and in C
@@ -347,14 +347,15 @@ constexpr size_t kPoolBytes = size_t(1) << 30;
 constexpr size_t kPoolBlocks = 256;
 int acquire_block(size_t bytes, DeviceBlock* b);  // on the current device
 void release_block(DeviceBlock* b);
-bool trim_blocks();  // the current device's idle blocks; true if there were any
+int trim_blocks(size_t* bytes);  // frees the current device's idle blocks
 
 template <typename T>
 int dmalloc(T** p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
     hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
-    if (e == hipErrorOutOfMemory && trim_blocks())
+    size_t idle = 0;
+    if (e == hipErrorOutOfMemory && trim_blocks(&idle) == TDS_OK && idle)
         e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
     if (e != hipSuccess) {
         (void)hipGetLastError();

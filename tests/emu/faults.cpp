@@ -11,6 +11,9 @@
 //   faults pinned  a search, a batch and a begun search of host arrays where the
 //       index has a workspace and there is no more pinned memory: their statuses and
 //       whether each found what it finds with it
+//   faults trim    device allocations left after an index was closed, bytes given
+//       back, allocations left then; the status of a build in a device that is full
+//       but for idle blocks
 //   faults grid    each copy of a grid search of device arrays fails in turn: the
 //       same three numbers
 #include <cstdio>
@@ -150,7 +153,8 @@ int run_pools() {
     tds::DeviceBlock again;
     if (tds::acquire_block(3 << 20, &again) != TDS_OK) return 4;
     tds::release_block(&again);
-    tds::trim_blocks();
+    size_t freed = 0;
+    if (tds::trim_blocks(&freed) != TDS_OK || freed == 0) return 4;
     for (auto* p : pins) tds::release_pin(p);
     emu_faults.news = false;
     if (emu_faults.live != 0) return 5;  // all blocks were freed
@@ -201,6 +205,30 @@ int run_pinned() {
     }
     tds::destroy_index(idx);
     printf("\n");
+    return 0;
+}
+
+int run_trim() {
+    const Segs D(200, 1), Q(70, 2), large(90000, 3);
+    std::vector<tds_result> out(20000);
+    const auto search_and_close = [&] {
+        tds_index* idx = build(D);
+        uint64_t n = 0;
+        const int st = call("search", idx, Q, out, &n);
+        tds::destroy_index(idx);
+        return st == TDS_OK && n;
+    };
+    if (!search_and_close()) return 3;
+    const long left = emu_faults.live;
+    size_t freed = 0;
+    if (tds::trim_blocks(&freed) != TDS_OK) return 3;
+    printf("%ld %zu %ld ", left, freed, emu_faults.live);
+    if (!search_and_close()) return 3;
+    emu_faults.most = emu_faults.live;  // only what the idle blocks make room for
+    tds_build_params bp{};
+    bp.num_bins = 2;
+    tds_index* idx = nullptr;
+    printf("%d\n", tds::build_impl(&large.s, &bp, nullptr, &idx));
     return 0;
 }
 
@@ -276,6 +304,7 @@ int main(int argc, char** argv) {
     if (mode == "waits" && argc > 2) return run_waits(argv[2]);
     if (mode == "pools") return run_pools();
     if (mode == "pinned") return run_pinned();
+    if (mode == "trim") return run_trim();
     if (mode == "merge") return run_merge();
     if (mode == "grid") return run_grid();
     return 2;

@@ -14,6 +14,7 @@ struct EmuFaults {
     long copies = 0;                 // copies queued
     bool news = false;               // operator new fails
     bool news_after_wait = false;    // from the next wait for a stream on
+    long most = -1;                  // device allocations at most, if >= 0
     long live = 0;                   // device allocations not freed
 };
 inline EmuFaults emu_faults;
@@ -28,7 +29,8 @@ inline bool emu_fails(long& left) {
     return true;
 }
 inline hipError_t emu_hipMalloc(void** p, size_t n) {
-    if (emu_fails(emu_faults.mallocs)) {
+    const bool full = emu_faults.most >= 0 && emu_faults.live >= emu_faults.most;
+    if (full || emu_fails(emu_faults.mallocs)) {
         *p = nullptr;
         return hipErrorOutOfMemory;
     }

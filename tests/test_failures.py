@@ -69,3 +69,12 @@ def test_searches_without_pinned_memory(faults):
     """The pinned block only saves copies: without one the arrays are copied as
     they are."""
     assert faults("pinned") == [0, 1] * 3
+
+
+def test_idle_blocks_go_back(faults):
+    """Closed indexes leave device blocks to the next; all of them go back when
+    asked for, and when an allocation finds no memory."""
+    left, freed, left_then, status = faults("trim")
+    assert left > 0 and freed >= left << 21
+    assert left_then == 0
+    assert status == 0
