@@ -29,6 +29,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
@@ -1466,6 +1467,45 @@ __device__ __forceinline__ Cand load_cand(const DistArgs& A, const ItemState& S,
     return {e.cx, e.cy, e.cz, e.r, valid ? e.ts : INFINITY, valid ? e.te : -INFINITY, v};
 }
 
+// Without block boxes: the first query of mask mk (not 0) that has lanes whose
+// candidate passes its sphere test and, with kTime, its time test: its number in
+// j, those lanes as the result; 0 if no query has.  Takes it and those before it
+// from mk.
+//
+// A block's entries lie anywhere, most queries have no survivors among them, and
+// then this loop is all that a query costs.  Two at a time: their records are
+// read together, and the loop's scalar steps are shared (the last one alone is
+// taken twice).  200,000 uniform segments on the temporal layout: kernel 267 us
+// with the older walk, a copy of the code per combination of time test and
+// partial ranges, 447 with the one-query steps that block boxes take, 303 so.  With
+// block boxes most queries that are left have survivors, and the second test is
+// in vain (a search of two particle sets close by: 2,441 -> 2,642 us).
+template <bool kTime>
+__device__ __forceinline__ uint64_t next_query(const WaveLDS& L, const Cand& c, uint64_t& mk,
+                                               uint32_t& j) {
+    for (;;) {
+        const uint64_t mk1 = mk & (mk - 1u), mk2 = mk1 & (mk1 - 1u);
+        const uint32_t j1 = (uint32_t)__builtin_ctzll(mk);
+        const uint32_t j2 = (uint32_t)__builtin_ctzll(mk1 ? mk1 : mk);
+        const QSphere q1 = L.qs[j1], q2 = L.qs[j2];
+        QTime t1 = {}, t2 = {};
+        if (kTime) {
+            t1 = L.qt[j1];
+            t2 = L.qt[j2];
+        }
+        uint64_t m1 = ballot(sphere_pass(q1.cx, q1.cy, q1.cz, q1.R, c.cx, c.cy, c.cz, c.r));
+        uint64_t m2 = ballot(sphere_pass(q2.cx, q2.cy, q2.cz, q2.R, c.cx, c.cy, c.cz, c.r));
+        if (kTime) {
+            m1 &= ballot(t1.a < c.te) & ballot(c.ts < t1.b);
+            m2 &= ballot(t2.a < c.te) & ballot(c.ts < t2.b);
+        }
+        mk = m1 ? mk1 : mk2;
+        j = m1 ? j1 : j2;
+        m1 = m1 ? m1 : m2;
+        if (m1 || !mk) return m1;
+    }
+}
+
 // Takes queued pairs on while a queue holds at least `from` of them (64 inside
 // an item, 1 at its end): refinement, then FP64 evaluation.
 __device__ __forceinline__ void take_queued(WaveLDS& L, ItemState& S, const DistArgs& A,
@@ -1506,12 +1546,11 @@ __device__ __forceinline__ void take_queued(WaveLDS& L, ItemState& S, const Dist
 // evaluations, 1577 -> 904 us; the same overlapping, 171 million, 6507 -> 4438;
 // 1 M uniform segments in a batch 145 -> 148; 89 k evaluations of a self-join
 // of 1 M, 240 -> 231; 8000 items of dense walks 165 -> 143.
-template <int kCpl, int kRef>
+template <int kCpl, int kRef, bool kCull>
 __device__ __forceinline__ void scan_chunk_fp32(WaveLDS& L, const DistArgs& A, ItemState& S,
                                                 const Box32& qbox, uint32_t qlo, uint32_t qhi,
                                                 bool uni, bool all_overlap) {
     const uint32_t lane = __lane_id();
-    const bool cull = A.I.bbox != nullptr;
     const uint64_t has_mask = ~0ull >> (kWave - S.nq);
     const uint32_t blk0 = S.c0 >> kBoxShift, blk1 = (S.c1 - 1) >> kBoxShift;
     Box32 wbox = {};  // box of block wb + lane
@@ -1521,7 +1560,7 @@ __device__ __forceinline__ void scan_chunk_fp32(WaveLDS& L, const DistArgs& A, I
 #pragma unroll
         for (int k = 0; k < kCpl; ++k)
             tc[k] = load_cand<kRef != TDS_REFINE_QUEUED>(A, S, tile + k);
-        if (cull && tile + kCpl - 1 - wb >= kWave) {
+        if (kCull && tile + kCpl - 1 - wb >= kWave) {
             wb = tile;
             wbox = A.I.bbox[min(wb + lane, blk1)].b;
         }
@@ -1535,7 +1574,7 @@ __device__ __forceinline__ void scan_chunk_fp32(WaveLDS& L, const DistArgs& A, I
                 mk &= ballot(qlo < b0 + kWave) & ballot(qhi > b0);
                 part = mk & ~(ballot(qlo <= b0) & ballot(qhi >= b0 + kWave));
             }
-            if (cull && mk) {
+            if (kCull && mk) {
                 const uint32_t l = blk - wb;
                 const Box32 box = {lane_val(wbox.lx, l), lane_val(wbox.ly, l),
                                    lane_val(wbox.lz, l), lane_val(wbox.hx, l),
@@ -1559,13 +1598,19 @@ __device__ __forceinline__ void scan_chunk_fp32(WaveLDS& L, const DistArgs& A, I
             const ERef ex = eref_of(c.cx, c.cy, c.cz, c.r, c.v, c.ts, c.te);
             for (;;) {
                 while (mk && max(S.qn, S.rqn) < kWave) {
-                    const uint32_t j = (uint32_t)__builtin_ctzll(mk);
-                    mk &= mk - 1u;
-                    const QSphere q = L.qs[j];
-                    uint64_t m = ballot(sphere_pass(q.cx, q.cy, q.cz, q.R, c.cx, c.cy, c.cz, c.r));
-                    if (timed) {
-                        const QTime t = L.qt[j];
-                        m &= ballot(t.a < c.te) & ballot(c.ts < t.b);
+                    uint32_t j;
+                    uint64_t m;
+                    if (!kCull) {
+                        m = timed ? next_query<true>(L, c, mk, j) : next_query<false>(L, c, mk, j);
+                    } else {
+                        j = (uint32_t)__builtin_ctzll(mk);
+                        mk &= mk - 1u;
+                        const QSphere q = L.qs[j];
+                        m = ballot(sphere_pass(q.cx, q.cy, q.cz, q.R, c.cx, c.cy, c.cz, c.r));
+                        if (timed) {
+                            const QTime t = L.qt[j];
+                            m &= ballot(t.a < c.te) & ballot(c.ts < t.b);
+                        }
                     }
                     if ((part >> j) & 1ull) {
                         const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)qlo, (int)j);
@@ -1617,7 +1662,7 @@ __device__ __forceinline__ void scan_chunk_fp64(WaveLDS& L, const DistArgs& A, I
     wave_sync();
 }
 
-template <int kPrec, int kCplT, int kRef>
+template <int kPrec, int kCplT, int kRef, bool kCull>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_distance(DistArgs A) {
     __shared__ WaveLDS wl[kWavesPerBlock];
     const uint32_t wid = uniform(threadIdx.x / kWave);
@@ -1788,7 +1833,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
         wave_sync();
         if (kPrec == TDS_PREC_FP32_RECHECK)
-            scan_chunk_fp32<kCplT, kRef>(
+            scan_chunk_fp32<kCplT, kRef, kCull>(
                 L, A, S, f.box, f.lo, f.hi, all_cover,
                 (ballot((double)f.a32 < bi.tmin_te) & ballot(bi.tmax_ts < (double)f.b32)) == ~0ull);
         else scan_chunk_fp64(L, A, S, e.c, f.lo, f.hi, all_cover);
@@ -2271,10 +2316,13 @@ int launch_distance(int prec, const DistArgs& A, uint32_t grid_waves, hipStream_
     if (!A.stage || A.stage_cap < (uint32_t)kWave) return TDS_E_DEVICE;
     constexpr int F32 = TDS_PREC_FP32_RECHECK, Q = TDS_REFINE_QUEUED, N = TDS_REFINE_INLINE;
     void (*kern)(DistArgs);
-    const bool t2 = A.cpl == 2;
-    if (prec == TDS_PREC_FP64) kern = k_distance<TDS_PREC_FP64, 2, Q>;
-    else if (A.refine == Q) kern = t2 ? k_distance<F32, 2, Q> : k_distance<F32, 4, Q>;
-    else kern = t2 ? k_distance<F32, 2, N> : k_distance<F32, 4, N>;
+    const auto fp32 = [&](auto cull) -> void (*)(DistArgs) {
+        constexpr bool C = decltype(cull)::value;
+        if (A.refine == Q) return A.cpl == 2 ? k_distance<F32, 2, Q, C> : k_distance<F32, 4, Q, C>;
+        return A.cpl == 2 ? k_distance<F32, 2, N, C> : k_distance<F32, 4, N, C>;
+    };
+    if (prec == TDS_PREC_FP64) kern = k_distance<TDS_PREC_FP64, 2, Q, false>;
+    else kern = A.I.bbox ? fp32(std::true_type()) : fp32(std::false_type());
     if (ev_begin && ev_end) {
         // the events take the dispatch's own start and end times (no marker
         // packets around the kernel, so no bubbles before and after it)
