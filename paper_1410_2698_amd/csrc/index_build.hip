@@ -478,8 +478,8 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
         }
     }
     uint32_t m = req_bins;
+    const double mean = dsum / (double)n;
     if (m == 0) {
-        const double mean = dsum / (double)n;
         double mm = std::nearbyint((tmax - tmin) / mean);
         if (!(mm >= 1.0)) mm = 1.0;
         if (mm > (double)kMaxBins) mm = (double)kMaxBins;
@@ -517,6 +517,7 @@ int build_impl(const tds_segments* D, const tds_build_params* p, hipStream_t str
     idx->t_min = tmin;
     idx->t_max = tmax;
     idx->bw = bw;
+    idx->mean_dt = mean;
     idx->layout = layout;
     const uint32_t nblk = ceil_div(n, 1u << kBoxShift);
     DeviceArena arrays;

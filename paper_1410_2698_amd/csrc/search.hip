@@ -421,6 +421,10 @@ __device__ inline void bucket_range(uint32_t b, uint32_t shift, uint32_t m,
 // them if none does: a search of few items leaves most waves idle while each
 // of the others walks its whole chunk.  Each halving at most doubles that
 // count, so a smaller chunk than the first never makes 2 target items or more.
+//
+// Where most items have mixed times (`mixed`, or their bucket spans several bins),
+// the chunk is not halved again either where that takes them from at most `fit`
+// to more (see item_fit).
 __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_count,
                                                       const uint32_t* __restrict__ b_hi,
                                                       const uint32_t* __restrict__ bin_first,
@@ -429,15 +433,17 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
                                                       uint32_t m, uint32_t shift,
                                                       uint32_t nb, uint32_t nparts, uint32_t chunk,
                                                       uint32_t levels, uint32_t target,
+                                                      uint32_t fit, uint32_t mixed,
                                                       uint32_t* __restrict__ b_start,
                                                       uint32_t* __restrict__ b_nch,
                                                       BucketInfo* __restrict__ binfo,
                                                       SearchHeader* hdr) {
     __shared__ uint32_t s_cnt[kPartedBuckets], s_hi[kPartedBuckets];
-    __shared__ uint32_t s_n0[kChunkLevels];
+    __shared__ uint32_t s_n0[kChunkLevels], s_mixed;
     __shared__ uint32_t s_c[1024 / kWave], s_i[1024 / kWave];
     const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = tid / kWave;
     if (tid < kChunkLevels) s_n0[tid] = 0;
+    if (tid == 0) s_mixed = 0;
     if (nparts == kCountParts) {
         // bucket totals and range maxima of the parts (nb <= kPartedBuckets),
         // each part's count replaced by its first slot in the bucket;
@@ -467,7 +473,7 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
         // chunk is a power of two; sums capped at the target, so that the
         // block's total fits 32 bits
         const uint32_t lg = (uint32_t)__builtin_ctz(chunk);
-        uint32_t n0[kChunkLevels] = {};
+        uint32_t n0[kChunkLevels] = {}, nm = 0;
         for (uint32_t b = b0; b < b1; ++b) {
             const uint32_t cnt = nparts == kCountParts ? s_cnt[b] : b_count[b];
             if (!cnt) continue;
@@ -480,16 +486,21 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
                 const uint64_t n = (uint64_t)((cnt + kWave - 1) / kWave) *
                                    ((len + (chunk >> l) - 1) >> (lg - l));
                 n0[l] = (uint32_t)min(n0[l] + n, (uint64_t)target);
+                if (l == 0 && (mixed || shift || b % kSpanClasses))
+                    nm = (uint32_t)min(nm + n, (uint64_t)target);
             }
         }
+        nm = wave_scan(nm);
+        if (lane == kWave - 1 && nm) atomicAdd(&s_mixed, nm);
 #pragma unroll
         for (uint32_t l = 0; l < kChunkLevels; ++l) {
             const uint32_t sum = wave_scan(n0[l]);
             if (lane == kWave - 1 && sum) atomicAdd(&s_n0[l], sum);
         }
         __syncthreads();
+        if (2 * s_mixed <= s_n0[0]) fit = 0;
         uint32_t l = 0;
-        while (l + 1 < levels && s_n0[l] < target) ++l;
+        while (l + 1 < levels && s_n0[l] < target && !(l && s_n0[l] <= fit && s_n0[l + 1] > fit)) ++l;
         chunk >>= l;
     }
     // the record of each bucket (all but its offsets), then the offsets after
@@ -2133,6 +2144,20 @@ uint32_t item_target(uint32_t grid_waves) {
     return launch_blocks(grid_waves) * kWavesPerBlock * 3 / 2;
 }
 
+// Items that every wave has one of.  Where the entries of a bucket begin and end at
+// times of their own, or a bin is much wider than a segment is long, most of an
+// item's pairs fail the time test, items are light and alike, and a second round of
+// smaller ones costs more than it evens out: walks with start times of their own,
+// call at 2829, 5150 and 9786 items 163, 190 and 199 us, at 3071 and 6043 101 and
+// 123 (but the first halving is made: 2833, 5420 and 10208 items 151, 144 and 150);
+// 40 trajectories in 19 bins, kernel at 858, 1716, 3432 and 6798 items 38, 36, 32
+// and 55.  Where all the entries of a bin share its times the items may be as
+// uneven as space is: stars near 60 others at 3724 and 7429 items 650 and 464.  The
+// FP64 form's items are long, and of one kind.
+uint32_t item_fit(int prec, uint32_t grid_waves) {
+    return prec == TDS_PREC_FP64 ? 0u : launch_blocks(grid_waves) * kWavesPerBlock;
+}
+
 // Upper bound of the work items of a batch of nq query segments: every
 // non-empty bucket contributes ceil(count / 64) groups, each split into at
 // most ceil((n + 63) / chunk) chunks (chunks count from a 64-entry block).
@@ -2382,6 +2407,7 @@ int enqueue_pipeline(const tds_index* idx, Workspace* w, const QueryView& Q, siz
     hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, s, w->b_count, w->b_hi,
                        idx->bin_first, idx->min_te, idx->max_ts, idx->m, shift, nb, nparts,
                        chunk & ~kChunkAuto, chunk_levels(prec, chunk), item_target(grid_waves),
+                       item_fit(prec, grid_waves), idx->bw > 1.5 * idx->mean_dt ? 1u : 0u,
                        w->b_start, w->b_nch, w->binfo, w->hdr);
     hipLaunchKernelGGL(k_scatter, dim3(qblocks + nb), dim3(kBlock), 0, s, w->desc, w->qkey,
                        w->qslot, w->b_start, w->b_count, nb, bpp, qblocks, w->qsorted, w->binfo,

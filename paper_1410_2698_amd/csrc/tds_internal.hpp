@@ -245,6 +245,7 @@ struct tds_index {
     uint64_t n = 0;
     uint32_t m = 0;
     double t_min = 0, t_max = 0, bw = 0;
+    double mean_dt = 0;            // mean duration of the entries
     tds::EntryF64* e64 = nullptr;
     tds::EntryF32* e32 = nullptr;
     tds::EntryV32* ev32 = nullptr; // FP32 velocity and mid time (refinement of the filter)
