@@ -206,10 +206,10 @@ typedef struct tds_stats {
     uint64_t fp64_evals;      /* pairs evaluated by the canonical FP64 code */
     uint64_t results;         /* result records found (may exceed the capacity) */
     uint32_t passes;          /* distance-kernel launches (> 1: incremental) */
-    uint32_t stage_flushes;   /* first pass, staged output: work items whose results
-                                 were reserved and written at the item's end (one
-                                 device-scope atomic per request in the item); direct
-                                 output: reservations that hold results */
+    uint32_t stage_flushes;   /* first pass, staged output: waves with results left
+                                 to write at their end (up to 64 requests), or work
+                                 items whose results were written at the item's end;
+                                 direct output: reservations that hold results */
     double kernel_ms;         /* distance kernel(s), measured with HIP events */
     double total_ms;          /* whole call, host wall clock */
     uint64_t filter_tests;    /* pairs put through the FP32 filter (FP32 form) or the

@@ -973,7 +973,7 @@ __global__ __launch_bounds__(1024) void k_fill(const Request* __restrict__ req,
 struct DistArgs {
     IndexView I;
     uint32_t self;           // self-join (see QueryView)
-    uint32_t one;            // one request
+    uint32_t keep;           // results stay staged from item to item (at most 64 requests)
     const uint32_t* qsorted; // query segments in bucket order
     const QF32* qf;          // their records in query order
     const QEval* qev;
@@ -991,7 +991,7 @@ struct DistArgs {
     uint32_t item_end;      // 0xFFFFFFFF: every item of the search
     uint32_t* item_count;   // results per work item, or nullptr
     tds_result* stage;      // per-wave result stages, stage_cap records each
-    uint32_t* stage_meta;   // group lane | index among the slot's staged results << 6
+    uint32_t* stage_meta;   // slot | index among the slot's staged results << 6
     uint32_t stage_cap;     // records per wave (a multiple of 64)
     uint32_t by_order;      // 1: a single-request item run whose results go to
                             // their order in the item (minus win_lo), no stage
@@ -1033,13 +1033,20 @@ struct QRef {
 static_assert(sizeof(QRef) == 32, "QRef layout");
 
 // Results go through a stage of stage_cap records per wave in device memory
-// and get their output positions when the stage is flushed (when the next
-// batch of evaluations might not fit, and at the end of every work item):
-// one device-scope atomic per request present in the item's query group
-// reserves exactly the staged results of that request.  A returning atomic
-// that every wave directs at its request's counter serialises across the
-// chip; one per 64 evaluations cost a search with 10^8 results most of its
-// time.  Positions within a request are unique and dense, in no fixed order.
+// and get their output positions when the stage is flushed: one device-scope
+// atomic per request slot with staged results reserves exactly their number.  A
+// returning atomic that every wave directs at its request's counter serialises
+// across the chip, 14 ns each: one per 64 evaluations cost a search with 10^8
+// results most of its time.  Positions within a request are unique and dense, in
+// no fixed order.
+//
+// With up to 64 requests (keep) slot r is request r and results stay staged from
+// item to item, until the next batch of evaluations might not fit or the wave has
+// no more items; then the workgroup's waves reserve together.  Flushed at the end
+// of every item, 10,000 items of dense walks took 142 us, 124 in a batch of three
+// requests, of which 65 are the walk.  With more requests a slot is the
+// first query of the group with the same request, which the next group shares
+// nothing with: flushed at the end of every item.
 //
 // With by_order set (one request, one work item, re-run to fill successive
 // windows of the host's buffer), a result's position is instead its order
@@ -1094,7 +1101,7 @@ struct ItemState {
     uint32_t nres;
     // per lane j of the group
     uint32_t qr;      // request of query j
-    uint32_t rslot;   // its request slot: the first lane with the same request
+    uint32_t rslot;   // its request slot (see DistArgs)
     uint32_t rcnt;    // staged results of request slot j (slot lanes only)
 };
 
@@ -1111,32 +1118,27 @@ __device__ inline void wave_sync_mem() {
 // flight together).
 constexpr int kFlushUnroll = 2;
 
-// Reserves the staged results of every request slot (one atomic each) and
-// copies them from the stage to their positions; the stage is then empty.
-// Slot lane s learns where its request's results go: staged result k of the
-// slot has request position base + k and is kept when that position falls
-// in the window [win_lo, win_lo + out_capacity), at out[dst + k].  The copy
-// then reads kFlushUnroll records per lane before it writes any, so a flush
-// waits for about one memory round trip per 256 records.
-__device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A0, ItemState& S) {
+// Copies the wave's nst staged results to their positions.  Slot lane s knows
+// where its results go: the n staged results of the slot have positions base + k of
+// request r, and k is kept when that falls in the window [win_lo, win_lo +
+// out_capacity), at out[dst + k].  The copy reads kFlushUnroll records per lane
+// before it writes any, so it waits for about one memory round trip per 128
+// records.
+__device__ __forceinline__ void stage_copy(const ArgsPtr A, uint64_t sbase, uint32_t nst,
+                                           uint32_t r, uint32_t n, uint64_t base) {
     const uint32_t lane = fresh_lane();
-    const ArgsPtr A = cold_args(A0);
-    wave_sync_mem();
     int64_t dst = 0;
     uint32_t klo = 0, khi = 0;  // kept staged results of slot `lane`: [klo, khi)
-    if (S.rcnt) {
-        const uint64_t base =
-            (uint64_t)atomicAdd(&A->rc[S.qr].count, (unsigned long long)S.rcnt);
-        const Request& R = A->req[S.qr];
-        const uint64_t w0 = A->win_lo, w1 = A->win_lo + R.out_capacity, n = S.rcnt;
-        klo = (uint32_t)min(max(w0, base) - base, n);
-        khi = (uint32_t)min(max(w1, base) - base, n);
+    if (n) {
+        const Request& R = A->req[r];
+        const uint64_t w0 = A->win_lo, w1 = A->win_lo + R.out_capacity, nn = n;
+        klo = (uint32_t)min(max(w0, base) - base, nn);
+        khi = (uint32_t)min(max(w1, base) - base, nn);
         dst = (int64_t)R.out_offset + (int64_t)base - (int64_t)A->win_lo;
     }
-    S.rcnt = 0;
     // (nothing to copy once the output is full)
-    const uint32_t nst = ballot(klo < khi) ? S.nst : 0u;
-    for (uint32_t p0 = 0; p0 < nst; p0 += kFlushUnroll * kWave) {
+    const uint32_t end = ballot(klo < khi) ? nst : 0u;
+    for (uint32_t p0 = 0; p0 < end; p0 += kFlushUnroll * kWave) {
         uint32_t meta[kFlushUnroll];
         uint4 ra[kFlushUnroll], rb[kFlushUnroll];
 #pragma unroll
@@ -1144,9 +1146,9 @@ __device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A0, Item
             const uint32_t p = p0 + u * kWave + lane;
             meta[u] = 0xFFFFFFFFu;  // no record (a real one is below 2^17)
             ra[u] = rb[u] = make_uint4(0u, 0u, 0u, 0u);
-            if (p < S.nst) {
-                meta[u] = A->stage_meta[S.sbase + p];
-                const uint4* src = reinterpret_cast<const uint4*>(A->stage + S.sbase + p);
+            if (p < nst) {
+                meta[u] = A->stage_meta[sbase + p];
+                const uint4* src = reinterpret_cast<const uint4*>(A->stage + sbase + p);
                 ra[u] = src[0];
                 rb[u] = src[1];
             }
@@ -1154,9 +1156,8 @@ __device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A0, Item
 #pragma unroll
         for (int u = 0; u < kFlushUnroll; ++u) {
             // every lane takes part in the shuffles
-            const uint32_t ql = meta[u] & (kWave - 1);
+            const uint32_t slot = meta[u] & (kWave - 1);
             const uint32_t k = (meta[u] >> 6) & 0x3FFFFFFu;
-            const uint32_t slot = (uint32_t)__shfl((int)S.rslot, (int)ql);
             const int64_t d = __shfl((long long)dst, (int)slot);
             const uint32_t lo = (uint32_t)__shfl((int)klo, (int)slot);
             const uint32_t hi = (uint32_t)__shfl((int)khi, (int)slot);
@@ -1168,6 +1169,19 @@ __device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A0, Item
             rejoin();
         }
     }
+}
+
+// Reserves the staged results of every request slot (one atomic each) and
+// copies them from the stage to their positions; the stage is then empty.
+__device__ __forceinline__ void stage_flush(WaveLDS& L, const DistArgs& A0, ItemState& S) {
+    const uint32_t lane = fresh_lane();
+    const ArgsPtr A = cold_args(A0);
+    wave_sync_mem();
+    const uint32_t r = A->keep ? lane : S.qr;
+    uint64_t base = 0;
+    if (S.rcnt) base = (uint64_t)atomicAdd(&A->rc[r].count, (unsigned long long)S.rcnt);
+    stage_copy(A, S.sbase, S.nst, r, S.rcnt, base);
+    S.rcnt = 0;
     S.nst = 0;
     wave_sync_mem();
 }
@@ -1274,7 +1288,7 @@ __device__ __forceinline__ void drain(WaveLDS& L, ItemState& S, const DistArgs& 
     }
     if (hit) {
         A->stage[S.sbase + S.nst + rank] = rec;
-        A->stage_meta[S.sbase + S.nst + rank] = ql | (idx << 6);
+        A->stage_meta[S.sbase + S.nst + rank] = slot | (idx << 6);
     }
     rejoin();
     S.nst += nhit;
@@ -1700,6 +1714,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint64_t dpos = dfirst, dend = dfirst + A.dir_chunk;
     uint32_t dg = 1;
     uint64_t found_total = 0;
+    uint32_t nst = 0, rcnt = 0;  // what stays staged between items (keep)
     // all items of the search, unless a range is given (incremental passes)
     const uint32_t item_end = (A.item_end == 0xFFFFFFFFu)
                                   ? uniform(min(A.hdr->n_items, A.desc->item_cap))
@@ -1823,7 +1838,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         S.rqn = 0;
         S.evals = 0;
         S.found = 0;
-        S.nst = 0;
+        S.nst = nst;
         S.ftests = 0;
         S.btests = 0;
         S.dpos = dpos;
@@ -1846,8 +1861,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         // does every query of the group cover the whole chunk?
         const bool all_cover = ballot(f.lo <= S.c0 && f.hi >= S.c1) == ~0ull;
         S.qr = f.req;
-        S.rslot = A.one ? 0u : request_slots(has, f.req);
-        S.rcnt = 0;
+        S.rslot = A.keep ? f.req : request_slots(has, f.req);
+        S.rcnt = rcnt;
         wave_sync();
         L.qe[lane] = e;
         if (kPrec == TDS_PREC_FP32_RECHECK) {
@@ -1866,9 +1881,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             rejoin();
             asked = true;
         }
-        // the item's results get their positions (the next item's group has
-        // other request slots)
-        if (S.nst) {
+        // the item's results get their positions where the next item's group has
+        // other request slots
+        if (A.keep) {
+            nst = S.nst;
+            rcnt = S.rcnt;
+        } else if (S.nst) {
             stage_flush(L, A, S);
             ++flushes;
         }
@@ -1897,6 +1915,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             pack_last((dend - size) / A.dir_chunk, dg, size - (uint32_t)(dend - dpos));
         if (A.dir_count && found_total)
             atomicAdd(&A.rc[0].count, (unsigned long long)found_total);
+    }
+    if (A.keep && !A.direct && !A.by_order) {
+        // what the workgroup's waves still have staged: lane r adds up request r's
+        // results, and one wave reserves for all
+        if (nst) ++flushes;
+        wave_sync();
+        L.queue[lane] = rcnt;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+        for (uint32_t w = 0; w < (uint32_t)kWavesPerBlock; ++w) {
+            const uint32_t c = wl[w].queue[lane];
+            before += w < wid ? c : 0u;
+            all += c;
+        }
+        unsigned long long* s_base = reinterpret_cast<unsigned long long*>(wl[0].rq);
+        if (wid == 0) {
+            unsigned long long base = 0;
+            if (all) base = atomicAdd(&A.rc[lane].count, (unsigned long long)all);
+            s_base[lane] = base;
+        }
+        __syncthreads();
+        wave_sync_mem();
+        stage_copy(cold_args(A), sbase, nst, lane, rcnt, s_base[lane] + before);
     }
     // the first reservation counts as one that was made, once it holds a result
     if (A.direct && !(dpos == dfirst)) ++flushes;
@@ -2299,7 +2340,7 @@ uint32_t direct_chunk(uint32_t stage_cap) {
 
 DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q, tds_result* out,
                    uint64_t win_lo, uint32_t item_begin, uint32_t item_end, uint32_t* item_count,
-                   uint32_t grid_waves, bool by_order, uint32_t cpl, bool one,
+                   uint32_t grid_waves, bool by_order, uint32_t cpl, uint32_t r_cap,
                    bool direct = false) {
     DistArgs A;
     A.cpl = cpl & 0xFFu;
@@ -2312,7 +2353,7 @@ DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q,
     A.by_order = by_order ? 1u : 0u;
     A.I = view_of(idx);
     A.self = Q.ent ? 1u : 0u;
-    A.one = one ? 1u : 0u;
+    A.keep = r_cap <= (uint32_t)kWave ? 1u : 0u;
     A.qsorted = w->qsorted;
     A.qf = w->qf;
     A.qev = w->qev;
@@ -2408,7 +2449,7 @@ int enqueue_pipeline(const tds_index* idx, Workspace* w, const QueryView& Q, siz
     const uint32_t nparts = count_parts(nb);
     const uint32_t zn = std::max(std::max(nb * nparts, r_cap), kCtrSlots * kCtrStride);
     const DistArgs A = dist_args(idx, w, Q, out, 0, 0, 0xFFFFFFFFu, item_count, grid_waves, false,
-                                 cpl, r_cap == 1, direct);
+                                 cpl, r_cap, direct);
     // k_zero also clears the request counters the distance kernel appends with
     hipLaunchKernelGGL(k_zero, dim3(ceil_div(zn, kBlock)), dim3(kBlock), 0, s, w->hdr, w->b_count,
                        w->b_hi, nb, nparts, w->req_ctr, r_cap, w->dyn_ctr,
@@ -2442,7 +2483,7 @@ int enqueue_range(const tds_index* idx, Workspace* w, const QueryView& Q, int pr
                        dim3(256), 0, s, w->req_ctr, r_cap, w->dyn_ctr);
     TDS_HIP(hipGetLastError());
     const DistArgs A = dist_args(idx, w, Q, out, win_lo, i0, i1, nullptr, grid_waves, by_order,
-                                 cpl, r_cap == 1);
+                                 cpl, r_cap);
     TDS_TRY(launch_distance(prec, A, grid_waves, s, ev_begin, ev_end));
     return launch_finish(A, w, grid_waves, s);
 }
