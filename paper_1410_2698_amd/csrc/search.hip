@@ -1003,7 +1003,8 @@ struct DistArgs {
     uint32_t direct;
     uint32_t dir_chunk;
     uint32_t dir_max;       // most chunks of one reservation
-    uint32_t dir_count;     // the waves add their results to the request's counter
+    uint32_t dir_given;     // every wave starts with the chunk of its number (k_fill); else
+                            // with none, and adds its results to the request's counter
     unsigned long long* dir_ctr;  // next free position (reservation counter)
     tds_result* dscratch;   // positions [cap, cap + dscratch_cap) (the stage buffer)
     uint64_t dscratch_cap;
@@ -1056,7 +1057,9 @@ static_assert(sizeof(QRef) == 32, "QRef layout");
 // straight to consecutive positions of the request that it reserved, first the
 // dir_chunk positions of its own number, then twice as many chunks as the last
 // time, up to dir_max (one atomic per reservation; whole aligned chunks),
-// keeping its last reservation open from one item to the next.  At the end it
+// keeping its last reservation open from one item to the next.  In launches of more
+// than kFillWaves waves it reserves a chunk when it has results: most waves have
+// none, and the holes that their first chunks would leave took 10 to 24 us.  At the end it
 // may be partly used; positions at or past the output capacity go to a scratch
 // buffer.  A fill pass (k_fill, or k_fill_plan and k_fill_copy) then moves the
 // results found past the final count (or the capacity) into the unused tails
@@ -1709,9 +1712,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint64_t tests = 0, evals_total = 0, ftests = 0, btests = 0;
     uint32_t flushes = 0;  // stage flushes at the end of an item (direct output: reservations)
     // direct output (see DistArgs): the wave's open reservation, at first the
-    // chunk of its number
-    const uint64_t dfirst = (uint64_t)(blockIdx.x * kWavesPerBlock + wid) * A.dir_chunk;
-    uint64_t dpos = dfirst, dend = dfirst + A.dir_chunk;
+    // chunk of its number or none
+    const uint64_t dfirst =
+        A.dir_given ? (uint64_t)(blockIdx.x * kWavesPerBlock + wid) * A.dir_chunk : 0ull;
+    uint64_t dpos = dfirst, dend = dfirst + (A.dir_given ? A.dir_chunk : 0u);
     uint32_t dg = 1;
     uint64_t found_total = 0;
     uint32_t nst = 0, rcnt = 0;  // what stays staged between items (keep)
@@ -1908,12 +1912,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
     }
     if (A.direct && lane == 0) {
-        // the wave's last reservation and, where the fill does not count them,
-        // its results
+        // the wave's last reservation (~0: none) and, where the fill does not
+        // count them, its results
         const uint32_t size = dg * A.dir_chunk;
         A.dlast[blockIdx.x * kWavesPerBlock + wid] =
-            pack_last((dend - size) / A.dir_chunk, dg, size - (uint32_t)(dend - dpos));
-        if (A.dir_count && found_total)
+            dend ? pack_last((dend - size) / A.dir_chunk, dg, size - (uint32_t)(dend - dpos))
+                 : ~0ull;
+        if (!A.dir_given && found_total)
             atomicAdd(&A.rc[0].count, (unsigned long long)found_total);
     }
     if (A.keep && !A.direct && !A.by_order) {
@@ -1940,7 +1945,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         stage_copy(cold_args(A), sbase, nst, lane, rcnt, s_base[lane] + before);
     }
     // the first reservation counts as one that was made, once it holds a result
-    if (A.direct && !(dpos == dfirst)) ++flushes;
+    if (A.direct && A.dir_given && !(dpos == dfirst)) ++flushes;
     // per-workgroup counters (folded into the header by k_stats_fold), each
     // wave's in the front of its own LDS, which it no longer uses
     wave_sync();
@@ -2172,6 +2177,10 @@ int ws_reserve_stage(Workspace* w, uint32_t grid_waves) {
 
 namespace {
 
+// 4 waves per SIMD on all 256 CUs (the occupancy the distance kernel's register
+// use allows).
+constexpr uint32_t kDefaultWaves = 256 * 4 * 4;
+
 uint32_t bucket_shift(uint32_t m) {
     uint32_t shift = 0;
     while ((((uint64_t)m * kSpanClasses - 1) >> shift) >= kMaxBuckets) ++shift;
@@ -2180,6 +2189,13 @@ uint32_t bucket_shift(uint32_t m) {
 
 uint32_t bucket_count(uint32_t m) {
     return (uint32_t)((((uint64_t)m * kSpanClasses - 1) >> bucket_shift(m)) + 1);
+}
+
+// Waves of a launch that run at a time, at most those of the default grid: items
+// are not made for more (8,192 waves, dense walks: 172 us with chunks for 4,096, 236
+// with chunks for 8,192; uniform walks 166 and 212).
+uint32_t busy_waves(uint32_t grid_waves) {
+    return std::min(launch_blocks(grid_waves) * kWavesPerBlock, kDefaultWaves);
 }
 
 // Candidates per work item, chosen by the item count (k_bucket_scan): from
@@ -2195,7 +2211,7 @@ uint32_t chunk_levels(int prec, uint32_t chunk) {
     return prec == TDS_PREC_FP64 ? 3 : 4;
 }
 uint32_t item_target(uint32_t grid_waves) {
-    return launch_blocks(grid_waves) * kWavesPerBlock * 3 / 2;
+    return busy_waves(grid_waves) * 3 / 2;
 }
 
 // Items that every wave has one of.  Where the entries of a bucket begin and end at
@@ -2209,7 +2225,13 @@ uint32_t item_target(uint32_t grid_waves) {
 // uneven as space is: stars near 60 others at 3724 and 7429 items 650 and 464.  The
 // FP64 form's items are long, and of one kind.
 uint32_t item_fit(int prec, uint32_t grid_waves) {
-    return prec == TDS_PREC_FP64 ? 0u : launch_blocks(grid_waves) * kWavesPerBlock;
+    return prec == TDS_PREC_FP64 ? 0u : busy_waves(grid_waves);
+}
+// Whether that holds whatever the buckets: bins wider than segments, or more waves
+// than have a first reservation given (dense walks in 8,192 waves, kernel at 2,500
+// and 10,000 items 84 and 166 us).
+uint32_t fit_always(const tds_index* idx, uint32_t grid_waves) {
+    return idx->bw > 1.5 * idx->mean_dt || grid_waves > kFillWaves ? 1u : 0u;
 }
 
 // Upper bound of the work items of a batch of nq query segments: every
@@ -2237,10 +2259,8 @@ uint32_t resolve_chunk(int prec, uint32_t chunk) {
     return kChunkAuto | (prec == TDS_PREC_FP64 ? 512u : 4096u);
 }
 
-// Default: 4 waves per SIMD on all 256 CUs (the occupancy the distance
-// kernel's register use allows).
 uint32_t resolve_grid(uint32_t grid_waves) {
-    return std::min(grid_waves ? grid_waves : 256u * 4u * 4u, kMaxDistBlocks * kWavesPerBlock);
+    return std::min(grid_waves ? grid_waves : kDefaultWaves, kMaxDistBlocks * kWavesPerBlock);
 }
 
 // Waves of a distance-kernel launch of grid_waves (whole workgroups).
@@ -2379,7 +2399,7 @@ DistArgs dist_args(const tds_index* idx, const Workspace* w, const QueryView& Q,
     const bool small = waves <= kFillWaves;
     A.dir_chunk = small ? direct_chunk(A.stage_cap) : A.stage_cap;
     A.dir_max = small ? std::min(A.stage_cap / A.dir_chunk, kFillChunks / waves) : 1u;
-    A.dir_count = small ? 0u : 1u;
+    A.dir_given = small ? 1u : 0u;
     A.dir_ctr = w->dyn_ctr + (size_t)kCtrDirect * kCtrStride;
     A.dscratch = w->stage;
     A.dscratch_cap = (uint64_t)waves * A.stage_cap;
@@ -2417,7 +2437,7 @@ int launch_distance(int prec, const DistArgs& A, uint32_t grid_waves, hipStream_
 // the fill of the holes left by the waves' last reservations.
 int launch_finish(const DistArgs& A, const Workspace* w, uint32_t grid_waves, hipStream_t s) {
     const uint32_t blocks = launch_blocks(grid_waves), nw = blocks * kWavesPerBlock;
-    if (A.direct && !A.dir_count) {
+    if (A.direct && A.dir_given) {
         hipLaunchKernelGGL(k_fill, dim3(kFillBlocks + 1), dim3(1024), 0, s, A.req, A.rc, A.dir_ctr,
                            A.dlast, nw, A.dir_chunk, A.out, A.dscratch, A.bstats, blocks, A.hdr);
         TDS_HIP(hipGetLastError());
@@ -2453,7 +2473,9 @@ int enqueue_pipeline(const tds_index* idx, Workspace* w, const QueryView& Q, siz
     // k_zero also clears the request counters the distance kernel appends with
     hipLaunchKernelGGL(k_zero, dim3(ceil_div(zn, kBlock)), dim3(kBlock), 0, s, w->hdr, w->b_count,
                        w->b_hi, nb, nparts, w->req_ctr, r_cap, w->dyn_ctr,
-                       (unsigned long long)launch_blocks(grid_waves) * kWavesPerBlock * A.dir_chunk);
+                       A.dir_given ? (unsigned long long)launch_blocks(grid_waves) * kWavesPerBlock *
+                                         A.dir_chunk
+                                   : 0ull);
     const uint32_t qblocks = std::max(1u, ceil_div(q_grid, kBlock));
     const uint32_t bpp = ceil_div(qblocks, nparts);  // workgroup b counts in part b / bpp < nparts
     hipLaunchKernelGGL(k_qprep, dim3(qblocks), dim3(kBlock), 0, s, Q, w->desc, w->req, I, w->qf,
@@ -2461,8 +2483,7 @@ int enqueue_pipeline(const tds_index* idx, Workspace* w, const QueryView& Q, siz
     hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, s, w->b_count, w->b_hi,
                        idx->bin_first, idx->min_te, idx->max_ts, idx->m, shift, nb, nparts,
                        chunk & ~kChunkAuto, chunk_levels(prec, chunk), item_target(grid_waves),
-                       item_fit(prec, grid_waves), idx->bw > 1.5 * idx->mean_dt ? 1u : 0u,
-                       w->b_start, w->b_nch, w->binfo, w->hdr);
+                       item_fit(prec, grid_waves), fit_always(idx, grid_waves), w->b_start, w->b_nch, w->binfo, w->hdr);
     hipLaunchKernelGGL(k_scatter, dim3(qblocks + nb), dim3(kBlock), 0, s, w->desc, w->qkey,
                        w->qslot, w->b_start, w->b_count, nb, bpp, qblocks, w->qsorted, w->binfo,
                        w->item_bucket, w->hdr);
