@@ -1097,6 +1097,8 @@ struct ItemState {
     uint32_t nst;     // results in the wave's stage
     uint64_t sbase;   // the wave's stage: records [sbase, sbase + stage_cap)
     uint64_t ftests, btests;
+    uint32_t hits;    // without boxes: kAhead times the queries that had survivors in
+                      // the last block, less its queries (kept across items)
     // direct output: the wave's open reservation [dpos, dend) (kept across
     // items) and its reservations so far
     uint64_t dpos, dend;
@@ -1513,37 +1515,57 @@ __device__ __forceinline__ Cand load_cand(const DistArgs& A, const ItemState& S,
 // j, those lanes as the result; 0 if no query has.  Takes it and those before it
 // from mk.
 //
-// A block's entries lie anywhere, most queries have no survivors among them, and
-// then this loop is all that a query costs.  Two at a time: their records are
-// read together, and the loop's scalar steps are shared (the last one alone is
-// taken twice).  200,000 uniform segments on the temporal layout: kernel 267 us
-// with the older walk, a copy of the code per combination of time test and
-// partial ranges, 447 with the one-query steps that block boxes take, 303 so.  With
-// block boxes most queries that are left have survivors, and the second test is
-// in vain (a search of two particle sets close by: 2,441 -> 2,642 us).
+// A block's entries lie anywhere, and where most queries have no survivors among
+// them this loop is all that a query costs.  kAhead at a time: their records are
+// read together, and the loop's scalar steps are shared (past the last one, the
+// first again).  Taken where at most one query in kAhead of the last block had
+// survivors, since the tests past one that has some are in vain.  200,000 uniform
+// segments on the temporal layout: kernel 268 us with the older walk, a copy of the
+// code per combination of time test and partial ranges, 447 with the one-query steps
+// that block boxes take, 303 two at a time, 275 four.
+constexpr uint32_t kAhead = 4;
 template <bool kTime>
 __device__ __forceinline__ uint64_t next_query(const WaveLDS& L, const Cand& c, uint64_t& mk,
                                                uint32_t& j) {
+    constexpr int kN = (int)kAhead;
     for (;;) {
-        const uint64_t mk1 = mk & (mk - 1u), mk2 = mk1 & (mk1 - 1u);
-        const uint32_t j1 = (uint32_t)__builtin_ctzll(mk);
-        const uint32_t j2 = (uint32_t)__builtin_ctzll(mk1 ? mk1 : mk);
-        const QSphere q1 = L.qs[j1], q2 = L.qs[j2];
-        QTime t1 = {}, t2 = {};
-        if (kTime) {
-            t1 = L.qt[j1];
-            t2 = L.qt[j2];
+        uint64_t rest[kN + 1];
+        uint32_t jn[kN];
+        QSphere q[kN];
+        QTime t[kN];
+        rest[0] = mk;
+#pragma unroll
+        for (int i = 0; i < kN; ++i) {
+            jn[i] = (uint32_t)__builtin_ctzll(i && !rest[i] ? mk : rest[i]);
+            rest[i + 1] = rest[i] & (rest[i] - 1u);
+            q[i] = L.qs[jn[i]];
+            if (kTime) t[i] = L.qt[jn[i]];
         }
-        uint64_t m1 = ballot(sphere_pass(q1.cx, q1.cy, q1.cz, q1.R, c.cx, c.cy, c.cz, c.r));
-        uint64_t m2 = ballot(sphere_pass(q2.cx, q2.cy, q2.cz, q2.R, c.cx, c.cy, c.cz, c.r));
-        if (kTime) {
-            m1 &= ballot(t1.a < c.te) & ballot(c.ts < t1.b);
-            m2 &= ballot(t2.a < c.te) & ballot(c.ts < t2.b);
+        uint64_t m[kN], any = 0;
+#pragma unroll
+        for (int i = 0; i < kN; ++i) {
+            m[i] = ballot(sphere_pass(q[i].cx, q[i].cy, q[i].cz, q[i].R, c.cx, c.cy, c.cz, c.r));
+            if (kTime) m[i] &= ballot(t[i].a < c.te) & ballot(c.ts < t[i].b);
+            any |= m[i];
         }
-        mk = m1 ? mk1 : mk2;
-        j = m1 ? j1 : j2;
-        m1 = m1 ? m1 : m2;
-        if (m1 || !mk) return m1;
+        if (any) {
+            j = jn[kN - 1];
+            mk = rest[kN];
+            uint64_t got = m[kN - 1];
+#pragma unroll
+            for (int i = kN - 2; i >= 0; --i)
+                if (m[i]) {
+                    j = jn[i];
+                    mk = rest[i + 1];
+                    got = m[i];
+                }
+            return got;
+        }
+        mk = rest[kN];
+        if (!mk) {
+            j = jn[0];
+            return 0;
+        }
     }
 }
 
@@ -1637,35 +1659,46 @@ __device__ __forceinline__ void scan_chunk_fp32(WaveLDS& L, const DistArgs& A, I
             const bool timed = !all_overlap || nv < kWave;
             const Cand c = tc[k];
             const ERef ex = eref_of(c.cx, c.cy, c.cz, c.r, c.v, c.ts, c.te);
+            // query j's survivors among the lanes go on
+            const auto pass = [&](uint32_t j, uint64_t m) {
+                if (!kCull) S.hits += kAhead;
+                if ((part >> j) & 1ull) {
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)qlo, (int)j);
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)qhi, (int)j);
+                    m &= ballot(cand >= lo) & ballot(cand < hi);
+                    if (!m) return;
+                }
+                if (kRef == TDS_REFINE_QUEUED) {
+                    enqueue(L.queue, S.qn, m, code | j);
+                    return;
+                }
+                const bool keep = refine32(L.qt[j], L.qref[j], ex.ox, ex.oy, ex.oz, ex.vx, ex.vy,
+                                           ex.vz, c.ts, c.te, ex.sc, ex.sv, ex.st);
+                enqueue(L.rq, S.rqn, m & ballot(keep), code | j);
+            };
+            const bool few = !kCull && (int32_t)S.hits <= 0;
+            if (!kCull) S.hits = 0u - (uint32_t)__popcll(mk);
             for (;;) {
-                while (mk && max(S.qn, S.rqn) < kWave) {
-                    uint32_t j;
-                    uint64_t m;
-                    if (!kCull) {
-                        m = timed ? next_query<true>(L, c, mk, j) : next_query<false>(L, c, mk, j);
-                    } else {
-                        j = (uint32_t)__builtin_ctzll(mk);
+                if (few) {
+                    while (mk && max(S.qn, S.rqn) < kWave) {
+                        uint32_t j;
+                        const uint64_t m =
+                            timed ? next_query<true>(L, c, mk, j) : next_query<false>(L, c, mk, j);
+                        if (m) pass(j, m);
+                    }
+                } else {
+                    while (mk && max(S.qn, S.rqn) < kWave) {
+                        const uint32_t j = (uint32_t)__builtin_ctzll(mk);
                         mk &= mk - 1u;
                         const QSphere q = L.qs[j];
-                        m = ballot(sphere_pass(q.cx, q.cy, q.cz, q.R, c.cx, c.cy, c.cz, c.r));
+                        uint64_t m =
+                            ballot(sphere_pass(q.cx, q.cy, q.cz, q.R, c.cx, c.cy, c.cz, c.r));
                         if (timed) {
                             const QTime t = L.qt[j];
                             m &= ballot(t.a < c.te) & ballot(c.ts < t.b);
                         }
+                        if (m) pass(j, m);
                     }
-                    if ((part >> j) & 1ull) {
-                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)qlo, (int)j);
-                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)qhi, (int)j);
-                        m &= ballot(cand >= lo) & ballot(cand < hi);
-                    }
-                    if (!m) continue;
-                    if (kRef == TDS_REFINE_QUEUED) {
-                        enqueue(L.queue, S.qn, m, code | j);
-                        continue;
-                    }
-                    const bool keep = refine32(L.qt[j], L.qref[j], ex.ox, ex.oy, ex.oz, ex.vx,
-                                               ex.vy, ex.vz, c.ts, c.te, ex.sc, ex.sv, ex.st);
-                    enqueue(L.rq, S.rqn, m & ballot(keep), code | j);
                 }
                 take_queued(L, S, A, mk ? (uint32_t)kWave : from);
                 if (!mk) break;
@@ -1719,6 +1752,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint32_t dg = 1;
     uint64_t found_total = 0;
     uint32_t nst = 0, rcnt = 0;  // what stays staged between items (keep)
+    uint32_t hits = 0;
     // all items of the search, unless a range is given (incremental passes)
     const uint32_t item_end = (A.item_end == 0xFFFFFFFFu)
                                   ? uniform(min(A.hdr->n_items, A.desc->item_cap))
@@ -1845,6 +1879,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         S.nst = nst;
         S.ftests = 0;
         S.btests = 0;
+        S.hits = hits;
         S.dpos = dpos;
         S.dend = dend;
         S.dg = dg;
@@ -1899,6 +1934,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         dg = S.dg;
         flushes += S.nres;
         found_total += S.found;
+        hits = S.hits;
         tests += (uint64_t)(S.c1 - S.c0) * S.nq;
         ftests += (kPrec == TDS_PREC_FP64) ? (uint64_t)(S.c1 - S.c0) * S.nq : S.ftests;
         btests += S.btests;
