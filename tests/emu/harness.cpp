@@ -11,6 +11,7 @@
 //   harness mergefull recs.bin capacity out.bin                   -> "status n"
 //   harness hostsearch D.bin Q.bin d t0 t1 out.bin                -> "status n candidates"
 //   harness fill seed W C K frac add align prefix                 -> "status count cap T holes R"
+//   harness fillgiven seed W C D K frac add align prefix -> "status count cap T holes R found tests"
 //   harness filtercheck seed n                                    -> "status accepted misses naive"
 //   harness cvt in.bin out.bin                                    -> "status n"
 //   harness fastpairs seed n                         -> "status accepted misses past dropped"
@@ -29,6 +30,12 @@
 // its position was kept in the output or scratch), prefix.before and
 // prefix.after (the first T = min(count, capacity) output records before and
 // after the fill; holes are 0xFFFFFFFF).
+//
+// "fillgiven" does the same with the fill of launches of up to 4,096 waves
+// (k_fill): every wave starts with the chunk of its number, its next reservations
+// are of 2, 4, .. D chunks (K results per wave at most).  "found" is the number of
+// results that the kernel worked out, "tests" the sum of the counters that it folds
+// (workgroup b's is b + 1).
 //
 // "filtercheck" draws n grazing pairs at random scales (coordinates, lengths
 // and d from 1e-3 to 1e9, separations of d (1 + eps) with eps down to 0) and
@@ -346,6 +353,93 @@ int run_fill(char** argv) {
     return 0;
 }
 
+int run_fillgiven(char** argv) {
+    std::mt19937_64 rng(strtoull(argv[2], nullptr, 10));
+    const uint32_t W = (uint32_t)atoi(argv[3]), C = (uint32_t)atoi(argv[4]),
+                   D = (uint32_t)atoi(argv[5]), K = (uint32_t)atoi(argv[6]);
+    const double frac = atof(argv[7]);
+    const int64_t add = strtoll(argv[8], nullptr, 10);
+    const bool align = atoi(argv[9]) != 0;
+    const std::string prefix = argv[10];
+    if (W == 0 || W > tds::kFillWaves || W % 4 || C < 64 || C % 64 || C * D > 2048 ||
+        W * D > tds::kFillChunks) {
+        printf("%d 0 0 0 0 0 0 0\n", TDS_E_INVALID);
+        return 0;
+    }
+    // evaluations of up to 64 results each, the waves' in a random interleaving (a
+    // third of the waves has none)
+    struct Wave {
+        uint64_t pos, end;
+        uint32_t g, left;
+    };
+    std::vector<Wave> wv(W);
+    std::vector<uint32_t> order;
+    for (uint32_t w = 0; w < W; ++w) {
+        wv[w] = {(uint64_t)w * C, (uint64_t)(w + 1) * C, 1, 0};
+        uint32_t left = K && rng() % 3 ? (uint32_t)(rng() % (K + 1)) : 0u;
+        for (wv[w].left = left; left; left -= std::min(left, 64u)) order.push_back(w);
+    }
+    std::shuffle(order.begin(), order.end(), rng);
+    uint64_t ctr = (uint64_t)W * C;
+    std::vector<uint64_t> at;  // position of each result
+    for (uint32_t w : order) {
+        Wave& v = wv[w];
+        const uint32_t nhit = std::min(v.left, 64u);
+        v.left -= nhit;
+        for (uint32_t r = 0; r < nhit; ++r) {
+            if (v.pos == v.end) {
+                v.g = std::min(2 * v.g, D);
+                v.pos = ctr;
+                v.end = ctr += (uint64_t)v.g * C;
+            }
+            at.push_back(v.pos++);
+        }
+    }
+    const uint64_t count = at.size(), scap = (uint64_t)W * C * D;
+    int64_t capi = (int64_t)std::floor((double)count * frac) + add;
+    uint64_t cap = capi < 0 ? 0 : (uint64_t)capi;
+    if (align) cap -= cap % C;
+    const uint64_t T = std::min(count, cap);
+    tds_result blank{};
+    blank.q_seg = blank.e_seg = 0xFFFFFFFFu;
+    std::vector<tds_result> out(std::max<uint64_t>(cap, 1), blank), scratch(scap, blank), all(count);
+    for (uint64_t i = 0; i < count; ++i) {
+        tds_result r{};
+        r.q_seg = (uint32_t)i;
+        r.e_seg = (uint32_t)at[i];
+        if (at[i] < cap) out[at[i]] = r;
+        else if (at[i] - cap < scap) scratch[at[i] - cap] = r;
+        r.e_traj = at[i] < cap + scap ? 1u : 0u;
+        all[i] = r;
+    }
+    std::vector<uint64_t> dlast(W);
+    uint64_t holes = 0;
+    for (uint32_t w = 0; w < W; ++w) {
+        const uint64_t size = (uint64_t)wv[w].g * C;
+        dlast[w] = tds::pack_last((wv[w].end - size) / C, wv[w].g,
+                                  (uint32_t)(size - (wv[w].end - wv[w].pos)));
+        if (wv[w].pos < T) holes += std::min(wv[w].end, T) - wv[w].pos;
+    }
+    write_records((prefix + ".all").c_str(), all, count);
+    write_records((prefix + ".before").c_str(), out, T);
+    tds::Request req{};
+    req.q_count = 1;
+    req.out_capacity = cap;
+    tds::ReqCounter rc{};
+    unsigned long long R = ctr;
+    const uint32_t nb = W / 4;
+    std::vector<tds::BlockStats> bs(nb);
+    for (uint32_t b = 0; b < nb; ++b) bs[b].tests = b + 1;
+    tds::SearchHeader hdr{};
+    hipLaunchKernelGGL(tds::k_fill, dim3(4), dim3(1024), 0, nullptr, &req, &rc, &R, dlast.data(), W,
+                       C, out.data(), scratch.data(), bs.data(), nb, &hdr);
+    write_records((prefix + ".after").c_str(), out, T);
+    printf("%d %llu %llu %llu %llu %llu %llu %llu\n", TDS_OK, (unsigned long long)count,
+           (unsigned long long)cap, (unsigned long long)T, (unsigned long long)holes,
+           (unsigned long long)R, (unsigned long long)rc.count, (unsigned long long)hdr.tests);
+    return 0;
+}
+
 // The closest-approach refinement, from the data the kernels keep.
 bool refine_keeps(const tds::QCanon& q, float qcx, float qcy, float qcz, float qR, float ecx,
                   float ecy, float ecz, float er, double evx, double evy, double evz, double ets,
@@ -588,6 +682,7 @@ int main(int argc, char** argv) {
     if (argc >= 5 && std::string(argv[1]) == "mergefull") return run_mergefull(argv);
     if (argc >= 8 && std::string(argv[1]) == "hostsearch") return run_hostsearch(argv);
     if (argc >= 10 && std::string(argv[1]) == "fill") return run_fill(argv);
+    if (argc >= 11 && std::string(argv[1]) == "fillgiven") return run_fillgiven(argv);
     if (argc >= 4 && std::string(argv[1]) == "filtercheck") return run_filtercheck(argv);
     if (argc >= 4 && std::string(argv[1]) == "cvt") return run_cvt(argv);
     if (argc >= 4 && std::string(argv[1]) == "fastpairs") return run_fastpairs(argv);
