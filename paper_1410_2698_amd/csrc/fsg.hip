@@ -8,13 +8,15 @@
 // table gives each cell's first listing (cells are few enough, at most 2^24,
 // for a dense table instead of the paper's searched array of non-empty cells).
 //
-// Search: one wave per query segment (persistent over the query set).  The
-// wave walks the cells overlapped by the query's box grown by d (scalar
-// loops); the lanes take the cell's listings 64 at a time, skip entries that
-// do not overlap the query in time, and evaluate the rest with the canonical
-// FP64 code.  A pair listed in several of the visited cells is reported only
-// from the lowest cell of the intersection of the two cell ranges, so no
-// duplicates are produced (the paper removed them on the host afterwards).
+// Search: a workgroup prepares a batch of query segments for each of its waves
+// (canonical data, cells overlapped by the box grown by d, and the range of
+// entry positions that may overlap in time).  A wave lays the runs of listings of
+// its batch's cells (cells that are neighbours along x hold consecutive listings)
+// end to end, tests them 64 at a time by entry position, queues the pairs that
+// stay and evaluates them 64 at a time with the canonical FP64 code.  A pair listed
+// in several of the visited cells is reported only from the lowest cell of the
+// intersection of the two cell ranges, so no duplicates are produced (the paper
+// removed them on the host afterwards).
 #include <algorithm>
 #include <chrono>
 #include <cmath>

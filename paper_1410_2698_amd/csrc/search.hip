@@ -12,8 +12,9 @@
 //   k_scatter    the numbers of the query segments by bucket, and the
 //                work-item table (item -> bucket);
 //   k_distance   persistent waves take work items (64 query segments of one
-//                bucket x one chunk of their common candidate range).  FP32 form: the lanes hold the chunk's candidates
-//                (coalesced loads) and the boxes of its 64-entry blocks; each
+//                bucket x one chunk of their common candidate range).  FP32
+//                form: the lanes hold the chunk's candidates (coalesced loads)
+//                and the boxes of its 64-entry blocks; each
 //                block's box is tested against every query of the group (one
 //                lane per query) and only the surviving queries are tested
 //                against the block's candidates.  FP64 plain form: one query
@@ -513,7 +514,9 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
         __syncthreads();
         if (2 * s_mixed <= s_n0[0]) fit = 0;
         uint32_t l = 0;
-        while (l + 1 < levels && s_n0[l] < target && !(l && s_n0[l] <= fit && s_n0[l + 1] > fit)) ++l;
+        while (l + 1 < levels && s_n0[l] < target &&
+               !(l && s_n0[l] <= fit && s_n0[l + 1] > fit))
+            ++l;
         chunk >>= l;
     }
     // the record of each bucket (all but its offsets), then the offsets after
@@ -725,12 +728,13 @@ __device__ void block_scan_1024(uint32_t n, F f, uint64_t* __restrict__ out) {
 // Direct output, after the distance kernel (one workgroup): the plan of the
 // fill.  T = min(count, capacity) is the end of the dense output.  The
 // holes are the unused tails of the waves' last chunks below T (at most one
-// per wave); the sources are the results at positions at or past T, in
-// position order, of which the first (total hole size) are moved.  Those lie
-// within W (C - 1) positions of T (every hole is shorter than C), so the
-// chunks c0 = T / C .. c0 + W are enough, and positions past the capacity
-// within W C of it are in the scratch buffer.  Writes the source prefix sums
-// per chunk, the hole prefix sums and starts per wave, and (T, c0, chunks).
+// per wave, none of a wave that reserved nothing: ~0 in dlast); the sources
+// are the results at positions at or past T, in position order, of which the
+// first (total hole size) are moved.  Those lie within W (C - 1) positions of T
+// (every hole is shorter than C), so the chunks c0 = T / C .. c0 + W are enough,
+// and positions past the capacity within W C of it are in the scratch buffer.
+// Writes the source prefix sums per chunk, the hole prefix sums and starts per
+// wave, and (T, c0, chunks).
 __global__ __launch_bounds__(1024) void k_fill_plan(const Request* __restrict__ req,
                                                     const ReqCounter* __restrict__ rc,
                                                     const unsigned long long* __restrict__ dir_ctr,
@@ -1770,9 +1774,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // more than half of a galaxy search).  The next item is asked for before
     // the current one's last evaluations, which hide most of the atomic's
     // latency (asked for at the item's start, it is bound to a wave that may
-    // be busy for long: 8.6 against 6.4 ms on galaxy), and the counters are read before an increment only by a wave that looks
-    // for another part: reading all eight per item, next to the atomics, took
-    // the whole chip 30 ns per item (1.9e6 items of 64 candidates: 57 ms).
+    // be busy for long: 8.6 against 6.4 ms on galaxy), and the counters are read
+    // before an increment only by a wave that looks for another part: reading
+    // all eight per item, next to the atomics, took the whole chip 30 ns per item
+    // (1.9e6 items of 64 candidates: 57 ms).
     // The 9,600 items of three uniform1m searches: 279 us that way, 197 asked
     // ahead, 145 with the line that says all parts are used up, 137 dealt
     // statically.
@@ -2192,10 +2197,12 @@ int ws_reserve_stage(Workspace* w, uint32_t grid_waves) {
         w->dlast = w->fill_s = w->fill_d = w->fill_dstart = w->fill_plan = nullptr;
         w->stage_waves = 0;
         TDS_TRY(dmalloc(&w->dlast, waves));
-        TDS_TRY(dmalloc(&w->fill_s, (size_t)waves + 2));
-        TDS_TRY(dmalloc(&w->fill_d, (size_t)waves + 1));
-        TDS_TRY(dmalloc(&w->fill_dstart, waves));
-        TDS_TRY(dmalloc(&w->fill_plan, 4));
+        if (waves > kFillWaves) {  // k_fill keeps its plan in LDS
+            TDS_TRY(dmalloc(&w->fill_s, (size_t)waves + 2));
+            TDS_TRY(dmalloc(&w->fill_d, (size_t)waves + 1));
+            TDS_TRY(dmalloc(&w->fill_dstart, waves));
+            TDS_TRY(dmalloc(&w->fill_plan, 4));
+        }
         w->stage_waves = waves;
     }
     if (w->stage_recs >= need && w->stage) return TDS_OK;
@@ -2519,7 +2526,8 @@ int enqueue_pipeline(const tds_index* idx, Workspace* w, const QueryView& Q, siz
     hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, s, w->b_count, w->b_hi,
                        idx->bin_first, idx->min_te, idx->max_ts, idx->m, shift, nb, nparts,
                        chunk & ~kChunkAuto, chunk_levels(prec, chunk), item_target(grid_waves),
-                       item_fit(prec, grid_waves), fit_always(idx, grid_waves), w->b_start, w->b_nch, w->binfo, w->hdr);
+                       item_fit(prec, grid_waves), fit_always(idx, grid_waves), w->b_start,
+                       w->b_nch, w->binfo, w->hdr);
     hipLaunchKernelGGL(k_scatter, dim3(qblocks + nb), dim3(kBlock), 0, s, w->desc, w->qkey,
                        w->qslot, w->b_start, w->b_count, nb, bpp, qblocks, w->qsorted, w->binfo,
                        w->item_bucket, w->hdr);
@@ -2600,9 +2608,6 @@ int reserve_items(const tds_index* idx, Workspace* w, uint64_t nq, uint32_t chun
     return TDS_OK;
 }
 
-// Runs the pipeline once for the batch whose requests the caller staged in
-// w->req_host (sent to the device here, with the descriptor), growing the
-// item table and re-running if the bound was too small.
 // Largest output that a one-request search stages unless told otherwise: 32
 // records per wave, 4 MB in all at the default grid, so that the second trip of
 // the records that are kept costs 2 us.  Small outputs are those of small

@@ -221,8 +221,9 @@ struct Workspace {
     size_t stage_recs = 0;
     DeviceBlock stage_block;        // holds both
     unsigned long long* dyn_ctr = nullptr;  // kCtrSlots counters, kCtrStride apart
-    // direct output (one-request searches): each wave's last reservation and
-    // the plan of the pass that fills the holes (sized for stage_waves waves)
+    // direct output (one-request searches): each wave's last reservation and, where
+    // waves are more than k_fill takes, the plan of the pass that fills the holes
+    // (sized for stage_waves waves)
     uint64_t* dlast = nullptr;
     uint64_t* fill_s = nullptr;      // source prefix sums of the chunks
     uint64_t* fill_d = nullptr;      // stage_waves + 1 hole prefix sums
