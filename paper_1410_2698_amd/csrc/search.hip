@@ -1663,15 +1663,17 @@ __device__ __forceinline__ void scan_chunk_fp32(WaveLDS& L, const DistArgs& A, I
             const bool timed = !all_overlap || nv < kWave;
             const Cand c = tc[k];
             const ERef ex = eref_of(c.cx, c.cy, c.cz, c.r, c.v, c.ts, c.te);
-            // query j's survivors among the lanes go on
+            // query j's survivors among the lanes go on (with block boxes most queries
+            // have some, and asking for that before the range cost two particle sets
+            // close by 943 -> 961 us)
             const auto pass = [&](uint32_t j, uint64_t m) {
                 if (!kCull) S.hits += kAhead;
                 if ((part >> j) & 1ull) {
                     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)qlo, (int)j);
                     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)qhi, (int)j);
                     m &= ballot(cand >= lo) & ballot(cand < hi);
-                    if (!m) return;
                 }
+                if (!m) return;
                 if (kRef == TDS_REFINE_QUEUED) {
                     enqueue(L.queue, S.qn, m, code | j);
                     return;
@@ -1701,7 +1703,7 @@ __device__ __forceinline__ void scan_chunk_fp32(WaveLDS& L, const DistArgs& A, I
                             const QTime t = L.qt[j];
                             m &= ballot(t.a < c.te) & ballot(c.ts < t.b);
                         }
-                        if (m) pass(j, m);
+                        if (kCull || m) pass(j, m);
                     }
                 }
                 take_queued(L, S, A, mk ? (uint32_t)kWave : from);
@@ -1755,7 +1757,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint64_t dpos = dfirst, dend = dfirst + (A.dir_given ? A.dir_chunk : 0u);
     uint32_t dg = 1;
     uint64_t found_total = 0;
-    uint32_t nst = 0, rcnt = 0;  // what stays staged between items (keep)
+    // what stays staged between items (keep): nst results, request r's number of
+    // them at queue[r], since the queue is empty then (in a register it was spilled,
+    // one more trip to memory per item)
+    uint32_t nst = 0, rcnt = 0;
     uint32_t hits = 0;
     // all items of the search, unless a range is given (incremental passes)
     const uint32_t item_end = (A.item_end == 0xFFFFFFFFu)
@@ -1906,7 +1911,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const bool all_cover = ballot(f.lo <= S.c0 && f.hi >= S.c1) == ~0ull;
         S.qr = f.req;
         S.rslot = A.keep ? f.req : request_slots(has, f.req);
-        S.rcnt = rcnt;
         wave_sync();
         L.qe[lane] = e;
         if (kPrec == TDS_PREC_FP32_RECHECK) {
@@ -1914,6 +1918,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             L.qt[lane] = QTime{f.a32, f.b32};
             L.qref[lane] = qref_of(e.c, f);
         }
+        S.rcnt = rcnt;
         wave_sync();
         if (kPrec == TDS_PREC_FP32_RECHECK)
             scan_chunk_fp32<kCplT, kRef, kCull>(
@@ -1927,13 +1932,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
         // the item's results get their positions where the next item's group has
         // other request slots
-        if (A.keep) {
-            nst = S.nst;
-            rcnt = S.rcnt;
-        } else if (S.nst) {
+        if (!A.keep && S.nst) {
             stage_flush(L, A, S);
             ++flushes;
         }
+        nst = S.nst;
+        rcnt = S.rcnt;
         dpos = S.dpos;
         dend = S.dend;
         dg = S.dg;
