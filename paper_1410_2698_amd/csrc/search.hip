@@ -1760,7 +1760,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // what stays staged between items (keep): nst results, request r's number of
     // them at queue[r], since the queue is empty then (in a register it was spilled,
     // one more trip to memory per item)
-    uint32_t nst = 0, rcnt = 0;
+    uint32_t nst = 0;
+    L.queue[lane] = 0u;
     uint32_t hits = 0;
     // all items of the search, unless a range is given (incremental passes)
     const uint32_t item_end = (A.item_end == 0xFFFFFFFFu)
@@ -1918,7 +1919,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             L.qt[lane] = QTime{f.a32, f.b32};
             L.qref[lane] = qref_of(e.c, f);
         }
-        S.rcnt = rcnt;
+        S.rcnt = L.queue[lane];
         wave_sync();
         if (kPrec == TDS_PREC_FP32_RECHECK)
             scan_chunk_fp32<kCplT, kRef, kCull>(
@@ -1937,7 +1938,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             ++flushes;
         }
         nst = S.nst;
-        rcnt = S.rcnt;
+        L.queue[lane] = S.rcnt;
         dpos = S.dpos;
         dend = S.dend;
         dg = S.dg;
@@ -1970,8 +1971,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         // what the workgroup's waves still have staged: lane r adds up request r's
         // results, and one wave reserves for all
         if (nst) ++flushes;
-        wave_sync();
-        L.queue[lane] = rcnt;
+        const uint32_t rcnt = L.queue[lane];
         __syncthreads();
         uint32_t before = 0, all = 0;
         for (uint32_t w = 0; w < (uint32_t)kWavesPerBlock; ++w) {
