@@ -475,33 +475,36 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(uint32_t* __restrict__ b_c
         // block's total fits 32 bits
         const uint32_t lg = (uint32_t)__builtin_ctz(chunk);
         uint32_t n0[kChunkLevels] = {}, nm = 0;
-        // any order will do: consecutive threads take consecutive buckets, and a few
-        // counts are asked for together (65,535 buckets, each thread's own one
-        // after another: 20 us)
-        constexpr uint32_t kAtOnce = 4;
-        for (uint32_t bb = tid; bb < nb; bb += 1024 * kAtOnce) {
-            uint32_t cnts[kAtOnce];
+        const auto add = [&](uint32_t b, uint32_t cnt, uint32_t rmax) {
+            uint32_t lo, hi;
+            bucket_range(b, shift, m, bin_first, rmax, &lo, &hi);
+            const uint64_t len = hi - (lo & ~(uint32_t)(kWave - 1));
 #pragma unroll
-            for (uint32_t i = 0; i < kAtOnce; ++i) {
-                const uint32_t b = bb + 1024 * i;
-                cnts[i] = b < nb ? (nparts == kCountParts ? s_cnt[b] : b_count[b]) : 0u;
+            for (uint32_t l = 0; l < kChunkLevels; ++l) {
+                const uint64_t n = (uint64_t)((cnt + kWave - 1) / kWave) *
+                                   ((len + (chunk >> l) - 1) >> (lg - l));
+                n0[l] = (uint32_t)min(n0[l] + n, (uint64_t)target);
+                if (l == 0 && (mixed || shift || b % kSpanClasses))
+                    nm = (uint32_t)min(nm + n, (uint64_t)target);
             }
+        };
+        if (nparts == kCountParts) {
+#pragma unroll 1
+            for (uint32_t b = tid; b < nb; b += 1024)
+                if (s_cnt[b]) add(b, s_cnt[b], s_hi[b]);
+        } else {
+            // any order will do: consecutive threads take consecutive buckets, and a
+            // few counts are asked for together (65,535 buckets, each thread's own
+            // one after another: 20 us)
+            constexpr uint32_t kAtOnce = 4;
+            for (uint32_t bb = tid; bb < nb; bb += 1024 * kAtOnce) {
+                uint32_t cnts[kAtOnce];
 #pragma unroll
-            for (uint32_t i = 0; i < kAtOnce; ++i) {
-                const uint32_t b = bb + 1024 * i, cnt = cnts[i];
-                if (!cnt) continue;
-                uint32_t lo, hi;
-                bucket_range(b, shift, m, bin_first, nparts == kCountParts ? s_hi[b] : b_hi[b],
-                             &lo, &hi);
-                const uint64_t len = hi - (lo & ~(uint32_t)(kWave - 1));
+                for (uint32_t i = 0; i < kAtOnce; ++i)
+                    cnts[i] = bb + 1024 * i < nb ? b_count[bb + 1024 * i] : 0u;
 #pragma unroll
-                for (uint32_t l = 0; l < kChunkLevels; ++l) {
-                    const uint64_t n = (uint64_t)((cnt + kWave - 1) / kWave) *
-                                       ((len + (chunk >> l) - 1) >> (lg - l));
-                    n0[l] = (uint32_t)min(n0[l] + n, (uint64_t)target);
-                    if (l == 0 && (mixed || shift || b % kSpanClasses))
-                        nm = (uint32_t)min(nm + n, (uint64_t)target);
-                }
+                for (uint32_t i = 0; i < kAtOnce; ++i)
+                    if (cnts[i]) add(bb + 1024 * i, cnts[i], b_hi[bb + 1024 * i]);
             }
         }
         nm = wave_scan(nm);
