@@ -2619,10 +2619,11 @@ int reserve_items(const tds_index* idx, Workspace* w, uint64_t nq, uint32_t chun
 // records per wave, 4 MB in all at the default grid, so that the second trip of
 // the records that are kept costs 2 us.  Small outputs are those of small
 // searches, which are latency: staged they end with the last item, direct with
-// one more kernel of 12.5 us (4,900 query segments, 6,000 records: the call 97
-// against 86 us; 400 query segments 135 against 125; but 100,000 with 472,000
-// records 189 against 202, and 71 million 4.7 against 6.9 ms, each result
-// written twice).
+// one more kernel of 12.5 us (4,900 query segments, 6,000 records: the call 100
+// direct, 93 staged; 201 query segments 88 and 82).  Large outputs lose by the second
+// trip (174 million records 4.8 and 7.1 ms).  Where results stay staged from item to
+// item the two meet past 466,000 records (186 and 177 us); flushed after every item,
+// for which the line was drawn, they met before that (189 and 202).
 uint64_t staged_room(uint32_t grid_waves) {
     return 32ull * launch_blocks(grid_waves) * kWavesPerBlock;
 }
